@@ -449,6 +449,117 @@ __global__ void __launch_bounds__(1024) k_hidden_quantize(const __half *__restri
     }
 }
 
+// The same for buffers aligned to 16 (values) and 8 (codes) bytes.  Memory bound in the large, latency bound at
+// decode sizes: a thread holds 8 consecutive values per chunk in registers, so x is read once, with 16-byte loads;
+// the quotients by the block's maximum are the IEEE ones from one reciprocal (q = x r corrected by the exact
+// remainder: three instructions); and the midpoints below a quotient are counted with ONE comparison: quotients
+// are binned by sign, exponent and 6 mantissa bits, no bin holds more than one midpoint, and a table says how many
+// lie below each bin.  29.4 M values (2048 rows of 14336) into codes and back: 163 -> 56 us with the wide
+// dequantizer below (92 us of it were the binary search over the 255 midpoints with two 2-byte reads of every value,
+// 66 us one 2-byte store and one 64-bit division per value).  512 threads with 1, 2 or 4 chunks cover blocks of up to 4096, 8192 and 16384.
+constexpr int CODE_SHIFT = 17, CODE_KEY0 = 105 << (23 - CODE_SHIFT);         // bin 0: everything below 2^-22, no midpoint there
+constexpr int CODE_BINS = (127 << (23 - CODE_SHIFT)) - CODE_KEY0 + 1;        // the last bin starts at 1.0
+struct CodeBins {
+    float mids[256];                 // mids[255] = +infinity
+    uint8_t below[2 * CODE_BINS];    // midpoints below the values of a bin: positive values, then negative ones
+};
+constexpr CodeBins make_code_bins() {
+    CodeBins t{};
+    const CodeTable tab = ps_make_code_table();
+    for (int i = 0; i < 255; i++) t.mids[i] = (tab.code[i] + tab.code[i + 1]) * 0.5f;
+    t.mids[255] = __builtin_huge_valf();
+    int c = 0;                                                               // positive bins, ascending
+    for (int b = 0; b < CODE_BINS; b++) {
+        const float lo = b == 0 ? 0.0f : __builtin_bit_cast(float, (uint32_t)(CODE_KEY0 + b) << CODE_SHIFT);
+        while (t.mids[c] < lo) c++;
+        t.below[b] = (uint8_t)c;
+    }
+    c = 0;                                                                   // negative bins, ascending from -1.0
+    for (int b = CODE_BINS - 1; b >= 0; b--) {
+        const float lo = -__builtin_bit_cast(float, ((uint32_t)(CODE_KEY0 + b + 1) << CODE_SHIFT) - 1u);
+        while (t.mids[c] < lo) c++;
+        t.below[CODE_BINS + b] = (uint8_t)c;
+    }
+    return t;
+}
+constexpr bool one_midpoint_per_bin(const CodeBins &t) {
+    for (int b = 0; b < CODE_BINS; b++) {
+        const float hi = __builtin_bit_cast(float, ((uint32_t)(CODE_KEY0 + b + 1) << CODE_SHIFT) - 1u);
+        if (t.below[b] < 254 && t.mids[t.below[b] + 1] < hi) return false;
+        const float nhi = b == 0 ? 0.0f : -__builtin_bit_cast(float, (uint32_t)(CODE_KEY0 + b) << CODE_SHIFT);
+        if (t.mids[t.below[CODE_BINS + b] + 1] < nhi) return false;
+    }
+    return true;
+}
+static_assert(one_midpoint_per_bin(make_code_bins()), "one comparison per value needs at most one midpoint per bin");
+static_assert(sizeof(CodeBins) % 4 == 0, "copied to LDS word by word");
+static __device__ const CodeBins d_code_bins = make_code_bins();
+
+template <int PER>
+__global__ void __launch_bounds__(512) k_hidden_quantize_wide(const __half *__restrict__ x, size_t n, int block,
+                                                              uint8_t *__restrict__ q, float *__restrict__ absmax) {
+    constexpr int NT = 512;
+    __shared__ CodeBins cb;
+    __shared__ uint32_t s_max[NT / 64];
+    const size_t b0 = (size_t)blockIdx.x * block;
+    const int len = (int)min((size_t)block, n - b0);
+    const __half *xb = x + b0;
+    v4i xv[PER];
+    uint32_t mb = 0;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int k = (threadIdx.x + i * NT) * 8;
+        xv[i] = (v4i){0, 0, 0, 0};
+        if (k + 8 <= len) {
+            xv[i] = *(const v4i *)(xb + k);
+        } else {
+            for (int e = 0; e < len - k; e++) ((__half *)&xv[i])[e] = xb[k + e];   // the ragged end of the last block
+        }
+    }
+    for (int i = threadIdx.x; i < (int)(sizeof(CodeBins) / 4); i += NT) ((uint32_t *)&cb)[i] = ((const uint32_t *)&d_code_bins)[i];
+#pragma unroll
+    for (int i = 0; i < PER; i++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) mb = max(mb, ((uint32_t)xv[i][e >> 1] >> ((e & 1) * 16)) & 0x7fffu);   // fp16 magnitudes order like their bits
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, off));
+    if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = mb;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NT / 64; w++) mb = max(mb, s_max[w]);
+    const unsigned short ab = (unsigned short)mb;
+    float a = __half2float(*(const __half *)&ab);
+    const bool finite = mb < 0x7c00u;
+    if (!finite) {                                             // infinities and NaN: the largest of the numbers, as fmaxf has it
+        a = 0.0f;
+        for (int k = 0; k < len; k++) a = fmaxf(a, fabsf(__half2float(xb[k])));
+    }
+    if (threadIdx.x == 0) absmax[blockIdx.x] = a;
+    const float r = a > 0.0f ? 1.0f / a : 0.0f;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int k = (threadIdx.x + i * NT) * 8;
+        uint32_t w[2] = {0u, 0u};
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const unsigned short hb = (unsigned short)((uint32_t)xv[i][e >> 1] >> ((e & 1) * 16));
+            const float f = __half2float(*(const __half *)&hb), q0 = f * r;
+            float v = fmaf(fmaf(-q0, a, f), r, q0);            // == f / a in fp32: r is the rounded 1 / a, the remainder exact
+            if (!finite) v = a > 0.0f ? f / a : 0.0f;
+            const int key = min(max((int)(__float_as_uint(fabsf(v)) >> CODE_SHIFT) - CODE_KEY0, 0), CODE_BINS - 1);
+            uint32_t c = cb.below[key + (v < 0.0f ? CODE_BINS : 0)];
+            c += cb.mids[c] < v ? 1u : 0u;
+            if (!finite && !(v == v)) c = 0;
+            w[e >> 2] |= c << (8 * (e & 3));
+        }
+        if (k + 8 <= len) {
+            *(uint2 *)(q + b0 + k) = make_uint2(w[0], w[1]);
+        } else {
+            for (int e = 0; e < len - k; e++) q[b0 + k + e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
+        }
+    }
+}
+
 __global__ void __launch_bounds__(256) k_hidden_dequantize(const uint8_t *__restrict__ q,
                                                            const float *__restrict__ absmax, size_t n, int block,
                                                            CodeTable tab, __half *__restrict__ y) {
@@ -457,6 +568,32 @@ __global__ void __launch_bounds__(256) k_hidden_dequantize(const uint8_t *__rest
     __syncthreads();
     size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) y[i] = __float2half_rn(keep_f32(code[q[i]] * absmax[i / (size_t)block]));
+}
+
+// The same for buffers aligned to 16 bytes and n below 2^35: 16 codes per thread, one 16-byte load and two 16-byte
+// stores, and one division for the block's number (blocks are multiples of 64 values: the 16 share one).  Memory bound.
+__global__ void __launch_bounds__(256) k_hidden_dequantize_wide(const uint8_t *__restrict__ q,
+                                                                const float *__restrict__ absmax, size_t n,
+                                                                uint32_t block16, __half *__restrict__ y) {
+    __shared__ float code[256];
+    const uint32_t c = blockIdx.x * 256u + threadIdx.x;
+    const size_t i = (size_t)c * 16;
+    v4i cv = {0, 0, 0, 0};
+    float am = 0.0f;
+    const bool full = i + 16 <= n;
+    if (full) cv = *(const v4i *)(q + i);
+    if (i < n) am = absmax[c / block16];
+    code[threadIdx.x] = d_code_table.code[threadIdx.x];
+    __syncthreads();
+    if (full) {
+        __half out[16];
+#pragma unroll
+        for (int e = 0; e < 16; e++) out[e] = decode_q8(code, ((uint32_t)cv[e >> 2] >> (8 * (e & 3))) & 255u, am);
+        *(v4i *)(y + i) = *(const v4i *)out;
+        *(v4i *)(y + i + 8) = *(const v4i *)(out + 8);
+    } else {
+        for (size_t e = i; e < n; e++) y[e] = decode_q8(code, q[e], am);
+    }
 }
 
 // ------------------------------------------------------------- cache copies
@@ -538,12 +675,24 @@ hipError_t ps_mask_to_bytes(const uint32_t *mask, int K, uint8_t *out, hipStream
 hipError_t ps_hidden_quantize(const __half *x, size_t n, int block, const CodeTable &tab, uint8_t *q, float *absmax,
                               hipStream_t st) {
     if (n == 0) return hipSuccess;
-    k_hidden_quantize<<<(unsigned)((n + block - 1) / block), 1024, 0, st>>>(x, n, block, tab, q, absmax);
+    const unsigned blocks = (unsigned)((n + block - 1) / block);
+    // (a block starts at a multiple of 64 values: aligned buffers make every chunk aligned)
+    if ((((uintptr_t)x & 15) | ((uintptr_t)q & 7)) == 0) {
+        if (block <= 4096) k_hidden_quantize_wide<1><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
+        else if (block <= 8192) k_hidden_quantize_wide<2><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
+        else k_hidden_quantize_wide<4><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
+    } else {
+        k_hidden_quantize<<<blocks, 1024, 0, st>>>(x, n, block, tab, q, absmax);
+    }
     return hipGetLastError();
 }
 hipError_t ps_hidden_dequantize(const uint8_t *q, const float *absmax, size_t n, int block, const CodeTable &tab,
                                 __half *y, hipStream_t st) {
     if (n == 0) return hipSuccess;
+    if ((((uintptr_t)q | (uintptr_t)y) & 15) == 0 && n < ((size_t)1 << 35)) {
+        k_hidden_dequantize_wide<<<(unsigned)((n + 4095) / 4096), 256, 0, st>>>(q, absmax, n, (uint32_t)block / 16, y);
+        return hipGetLastError();
+    }
     k_hidden_dequantize<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(q, absmax, n, block, tab, y);
     return hipGetLastError();
 }
