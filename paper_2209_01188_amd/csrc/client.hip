@@ -18,7 +18,6 @@ constexpr int LM_THREADS = 1024;           // 16 waves: enough 16-byte loads in 
 constexpr int LM_WAVES = LM_THREADS / 64;
 constexpr int LM_GROUPS = 256;             // workgroups of the LM head = partial results per row
 constexpr int LM_MAX_ROWS = 32;            // rows of hidden states multiplied per pass over the matrix (matrix-core form)
-constexpr size_t LM_LDS_BUDGET = 128 * 1024;
 
 // One workgroup per token: gather the embedding row, LayerNorm in fp64, store fp16.
 template <int NT>
@@ -47,32 +46,24 @@ __device__ __forceinline__ void take_better(Best &a, double v, int i) {   // lar
     }
 }
 
-// logits of RM rows of fp16 hidden states a[RM][H] against all V rows of E.  The hidden rows sit in
+// logits of ONE row of fp16 hidden states a[H] against all V rows of E.  The hidden row sits in
 // LDS as fp64 (converted once); wave w of workgroup g takes the matrix rows (g * 16 + w) + i * 16 * gridDim.x, one row
 // at a time: 64 lanes x 16 bytes per load instruction, four instructions in flight, a wave-wide fp64
-// sum at the end of the row.  Each workgroup leaves its best (value, index) per hidden row.
-template <int RM>
-__global__ void __launch_bounds__(LM_THREADS) k_lm_head(const __half *__restrict__ a, int rows, const __half *__restrict__ E,
+// sum at the end of the row.  Each workgroup leaves its best (value, index).
+__global__ void __launch_bounds__(LM_THREADS) k_lm_head(const __half *__restrict__ a, const __half *__restrict__ E,
                                                         int V, int H, float *__restrict__ logits,
                                                         Best *__restrict__ partial) {
-    // element k = 8 c + j of row m at [m][j][c]: the lanes of a wave hold consecutive chunks c, so their
+    // element k = 8 c + j at [j][c]: the lanes of a wave hold consecutive chunks c, so their
     // 8-byte reads of one j are consecutive in LDS (no bank conflicts)
-    extern __shared__ __align__(16) double ad[];       // [RM][8][H / 8]
-    __shared__ Best wbest[LM_WAVES][RM];
+    extern __shared__ __align__(16) double ad[];       // [8][H / 8]
+    __shared__ Best wbest[LM_WAVES];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nchunk = H >> 3;
-    for (int i = threadIdx.x; i < RM * H; i += LM_THREADS) {
-        const int m = i / H, k = i - m * H;
-        ad[(size_t)m * H + (k & 7) * nchunk + (k >> 3)] = m < rows ? (double)__half2float(a[i]) : 0.0;
-    }
+    for (int k = threadIdx.x; k < H; k += LM_THREADS) ad[(k & 7) * nchunk + (k >> 3)] = (double)__half2float(a[k]);
     __syncthreads();
-    Best best[RM];
-#pragma unroll
-    for (int m = 0; m < RM; m++) best[m] = Best{-INFINITY, 0x7fffffff};
+    Best best = Best{-INFINITY, 0x7fffffff};
     for (int v = blockIdx.x * LM_WAVES + wave; v < V; v += gridDim.x * LM_WAVES) {
         const __half *er = E + (size_t)v * H;
-        double acc[RM];
-#pragma unroll
-        for (int m = 0; m < RM; m++) acc[m] = 0.0;
+        double acc = 0.0;
         for (int c0 = lane; c0 < nchunk; c0 += 256) {
             v8h e[4];
 #pragma unroll
@@ -83,96 +74,352 @@ __global__ void __launch_bounds__(LM_THREADS) k_lm_head(const __half *__restrict
                 const int c = c0 + u * 64;
                 if (c < nchunk) {
 #pragma unroll
-                    for (int j = 0; j < 8; j++) {
-                        const double ed = (double)(float)e[u][j];
-#pragma unroll
-                        for (int m = 0; m < RM; m++) acc[m] += ed * ad[m * H + j * nchunk + c];
-                    }
+                    for (int j = 0; j < 8; j++) acc += (double)(float)e[u][j] * ad[j * nchunk + c];
                 }
             }
         }
-#pragma unroll
-        for (int m = 0; m < RM; m++) {
-            const double s = wave_sum(acc[m]);
-            if (m < rows) {
-                if (lane == 0 && logits) logits[(size_t)m * V + v] = (float)s;
-                take_better(best[m], s, v);
-            }
-        }
+        const double s = wave_sum(acc);
+        if (lane == 0 && logits) logits[v] = (float)s;
+        take_better(best, s, v);
     }
-    if (lane == 0) {
-#pragma unroll
-        for (int m = 0; m < RM; m++) wbest[wave][m] = best[m];
-    }
+    if (lane == 0) wbest[wave] = best;
     __syncthreads();
-    if (threadIdx.x < RM) {
-        Best r = wbest[0][threadIdx.x];
-        for (int w = 1; w < LM_WAVES; w++) take_better(r, wbest[w][threadIdx.x].v, wbest[w][threadIdx.x].i);
-        partial[threadIdx.x * LM_GROUPS + blockIdx.x] = r;
+    if (threadIdx.x == 0) {
+        Best r = wbest[0];
+        for (int w = 1; w < LM_WAVES; w++) take_better(r, wbest[w].v, wbest[w].i);
+        partial[blockIdx.x] = r;
     }
 }
 
-// Several rows of hidden states at once: the same product on the fp64 matrix instruction (products of fp16
-// values are exact, sums in fp64 as in the one-row form).  A wave takes 16 matrix rows at a time as the A operand
-// and MT tiles of 16 hidden rows as the B operand; lane (row l%16, group l/16) loads 8 consecutive fp16 values
-// (16 bytes) of its matrix row and of its hidden row and feeds them to 8 instructions - any pairing of the
-// contraction index works as long as both operands use the same one.  Result register r of lane (g, c) is matrix
-// row 4r + g, hidden row c.  The matrix is streamed from HBM once per pass; the hidden rows come from L2.
-template <int MT>
-__global__ void __launch_bounds__(256) k_lm_head_mfma(const __half *__restrict__ a, int rows, const __half *__restrict__ E,
-                                                      int V, int H, float *__restrict__ logits, Best *__restrict__ partial) {
-    __shared__ Best wbest[4][MT * 16];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
-    const int ntiles = (V + 15) >> 4, nchunk = H >> 5;
-    const __half *ar[MT];
+// Several rows of hidden states at once, exactly, on the int8 matrix instruction.  Every fp16 value is an integer
+// multiple of 2^-24, so with balanced 8-bit digits x = 2^-24 sum_j 256^j d_j, d_j in [-128, 127], four digits cover
+// |x| < 127.5.  A product of two such values is the sum over the digit pairs (i, j) of 256^(i + j) d_i d_j: the pairs
+// with the same i + j share an int32 accumulator (at most 4 * 2^14 * 16384 = 2^30), and the seven sums meet in fp64
+// once per logit - a few roundings of 2^-53 instead of one per column.  What was slow before: 16 fp64 matrix
+// instructions (64 clocks each) per 16 x 16 x 64 products against 16 int8 ones (16 clocks; 12 where the matrix tile
+// stays below 0.246, as embeddings do), and the passes over the matrix: up to four rows per pass with the hidden rows
+// as fp64 in LDS.  250880 x 4096, 8 rows: two passes of 560 us before, 380 us
+// now (5.4 TB/s; 450 us with every workgroup starting at column 0, the digit arithmetic and the matrix instructions
+// taken out change nothing: the 16 rows' separate 64-byte pieces are what is left, contiguous reads would take 335).
+//
+// The matrix is streamed once per 32 hidden rows: a wave owns WN tiles of 16 matrix rows (A operand) and walks their
+// columns 64 at a time; lane (row l%16, group l/16) holds columns 8 g .. +8 and 32 + 8 g .. +8 of the 64 as fp16, a
+// chunk of CH such pieces in flight in registers, and cuts them into digit planes itself (5 instructions per value).  The hidden rows' digits (k_lm_prepare) go through LDS, shared by the 8 waves, one
+// barrier per chunk.  A tile with a value of 127.5 or more in magnitude (or a NaN), and every tile if a hidden row
+// has one, is done again on the fp64 matrix instruction, where nothing bounds the values.
+constexpr int LMD_CH = 4;                  // 64-column pieces per chunk
+constexpr uint32_t LMD_BIG = 0x57f8;       // fp16 bits of 127.5
+constexpr uint32_t LMD_SMALL = 0x33e0;     // fp16 bits of 0.246: below it three digits do, and lm_planes_small holds
+
+__device__ __forceinline__ uint32_t lm_pk_max(uint32_t a, uint32_t b) {      // of the two halves
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    const us2 r = __builtin_elementwise_max(*(us2 *)&a, *(us2 *)&b);
+    return *(const uint32_t *)&r;
+}
+// three planes of four values below LMD_SMALL in magnitude (two words of two halves).  x * 2^24 + 2^23 + 0x408080 is
+// exact in fp32 and its low bytes are the digits plus 0x80, 0x80 and 0x40: one multiply-add straight from fp16
+// (conversions to and from integers run at a quarter of its rate), then byte permutations.
+__device__ __forceinline__ void lm_planes_small(uint32_t w0, uint32_t w1, int (&p)[4]) {
+    const uint32_t hb[4] = {w0 & 0xffffu, w0 >> 16, w1 & 0xffffu, w1 >> 16};
+    uint32_t u[4];
 #pragma unroll
-    for (int j = 0; j < MT; j++) ar[j] = a + (size_t)min(j * 16 + c, rows - 1) * H + g * 8;
-    Best best[MT];
+    for (int i = 0; i < 4; i++)
+        u[i] = __float_as_uint(fmaf(__half2float(__ushort_as_half((unsigned short)hb[i])), 16777216.0f, 8388608.0f + 0x408080));
+    const uint32_t a = __builtin_amdgcn_perm(u[1], u[0], 0x05010400), b = __builtin_amdgcn_perm(u[3], u[2], 0x05010400);
+    const uint32_t c = __builtin_amdgcn_perm(u[1], u[0], 0x0c0c0602), d = __builtin_amdgcn_perm(u[3], u[2], 0x0c0c0602);
+    p[0] = (int)(__builtin_amdgcn_perm(b, a, 0x05040100) ^ 0x80808080u);
+    p[1] = (int)(__builtin_amdgcn_perm(b, a, 0x07060302) ^ 0x80808080u);
+    const uint32_t t = __builtin_amdgcn_perm(d, c, 0x05040100);            // bytes 0 .. 0x7f: the digits plus 0x40
+    p[2] = (int)(((t ^ 0x80808080u) - 0x40404040u) ^ 0x80808080u);
+}
+
+__device__ __forceinline__ uint32_t lm_digits(float f) {       // bytes = the four digits (|f| < 127.5)
+    return ((uint32_t)(int)(f * 16777216.0f) + 0x80808080u) ^ 0x80808080u;
+}
+// four values' digit words -> one word per plane (byte k = value k)
+__device__ __forceinline__ void lm_planes(const uint32_t (&u)[4], int (&p)[4]) {
+    const uint32_t a = __builtin_amdgcn_perm(u[1], u[0], 0x05010400), b = __builtin_amdgcn_perm(u[3], u[2], 0x05010400);
+    const uint32_t c = __builtin_amdgcn_perm(u[1], u[0], 0x07030602), d = __builtin_amdgcn_perm(u[3], u[2], 0x07030602);
+    p[0] = (int)__builtin_amdgcn_perm(b, a, 0x05040100);
+    p[1] = (int)__builtin_amdgcn_perm(b, a, 0x07060302);
+    p[2] = (int)__builtin_amdgcn_perm(d, c, 0x05040100);
+    p[3] = (int)__builtin_amdgcn_perm(d, c, 0x07060302);
+}
+
+// LayerNorm of one hidden row per workgroup: the fp16 row to a (what the fp64 form reads), its digit planes to
+// dig[(kt * 4 + plane) * MT + row tile][lane][16 bytes], flag[row] = 1 if four digits do not cover it.  Rows beyond
+// `rows` (up to the end of the row tile) get zero digits.
+template <int PER>
+__global__ void __launch_bounds__(512) k_lm_prepare(const __half *__restrict__ x, const __half *__restrict__ g,
+                                                    const __half *__restrict__ b, float eps, int rows, int H, int MT,
+                                                    __half *__restrict__ a, uint8_t *__restrict__ dig, int *__restrict__ flag) {
+    constexpr int NT = 512;
+    __shared__ double sm[NT / 64];
+    __shared__ float smf[NT / 64];
+    const int t = blockIdx.x, mt = t >> 4, row = t & 15;
+    const __half *xr = x + (size_t)t * H;
+    const bool live = t < rows;
+    v8h v[PER];
+    double s = 0.0, q = 0.0, mean = 0.0, inv = 0.0;
+    if (live) {
 #pragma unroll
-    for (int j = 0; j < MT; j++) best[j] = Best{-INFINITY, 0x7fffffff};
-    for (int vt = blockIdx.x * 4 + wave; vt < ntiles; vt += gridDim.x * 4) {
-        const __half *er = E + (size_t)min(vt * 16 + c, V - 1) * H + g * 8;
-        v4d acc[MT];
+        for (int i = 0; i < PER; i++) {
+            const int k = (threadIdx.x + i * NT) * 8;
+            if (k < H) {
+                v[i] = *(const v8h_any *)(xr + k);
 #pragma unroll
-        for (int j = 0; j < MT; j++) acc[j] = (v4d){0.0, 0.0, 0.0, 0.0};
-        for (int ch = 0; ch < nchunk; ch += 2) {          // H is a multiple of 64: two 32-column chunks per round
-            v8h e0 = __builtin_nontemporal_load((const v8h *)(er + (size_t)ch * 32));
-            v8h e1 = __builtin_nontemporal_load((const v8h *)(er + (size_t)(ch + 1) * 32));
-            v8h b0[MT], b1[MT];
-#pragma unroll
-            for (int j = 0; j < MT; j++) {
-                b0[j] = *(const v8h *)(ar[j] + (size_t)ch * 32);
-                b1[j] = *(const v8h *)(ar[j] + (size_t)(ch + 1) * 32);
-            }
-#pragma unroll
-            for (int q = 0; q < 8; q++) {
-                const double ea = (double)(float)e0[q];
-#pragma unroll
-                for (int j = 0; j < MT; j++)
-                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ea, (double)(float)b0[j][q], acc[j], 0, 0, 0);
-            }
-#pragma unroll
-            for (int q = 0; q < 8; q++) {
-                const double ea = (double)(float)e1[q];
-#pragma unroll
-                for (int j = 0; j < MT; j++)
-                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ea, (double)(float)b1[j][q], acc[j], 0, 0, 0);
+                for (int e = 0; e < 8; e++) s += (double)(float)v[i][e];
             }
         }
+        mean = block_sum<NT / 64>(s, sm) / (double)H;
 #pragma unroll
-        for (int j = 0; j < MT; j++) {
-            const int t = j * 16 + c;
+        for (int i = 0; i < PER; i++) {
+            if ((int)(threadIdx.x + i * NT) * 8 < H) {
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int v = vt * 16 + 4 * r + g;
-                if (t < rows && v < V) {
-                    if (logits) logits[(size_t)t * V + v] = (float)acc[j][r];
-                    take_better(best[j], acc[j][r], v);
+                for (int e = 0; e < 8; e++) {
+                    const double d = (double)(float)v[i][e] - mean;
+                    q += d * d;
                 }
             }
         }
+        inv = 1.0 / sqrt(block_sum<NT / 64>(q, sm) / (double)H + (double)eps);
     }
-    // the four lane groups of a wave hold candidates of the same hidden rows, then the four waves
+    bool big = false;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int k = (threadIdx.x + i * NT) * 8;
+        if (k < H) {
+            __half out[8];
+            int lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
+            if (live) {
+                const v8h gv = *(const v8h_any *)(g + k), bv = *(const v8h_any *)(b + k);
+                uint32_t u[2][4];
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    out[e] = d2h_rn(((double)(float)v[i][e] - mean) * inv * (double)(float)gv[e] + (double)(float)bv[e]);
+                    big |= (__half_as_ushort(out[e]) & 0x7fffu) >= LMD_BIG;
+                    u[e >> 2][e & 3] = lm_digits(__half2float(out[e]));
+                }
+                *(v8h *)(a + (size_t)t * H + k) = *(const v8h *)out;
+                lm_planes(u[0], lo);
+                lm_planes(u[1], hi);
+            }
+            // columns 64 kt + 32 h + 8 g .. +8: bytes 8 h .. +8 of lane (g, row)
+            const int kt = k >> 6, h = (k >> 5) & 1, gg = (k >> 3) & 3;
+#pragma unroll
+            for (int pl = 0; pl < 4; pl++)
+                *(v2i *)(dig + (((size_t)(kt * 4 + pl) * MT + mt) * 64 + gg * 16 + row) * 16 + h * 8) = (v2i){lo[pl], hi[pl]};
+        }
+    }
+    const float any = block_max<NT / 64>(big ? 1.0f : 0.0f, smf);
+    if (threadIdx.x == 0) flag[t] = any > 0.0f ? 1 : 0;
+}
+
+// the fp64 form of one wave's products: 16 matrix rows x MT tiles of 16 hidden rows.  Lane (row l%16, group l/16)
+// feeds 8 consecutive values of its matrix row and of its hidden row to 8 instructions - any pairing of the
+// contraction index works as long as both operands use the same one.  Register r of lane (g, c): matrix row 4r + g.
+template <int MT>
+__device__ __forceinline__ void lm_tile_f64(const __half *__restrict__ er, const __half *__restrict__ a, int rows, int H,
+                                                      v4d (&acc)[MT]) {
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < MT; j++) acc[j] = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int k = 0; k < H; k += 32) {
+        const v8h e = *(const v8h *)(er + k);
+#pragma unroll
+        for (int j = 0; j < MT; j++) {
+            const v8h x = *(const v8h *)(a + (size_t)min(j * 16 + c, rows - 1) * H + g * 8 + k);
+#pragma unroll
+            for (int q = 0; q < 8; q++)
+                acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(float)e[q], (double)(float)x[q], acc[j], 0, 0, 0);
+        }
+    }
+}
+
+template <int WN, int MT>
+__global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restrict__ a, const uint8_t *__restrict__ dig,
+                                                           const int *__restrict__ flag, int rows, const __half *__restrict__ E,
+                                                           int V, int H, float *__restrict__ logits, Best *__restrict__ partial) {
+    constexpr int CH = LMD_CH, CHUNK = CH * 4 * MT * 1024, SR = CHUNK / (512 * 16);
+    __shared__ __align__(16) unsigned char stage[2][CHUNK];
+    __shared__ Best wbest[8][MT * 16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int KT = H >> 6, nch = (KT + CH - 1) / CH, ntiles = (V + 15) >> 4;
+    const size_t dig_last = (size_t)KT * 4 * MT * 1024 - 16;
+    const bool all_f64 = __syncthreads_or(threadIdx.x < (unsigned)rows ? flag[threadIdx.x] : 0);
+    const bool wide_store = logits && V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
+    Best best[MT];
+#pragma unroll
+    for (int j = 0; j < MT; j++) best[j] = Best{-INFINITY, 0x7fffffff};
+
+    // The pipeline runs through the rounds of a workgroup without draining: behind the last chunk of a round come the
+    // first chunk of the next one (rows clamped into the matrix) and the digits of chunk 0.  All its requests are
+    // unconditional: where two paths with different numbers of loads in flight meet, the compiler waits for all of them.
+    v4i e[CH][WN][2], sr[SR];
+    const __half *er[WN];
+    auto row_ptrs = [&](int grp, const __half *(&ptr)[WN]) {
+#pragma unroll
+        for (int p = 0; p < WN; p++) ptr[p] = E + (size_t)min(((grp * 8 + wave) * WN + p) * 16 + c, V - 1) * H + g * 8;
+    };
+    auto load_e = [&](int u, const __half *const (&ptr)[WN], int kt) {
+#pragma unroll
+        for (int p = 0; p < WN; p++) {
+            const __half *src = ptr[p] + (size_t)min(kt, KT - 1) * 64;
+            e[u][p][0] = __builtin_nontemporal_load((const v4i *)src);
+            e[u][p][1] = __builtin_nontemporal_load((const v4i *)(src + 32));
+        }
+    };
+    auto load_s = [&](int ch) {
+#pragma unroll
+        for (int i = 0; i < SR; i++) {
+            const size_t off = (size_t)ch * CHUNK + i * 8192 + threadIdx.x * 16;
+            sr[i] = *(const v4i *)(dig + (off < dig_last ? off : dig_last));
+        }
+    };
+    auto store_s = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < SR; i++) *(v4i *)(stage[buf] + i * 8192 + threadIdx.x * 16) = sr[i];
+    };
+    // Every workgroup starts its rows at another chunk and wraps around: rows are a power of two or so of bytes apart,
+    // and with all workgroups at the same column the requests of the whole device fall on a few memory channels.
+    const int rot = (blockIdx.x >> 3) % nch;
+    int buf = 0;
+    row_ptrs(blockIdx.x, er);
+    if (!all_f64) {
+        load_s(rot);
+#pragma unroll
+        for (int u = 0; u < CH; u++) load_e(u, er, rot * CH + u);
+        store_s(0);
+    }
+    for (int grp = blockIdx.x; grp * 8 * WN < ntiles; grp += gridDim.x) {       // the same rounds for the whole workgroup
+        const int vt0 = (grp * 8 + wave) * WN;
+        const __half *en[WN];
+        row_ptrs(grp + gridDim.x, en);
+        v4i acc[WN][MT][7];
+#pragma unroll
+        for (int p = 0; p < WN; p++)
+#pragma unroll
+            for (int j = 0; j < MT; j++)
+#pragma unroll
+                for (int s = 0; s < 7; s++) acc[p][j][s] = (v4i){0, 0, 0, 0};
+        bool slow = all_f64;
+        if (!all_f64) {
+            int ch = rot;
+            for (int i_ch = 0; i_ch < nch; i_ch++, buf ^= 1) {
+                const bool last = i_ch + 1 == nch;                       // then ch_next is rot again, of the next round
+                const int ch_next = ch + 1 == nch ? 0 : ch + 1;
+                const __half *nx[WN];
+#pragma unroll
+                for (int p = 0; p < WN; p++) nx[p] = last ? en[p] : er[p];
+                load_s(ch_next);
+                lds_barrier();                   // this chunk's digits are there; everybody is done with the chunk before
+#pragma unroll
+                for (int u = 0; u < CH; u++) {
+                    const int kt = ch * CH + u;
+                    uint32_t mx = 0;                         // largest magnitude bits of this lane's values
+#pragma unroll
+                    for (int p = 0; p < WN; p++)
+#pragma unroll
+                        for (int i = 0; i < 8; i++) mx = lm_pk_max(mx, (uint32_t)e[u][p][i >> 2][i & 3] & 0x7fff7fffu);
+                    mx = max(mx & 0xffffu, mx >> 16);
+                    const bool four = __any(mx >= LMD_SMALL);
+                    v4i d[WN][4];
+                    if (!four) {
+#pragma unroll
+                        for (int p = 0; p < WN; p++)
+#pragma unroll
+                            for (int q = 0; q < 4; q++) {    // values 4 q .. +4 of this lane's 16
+                                int pl[4];
+                                lm_planes_small((uint32_t)e[u][p][q >> 1][2 * (q & 1)], (uint32_t)e[u][p][q >> 1][2 * (q & 1) + 1], pl);
+#pragma unroll
+                                for (int i = 0; i < 3; i++) d[p][i][q] = pl[i];
+                            }
+                    } else {
+#pragma unroll
+                        for (int p = 0; p < WN; p++)
+#pragma unroll
+                            for (int q = 0; q < 4; q++) {
+                                const uint32_t w0 = (uint32_t)e[u][p][q >> 1][2 * (q & 1)], w1 = (uint32_t)e[u][p][q >> 1][2 * (q & 1) + 1];
+                                const uint32_t hb[4] = {w0 & 0xffffu, w0 >> 16, w1 & 0xffffu, w1 >> 16};
+                                uint32_t dw[4];
+                                int pl[4];
+#pragma unroll
+                                for (int i = 0; i < 4; i++) dw[i] = lm_digits(__half2float(__ushort_as_half((unsigned short)hb[i])));
+                                lm_planes(dw, pl);
+#pragma unroll
+                                for (int i = 0; i < 4; i++) d[p][i][q] = pl[i];
+                            }
+                        slow |= (bool)__any(mx >= LMD_BIG);
+                    }
+                    load_e(u, nx, ch_next * CH + u);              // the same piece of the next chunk
+                    if (kt >= KT) continue;                  // ragged last chunk
+                    const unsigned char *sb = stage[buf] + (size_t)u * 4 * MT * 1024 + lane * 16;
+#pragma unroll
+                    for (int j = 0; j < 4; j++)
+#pragma unroll
+                        for (int m = 0; m < MT; m++) {
+                            const v4i xb = *(const v4i *)(sb + (j * MT + m) * 1024);
+#pragma unroll
+                            for (int i = 0; i < 3; i++)
+#pragma unroll
+                                for (int p = 0; p < WN; p++)
+                                    acc[p][m][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[p][i], xb, acc[p][m][i + j], 0, 0, 0);
+                        }
+                    if (four) {
+#pragma unroll
+                        for (int j = 0; j < 4; j++)
+#pragma unroll
+                            for (int m = 0; m < MT; m++) {
+                                const v4i xb = *(const v4i *)(sb + (j * MT + m) * 1024);
+#pragma unroll
+                                for (int p = 0; p < WN; p++)
+                                    acc[p][m][3 + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[p][3], xb, acc[p][m][3 + j], 0, 0, 0);
+                            }
+                    }
+                }
+                store_s(buf ^ 1);
+                ch = ch_next;
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < WN; p++) {
+            if (vt0 + p >= ntiles) continue;                 // wave-uniform
+            v4d val[MT];
+            if (slow) {
+                lm_tile_f64<MT>(er[p], a, rows, H, val);
+            } else {
+#pragma unroll
+                for (int j = 0; j < MT; j++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) {
+                        double t = (double)acc[p][j][6][r];
+#pragma unroll
+                        for (int s = 5; s >= 0; s--) t = t * 256.0 + (double)acc[p][j][s][r];
+                        val[j][r] = t * 0x1p-48;
+                    }
+            }
+#pragma unroll
+            for (int j = 0; j < MT; j++) {
+                const int t = j * 16 + c;
+                if (t >= rows) continue;
+                // the fp64 instruction returns matrix row 4r + g in register r of lane group g, the int8 one 4g + r
+                const int v0 = (vt0 + p) * 16 + (slow ? g : 4 * g), dv = slow ? 4 : 1;
+                if (wide_store && !slow && v0 < V)
+                    *(v4f *)(logits + (size_t)t * V + v0) = (v4f){(float)val[j][0], (float)val[j][1], (float)val[j][2], (float)val[j][3]};
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const int v = v0 + r * dv;
+                    if (v >= V) continue;
+                    if (logits && (slow || !wide_store)) logits[(size_t)t * V + v] = (float)val[j][r];
+                    take_better(best[j], val[j][r], v);
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < WN; p++) er[p] = en[p];
+    }
+    // the four lane groups of a wave hold candidates of the same hidden rows, then the waves
 #pragma unroll
     for (int j = 0; j < MT; j++) {
 #pragma unroll
@@ -186,7 +433,7 @@ __global__ void __launch_bounds__(256) k_lm_head_mfma(const __half *__restrict__
     __syncthreads();
     if (threadIdx.x < MT * 16 && (int)threadIdx.x < rows) {
         Best r = wbest[0][threadIdx.x];
-        for (int w2 = 1; w2 < 4; w2++) take_better(r, wbest[w2][threadIdx.x].v, wbest[w2][threadIdx.x].i);
+        for (int w2 = 1; w2 < 8; w2++) take_better(r, wbest[w2][threadIdx.x].v, wbest[w2][threadIdx.x].i);
         partial[threadIdx.x * LM_GROUPS + blockIdx.x] = r;
     }
 }
@@ -206,11 +453,6 @@ __global__ void __launch_bounds__(64) k_lm_pick(const Best *__restrict__ partial
 }
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
-
-int rows_per_pass(int H) {
-    int rm = (int)(LM_LDS_BUDGET / ((size_t)H * 8));
-    return rm >= 4 ? 4 : (rm >= 2 ? 2 : 1);
-}
 
 }  // namespace
 
@@ -771,9 +1013,11 @@ struct petals_client {
     petals_client_params p;
     __half *a;          // LayerNorm output of the rows of one lm_head call
     Best *partial;      // [LM_MAX_ROWS][LM_GROUPS]
+    uint8_t *dig;       // digit planes of up to LM_MAX_ROWS hidden rows: [H / 64][4][row tiles][1024]
+    int *flag;          // [LM_MAX_ROWS]
     SegStat *seg;       // [max_rows_per_call][segments of the vocabulary]: per-segment results of the sampler
     Cand *cand;         // [max_rows_per_call][segments][SAMPLE_KMAX]: per-segment candidates of top-k sampling
-    bool lds_attr_set[3];
+    bool lds_attr_set;
 };
 
 namespace {
@@ -793,6 +1037,7 @@ int petals_client_workspace_bytes(const petals_client_config *cfg, size_t *bytes
     if (!bytes) return ps_fail(PETALS_ERR_INVALID_ARG, "null pointer");
     if (int rc = check_client_config(cfg)) return rc;
     *bytes = align_up((size_t)cfg->max_rows_per_call * cfg->hidden * 2) + align_up(sizeof(Best) * LM_MAX_ROWS * LM_GROUPS) +
+             align_up((size_t)4 * LM_MAX_ROWS * cfg->hidden) + align_up(sizeof(int) * LM_MAX_ROWS) +
              align_up(sizeof(SegStat) * (size_t)cfg->max_rows_per_call * ((cfg->vocab + SAMPLE_SEG - 1) / SAMPLE_SEG)) +
              align_up(sizeof(Cand) * SAMPLE_KMAX * (size_t)cfg->max_rows_per_call * ((cfg->vocab + SAMPLE_SEG - 1) / SAMPLE_SEG));
     return PETALS_OK;
@@ -812,10 +1057,12 @@ int petals_client_create(const petals_client_config *cfg, const petals_client_pa
     c->p = *params;
     c->a = (__half *)dev_workspace;
     c->partial = (Best *)((uint8_t *)dev_workspace + align_up((size_t)cfg->max_rows_per_call * cfg->hidden * 2));
-    c->seg = (SegStat *)((uint8_t *)c->partial + align_up(sizeof(Best) * LM_MAX_ROWS * LM_GROUPS));
+    c->dig = (uint8_t *)c->partial + align_up(sizeof(Best) * LM_MAX_ROWS * LM_GROUPS);
+    c->flag = (int *)(c->dig + align_up((size_t)4 * LM_MAX_ROWS * cfg->hidden));
+    c->seg = (SegStat *)((uint8_t *)c->flag + align_up(sizeof(int) * LM_MAX_ROWS));
     c->cand = (Cand *)((uint8_t *)c->seg + align_up(sizeof(SegStat) * (size_t)cfg->max_rows_per_call *
                                                      ((cfg->vocab + SAMPLE_SEG - 1) / SAMPLE_SEG)));
-    c->lds_attr_set[0] = c->lds_attr_set[1] = c->lds_attr_set[2] = false;
+    c->lds_attr_set = false;
     *out = c;
     return PETALS_OK;
 }
@@ -850,43 +1097,40 @@ int petals_client_lm_head(petals_client *c, const void *hidden_in, int32_t M, fl
     if (M > c->cfg.max_rows_per_call) return ps_fail(PETALS_ERR_CAPACITY, "%d rows exceed max_rows_per_call %d", M, c->cfg.max_rows_per_call);
     hipStream_t st = (hipStream_t)stream;
     const int H = c->cfg.hidden, V = c->cfg.vocab;
-    HIP_TRY(ps_layernorm((const __half *)hidden_in, (const __half *)c->p.final_ln_g, (const __half *)c->p.final_ln_b,
-                         c->cfg.ln_eps, M, H, c->a, nullptr, 0.0f, st));
-    const int rm = rows_per_pass(H);
-    const __half *E = (const __half *)c->p.embeddings;
-    if (M > 4 * rm) {
-        // more rows than four passes of the one-row form cover (one matrix-core pass over 250880 x 14336 takes
-        // about as long as four of those): matrix-core form, up to 32 rows per pass
-        const int groups = min(LM_GROUPS, ((V + 15) / 16 + 3) / 4);
-        for (int m0 = 0; m0 < M; m0 += 32) {
-            const int rows = min(32, M - m0);
-            const __half *a = c->a + (size_t)m0 * H;
-            float *lg = logits_out ? logits_out + (size_t)m0 * V : nullptr;
-            if (rows > 16) k_lm_head_mfma<2><<<groups, 256, 0, st>>>(a, rows, E, V, H, lg, c->partial);
-            else k_lm_head_mfma<1><<<groups, 256, 0, st>>>(a, rows, E, V, H, lg, c->partial);
+    const __half *E = (const __half *)c->p.embeddings, *x = (const __half *)hidden_in;
+    const __half *lng = (const __half *)c->p.final_ln_g, *lnb = (const __half *)c->p.final_ln_b;
+    if (M == 1) {
+        // one row: the matrix streams at 6.6 TB/s past one fp64 multiply-add per value
+        HIP_TRY(ps_layernorm(x, lng, lnb, c->cfg.ln_eps, 1, H, c->a, nullptr, 0.0f, st));
+        const size_t lds = (size_t)H * 8;
+        if (!c->lds_attr_set) {
+            HIP_TRY(hipFuncSetAttribute((const void *)k_lm_head, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            c->lds_attr_set = true;
+        }
+        const int groups = min(LM_GROUPS, (V + LM_WAVES - 1) / LM_WAVES);
+        k_lm_head<<<groups, LM_THREADS, lds, st>>>(c->a, E, V, H, logits_out, c->partial);
+        HIP_TRY(hipGetLastError());
+        if (next_token_out) {
+            k_lm_pick<<<1, 64, 0, st>>>(c->partial, groups, next_token_out);
             HIP_TRY(hipGetLastError());
-            if (next_token_out) {
-                k_lm_pick<<<rows, 64, 0, st>>>(c->partial, groups, next_token_out + m0);
-                HIP_TRY(hipGetLastError());
-            }
         }
         return PETALS_OK;
     }
-    const int groups = min(LM_GROUPS, (V + LM_WAVES - 1) / LM_WAVES);
-    const size_t lds = (size_t)rm * H * 8;
-    const int slot = rm == 4 ? 2 : (rm == 2 ? 1 : 0);
-    if (!c->lds_attr_set[slot]) {
-        const void *fn = rm == 4 ? (const void *)k_lm_head<4> : (rm == 2 ? (const void *)k_lm_head<2> : (const void *)k_lm_head<1>);
-        HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        c->lds_attr_set[slot] = true;
-    }
-    for (int m0 = 0; m0 < M; m0 += rm) {
-        const int rows = min(rm, M - m0);
-        const __half *a = c->a + (size_t)m0 * H;
+    const int ntiles = (V + 15) / 16;
+    for (int m0 = 0; m0 < M; m0 += LM_MAX_ROWS) {
+        const int rows = min(LM_MAX_ROWS, M - m0), mt = rows > 16 ? 2 : 1;
+        const __half *xr = x + (size_t)m0 * H;
+        __half *a = c->a + (size_t)m0 * H;
         float *lg = logits_out ? logits_out + (size_t)m0 * V : nullptr;
-        if (rm == 4) k_lm_head<4><<<groups, LM_THREADS, lds, st>>>(a, rows, E, V, H, lg, c->partial);
-        else if (rm == 2) k_lm_head<2><<<groups, LM_THREADS, lds, st>>>(a, rows, E, V, H, lg, c->partial);
-        else k_lm_head<1><<<groups, LM_THREADS, lds, st>>>(a, rows, E, V, H, lg, c->partial);
+        // up to 16 rows: two matrix tiles per wave (the digits read from LDS then serve both) once that leaves every
+        // compute unit a workgroup of 8 waves; with 17 to 32 rows two tiles need more registers than there are
+        const int wn = mt == 1 && ntiles >= 256 * 16 ? 2 : 1, groups = min(LM_GROUPS, (ntiles + 8 * wn - 1) / (8 * wn));
+        if (H <= 4096) k_lm_prepare<1><<<16 * mt, 512, 0, st>>>(xr, lng, lnb, c->cfg.ln_eps, rows, H, mt, a, c->dig, c->flag);
+        else k_lm_prepare<4><<<16 * mt, 512, 0, st>>>(xr, lng, lnb, c->cfg.ln_eps, rows, H, mt, a, c->dig, c->flag);
+        HIP_TRY(hipGetLastError());
+        if (wn == 2) k_lm_head_digits<2, 1><<<groups, 512, 0, st>>>(a, c->dig, c->flag, rows, E, V, H, lg, c->partial);
+        else if (mt == 2) k_lm_head_digits<1, 2><<<groups, 512, 0, st>>>(a, c->dig, c->flag, rows, E, V, H, lg, c->partial);
+        else k_lm_head_digits<1, 1><<<groups, 512, 0, st>>>(a, c->dig, c->flag, rows, E, V, H, lg, c->partial);
         HIP_TRY(hipGetLastError());
         if (next_token_out) {
             k_lm_pick<<<rows, 64, 0, st>>>(c->partial, groups, next_token_out + m0);

@@ -13,6 +13,8 @@ typedef int v2i __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+// eight halves at any address (callers' tensors carry no alignment promise; the hardware loads them in one piece)
+typedef _Float16 v8h_any __attribute__((ext_vector_type(8), aligned(2)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 #define PS_MAX_SESSIONS 64
@@ -254,6 +256,11 @@ __device__ __forceinline__ float block_sum(float v, float *sm) {
     __syncthreads();
     return r;
 }
+// Workgroup barrier that orders the LDS traffic only.  (__syncthreads() would also wait for
+// every load from global memory in flight, e.g. for weights requested ahead.)
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
 // Keeps an fp32 value in a register as fp32: the compiler may otherwise fold "fp32 multiply,
 // then convert to fp16" into one mixed-precision instruction that rounds the exact product
 // once, which differs from the two-step result on double-rounding cases.
@@ -270,18 +277,14 @@ __device__ __forceinline__ double gelu_tanh(double v) {
     const double u = 0.7978845608028654 * (v + 0.044715 * v * v * v);
     return v / (1.0 + exp(-2.0 * u));
 }
-// double -> fp16 with ONE rounding (to nearest even): go through fp32 rounded to odd, which
-// keeps enough information for the final fp16 rounding to be exact.  Round-to-odd is built
-// from the ordinary conversion: undo a rounding away from zero, then set the sticky bit.
+// double -> fp16 with ONE rounding (to nearest even): the value is first rounded to odd at the 20 mantissa bits of
+// its high word (the low word only says whether anything lies below them), which is exact in fp32 and keeps enough
+// for the rounding to fp16 to be the only one.  (keep_f32: the compiler would otherwise see one conversion from fp64
+// to fp16, for which there is no instruction, and expand it into forty.)
 __device__ __forceinline__ __half d2h_rn(double v) {
-    float f = (float)v;
-    const double fd = (double)f;
-    if (fd != v) {
-        uint32_t u = __float_as_uint(f);
-        if (fabs(fd) > fabs(v)) u -= 1u;
-        f = __uint_as_float(u | 1u);
-    }
-    return __float2half_rn(f);
+    const uint64_t u = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32) | min(lo, 1u);
+    return __float2half_rn(keep_f32((float)__longlong_as_double((long long)((uint64_t)hi << 32))));
 }
 // int8 code of one activation/weight: fp32 product, round half to even, clamp
 __device__ __forceinline__ int q8(float x, float r) {

@@ -601,24 +601,10 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
 #pragma unroll
                     for (int e = 0; e < NE; e++) vv[e] += (double)(float)r4[e >> 2][e & 3];
                 }
-                // one rounding to fp16: through fp32 rounded to odd (see d2h_rn)
-                float ff[NE];
-#pragma unroll
-                for (int e = 0; e < NE; e++) ff[e] = (float)vv[e];
-                bool inexact[NE], away[NE];
-#pragma unroll
-                for (int e = 0; e < NE; e++) {
-                    const double fd = (double)ff[e];
-                    inexact[e] = fd != vv[e];
-                    away[e] = fabs(fd) > fabs(vv[e]);
-                }
+                // one rounding to fp16 (see d2h_rn)
                 __half out[TM][4];
 #pragma unroll
-                for (int e = 0; e < NE; e++) {
-                    uint32_t u = __float_as_uint(ff[e]);
-                    u = inexact[e] ? ((away[e] ? u - 1u : u) | 1u) : u;
-                    out[e >> 2][e & 3] = __float2half_rn(__uint_as_float(u));
-                }
+                for (int e = 0; e < NE; e++) out[e >> 2][e & 3] = d2h_rn(vv[e]);
                 // (pins the arithmetic above this point: otherwise the compiler sinks each token tile's share of it
                 // into that tile's conditional store below, and the chains no longer overlap)
                 v2i packed[TM];

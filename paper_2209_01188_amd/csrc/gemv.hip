@@ -68,12 +68,6 @@ __device__ __forceinline__ double outlier_group(const v4i &w, uint32_t bits, con
 
 constexpr int GEMV_GROUP = 512;      // 8 waves share one 16-row panel at a time
 
-// Workgroup barrier of the row preparation: it orders the LDS traffic only.  (__syncthreads() would also wait for
-// every load from global memory in flight, i.e. for the weight chunks requested ahead.)
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Persistent-style one-row linear.  The grid is sized so that every workgroup is resident at
 // once (up to two per compute unit) and owns a contiguous range of 16-row panels.  Each workgroup
 //  1. (LN variant) normalises the row in fp64,

@@ -166,63 +166,124 @@ __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restric
     }
 }
 
-// Many rows (a prefill-size call): 256 threads per row and 16-byte loads, so that a compute unit holds eight rows
-// in different phases (loading, reducing, storing) instead of two; with two, memory idles during the reductions.
-// The elements a thread sums differ from the kernels above, i.e. the fp64 sums are rounded in another order.
-template <int PER>
-__global__ void __launch_bounds__(256) k_layernorm_rows(const __half *__restrict__ x, const __half *__restrict__ g,
-                                                        const __half *__restrict__ b, float eps, int H,
-                                                        __half *__restrict__ y, uint32_t *__restrict__ mask,
-                                                        float theta) {
+// Many rows (a prefill-size call): 256 threads per row and 16-byte loads.  A workgroup takes every gridDim.x-th row;
+// the next row is requested before the current one is reduced, so a compute unit's few workgroups keep memory busy,
+// and the outlier columns of all its rows are flagged ONCE, at the end.  (One workgroup per row sent every row's
+// flags to the same few words of the mask: an outlier feature is one in every row, another XCD's bits are not seen
+// in this one's L2, and the memory takes 7 ns per access to one address - 4096 rows of 4096 with four outlier
+// columns: 58 us, without any 28 us.)  The elements a thread sums differ from the kernels above, i.e. the fp64 sums
+// are rounded in another order.  PER chunks of 8 columns per thread (H <= 2048 PER).  Q8: the rows arrive as 8-bit
+// codes, see k_layernorm_q8.
+template <int PER, bool Q8>
+__global__ void __launch_bounds__(256) k_layernorm_rows(const __half *__restrict__ x, QuantIn qin,
+                                                        const __half *__restrict__ g, const __half *__restrict__ b,
+                                                        float eps, int M, int H, __half *__restrict__ y,
+                                                        uint32_t *__restrict__ mask, float theta) {
     constexpr int NT = 256;
     __shared__ double sm[NT / 64];
-    const __half *xr = x + (size_t)blockIdx.x * H;
-    __half *yr = y + (size_t)blockIdx.x * H;
-    v8h v[PER];
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < PER; i++) {
-        const int k = (threadIdx.x + i * NT) * 8;
-        if (k < H) {
-            v[i] = *(const v8h *)(xr + k);
-#pragma unroll
-            for (int e = 0; e < 8; e++) s += (double)(float)v[i][e];
-        }
+    __shared__ float table[Q8 ? 256 : 1];
+    if constexpr (Q8) {
+        table[threadIdx.x] = d_code_table.code[threadIdx.x];
+        __syncthreads();
     }
-    const double mean = block_sum<NT / 64>(s, sm) / (double)H;
-    double q = 0.0;
+    // raw bits of the row in flight: fp16 values, or 8 codes and their block's maximum
+    struct Raw {
+        v8h h;
+        uint2 q;
+        float am;
+    };
+    Raw nx[PER];
+    auto request = [&](int row) {
+        const size_t row0 = (size_t)row * H;
 #pragma unroll
-    for (int i = 0; i < PER; i++) {
-        if ((int)(threadIdx.x + i * NT) * 8 < H) {
+        for (int i = 0; i < PER; i++) {
+            const int k = (threadIdx.x + i * NT) * 8;
+            if (k < H) {
+                if constexpr (Q8) {                          // H and the codec block are multiples of 8: one block per chunk
+                    nx[i].q = *(const uint2 *)(qin.q + row0 + k);
+                    nx[i].am = qin.absmax[(row0 + k) / (size_t)qin.block];
+                } else {
+                    nx[i].h = *(const v8h_any *)(x + row0 + k);
+                }
+            }
+        }
+    };
+    uint32_t flags[PER] = {};
+    if ((int)blockIdx.x < M) request(blockIdx.x);
+    for (int row = blockIdx.x; row < M; row += gridDim.x) {
+        const size_t row0 = (size_t)row * H;
+        v8h v[PER];
 #pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const double a = (double)(float)v[i][e] - mean;
-                q += a * a;
+        for (int i = 0; i < PER; i++) {
+            const int k = (threadIdx.x + i * NT) * 8;
+            if (k < H) {
+                if constexpr (Q8) {
+                    __half dec[8];
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        dec[e] = decode_q8(table, ((e < 4 ? nx[i].q.x : nx[i].q.y) >> ((e & 3) * 8)) & 255u, nx[i].am);
+                    v[i] = *(const v8h *)dec;
+                    *(v8h *)(qin.x_out + row0 + k) = v[i];
+                } else {
+                    v[i] = nx[i].h;
+                }
+            }
+        }
+        if (row + (int)gridDim.x < M) request(row + gridDim.x);
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            if ((int)(threadIdx.x + i * NT) * 8 < H) {
+#pragma unroll
+                for (int e = 0; e < 8; e++) s += (double)(float)v[i][e];
+            }
+        }
+        const double mean = block_sum<NT / 64>(s, sm) / (double)H;
+        double q = 0.0;
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            if ((int)(threadIdx.x + i * NT) * 8 < H) {
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const double a = (double)(float)v[i][e] - mean;
+                    q += a * a;
+                }
+            }
+        }
+        const double inv = 1.0 / sqrt(block_sum<NT / 64>(q, sm) / (double)H + (double)eps);
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            const int k = (threadIdx.x + i * NT) * 8;
+            if (k < H) {
+                const v8h gv = *(const v8h_any *)(g + k), bv = *(const v8h_any *)(b + k);
+                __half out[8];
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    out[e] = d2h_rn(((double)(float)v[i][e] - mean) * inv * (double)(float)gv[e] + (double)(float)bv[e]);
+                    flags[i] |= (fabsf(__half2float(out[e])) >= theta ? 1u : 0u) << e;
+                }
+                *(v8h *)(y + row0 + k) = *(const v8h *)out;
             }
         }
     }
-    const double inv = 1.0 / sqrt(block_sum<NT / 64>(q, sm) / (double)H + (double)eps);
+    if (mask) {
 #pragma unroll
-    for (int i = 0; i < PER; i++) {
-        const int k = (threadIdx.x + i * NT) * 8;
-        if (k < H) {
-            const v8h gv = *(const v8h *)(g + k), bv = *(const v8h *)(b + k);
-            v8h ov;
-            uint32_t bits = 0;
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                const __half2 o = ln_affine(__halves2half2(__float2half((float)v[i][e]), __float2half((float)v[i][e + 1])),
-                                            __halves2half2(__float2half((float)gv[e]), __float2half((float)gv[e + 1])),
-                                            __halves2half2(__float2half((float)bv[e]), __float2half((float)bv[e + 1])),
-                                            mean, inv);
-                ov[e] = (_Float16)__half2float(o.x);
-                ov[e + 1] = (_Float16)__half2float(o.y);
-                bits |= (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) << e | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u) << e;
-            }
-            *(v8h *)(yr + k) = ov;
-            if (mask) flag_outlier_bits(mask, k >> 5, bits << (k & 31));
+        for (int i = 0; i < PER; i++) {
+            const int k = (threadIdx.x + i * NT) * 8;
+            if (k < H) flag_outlier_bits(mask, k >> 5, flags[i] << (k & 31));
         }
     }
+}
+
+constexpr int LN_ROWS_GRID = 1024;
+
+template <bool Q8>
+void launch_layernorm_rows(const __half *x, const QuantIn &qin, const __half *g, const __half *b, float eps, int M, int H,
+                           __half *y, uint32_t *mask, float theta, hipStream_t st) {
+    const int grid = M < LN_ROWS_GRID ? M : LN_ROWS_GRID;
+    if (H <= 4096) k_layernorm_rows<2, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
+    else if (H <= 8192) k_layernorm_rows<4, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
+    else k_layernorm_rows<8, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
 }
 
 // -------------------------------------------------- many rows: mask, then quantize
@@ -636,7 +697,7 @@ hipError_t ps_copy_bytes(const void *src, void *dst, size_t n, hipStream_t st) {
 hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float eps, int M, int H, __half *y,
                         uint32_t *mask, float theta, hipStream_t st) {
     // few rows: more threads per row (latency), many rows: more rows in flight
-    if (M >= 512 && H % 8 == 0 && H >= 4096 && H <= 16384) k_layernorm_rows<8><<<M, 256, 0, st>>>(x, g, b, eps, H, y, mask, theta);
+    if (M >= 512 && H % 8 == 0 && H <= 16384) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
     else if (H >= 4096 && H <= 16384) k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     else if (M <= 256 && H >= 4096) k_layernorm<1024><<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     else k_layernorm<256><<<M, 256, 0, st>>>(x, g, b, eps, H, y, mask, theta);
@@ -644,7 +705,9 @@ hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
                            int H, __half *y, uint32_t *mask, float theta, hipStream_t st) {
-    if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, theta);
+    if (M >= 512 && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
+        launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, theta, st);
+    else if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, theta);
     else k_layernorm_q8<256><<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, theta);
     return hipGetLastError();
 }

@@ -1,0 +1,58 @@
+"""LayerNorm of calls of many rows (a workgroup takes several rows and flags the outlier columns of all of them once)
+and the rounding of fp64 to fp16, against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import oracle  # noqa: E402
+from paper_2209_01188_amd import binding, synth  # noqa: E402
+from tests.gpu_util import DEV, build_pair, to_dev, to_np  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+# rows: the smallest call of this form, one row per workgroup or several, a last round of few rows; hidden: every
+# register-chunk count and its edges
+@pytest.mark.parametrize("M,H,nh", [(512, 64, 4), (1023, 1024, 16), (1025, 2048, 16), (2049, 192, 3), (513, 4096, 32),
+                                    (520, 4160, 65), (700, 8192, 64), (515, 8256, 129), (513, 16384, 128)])
+def test_layernorm_of_many_rows(M, H, nh):
+    r = np.random.default_rng(M + H)
+    span = binding.Span(1, H, nh, 64, M, device=DEV)
+    p = {n: torch.zeros(s, dtype=torch.float32, device=DEV)
+         for n, s in (("w_qkv", (3 * H, H)), ("w_dense", (H, H)), ("w_up", (64, H)), ("w_down", (H, 64)))}
+    for n, s in (("b_qkv", 3 * H), ("b_dense", H), ("b_up", 64), ("b_down", H)):
+        p[n] = torch.zeros(s, dtype=torch.float16, device=DEV)
+    host = {n: r.normal(1.0 if n.endswith("g") else 0.0, 0.3, H).astype(np.float16) for n in ("ln1_g", "ln1_b", "ln2_g", "ln2_b")}
+    span.load_block(0, dict(p, **{n: to_dev(v) for n, v in host.items()}))
+    x = r.standard_normal((M, H)).astype(np.float16)
+    x[r.integers(0, M, 3), r.integers(0, H, 3)] = 60.0         # outliers in a few rows only
+    x[M - 1, H - 1] = -90.0                                    # and in the very last value
+    got = span.debug_layernorm(0, 1, to_dev(x), want_quantized=True)
+    ref = oracle.layernorm(x, host["ln2_g"], host["ln2_b"])
+    assert np.array_equal(to_np(got["y"]).view(np.uint16), ref.view(np.uint16))
+    assert np.array_equal(to_np(got["mask"]).astype(bool), (np.abs(ref.astype(np.float32)) >= 6.0).any(0))
+    span.close()
+
+
+@pytest.mark.parametrize("B,T,H,block", [(2, 256, 64, 64), (3, 171, 192, 4096), (1, 1025, 128, 1024)])
+def test_codes_of_many_rows_as_span_input(B, T, H, block):
+    cfg = synth.SpanConfig("rows", 2, H, H // 32, B, T, 1, 1, (20.0, 40.0), 7)
+    _, span, _ = build_pair(cfg, max_rows=B * T)
+    x = to_dev(synth.hidden_states(cfg, 0, B, T))
+    n = x.numel()
+    q, am = torch.empty(n, dtype=torch.uint8, device=DEV), torch.empty(-(-n // block), dtype=torch.float32, device=DEV)
+    binding.petals_hidden_quantize(x, block, q, am)
+    dec = torch.empty_like(x)
+    binding.petals_hidden_dequantize(q, am, block, dec)
+    a = [span.open_session(T) for _ in range(B)]
+    b = [span.open_session(T) for _ in range(B)]
+    want = span.prefill(a, dec)
+    got = span.prefill_q8(b, T, q, am, block)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    for s, t in zip(a, b):
+        for blk in range(2):
+            assert torch.equal(s.export_kv(blk).view(torch.int16), t.export_kv(blk).view(torch.int16))
+    span.close()
