@@ -4,9 +4,13 @@
 // wave-local online softmax, k_attn_combine merges the key ranges.  Prefill (several queries per
 // session): k_attn_prefill on the fp64 matrix instruction; for the backward pass it can also store the
 // log of the softmax denominators and the context before its fp16 rounding.
+#include <mutex>
+
 #include "common.h"
 
 namespace {
+
+constexpr int ATTN_SPLIT_BELOW = 256;
 
 __global__ void k_set_table(SessTable t, SessTable *dst) {
     // 64 threads copy the table word by word
@@ -177,6 +181,170 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
     }   // pass
 }
 
+// N consecutive halves at an address aligned to min(16, 2 N) bytes
+template <int N>
+__device__ __forceinline__ void load_halves(const __half *p, __half (&dst)[N]) {
+    if constexpr (N >= 8) {
+#pragma unroll
+        for (int i = 0; i < N / 8; i++) *(v8h *)(dst + 8 * i) = *(const v8h *)(p + 8 * i);
+    } else if constexpr (N == 4) {
+        *(v4h *)dst = *(const v4h *)p;
+    } else if constexpr (N == 2) {
+        *(__half2 *)dst = *(const __half2 *)p;
+    } else {
+        dst[0] = *p;
+    }
+}
+
+// The same attention for launches of few workgroups (short prompts, few sessions and heads: 128 tokens x 16 heads
+// made 16 workgroups of k_attn_prefill, and 33 us of a 120 us block).  A workgroup owns ONE tile of 16 queries; its
+// NWK waves share out the KEY tiles (wave w takes tiles w, w + NWK, ...), each with its own online softmax, and the
+// states meet in LDS at the end, added in wave order.  No operand is shared between waves, so every lane loads its
+// fragments of the next key tile straight into registers (both products' A operands are consecutive halves of a key
+// or value row) and converts them itself: twice the conversions of the other form per matrix instruction, but 8 times
+// as many workgroups with a quarter of the chain.  Operand layouts and arithmetic as in k_attn_prefill.
+template <int D, int NWK>
+__global__ void __launch_bounds__(64 * NWK) k_attn_prefill_split(const __half *__restrict__ q, const SessTable *__restrict__ sess,
+                                                                 int blk, int B, int T, int nh, __half *__restrict__ ctx,
+                                                                 uint32_t *__restrict__ mask, float theta,
+                                                                 float *__restrict__ lse, float *__restrict__ ctx32) {
+    constexpr int DS = D / 4, NB = D / 16;
+    extern __shared__ __align__(16) double part[];   // [NWK][4 r][NB b][64 lanes] outputs, then [NWK][16] m, [NWK][16] l
+    double *pm = part + NWK * 4 * NB * 64, *pl = pm + NWK * 16;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    // all query tiles of one (session, head) on one XCD, those with the most keys first
+    const int nqt = (T + 15) / 16, grp = blockIdx.x / (8 * nqt), rem = blockIdx.x - grp * 8 * nqt;
+    const int pair = grp * 8 + (rem & 7), qt = nqt - 1 - (rem >> 3);
+    if (pair >= B * nh) return;                       // the whole workgroup
+    const int s = pair / nh, h = pair - s * nh;
+    const int L = sess->len[s], cap = sess->cap[s], H = nh * D;
+    const __half *Kc = sess->kv[s] + ((size_t)blk * 2 * nh + h) * cap * D;
+    const __half *Vc = Kc + (size_t)nh * cap * D;
+    const double slope = sess->slopes[h], inv_rsd = 1.0 / sqrt((double)D);
+    const int last_key = L + T - 1, tq = qt * 16 + c, qpos = L + tq;
+    const size_t qrow = (size_t)s * T + min(tq, T - 1);
+    const int nkt = min(L + qt * 16 + 15, last_key) / 16 + 1;
+
+    __half kn[DS], vn[4][NB];
+    auto fetch = [&](int kt) {                        // this lane's fragments of a key tile (rows clamped to the newest key)
+        load_halves<DS>(Kc + (size_t)min(kt * 16 + c, last_key) * D + g * DS, kn);
+#pragma unroll
+        for (int r = 0; r < 4; r++) load_halves<NB>(Vc + (size_t)min(kt * 16 + 4 * r + g, last_key) * D + c * NB, vn[r]);
+    };
+    fetch(min(wave, nkt - 1));
+    double qd[DS];
+    {
+        __half qh[DS];
+        load_halves<DS>(q + qrow * H + h * D + g * DS, qh);
+#pragma unroll
+        for (int e = 0; e < DS; e++) qd[e] = (double)__half2float(qh[e]) * inv_rsd;
+    }
+    v4d O[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) O[b] = (v4d){0.0, 0.0, 0.0, 0.0};
+    double m_run = -INFINITY, l_run = 0.0;
+    for (int kt = wave; kt < nkt; kt += NWK) {
+        __half kc[DS], vc[4][NB];
+#pragma unroll
+        for (int e = 0; e < DS; e++) kc[e] = kn[e];
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+#pragma unroll
+            for (int b = 0; b < NB; b++) vc[r][b] = vn[r][b];
+        fetch(min(kt + NWK, nkt - 1));
+        constexpr int NCH = DS >= 16 ? 4 : (DS >= 8 ? 2 : 1);
+        v4d Sp[NCH];
+#pragma unroll
+        for (int i = 0; i < NCH; i++) Sp[i] = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < DS; e++)
+            Sp[e % NCH] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__half2float(kc[e]), qd[e], Sp[e % NCH], 0, 0, 0);
+        v4d S = Sp[0];
+#pragma unroll
+        for (int i = 1; i < NCH; i++) S += Sp[i];
+        double sc[4], mt = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int kpos = kt * 16 + 4 * r + g;
+            sc[r] = (kpos <= qpos && kpos <= last_key) ? S[r] - slope * (double)(qpos - kpos) : -INFINITY;
+            mt = fmax(mt, sc[r]);
+        }
+        mt = fmax(mt, __shfl_xor(mt, 16));
+        mt = fmax(mt, __shfl_xor(mt, 32));
+        const double m_new = fmax(m_run, mt);         // -infinity while this wave has seen no key of this query
+        const double alpha = (m_run == -INFINITY) ? 0.0 : exp(m_run - m_new);
+        double p[4], psum = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            p[r] = (sc[r] == -INFINITY) ? 0.0 : exp(sc[r] - m_new);
+            psum += p[r];
+        }
+        l_run = l_run * alpha + psum;
+        m_run = m_new;
+#pragma unroll
+        for (int b = 0; b < NB; b++) O[b] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+#pragma unroll
+            for (int b = 0; b < NB; b++)
+                O[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__half2float(vc[r][b]), p[r], O[b], 0, 0, 0);
+    }
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+    // states of the waves -> LDS; wave r < 4 finishes register r of every output block
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+#pragma unroll
+        for (int b = 0; b < NB; b++) part[((wave * 4 + r) * NB + b) * 64 + lane] = O[b][r];
+    if (g == 0) { pm[wave * 16 + c] = m_run; pl[wave * 16 + c] = l_run; }
+    __syncthreads();
+    if (wave >= 4 || tq >= T) return;
+    double m = pm[c], l = 0.0, o[NB], f[NWK];
+#pragma unroll
+    for (int w = 1; w < NWK; w++) m = fmax(m, pm[w * 16 + c]);     // key 0 is visible to every query: finite
+#pragma unroll
+    for (int w = 0; w < NWK; w++) {
+        f[w] = exp(pm[w * 16 + c] - m);
+        l += f[w] * pl[w * 16 + c];
+    }
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        o[b] = 0.0;
+#pragma unroll
+        for (int w = 0; w < NWK; w++) o[b] += f[w] * part[((w * 4 + wave) * NB + b) * 64 + lane];
+    }
+    if (lse && g == 0 && wave == 0) lse[(size_t)h * B * T + qrow] = (float)(m + log(l));
+    const int d0 = (4 * wave + g) * NB;               // NB consecutive dims
+    __half *dst = ctx + qrow * H + h * D + d0;
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        const double v = o[b] / l;
+        const __half hv = d2h_rn(v);
+        dst[b] = hv;
+        flag_outlier(mask, theta, h * D + d0 + b, hv);
+        if (ctx32) ctx32[qrow * H + h * D + d0 + b] = (float)v;
+    }
+}
+
+template <int D, int NWK>
+hipError_t launch_prefill_split(const __half *q, const SessTable *sess, int blk, int B, int T, int nh, __half *ctx, uint32_t *mask,
+                                float theta, float *lse, float *ctx32, hipStream_t st) {
+    const size_t lds = ((size_t)NWK * 4 * (D / 16) * 64 + 2 * NWK * 16) * 8;
+    auto kern = k_attn_prefill_split<D, NWK>;
+    if (lds > 64 * 1024) {
+        static std::mutex attr_lock;
+        static bool attr_set = false;
+        std::lock_guard<std::mutex> hold(attr_lock);
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    kern<<<(B * nh + 7) / 8 * 8 * ((T + 15) / 16), 64 * NWK, lds, st>>>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32);
+    return hipGetLastError();
+}
+
 // softmax state of a set of keys: running maximum m, sum l of exp(z - m), weighted value sum o
 __device__ __forceinline__ void merge_state(double &m, double &l, double *o, double m2, double l2, const double *o2,
                                             int n) {
@@ -339,6 +507,14 @@ hipError_t attn_launch(const __half *q, const SessTable *sess, int blk, int M, i
     if (nsplit == 1) CH = 1 << 30;
     if (T > 1 || lse) {   // the matrix-core kernel also covers T = 1; it is the one that can report the denominators
         const int B = M / T;
+        // Few workgroups of the shared-tile form (64 to 128 queries each): 16-query workgroups that split the keys.
+        // The line: one workgroup of the shared form per compute unit (128 tokens, 16 heads of 64: 33 -> 8 us; 3 x 117 tokens, 32 heads of 128: 94 -> 40 us;
+        // at 256 workgroups and more the shared conversions win).
+        if (B * nh * (((T + 63) / 64 + 1) / 2) < ATTN_SPLIT_BELOW) {
+            if (max_keys > 512 && B * nh * ((T + 15) / 16) <= 256)
+                return launch_prefill_split<D, 8>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32, st);
+            return launch_prefill_split<D, 4>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32, st);
+        }
         k_attn_prefill<D><<<(B * nh + 7) / 8 * 8 * (((T + 63) / 64 + 1) / 2), 256, (size_t)2 * 2 * 16 * D * 8, st>>>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32);
         return hipGetLastError();
     }

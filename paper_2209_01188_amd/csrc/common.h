@@ -149,14 +149,14 @@ hipError_t ps_gemv_row(const LinearW &w, const __half *x, const __half *ln_g, co
 // full_list (may be null): receives the ascending list of all outlier columns when they are more than that
 hipError_t ps_outlier_prep(const LinearW &w, const uint32_t *mask, const __half *X, int M, int *count, double *wd64,
                            double *x64, int *full_list, hipStream_t st);
-// batched-decode linear, 2 <= M <= 64 rows (int8 MFMA, outlier columns exactly on fp64 MFMA inside the
+#define PS_CHUNKED_ROWS_MAX 512
+// batched-decode linear, 2 <= M <= PS_CHUNKED_ROWS_MAX rows, 64 per workgroup (int8 MFMA, outlier columns exactly on fp64 MFMA inside the
 // loop); xq_tiled and xo_tiled as written by ps_rowquant_tiled
 hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,
                    const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, hipStream_t st);
-// Calls of more than 64 rows that are better served by ps_gemm on 64 rows at a time (each pass streams the
-// weights once, with every compute unit busy) than by the 256 x 256 output blocks of ps_gemm_lds, which
+// Calls of more than 64 rows that are better served by ps_gemm, 64 rows per workgroup (the weights are streamed once
+// per 64 rows, with every compute unit busy) than by the 256 x 256 output blocks of ps_gemm_lds, which
 // leave most of the GPU idle when the call has few of them.  PS_CHUNKED_ROWS_MAX bounds such calls.
-#define PS_CHUNKED_ROWS_MAX 512
 bool ps_gemm_prefers_chunks(const LinearW &w, int M);
 
 // attention of M = B*T query rows against the caches (new keys/values already appended)

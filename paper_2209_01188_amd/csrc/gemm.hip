@@ -112,7 +112,26 @@ __global__ void __launch_bounds__(64 * WVK)
 k_gemm(LinearW w, const int8_t *__restrict__ xq_tiled, const int8_t *__restrict__ xo_tiled,
        const uint32_t *__restrict__ mask, const __half *__restrict__ X, const float *__restrict__ sx, int M,
        OutDesc o, const SessTable *__restrict__ sess) {
-    const int K = w.K, KT = K >> 6, N = w.N, MTT = (M + 15) >> 4;
+    const int K = w.K, KT = K >> 6, N = w.N;
+    if (gridDim.y > 1) {
+        // a call of more than 64 rows: blockIdx.y takes rows 64 y .. +64 of it
+        const int r0 = blockIdx.y * 64;
+        const size_t at = (size_t)r0 * N;
+        xq_tiled += (size_t)(r0 >> 4) * KT * 1024;
+        xo_tiled += (size_t)(r0 >> 4) * KT * 1024;
+        X += (size_t)r0 * K;
+        sx += r0;
+        M = min(64, M - r0);
+        if (o.scatter) {
+            o.t0 = r0;
+        } else {
+            o.y += at;
+            if (o.resid) o.resid += at;
+            if (o.pre_out) o.pre_out += at;
+        }
+        if (o.acc_out) o.acc_out += at;
+    }
+    const int MTT = (M + 15) >> 4;
     const int wk = threadIdx.x >> 6, lane = threadIdx.x & 63, row = lane & 15, kg = lane >> 4;
     const int nt0 = blockIdx.x * WN;
 
@@ -273,7 +292,7 @@ hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_til
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    k_gemm<WN, MT, UK, WVK><<<w.N / (16 * WN), 64 * WVK, lds, st>>>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess);
+    k_gemm<WN, MT, UK, WVK><<<dim3(w.N / (16 * WN), (M + 63) / 64), 64 * WVK, lds, st>>>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess);
     return hipGetLastError();
 }
 
@@ -331,7 +350,7 @@ hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_ti
         if (wn == 2) PS_GEMM_CASE(2, 2, 2);
         PS_GEMM_CASE(1, 2, 2);
     }
-    if (M <= 64) {
+    if (M <= PS_CHUNKED_ROWS_MAX) {   // more than 64 rows: 64 per workgroup, see the kernel
         if (wn >= 2) PS_GEMM_CASE(2, 4, 1);
         PS_GEMM_CASE(1, 4, 1);
     }

@@ -281,7 +281,8 @@ template <bool Q8>
 void launch_layernorm_rows(const __half *x, const QuantIn &qin, const __half *g, const __half *b, float eps, int M, int H,
                            __half *y, uint32_t *mask, float theta, hipStream_t st) {
     const int grid = M < LN_ROWS_GRID ? M : LN_ROWS_GRID;
-    if (H <= 4096) k_layernorm_rows<2, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
+    if (H <= 2048) k_layernorm_rows<1, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
+    else if (H <= 4096) k_layernorm_rows<2, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
     else if (H <= 8192) k_layernorm_rows<4, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
     else k_layernorm_rows<8, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
 }
@@ -697,7 +698,7 @@ hipError_t ps_copy_bytes(const void *src, void *dst, size_t n, hipStream_t st) {
 hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float eps, int M, int H, __half *y,
                         uint32_t *mask, float theta, hipStream_t st) {
     // few rows: more threads per row (latency), many rows: more rows in flight
-    if (M >= 512 && H % 8 == 0 && H <= 16384) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
+    if ((M >= 512 || H < 4096) && H % 8 == 0 && H <= 16384) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
     else if (H >= 4096 && H <= 16384) k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     else if (M <= 256 && H >= 4096) k_layernorm<1024><<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     else k_layernorm<256><<<M, 256, 0, st>>>(x, g, b, eps, H, y, mask, theta);
@@ -705,7 +706,7 @@ hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
                            int H, __half *y, uint32_t *mask, float theta, hipStream_t st) {
-    if (M >= 512 && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
+    if ((M >= 512 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
         launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, theta, st);
     else if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, theta);
     else k_layernorm_q8<256><<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, theta);

@@ -9,7 +9,7 @@ if not torch.cuda.is_available():
 
 import oracle  # noqa: E402
 from paper_2209_01188_amd import binding, synth  # noqa: E402
-from tests.gpu_util import DEV, build_pair, to_dev, to_np  # noqa: E402
+from tests.gpu_util import DEV, build_pair, hidden_close, to_dev, to_np  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +56,23 @@ def test_codes_of_many_rows_as_span_input(B, T, H, block):
         for blk in range(2):
             assert torch.equal(s.export_kv(blk).view(torch.int16), t.export_kv(blk).view(torch.int16))
     span.close()
+
+
+# Attention of calls that make few workgroups: 16-query workgroups whose waves split the keys (4 waves; 8 when the
+# caches are long).  T: edges of the 16-query tiles; first: tokens already cached (an empty cache, a partial key tile,
+# long enough for the 8-wave form); every head_dim.
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("first,T", [(0, 2), (0, 17), (5, 15), (0, 130), (33, 65), (610, 16), (530, 33)])
+def test_attention_of_few_workgroups(d, first, T):
+    cfg = synth.SpanConfig("few", 1, 3 * d if d >= 64 else 4 * d, 3 if d >= 64 else 4, 2, T, 1, 1, (20.0, 40.0), d + T)
+    osp, span, _ = build_pair(cfg, max_rows=2 * max(first, T))
+    oses, gses = [osp.open_session(first + T) for _ in range(2)], [span.open_session(first + T) for _ in range(2)]
+    for call, t in enumerate([first, T]):
+        if t == 0:
+            continue
+        x = synth.hidden_states(cfg, call, 2, t)
+        ref, got = osp.step(oses, x), to_np(span.prefill(gses, to_dev(x)))
+        hidden_close(got, ref, "call %d" % call)
+        assert (got.view(np.uint16) == ref.view(np.uint16)).mean() > 0.999
+    span.close()
+    osp.destroy()
