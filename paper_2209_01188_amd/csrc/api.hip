@@ -8,6 +8,7 @@
 #include <mutex>
 #include <new>
 
+#include "outlier_prep.h"
 #include "span_internal.h"
 
 namespace {
@@ -74,14 +75,15 @@ Workspace carve(const petals_span_config &c, uint8_t *base) {
     w.ocount = (int *)take(256);
     const size_t Nmax = 3 * H > F ? 3 * H : F;
     w.wd64 = w.x64 = nullptr;
-    w.many = ManyOutliers{nullptr, nullptr, nullptr, nullptr};
+    w.many = ManyOutliers{};
     if (M > 64) {   // prefill-size calls: compacted exact outlier operands, and room for the case that most columns are outliers
         w.wd64 = (double *)take(Nmax / 16 * PS_OUTLIER_CHUNKS * 64 * 8);
         w.x64 = (double *)take(Mp / 16 * PS_OUTLIER_CHUNKS * 64 * 8);
         const size_t NKmax = (size_t)(3 * H > F ? 3 * H : F) * H > H * F ? (size_t)(3 * H > F ? 3 * H : F) * H : H * F;
         w.many.list = (int *)take((Kmax + 64) * 4);
         w.many.xl = (int8_t *)take((size_t)PS_X_DIGITS * Mp * (Kmax + 64));
-        w.many.wd = (int8_t *)take(2 * (NKmax + 64 * Nmax));
+        w.many.wd_bytes = 2 * (NKmax + 64 * Nmax);
+        w.many.wd = (int8_t *)take(w.many.wd_bytes);
         w.many.od = (double *)take(Mp * Nmax * 8);
     }
     w.total = off;
@@ -143,11 +145,12 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
         // calls of a few hundred rows whose output would be too few 256 x 256 blocks to fill the GPU go through
         // the batched-decode kernel, 64 rows per workgroup (same outlier columns for all: those of the whole call)
         const bool chunks = ps_gemm_prefers_chunks(w, M);
-        HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ws.xq, (M <= 64 || chunks) ? ws.xo : nullptr, ws.sx, xq_dbg, st));
+        const bool small = M <= 64 || chunks;
+        const OutlierPrep prep = {w, small ? nullptr : ws.ocount, ws.wd64, ws.x64, ws.many.list};
+        HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ws.xq, small ? ws.xo : nullptr, ws.sx, xq_dbg, prep, st));
         const OutlierSet os = {ws.ocount, ws.wd64, ws.x64};
-        if (M > 64 && !chunks) HIP_TRY(ps_outlier_prep(w, mask, X, M, ws.ocount, ws.wd64, ws.x64, ws.many.list, st));
         const bool pr = sp->prof.begin(PETALS_PROFILE_GEMM, which, st);
-        if (M <= 64 || chunks) {
+        if (small) {
             HIP_TRY(ps_gemm(w, ws.xq, ws.xo, mask, X, ws.sx, M, o, ws.table, st));
         } else {
             HIP_TRY(ps_gemm_lds(w, ws.xq, mask, X, ws.sx, M, os, ws.many, o, ws.table, st));

@@ -204,7 +204,7 @@ __device__ __forceinline__ void load_halves(const __half *p, __half (&dst)[N]) {
 // or value row) and converts them itself: twice the conversions of the other form per matrix instruction, but 8 times
 // as many workgroups with a quarter of the chain.  Operand layouts and arithmetic as in k_attn_prefill.
 template <int D, int NWK>
-__global__ void __launch_bounds__(64 * NWK) k_attn_prefill_split(const __half *__restrict__ q, const SessTable *__restrict__ sess,
+__global__ void __launch_bounds__(64 * NWK, 2) k_attn_prefill_split(const __half *__restrict__ q, const SessTable *__restrict__ sess,
                                                                  int blk, int B, int T, int nh, __half *__restrict__ ctx,
                                                                  uint32_t *__restrict__ mask, float theta,
                                                                  float *__restrict__ lse, float *__restrict__ ctx32) {

@@ -92,7 +92,7 @@ struct QuantIn {
 #define PS_OUTLIER_CHUNKS (PS_EXACT_OUTLIERS / 4)
 // Compacted outlier operands of one linear call, in v_mfma_f64_16x16x4_f64 lane order:
 // chunk c of tile r holds 64 doubles, lane l = column list[4c + l/16] of row 16r + l%16
-// (weight rows permuted inside a tile, see k_outlier_prep).
+// (weight rows permuted inside a tile, see outlier_prep_wave).
 struct OutlierSet {
     const int *count;       // [0] number of outlier columns of this call, [1] digit planes its activations need
     const double *wd64;     // [N/16][PS_OUTLIER_CHUNKS][64] dequantized fp16 weights
@@ -114,8 +114,10 @@ hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask
 // M rows -> tiled int8 codes (rows padded to 16 with zeros), row scales; mask given
 // xo_tiled (may be null): same tile order, 16 bytes per (token, 16-column group) = the fp16 values of the
 // group's first 8 outlier columns in ascending order; groups without outliers are not written
+// pr (pr.count may be null): the linear's outlier columns are counted and, if they are few, compacted in the same launch
+struct OutlierPrep;
 hipError_t ps_rowquant_tiled(const __half *X, int M, int K, const uint32_t *mask, int8_t *xq_tiled, int8_t *xo_tiled,
-                             float *sx, int8_t *xq_rowmajor_dbg, hipStream_t st);
+                             float *sx, int8_t *xq_rowmajor_dbg, const OutlierPrep &pr, hipStream_t st);
 hipError_t ps_mask_to_bytes(const uint32_t *mask, int K, uint8_t *out, hipStream_t st);
 hipError_t ps_mask_count(const uint32_t *masks, int n_masks, int words, int32_t *out, hipStream_t st);
 
@@ -127,6 +129,7 @@ struct ManyOutliers {
     int8_t *xl;     // digit tiles of the activations [PS_X_DIGITS][ceil(M/16)][ceil(n_out/64)][1024]
     int8_t *wd;     // digit tiles of the dequantized weights [2][N/16][ceil(n_out/64)][1024]
     double *od;     // [M, N] the outlier product
+    size_t wd_bytes;   // room at wd: once the digit products are done it holds the partial sums of a split contraction
 };
 // LDS-staged linear for M > 64 rows (any number of outlier columns)
 hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t *mask, const __half *X, const float *sx,
@@ -145,10 +148,6 @@ struct RowDebug {
 hipError_t ps_gemv_row(const LinearW &w, const __half *x, const __half *ln_g, const __half *ln_b, float eps,
                        float theta, const RowDebug &dbg, const OutDesc &o, const SessTable *sess, const QuantIn *qin,
                        hipStream_t st);
-// counts the outlier columns of a prefill-size call and, if they are few, compacts their operands
-// full_list (may be null): receives the ascending list of all outlier columns when they are more than that
-hipError_t ps_outlier_prep(const LinearW &w, const uint32_t *mask, const __half *X, int M, int *count, double *wd64,
-                           double *x64, int *full_list, hipStream_t st);
 #define PS_CHUNKED_ROWS_MAX 512
 // batched-decode linear, 2 <= M <= PS_CHUNKED_ROWS_MAX rows, 64 per workgroup (int8 MFMA, outlier columns exactly on fp64 MFMA inside the
 // loop); xq_tiled and xo_tiled as written by ps_rowquant_tiled
@@ -158,6 +157,8 @@ hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_ti
 // per 64 rows, with every compute unit busy) than by the 256 x 256 output blocks of ps_gemm_lds, which
 // leave most of the GPU idle when the call has few of them.  PS_CHUNKED_ROWS_MAX bounds such calls.
 bool ps_gemm_prefers_chunks(const LinearW &w, int M);
+// workgroups that share the contraction of one output block of ps_gemm_lds
+int ps_gemm_lds_ksplit(int N, int ktiles, int M);
 
 // attention of M = B*T query rows against the caches (new keys/values already appended)
 hipError_t ps_set_table(const SessTable &host_table, SessTable *dev_table, hipStream_t st);

@@ -3,7 +3,6 @@
 // columns are added exactly, inside the loop, from the weight bytes already in registers: on a
 // 64-column tile that holds outliers, each of the four 16-column lane groups hands its next outlier
 // column to one k-slot of v_mfma_f64_16x16x4_f64 (products of fp16 values are exact in fp64).
-// Also here: the compaction kernel that prefill-size calls use for the same exact product.
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -14,80 +13,6 @@
 #include "epilogue.h"
 
 namespace {
-
-// Counts the outlier columns and, when there are at most PS_EXACT_OUTLIERS, gathers their
-// dequantized weights (one workgroup per 16 output rows) and activations (one per 16
-// tokens) as doubles in matrix-instruction lane order.  Every workgroup rebuilds the short
-// column list from the bit mask itself.
-__global__ void __launch_bounds__(64) k_outlier_prep(LinearW w, const uint32_t *__restrict__ mask,
-                                                     const __half *__restrict__ X, int M, int *__restrict__ count,
-                                                     double *__restrict__ wd64, double *__restrict__ x64,
-                                                     int *__restrict__ full_list) {
-    __shared__ int list[PS_EXACT_OUTLIERS];
-    const int K = w.K, KT = K >> 6, nwords = K >> 5, lane = threadIdx.x;
-    const int wpt = (nwords + 63) / 64, w0 = min(nwords, lane * wpt), w1 = min(nwords, w0 + wpt);
-    int cnt = 0;
-    for (int i = w0; i < w1; i++) cnt += __popc(mask[i]);
-    int incl = cnt;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(incl, off);
-        if (lane >= off) incl += v;
-    }
-    const int total = __shfl(incl, 63);
-    if (blockIdx.x == 0 && lane == 0) { count[0] = total; count[1] = 4; }   // [1]: digit planes, raised by k_digit_tiles
-    if (total > PS_EXACT_OUTLIERS && blockIdx.x == 0 && full_list) {
-        // more columns than the fp64 path takes: workgroup 0 leaves their ascending list for the digit products,
-        // padded with -1 up to the next multiple of 64
-        int at = incl - cnt;
-        for (int i = w0; i < w1; i++) {
-            uint32_t b = mask[i];
-            while (b) {
-                const int j = __ffs(b) - 1;
-                b &= b - 1;
-                full_list[at++] = i * 32 + j;
-            }
-        }
-        const int padded = (total + 63) & ~63;
-        for (int i = total + lane; i < padded; i += 64) full_list[i] = -1;
-    }
-    if (total == 0 || total > PS_EXACT_OUTLIERS) return;
-    int pos = incl - cnt;
-    for (int i = w0; i < w1; i++) {
-        uint32_t b = mask[i];
-        while (b) {
-            const int j = __ffs(b) - 1;
-            b &= b - 1;
-            list[pos++] = i * 32 + j;
-        }
-    }
-    __syncthreads();
-    const int NT = w.N >> 4, row = lane & 15, kq = lane >> 4, nch = (total + 3) >> 2;
-    if ((int)blockIdx.x < NT) {
-        // the fp64 matrix instruction returns row 4r + g in register r of lane group g, the int8 one
-        // row 4g + r: store the weight rows permuted so both results line up in the same registers
-        const int nt = blockIdx.x, nrow = 4 * (row & 3) + (row >> 2);
-        const float swd = w.sw[nt * 16 + nrow] / 127.0f;
-        for (int c = 0; c < nch; c++) {
-            const int j = c * 4 + kq;
-            double v = 0.0;
-            if (j < total) {
-                const int k = list[j];
-                const int code = w.wt[((size_t)nt * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + nrow) * 16 + (k & 15)];
-                v = (double)dequant_w16(code, swd);
-            }
-            wd64[((size_t)nt * PS_OUTLIER_CHUNKS + c) * 64 + lane] = v;
-        }
-    } else {
-        const int mt = blockIdx.x - NT, t = mt * 16 + row;
-        for (int c = 0; c < nch; c++) {
-            const int j = c * 4 + kq;
-            double v = 0.0;
-            if (j < total && t < M) v = (double)__half2float(X[(size_t)t * K + list[j]]);
-            x64[((size_t)mt * PS_OUTLIER_CHUNKS + c) * 64 + lane] = v;
-        }
-    }
-}
 
 __device__ __forceinline__ int byte_of16(const v4i &w, int j) {
     const int word = (j < 8) ? ((j < 4) ? w[0] : w[1]) : ((j < 12) ? w[2] : w[3]);
@@ -298,12 +223,6 @@ hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_til
 
 }  // namespace
 
-hipError_t ps_outlier_prep(const LinearW &w, const uint32_t *mask, const __half *X, int M, int *count, double *wd64,
-                           double *x64, int *full_list, hipStream_t st) {
-    k_outlier_prep<<<w.N / 16 + (M + 15) / 16, 64, 0, st>>>(w, mask, X, M, count, wd64, x64, full_list);
-    return hipGetLastError();
-}
-
 // Rough times in microseconds, fitted to measurements on BLOOM-560M-, 7B1- and 176B-shaped linears at 96 to 512
 // rows.  64-row passes: each streams the N*K weight bytes at about 3 TB/s (what the 64-row form reaches), 5 us per
 // launch, 20 us for the row kernels in front.  Output blocks: a 256 x 256 block walks K/64 stages of about 0.7 us
@@ -311,6 +230,8 @@ hipError_t ps_outlier_prep(const LinearW &w, const uint32_t *mask, const __half 
 // blocks), 256 blocks at a time, never faster than the weights stream at 4 TB/s, behind about 45 us of row, outlier
 // and digit kernels that are launched whatever the data.
 // PETALS_SPAN_MIDSIZE=blocks / =chunks in the environment overrides the choice (tests run both ways).
+constexpr double BLOCKS_FIXED = 35.0;
+
 bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
     if (M <= 64 || M > PS_CHUNKED_ROWS_MAX) return false;
     if (const char *force = getenv("PETALS_SPAN_MIDSIZE")) {
@@ -320,11 +241,13 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
     const double passes = (M + 63) / 64, bytes = (double)w.N * w.K;
     const double t_chunks = 20.0 + passes * (bytes / 3.0e6 + 5.0);
     double blocks = (double)((w.N + 255) / 256) * ((M + 255) / 256), stage = 0.7;
+    int split = 1;
     if (M <= 128 || blocks * 2 <= 256) {
-        blocks = (double)((w.N + 255) / 256) * ((M + 127) / 128);
+        split = ps_gemm_lds_ksplit(w.N, w.K / 64, M);
+        blocks = (double)((w.N + 255) / 256) * ((M + 127) / 128) * split;
         stage = 0.45;
     }
-    const double t_blocks = 45.0 + fmax(ceil(blocks / 256.0) * (w.K / 64) * stage, bytes / 4.0e6);
+    const double t_blocks = BLOCKS_FIXED + (split > 1 ? 8.0 : 0.0) + fmax(ceil(blocks / 256.0) * (w.K / 64) / split * stage, bytes / 4.0e6);
     return t_chunks < t_blocks;
 }
 

@@ -210,6 +210,10 @@ struct GemmArgs {
     // 1 takes planes 4.. (present only when some outlier value reaches 127.5 in magnitude) and adds to it
     int plane_group;
     double *od;               // [M, N] fp64: the product over the outlier columns
+    // int8 product with EPI_PARTIAL only: the k-tiles are shared out over ksplit workgroups per output block, each of
+    // which stores its raw sums to part[split][weight panel][token tile][lane]; k_split_finish adds and finishes them
+    int ksplit;
+    v4i *part;
     float *f32_out;           // plain fp16 product: [M, N] fp32 result
 };
 
@@ -227,6 +231,7 @@ __global__ void __launch_bounds__(64) k_digit_tiles(const __half *__restrict__ X
 }
 
 enum { GEMM_INT8 = 0, GEMM_F16 = 1, GEMM_DIGITS = 2 };
+constexpr int EPI_PARTIAL = 3;
 
 // MODE GEMM_INT8: the regular columns with the full epilogue.  GEMM_F16: plain fp16 product (backward pass).
 // GEMM_DIGITS: int8 digit products of the outlier columns, reassembled per wave into the fp64 product.  A
@@ -250,14 +255,23 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     if (DIG && !many) return;
     // k-tiles to walk (64 int8 or 32 fp16 columns each).  If EVERY column is an outlier all int8 codes are
     // zero: the int8 product is skipped and only the epilogue runs.
-    const int NS = F16 ? ga.ktiles : DIG ? (n_out + 63) >> 6 : (n_out == ga.ktiles * 64 ? 0 : ga.ktiles);
+    const int KTILES = F16 ? ga.ktiles : DIG ? (n_out + 63) >> 6 : ga.ktiles;       // tiles per row of the operands
+    int NS = !F16 && !DIG && n_out == ga.ktiles * 64 ? 0 : KTILES;
 
     // Workgroup -> output block.  Consecutive workgroup ids land on different XCDs (8 of them, each
     // with its own L2); give each XCD a contiguous run of blocks, ordered in strips of STRIP
     // m-blocks, so that the blocks an XCD works on at one time share weight and token tiles in its L2.
-    const int nb_n = ga.nb_n, nb_m = ga.nb_m, total = nb_n * nb_m, per_xcd = (total + 7) >> 3;
-    const int ord = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const int nb_n = ga.nb_n, nb_m = ga.nb_m, ksplit = EPI == EPI_PARTIAL ? ga.ksplit : 1;
+    const int total = nb_n * nb_m * ksplit, per_xcd = (total + 7) >> 3;
+    int ord = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per_xcd || ord >= total) return;
+    int split = 0, s_first = 0;                      // this workgroup's k-tiles: [s_first, s_first + NS)
+    if constexpr (EPI == EPI_PARTIAL) {
+        split = ord / (nb_n * nb_m);
+        ord -= split * nb_n * nb_m;
+        s_first = (int)((long long)NS * split / ksplit);
+        NS = (int)((long long)NS * (split + 1) / ksplit) - s_first;
+    }
     const int nstrips = (nb_m + STRIP - 1) / STRIP;
     const int strip = min(ord / (STRIP * nb_n), nstrips - 1);
     const int rem = ord - strip * STRIP * nb_n, sw_this = min(STRIP, nb_m - strip * STRIP);
@@ -278,14 +292,14 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
             static_assert(MODE != GEMM_DIGITS || (TN == 8 && TM == 4), "digit slots: 2 digits x 4 panels, 4 planes of one token tile");
             if (s < BN) {                    // slot: wave column s / 8, digit (s % 8) / 4, panel 4 * (2 bn + s / 8) + s % 4
                 const int panel = min((bn * WVN + s / TN) * 4 + (s & 3), NT - 1);
-                src[j] = ga.a_tiles + ((size_t)((s % TN) / 4) * NT + panel) * NS * 1024 + lane * 16;
+                src[j] = ga.a_tiles + ((size_t)((s % TN) / 4) * NT + panel) * KTILES * 1024 + lane * 16;
             } else {                         // slot: wave row t / 4 = token tile, plane t % 4 of the group
                 const int t = s - BN, plane = min(ga.plane_group * 4 + (t & 3), PS_X_DIGITS - 1);
-                src[j] = ga.b_tiles + ((size_t)plane * MTT + min(bm * WVM + t / TM, MTT - 1)) * NS * 1024 + lane * 16;
+                src[j] = ga.b_tiles + ((size_t)plane * MTT + min(bm * WVM + t / TM, MTT - 1)) * KTILES * 1024 + lane * 16;
             }
         } else {
-            if (s < BN) src[j] = ga.a_tiles + (size_t)min(nt0 + s, NT - 1) * NS * 1024 + lane * 16;
-            else src[j] = ga.b_tiles + (size_t)min(mt0 + s - BN, MTT - 1) * NS * 1024 + lane * 16;
+            if (s < BN) src[j] = ga.a_tiles + ((size_t)min(nt0 + s, NT - 1) * KTILES + s_first) * 1024 + lane * 16;
+            else src[j] = ga.b_tiles + ((size_t)min(mt0 + s - BN, MTT - 1) * KTILES + s_first) * 1024 + lane * 16;
         }
     }
 
@@ -482,6 +496,14 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
                 }
             }
         }
+    } else if constexpr (EPI == EPI_PARTIAL) {
+#pragma unroll
+        for (int i = 0; i < TN; i++)
+#pragma unroll
+            for (int j = 0; j < TM; j++) {
+                const int nt = nt0 + wn * TN + i, mt = mt0 + wm * TM + j;
+                if (nt < NT && mt < MTT) ga.part[(((size_t)split * NT + nt) * MTT + mt) * 64 + lane] = acc[i][j];
+            }
     } else {
         constexpr size_t PARK = (size_t)NW * QN * TM * 1024;
         double *col_swd = (double *)(lds + PARK);                        // [BN * 16] weight scale / 127
@@ -653,11 +675,32 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     }
 }
 
+// Second half of a split contraction: one wave per 16 x 16 output tile adds the partial sums, the outlier part and the
+// linear's fused tail.
+__global__ void __launch_bounds__(256) k_split_finish(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os,
+                                                      const double *__restrict__ outl, OutDesc o,
+                                                      const SessTable *__restrict__ sess) {
+    const int NT = ga.N >> 4, MTT = (ga.M + 15) >> 4, lane = threadIdx.x & 63;
+    const int item = blockIdx.x * 4 + (threadIdx.x >> 6), nt = item / MTT, mt = item - nt * MTT;
+    if (nt >= NT) return;
+    const int t = mt * 16 + (lane & 15), n0 = nt * 16 + 4 * (lane >> 4), n_out = os.count[0];
+    v4i acc = {0, 0, 0, 0};
+    for (int s = 0; s < ga.ksplit; s++) acc += ga.part[(((size_t)s * NT + nt) * MTT + mt) * 64 + lane];
+    v4d od = {0.0, 0.0, 0.0, 0.0};
+    if (n_out > PS_EXACT_OUTLIERS) {
+        if (t < ga.M) od = *(const v4d *)(outl + (size_t)t * ga.N + n0);
+    } else {
+        const double *ap = os.wd64 + (size_t)nt * PS_OUTLIER_CHUNKS * 64 + lane, *bp = os.x64 + (size_t)mt * PS_OUTLIER_CHUNKS * 64 + lane;
+        for (int c = 0; c < (n_out + 3) >> 2; c++) od = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[c * 64], bp[c * 64], od, 0, 0, 0);
+    }
+    if (t < ga.M) emit_output4(o, sess, ga.N, t, n0, acc, od, sx[t] / 127.0f, w.sw, w.bias);
+}
+
 template <int MODE, int TM, int EPI = 0>
 hipError_t launch_one(const GemmArgs &ga, const LinearW &w, const float *sx, const OutlierSet &os, const double *outl,
                       const OutDesc &o, const SessTable *sess, hipStream_t st) {
     constexpr int WVN = 2, WVM = 4, TN = 8, NSLOT = 4, BN = WVN * TN, BM = WVM * TM;   // 8 waves, 128 x (16 TM) per wave
-    const int total = ga.nb_n * ga.nb_m;
+    const int total = ga.nb_n * ga.nb_m * (EPI == EPI_PARTIAL ? ga.ksplit : 1);
     const size_t lds_stage = (size_t)NSLOT * (BN + BM) * 1024;
     const size_t lds_epi = (size_t)WVN * WVM * (TN / 2) * TM * 1024 + (size_t)BN * 16 * 16 + (size_t)BN * 4 * 8 + (size_t)BN / 2 * 4;
     const size_t lds = lds_stage > lds_epi ? lds_stage : lds_epi;
@@ -693,7 +736,7 @@ hipError_t launch_epi(const GemmArgs &ga, const LinearW &w, const float *sx, con
 
 template <int MODE>
 hipError_t launch_lds(const GemmArgs &ga0, const LinearW &w, const float *sx, const OutlierSet &os, const double *outl,
-                      const OutDesc &o, const SessTable *sess, hipStream_t st) {
+                      const OutDesc &o, const SessTable *sess, hipStream_t st, size_t part_bytes = 0) {
     constexpr int BN = 16, BM = 16, UNITS = 256;
     GemmArgs ga = ga0;
     const int NT = ga.N / 16, MTT = (ga.M + 15) / 16;
@@ -705,6 +748,16 @@ hipError_t launch_lds(const GemmArgs &ga0, const LinearW &w, const float *sx, co
         // at most 128 rows, or so few blocks that half the compute units would idle: blocks of half the height
         // (no block is half empty, and there are twice as many of them)
         ga.nb_m = (MTT + BM / 2 - 1) / (BM / 2);
+        if constexpr (MODE == GEMM_INT8) {
+            ga.ksplit = ps_gemm_lds_ksplit(ga.N, ga.ktiles, ga.M);
+            while (ga.ksplit > 1 && (size_t)ga.ksplit * NT * MTT * 1024 > part_bytes) ga.ksplit--;
+            if (ga.ksplit > 1) {
+                hipError_t e = launch_one<MODE, 2, EPI_PARTIAL>(ga, w, sx, os, outl, o, sess, st);
+                if (e != hipSuccess) return e;
+                k_split_finish<<<(NT * MTT + 3) / 4, 256, 0, st>>>(ga, w, sx, os, outl, o, sess);
+                return hipGetLastError();
+            }
+        }
         return launch_epi<MODE, 2>(ga, w, sx, os, outl, o, sess, st);
     }
     if (total > UNITS && rest > 0 && rest <= UNITS / 2 && rest % ga.nb_m == 0) {
@@ -733,6 +786,14 @@ GemmArgs gemm_args(const void *a_tiles, const void *b_tiles, int ktiles, int M, 
 
 }  // namespace
 
+// Workgroups that share the k-tiles of a 256 x 128 output block of a call that makes few blocks (a 351-row call on a
+// 4096 x 16384 linear: 48 blocks on 256 compute units, 110 us; split five ways SPLITUS): as many as fill the compute
+// units once, each with at least 16 k-tiles to walk.
+int ps_gemm_lds_ksplit(int N, int ktiles, int M) {
+    const int blocks = ((N + 255) / 256) * ((M + 127) / 128);
+    return max(1, min(min(256 / blocks, ktiles / 16), 8));
+}
+
 hipError_t ps_gemm_f16_tiles(const __half *feat_tiles, const __half *tok_tiles, int ktiles, int M, int n_feat,
                              float *out, const __half *gelu_pre, __half *tile_out, hipStream_t st) {
     if (ktiles < 1 || M < 1 || n_feat < 16 || n_feat % 16) return hipErrorInvalidValue;
@@ -754,7 +815,7 @@ hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t 
                        int M, const OutlierSet &os, const ManyOutliers &mo, const OutDesc &o, const SessTable *sess,
                        hipStream_t st) {
     // The outlier-heavy case first (every kernel of it returns at once when the call has few outlier columns):
-    // column list, digit tiles of the activations and of the dequantized weights, the digit products (a second
+    // digit tiles of the activations and of the dequantized weights, the digit products (a second
     // launch for digit planes 4 and 5, which only activations of magnitude 127.5 and more have).
     k_digit_tiles<2><<<2048 + 4096, 64, 0, st>>>(X, M, w, (int *)os.count, mo.list, mo.xl, mo.wd, 2048);
     hipError_t e = hipGetLastError();
@@ -769,5 +830,6 @@ hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t 
         if (e != hipSuccess) return e;
     }
     GemmArgs gi = gemm_args(w.wt, xq_tiled, w.K / 64, M, w.N);
-    return launch_lds<GEMM_INT8>(gi, w, sx, os, mo.od, o, sess, st);
+    gi.part = (v4i *)mo.wd;                  // the digit tiles have been read when the int8 product starts
+    return launch_lds<GEMM_INT8>(gi, w, sx, os, mo.od, o, sess, st, mo.wd_bytes);
 }

@@ -2,6 +2,7 @@
 // streaming tile order, LayerNorm, outlier-column detection, row-wise int8
 // quantization of activations, the blockwise 8-bit hidden-state codec, cache copies.
 #include "common.h"
+#include "outlier_prep.h"
 #include "rowops.h"
 
 namespace {
@@ -309,10 +310,17 @@ __global__ void __launch_bounds__(256) k_colmask(const __half *__restrict__ X, i
 // Row of a workgroup of the row quantizers.  Consecutive workgroup ids land on different XCDs (8, each with its
 // own L2), and the 16 rows of a token tile interleave their 16-byte pieces in every 128-byte line of the tile: each
 // XCD gets a contiguous run of whole tiles, so that a line is completed in ONE L2 instead of being written back
-// in pieces by eight.  The grid has 8 * per workgroups, per a multiple of 16; ids beyond `rows` have nothing to do.
-__device__ __forceinline__ int rowquant_row() {
-    const int per = (int)gridDim.x >> 3;
+// in pieces by eight.  8 * per workgroups (`grid`), per a multiple of 16; ids beyond `rows` have nothing to do.  The
+// workgroups behind them prepare the linear's outlier columns.
+__device__ __forceinline__ int rowquant_row(int grid) {
+    const int per = grid >> 3;
     return ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+}
+template <int NT>
+__device__ __forceinline__ void rowquant_prep(const OutlierPrep &pr, const uint32_t *mask, const __half *X, int M, int grid,
+                                              int *list) {
+    const int wave = threadIdx.x >> 6, item = ((int)blockIdx.x - grid) * (NT / 64) + wave;
+    if (item < outlier_prep_items(pr, M)) outlier_prep_wave(pr, mask, X, M, item, list + wave * PS_EXACT_OUTLIERS);
 }
 __host__ inline int rowquant_grid(int rows) { return 8 * (((rows / 16 + 7) / 8) * 16); }
 
@@ -323,9 +331,14 @@ __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict
                                                         const uint32_t *__restrict__ mask,
                                                         int8_t *__restrict__ xq_tiled,
                                                         int8_t *__restrict__ xo_tiled, float *__restrict__ sx,
-                                                        int8_t *__restrict__ xq_dbg, int rows) {
+                                                        int8_t *__restrict__ xq_dbg, int rows, int grid, OutlierPrep pr) {
     __shared__ float sm[4];
-    const int t = rowquant_row(), KT = K >> 6, nchunk = K >> 4;
+    __shared__ int list[4 * PS_EXACT_OUTLIERS];
+    if ((int)blockIdx.x >= grid) {
+        rowquant_prep<256>(pr, mask, X, M, grid, list);
+        return;
+    }
+    const int t = rowquant_row(grid), KT = K >> 6, nchunk = K >> 4;
     if (t >= rows) return;
     const uint16_t *mask16 = (const uint16_t *)mask;
     const size_t tile_row = (size_t)(t >> 4) * KT;
@@ -394,9 +407,14 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
                                                              const uint32_t *__restrict__ mask,
                                                              int8_t *__restrict__ xq_tiled,
                                                              int8_t *__restrict__ xo_tiled, float *__restrict__ sx,
-                                                             int8_t *__restrict__ xq_dbg, int rows) {
+                                                             int8_t *__restrict__ xq_dbg, int rows, int grid, OutlierPrep pr) {
     __shared__ float sm[NT / 64];
-    const int t = rowquant_row(), KT = K >> 6, nchunk = K >> 4;
+    __shared__ int list[NT / 64 * PS_EXACT_OUTLIERS];
+    if ((int)blockIdx.x >= grid) {
+        rowquant_prep<NT>(pr, mask, X, M, grid, list);
+        return;
+    }
+    const int t = rowquant_row(grid), KT = K >> 6, nchunk = K >> 4;
     if (t >= rows) return;
     const uint16_t *mask16 = (const uint16_t *)mask;
     const size_t tile_row = (size_t)(t >> 4) * KT;
@@ -718,14 +736,14 @@ hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask
     return hipGetLastError();
 }
 hipError_t ps_rowquant_tiled(const __half *X, int M, int K, const uint32_t *mask, int8_t *xq_tiled, int8_t *xo_tiled,
-                             float *sx, int8_t *xq_dbg, hipStream_t st) {
-    const int rows = (M + 15) / 16 * 16, grid = rowquant_grid(rows);
+                             float *sx, int8_t *xq_dbg, const OutlierPrep &pr, hipStream_t st) {
+    const int rows = (M + 15) / 16 * 16, grid = rowquant_grid(rows), items = outlier_prep_items(pr, M);
     if (K >= 4096 && K <= 16384 && M >= 512)   // many rows: four times as many rows in flight per compute unit
-        k_rowquant_tiled_wide<256, 4><<<grid, 256, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows);
+        k_rowquant_tiled_wide<256, 4><<<grid + (items + 3) / 4, 256, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
     else if (K >= 4096 && K <= 65536)          // wide rows: 1024 threads keep the row in registers, one pass over X
-        k_rowquant_tiled_wide<1024, 4><<<grid, 1024, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows);
+        k_rowquant_tiled_wide<1024, 4><<<grid + (items + 15) / 16, 1024, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
     else
-        k_rowquant_tiled<<<grid, 256, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows);
+        k_rowquant_tiled<<<grid + (items + 3) / 4, 256, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
     return hipGetLastError();
 }
 hipError_t ps_mask_count(const uint32_t *masks, int n_masks, int words, int32_t *out, hipStream_t st) {
