@@ -536,7 +536,8 @@ __global__ void __launch_bounds__(1024) k_hidden_quantize(const __half *__restri
 // are binned by sign, exponent and 6 mantissa bits, no bin holds more than one midpoint, and a table says how many
 // lie below each bin.  29.4 M values (2048 rows of 14336) into codes and back: 163 -> 56 us with the wide
 // dequantizer below (92 us of it were the binary search over the 255 midpoints with two 2-byte reads of every value,
-// 66 us one 2-byte store and one 64-bit division per value).  512 threads with 1, 2 or 4 chunks cover blocks of up to 4096, 8192 and 16384.
+// 66 us one 2-byte store and one 64-bit division per value).  128 threads cover blocks
+// of up to 1024 values, 512 with 1, 2 or 4 chunks blocks of up to 4096, 8192 and 16384.
 constexpr int CODE_SHIFT = 17, CODE_KEY0 = 105 << (23 - CODE_SHIFT);         // bin 0: everything below 2^-22, no midpoint there
 constexpr int CODE_BINS = (127 << (23 - CODE_SHIFT)) - CODE_KEY0 + 1;        // the last bin starts at 1.0
 struct CodeBins {
@@ -575,10 +576,9 @@ static_assert(one_midpoint_per_bin(make_code_bins()), "one comparison per value 
 static_assert(sizeof(CodeBins) % 4 == 0, "copied to LDS word by word");
 static __device__ const CodeBins d_code_bins = make_code_bins();
 
-template <int PER>
-__global__ void __launch_bounds__(512) k_hidden_quantize_wide(const __half *__restrict__ x, size_t n, int block,
+template <int NT, int PER>
+__global__ void __launch_bounds__(NT) k_hidden_quantize_wide(const __half *__restrict__ x, size_t n, int block,
                                                               uint8_t *__restrict__ q, float *__restrict__ absmax) {
-    constexpr int NT = 512;
     __shared__ CodeBins cb;
     __shared__ uint32_t s_max[NT / 64];
     const size_t b0 = (size_t)blockIdx.x * block;
@@ -593,7 +593,9 @@ __global__ void __launch_bounds__(512) k_hidden_quantize_wide(const __half *__re
         if (k + 8 <= len) {
             xv[i] = *(const v4i *)(xb + k);
         } else {
-            for (int e = 0; e < len - k; e++) ((__half *)&xv[i])[e] = xb[k + e];   // the ragged end of the last block
+#pragma unroll
+            for (int e = 0; e < 8; e++)                        // the ragged end of the last block
+                if (k + e < len) xv[i][e >> 1] |= (int)((uint32_t)__half_as_ushort(xb[k + e]) << ((e & 1) * 16));
         }
     }
     for (int i = threadIdx.x; i < (int)(sizeof(CodeBins) / 4); i += NT) ((uint32_t *)&cb)[i] = ((const uint32_t *)&d_code_bins)[i];
@@ -635,7 +637,9 @@ __global__ void __launch_bounds__(512) k_hidden_quantize_wide(const __half *__re
         if (k + 8 <= len) {
             *(uint2 *)(q + b0 + k) = make_uint2(w[0], w[1]);
         } else {
-            for (int e = 0; e < len - k; e++) q[b0 + k + e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                if (k + e < len) q[b0 + k + e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
         }
     }
 }
@@ -760,9 +764,10 @@ hipError_t ps_hidden_quantize(const __half *x, size_t n, int block, const CodeTa
     const unsigned blocks = (unsigned)((n + block - 1) / block);
     // (a block starts at a multiple of 64 values: aligned buffers make every chunk aligned)
     if ((((uintptr_t)x & 15) | ((uintptr_t)q & 7)) == 0) {
-        if (block <= 4096) k_hidden_quantize_wide<1><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
-        else if (block <= 8192) k_hidden_quantize_wide<2><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
-        else k_hidden_quantize_wide<4><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
+        if (block <= 1024) k_hidden_quantize_wide<128, 1><<<blocks, 128, 0, st>>>(x, n, block, q, absmax);
+        else if (block <= 4096) k_hidden_quantize_wide<512, 1><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
+        else if (block <= 8192) k_hidden_quantize_wide<512, 2><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
+        else k_hidden_quantize_wide<512, 4><<<blocks, 512, 0, st>>>(x, n, block, q, absmax);
     } else {
         k_hidden_quantize<<<blocks, 1024, 0, st>>>(x, n, block, tab, q, absmax);
     }
