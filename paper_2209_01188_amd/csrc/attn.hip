@@ -7,6 +7,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "digits.h"
 
 namespace {
 
@@ -19,28 +20,86 @@ __global__ void k_set_table(SessTable t, SessTable *dst) {
     for (int i = threadIdx.x; i < (int)(sizeof(SessTable) / 4); i += blockDim.x) d[i] = s[i];
 }
 
-// Prefill (T > 1 new tokens per session): exact attention on the fp64 matrix cores.
+// N consecutive halves at an address aligned to min(16, 2 N) bytes
+template <int N>
+__device__ __forceinline__ void load_halves(const __half *p, __half (&dst)[N]) {
+    if constexpr (N >= 8) {
+#pragma unroll
+        for (int i = 0; i < N / 8; i++) *(v8h *)(dst + 8 * i) = *(const v8h *)(p + 8 * i);
+    } else if constexpr (N == 4) {
+        *(v4h *)dst = *(const v4h *)p;
+    } else if constexpr (N == 2) {
+        *(__half2 *)dst = *(const __half2 *)p;
+    } else {
+        dst[0] = *p;
+    }
+}
+
+// Scores of one tile of 16 keys x 16 queries as exact int8 digit products (D = 64 or 128): ka holds the keys' digit
+// planes as A operands, qa the queries' as B operands ([plane][64 dims]); lane (g, c), register r of the result is key
+// 4r + g of query c, as the fp64 instruction returns it, scaled by inv_rsd.  The pairs with the same i + j share an
+// accumulator (at most 4 * 2^14 * 128 = 2^23); the two lowest and the fifth and sixth meet in int32 (2^30 at most).
+// The int8 instruction returns row 4g + r: the tile's keys are handed in permuted, see digit_key_slot.
+template <int HALVES>
+__device__ __forceinline__ v4d digit_scores(const v4i (&ka)[4][HALVES], const v4i (&qa)[4][HALVES], double scale) {
+    v4i acc[7];
+#pragma unroll
+    for (int s = 0; s < 7; s++) acc[s] = (v4i){0, 0, 0, 0};
+#pragma unroll
+    for (int h = 0; h < HALVES; h++)
+#pragma unroll
+        for (int d = 0; d < 4; d++)               // diagonals of the pair table: consecutive products are independent
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int j = (i + d) & 3;
+                acc[i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ka[i][h], qa[j][h], acc[i + j], 0, 0, 0);
+            }
+    v4d S;
+    const double sc = scale * 0x1p-48;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        double t = (double)acc[6][r];
+        t = t * 65536.0 + (double)((acc[5][r] << 8) + acc[4][r]);
+        t = t * 256.0 + (double)acc[3][r];
+        t = t * 256.0 + (double)acc[2][r];
+        t = t * 65536.0 + (double)((acc[1][r] << 8) + acc[0][r]);
+        S[r] = t * sc;
+    }
+    return S;
+}
+// slot (row of the A operand) of key k of a tile: row 4g + r of the result belongs to key 4r + g
+__device__ __forceinline__ constexpr int digit_key_slot(int k) { return 4 * (k & 3) + (k >> 2); }
+
+// Prefill (T > 1 new tokens per session): exact attention on the matrix cores.
 // A workgroup of four waves owns 64 consecutive query rows of one (session, head), 16 per wave, and
 // walks the key tiles (16 keys each) up to the causal limit with an online softmax per wave.
-//   S^T = K Q^T   : v_mfma_f64_16x16x4_f64, A = keys (row = key), B = queries (column = query);
+//   S^T = K Q^T: head_dim 64 and 128 as exact int8 digit products (32 instructions of 16 clocks and some 30 vector
+//   instructions per tile and 128 dims, where the fp64 instruction takes 32 of 64 clocks); smaller head_dims, and tiles
+//   in which a key or query value of 127.5 or more does not fit four digits, on
+//   v_mfma_f64_16x16x4_f64, A = keys (row = key), B = queries (column = query);
 //                   lane l feeds row/column l%16 and the dims [l/16 * D/4, +D/4) - any pairing of
 //                   the contraction index works as long as both operands use the same one.
 //   the result registers hold S^T[key 4r + l/16][query l%16], which is exactly the B operand of
-//   O^T += V^T P^T (A = values with row i = output dims i*D/16 + blk), so the probabilities never
-//   change lanes.  Products of fp16 inputs are exact in fp64; the fp16 context equals the exactly
+//   O^T += V^T P^T on the fp64 instruction (A = values with row i = output dims i*D/16 + blk), so the probabilities
+//   never change lanes.  Products of fp16 inputs are exact in fp64; the fp16 context equals the exactly
 //   rounded one (a different summation order moves the fp64 sum by ~1e-16 relative).
-// The fp16 -> fp64 conversions of a key / value tile cost about as much vector-ALU time as its
+// The conversions of a key / value tile (fp16 to digits, to fp64) cost about as much vector-ALU time as its
 // matrix instructions take, so they are done once per workgroup: the four waves convert the next
-// tile together into LDS, already in A-operand order (one 8-byte read per lane and instruction),
+// tile together into LDS, already in A-operand order,
 // while the current one is multiplied.  Queries are converted once per wave and stay in registers.
+// 8 x 512 tokens, 32 heads of 128: 445 us with fp64 scores, 375 us with digits.
 template <int D>
 __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restrict__ q, const SessTable *__restrict__ sess,
                                                          int blk, int B, int T, int nh, __half *__restrict__ ctx,
                                                          uint32_t *__restrict__ mask, float theta,
                                                          float *__restrict__ lse, float *__restrict__ ctx32) {
     constexpr int DS = D / 4, NB = D / 16;           // dims per lane group; output blocks of 16 dims
-    constexpr int TILE = 16 * D;                     // fp64 values of one key or value tile
-    extern __shared__ __align__(16) double kvd[];    // [2 buffers][keys | values][TILE]
+    constexpr bool DIGITS = D >= 64;
+    constexpr int HALVES = DIGITS ? D / 64 : 1;
+    constexpr int VT = 16 * D * 8;                   // bytes of a value tile (fp64)
+    constexpr int KTB = DIGITS ? 4 * HALVES * 1024 : 16 * D * 8;     // bytes of a key tile (digit planes or fp64)
+    extern __shared__ __align__(16) unsigned char kvl[];             // [2 buffers][keys | values]
+    __shared__ int kbig[2];                          // DIGITS: tile + 1 of a buffer's tile that needs the fp64 form
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     // One-dimensional grid.  Consecutive workgroup ids land on different XCDs (8, each with its own L2): the id
     // is decoded so that all query blocks of one (session, head) run on the same XCD and share its keys/values.
@@ -51,6 +110,8 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
     const int pair = grp * 8 + (rem & 7);
     if (pair >= B * nh) return;                       // the whole workgroup
     const int qb0 = rem >> 3, s = pair / nh, h = pair - s * nh;
+    if (threadIdx.x < 2) kbig[threadIdx.x] = 0;
+    if constexpr (DIGITS) __syncthreads();
     for (int pass = 0; pass < 2; pass++) {
     const int qb = pass ? nbx - 1 - qb0 : qb0;
     if (pass && qb == qb0) break;                     // odd count: the middle block stands alone
@@ -65,11 +126,30 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
     const int qpos = L + tq;                          // its absolute position
     const size_t qrow = (size_t)s * T + min(tq, T - 1);
 
-    double qd[DS];
-    {
-        const __half *qp = q + qrow * H + h * D + g * DS;
+    const __half *qp = q + qrow * H + h * D;
+    double qd[DIGITS ? 1 : DS];
+    v4i qa[4][HALVES];
+    bool q_big = false;
+    if constexpr (DIGITS) {
 #pragma unroll
-        for (int e = 0; e < DS; e++) qd[e] = (double)__half2float(qp[e]) * inv_rsd;   // 1/sqrt(d) folded into the query
+        for (int hf = 0; hf < HALVES; hf++) {
+            __half x[16];
+            load_halves<16>(qp + hf * 64 + g * 16, x);
+#pragma unroll
+            for (int w = 0; w < 4; w++) {
+                const __half x4[4] = {x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3]};
+                int pl[4];
+                digit_planes4(x4, pl);
+#pragma unroll
+                for (int i = 0; i < 4; i++) qa[i][hf][w] = pl[i];
+            }
+#pragma unroll
+            for (int e = 0; e < 16; e++) q_big |= (__half_as_ushort(x[e]) & 0x7fffu) >= DIGITS_BIG;
+        }
+        q_big = __any(q_big);
+    } else {
+#pragma unroll
+        for (int e = 0; e < DS; e++) qd[e] = (double)__half2float(qp[g * DS + e]) * inv_rsd;   // 1/sqrt(d) folded into the query
     }
     v4d O[NB];
 #pragma unroll
@@ -85,22 +165,45 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
     __half kraw[NB], vraw[NB];
     auto fetch = [&](int kt) {
         const size_t off = (size_t)min(kt * 16 + fk, last_key) * D + fd;
-#pragma unroll
-        for (int i = 0; i < NB; i++) {
-            kraw[i] = Kc[off + i];
-            vraw[i] = Vc[off + i];
-        }
+        load_halves<NB>(Kc + off, kraw);
+        load_halves<NB>(Vc + off, vraw);
     };
-    auto stash = [&](int buf) {
-        double *kd = kvd + (size_t)buf * 2 * TILE, *vd = kd + TILE;
+    auto stash = [&](int kt) {
+        const int buf = kt & 1;
+        double *vd = (double *)(kvl + (size_t)buf * (KTB + VT) + KTB);
+        if constexpr (DIGITS) {
+            unsigned char *kb = kvl + (size_t)buf * (KTB + VT);
+            // dims fd .. fd + NB: half fd / 64, lane group fd % 64 / 16; the 16 keys of a (half, group) are rotated by 4 per
+            // group so that the writes of a wave spread over the banks (a read takes all 16)
+            const int hf = fd >> 6, gg = (fd & 63) >> 4, slot = gg * 16 + ((digit_key_slot(fk) + 4 * gg) & 15);
+            int pl[NB / 4][4];
+            bool big = false;
+#pragma unroll
+            for (int w = 0; w < NB / 4; w++) {
+                const __half x4[4] = {kraw[4 * w], kraw[4 * w + 1], kraw[4 * w + 2], kraw[4 * w + 3]};
+                digit_planes4(x4, pl[w]);
+            }
+#pragma unroll
+            for (int i = 0; i < NB; i++) big |= (__half_as_ushort(kraw[i]) & 0x7fffu) >= DIGITS_BIG;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                unsigned char *dst = kb + ((size_t)(i * HALVES + hf) * 64 + slot) * 16 + (fd & 15);
+                if constexpr (NB == 8) *(v2i *)dst = (v2i){pl[0][i], pl[1][i]};
+                else *(int *)dst = pl[0][i];
+            }
+            if (__any(big) && lane == 0) kbig[buf] = kt + 1;
+        }
 #pragma unroll
         for (int i = 0; i < NB; i++) {
-            const int d = fd + i;
-            // keys: A operand of step e is K[key][g * DS + e] at lane (g, key); the 64 values of a step are
-            // rotated by 4 * (e / 8) positions so that the 64 threads of a wave, which write 4 steps, 4 lane
-            // groups and 4 keys at a time, spread over all LDS banks (reads stay 64 consecutive values)
-            const int e = d % DS;
-            kd[e * 64 + (((d / DS) * 16 + fk + 4 * (e >> 3)) & 63)] = (double)__half2float(kraw[i]);
+            if constexpr (!DIGITS) {
+                double *kd = (double *)(kvl + (size_t)buf * (KTB + VT));
+                const int d = fd + i;
+                // keys: A operand of step e is K[key][g * DS + e] at lane (g, key); the 64 values of a step are
+                // rotated by 4 * (e / 8) positions so that the 64 threads of a wave, which write 4 steps, 4 lane
+                // groups and 4 keys at a time, spread over all LDS banks (reads stay 64 consecutive values)
+                const int e = d % DS;
+                kd[e * 64 + (((d / DS) * 16 + fk + 4 * (e >> 3)) & 63)] = (double)__half2float(kraw[i]);
+            }
             // values: A operand of step (r, b) is V[key 4r + g][c * NB + b] at lane (g, c)
             vd[((fk >> 2) * NB + i) * 64 + (fk & 3) * 16 + (threadIdx.x & 15)] = (double)__half2float(vraw[i]);
         }
@@ -111,20 +214,39 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
     for (int kt = 0; kt < nkt; kt++) {
         if (kt + 1 < nkt) fetch(kt + 1);              // in flight during the multiplications below
         if (kt < nkt_w) {
-            const double *kd0 = kvd + (size_t)(kt & 1) * 2 * TILE, *vd = kd0 + TILE + lane;
-            // scores of 16 keys x 16 queries
-            // (a dependent fp64 matrix instruction issues at about half the rate of independent ones:
-            // up to four partial sums run side by side)
-            constexpr int NCH = DS >= 16 ? 4 : (DS >= 8 ? 2 : 1);
-            v4d Sp[NCH];
+            const unsigned char *kb = kvl + (size_t)(kt & 1) * (KTB + VT);
+            const double *kd0 = (const double *)kb, *vd = (const double *)(kb + KTB) + lane;
+            v4d S;
+            if (DIGITS && !q_big && kbig[kt & 1] != kt + 1) {
+                v4i ka[4][HALVES];
 #pragma unroll
-            for (int i = 0; i < NCH; i++) Sp[i] = (v4d){0.0, 0.0, 0.0, 0.0};
+                for (int i = 0; i < 4; i++)
 #pragma unroll
-            for (int e = 0; e < DS; e++)
-                Sp[e % NCH] = __builtin_amdgcn_mfma_f64_16x16x4f64(kd0[e * 64 + ((lane + 4 * (e >> 3)) & 63)], qd[e], Sp[e % NCH], 0, 0, 0);
-            v4d S = Sp[0];
+                    for (int hf = 0; hf < HALVES; hf++)
+                        ka[i][hf] = *(const v4i *)(kb + ((size_t)(i * HALVES + hf) * 64 + g * 16 + ((c + 4 * g) & 15)) * 16);
+                S = digit_scores<HALVES>(ka, qa, inv_rsd);
+            } else {
+                // scores of 16 keys x 16 queries in fp64
+                // (a dependent fp64 matrix instruction issues at about half the rate of independent ones:
+                // up to four partial sums run side by side)
+                constexpr int NCH = DS >= 16 ? 4 : (DS >= 8 ? 2 : 1);
+                v4d Sp[NCH];
 #pragma unroll
-            for (int i = 1; i < NCH; i++) S += Sp[i];
+                for (int i = 0; i < NCH; i++) Sp[i] = (v4d){0.0, 0.0, 0.0, 0.0};
+                if constexpr (DIGITS) {               // rare: straight from the cache
+                    const __half *kr = Kc + (size_t)min(kt * 16 + c, last_key) * D + g * DS;
+#pragma unroll 4
+                    for (int e = 0; e < DS; e++)
+                        Sp[0] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__half2float(kr[e]), (double)__half2float(qp[g * DS + e]) * inv_rsd, Sp[0], 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < DS; e++)
+                        Sp[e % NCH] = __builtin_amdgcn_mfma_f64_16x16x4f64(kd0[e * 64 + ((lane + 4 * (e >> 3)) & 63)], qd[e], Sp[e % NCH], 0, 0, 0);
+                }
+                S = Sp[0];
+#pragma unroll
+                for (int i = 1; i < NCH; i++) S += Sp[i];
+            }
             double sc[4], mt = -INFINITY;
 #pragma unroll
             for (int r = 0; r < 4; r++) {
@@ -152,7 +274,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
                 for (int b = 0; b < NB; b++)
                     O[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(vd[(r * NB + b) * 64], p[r], O[b], 0, 0, 0);
         }
-        if (kt + 1 < nkt) stash((kt + 1) & 1);        // that buffer was last read before the previous barrier
+        if (kt + 1 < nkt) stash(kt + 1);              // that buffer was last read before the previous barrier
         __syncthreads();
     }
     l_run += __shfl_xor(l_run, 16);
@@ -179,21 +301,6 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
         }
     }
     }   // pass
-}
-
-// N consecutive halves at an address aligned to min(16, 2 N) bytes
-template <int N>
-__device__ __forceinline__ void load_halves(const __half *p, __half (&dst)[N]) {
-    if constexpr (N >= 8) {
-#pragma unroll
-        for (int i = 0; i < N / 8; i++) *(v8h *)(dst + 8 * i) = *(const v8h *)(p + 8 * i);
-    } else if constexpr (N == 4) {
-        *(v4h *)dst = *(const v4h *)p;
-    } else if constexpr (N == 2) {
-        *(__half2 *)dst = *(const __half2 *)p;
-    } else {
-        dst[0] = *p;
-    }
 }
 
 // The same attention for launches of few workgroups (short prompts, few sessions and heads: 128 tokens x 16 heads
@@ -515,7 +622,7 @@ hipError_t attn_launch(const __half *q, const SessTable *sess, int blk, int M, i
                 return launch_prefill_split<D, 8>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32, st);
             return launch_prefill_split<D, 4>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32, st);
         }
-        k_attn_prefill<D><<<(B * nh + 7) / 8 * 8 * (((T + 63) / 64 + 1) / 2), 256, (size_t)2 * 2 * 16 * D * 8, st>>>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32);
+        k_attn_prefill<D><<<(B * nh + 7) / 8 * 8 * (((T + 63) / 64 + 1) / 2), 256, D >= 64 ? (size_t)2 * (D * 64 + 16 * D * 8) : (size_t)2 * 2 * 16 * D * 8, st>>>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32);
         return hipGetLastError();
     }
     if (nsplit == 2) {   // twice the waves per workgroup instead of two key ranges: nothing to merge afterwards

@@ -1,0 +1,32 @@
+// fp16 values as balanced 8-bit digits for exact products on the int8 matrix instruction.
+// Every fp16 value is an integer multiple of 2^-24: x = 2^-24 sum_j 256^j d_j with d_j in [-128, 127]; four digits
+// cover |x| < 127.5.  A sum of products of two such values is the sum over the digit pairs (i, j) of 256^(i + j - 6)
+// sum d_i d_j (in units of 1), i.e. sixteen int8 x int8 -> int32 products, exact.
+#pragma once
+#include "common.h"
+
+constexpr uint32_t DIGITS_BIG = 0x57f8;    // fp16 bits of 127.5: from here on four digits do not do
+
+// The digit planes of four values below 127.5 in magnitude, one word per plane (byte k = value k).
+// x * 256 rounded to an integer (up to a lower half in [-32896, 32639], which is what two balanced digits hold: the
+// addend moves the rounding boundary by a little over 2^-9) carries the upper two digits, the exact rest times 2^24
+// the lower two; both sit, plus 0x8080, in the low bytes of an fp32 sum.  Multiply-adds run at the full rate;
+// conversions to and from integers at a quarter of it.
+__device__ __forceinline__ void digit_planes4(const __half (&x)[4], int (&p)[4]) {
+    constexpr float M = 8388608.0f + 0x8080;
+    uint32_t t[4], u[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const float f = __half2float(x[i]);
+        const float hi = fmaf(f, 256.0f, 0.001953125f + 0.00000762939453125f) + M;
+        const float rest = fmaf(hi - M, -0.00390625f, f);
+        t[i] = __float_as_uint(hi);
+        u[i] = __float_as_uint(fmaf(rest, 16777216.0f, M));
+    }
+    const uint32_t a = __builtin_amdgcn_perm(u[1], u[0], 0x05010400), b = __builtin_amdgcn_perm(u[3], u[2], 0x05010400);
+    const uint32_t c = __builtin_amdgcn_perm(t[1], t[0], 0x05010400), d = __builtin_amdgcn_perm(t[3], t[2], 0x05010400);
+    p[0] = (int)(__builtin_amdgcn_perm(b, a, 0x05040100) ^ 0x80808080u);
+    p[1] = (int)(__builtin_amdgcn_perm(b, a, 0x07060302) ^ 0x80808080u);
+    p[2] = (int)(__builtin_amdgcn_perm(d, c, 0x05040100) ^ 0x80808080u);
+    p[3] = (int)(__builtin_amdgcn_perm(d, c, 0x07060302) ^ 0x80808080u);
+}

@@ -76,3 +76,27 @@ def test_attention_of_few_workgroups(d, first, T):
         assert (got.view(np.uint16) == ref.view(np.uint16)).mean() > 0.999
     span.close()
     osp.destroy()
+
+
+# Attention of calls that fill the GPU: scores as int8 digit products for head_dim 64 and 128.  scale: QKV weights that
+# keep every query and key below 127.5 (digits), push single ones over it (the fp64 form for their tiles) and most of
+# them; T: one and several 64-query blocks per workgroup, an odd count of blocks; second call onto a filled cache.
+@pytest.mark.parametrize("d,nh,B,T", [(64, 8, 32, 17), (128, 4, 64, 20), (64, 16, 8, 140)])
+@pytest.mark.parametrize("scale", [1.0, 40.0, 400.0])
+def test_attention_with_digit_scores(d, nh, B, T, scale):
+    H = d * nh
+    cfg = synth.SpanConfig("digits", 1, H, nh, B, T, 1, 1, (20.0, 40.0), d + T, ffn=256)
+    osp = oracle.Span(1, H, nh, 256, 1e-5, 6.0)
+    span = binding.Span(1, H, nh, 256, B * T, 1e-5, 6.0, DEV)
+    p = synth.block_params(cfg, 0)
+    p["w_qkv"] = p["w_qkv"] * np.float32(scale)
+    osp.load_block(0, p)
+    span.load_block(0, p)
+    oses, gses = [osp.open_session(2 * T) for _ in range(B)], [span.open_session(2 * T) for _ in range(B)]
+    for call in range(2):
+        x = synth.hidden_states(cfg, call, B, T)
+        ref, got = osp.step(oses, x), to_np(span.prefill(gses, to_dev(x)))
+        hidden_close(got, ref, "call %d" % call)
+        assert (got.view(np.uint16) == ref.view(np.uint16)).mean() > 0.999
+    span.close()
+    osp.destroy()
