@@ -208,11 +208,14 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
             vd[((fk >> 2) * NB + i) * 64 + (fk & 3) * 16 + (threadIdx.x & 15)] = (double)__half2float(vraw[i]);
         }
     };
-    fetch(0);
-    stash(0);
+    // Newest tile first: the running maximum is then found early (the ALiBi bias falls with the distance), and the
+    // rescaling of sums and outputs is skipped while no query of the wave has a new one.
+    fetch(nkt - 1);
+    stash(nkt - 1);
     __syncthreads();
-    for (int kt = 0; kt < nkt; kt++) {
-        if (kt + 1 < nkt) fetch(kt + 1);              // in flight during the multiplications below
+    double dist = (double)(qpos - (nkt - 1) * 16 - g);               // distance to this lane's first key of the tile
+    for (int kt = nkt - 1; kt >= 0; kt--, dist += 16.0) {
+        if (kt > 0) fetch(kt - 1);                    // in flight during the multiplications below
         if (kt < nkt_w) {
             const unsigned char *kb = kvl + (size_t)(kt & 1) * (KTB + VT);
             const double *kd0 = (const double *)kb, *vd = (const double *)(kb + KTB) + lane;
@@ -249,32 +252,39 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
             }
             double sc[4], mt = -INFINITY;
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int kpos = kt * 16 + 4 * r + g;
-                sc[r] = (kpos <= qpos && kpos <= last_key) ? S[r] - slope * (double)(qpos - kpos) : -INFINITY;
-                mt = fmax(mt, sc[r]);
+            for (int r = 0; r < 4; r++) sc[r] = fma(-slope, dist - 4.0 * r, S[r]);
+            if (kt * 16 + 15 > L + qt * 16) {         // wave-uniform: keys some query of the wave does not see
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const int kpos = kt * 16 + 4 * r + g;
+                    if (kpos > qpos || kpos > last_key) sc[r] = -INFINITY;
+                }
             }
+#pragma unroll
+            for (int r = 0; r < 4; r++) mt = fmax(mt, sc[r]);
             mt = fmax(mt, __shfl_xor(mt, 16));
             mt = fmax(mt, __shfl_xor(mt, 32));
             const double m_new = fmax(m_run, mt);
-            const double alpha = (m_run == -INFINITY) ? 0.0 : exp(m_run - m_new);
-            double p[4], psum = 0.0;
+            if (__any(m_new > m_run)) {
+                const double alpha = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - m_new);
+                l_run *= alpha;
+#pragma unroll
+                for (int b = 0; b < NB; b++) O[b] *= alpha;
+                m_run = m_new;
+            }
+            double p[4];
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                p[r] = (sc[r] == -INFINITY) ? 0.0 : exp(sc[r] - m_new);
-                psum += p[r];
+                p[r] = (sc[r] == -INFINITY) ? 0.0 : exp_f64(sc[r] - m_run);
+                l_run += p[r];                        // per lane group; the groups are added at the end
             }
-            l_run = l_run * alpha + psum;             // per lane group; the groups are added at the end
-            m_run = m_new;
-#pragma unroll
-            for (int b = 0; b < NB; b++) O[b] *= alpha;
 #pragma unroll
             for (int r = 0; r < 4; r++)
 #pragma unroll
                 for (int b = 0; b < NB; b++)
                     O[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(vd[(r * NB + b) * 64], p[r], O[b], 0, 0, 0);
         }
-        if (kt + 1 < nkt) stash(kt + 1);              // that buffer was last read before the previous barrier
+        if (kt > 0) stash(kt - 1);                    // that buffer was last read before the previous barrier
         __syncthreads();
     }
     l_run += __shfl_xor(l_run, 16);
@@ -379,11 +389,11 @@ __global__ void __launch_bounds__(64 * NWK, 2) k_attn_prefill_split(const __half
         mt = fmax(mt, __shfl_xor(mt, 16));
         mt = fmax(mt, __shfl_xor(mt, 32));
         const double m_new = fmax(m_run, mt);         // -infinity while this wave has seen no key of this query
-        const double alpha = (m_run == -INFINITY) ? 0.0 : exp(m_run - m_new);
+        const double alpha = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - m_new);
         double p[4], psum = 0.0;
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-            p[r] = (sc[r] == -INFINITY) ? 0.0 : exp(sc[r] - m_new);
+            p[r] = (sc[r] == -INFINITY) ? 0.0 : exp_f64(sc[r] - m_new);
             psum += p[r];
         }
         l_run = l_run * alpha + psum;
@@ -411,7 +421,7 @@ __global__ void __launch_bounds__(64 * NWK, 2) k_attn_prefill_split(const __half
     for (int w = 1; w < NWK; w++) m = fmax(m, pm[w * 16 + c]);     // key 0 is visible to every query: finite
 #pragma unroll
     for (int w = 0; w < NWK; w++) {
-        f[w] = exp(pm[w * 16 + c] - m);
+        f[w] = exp_f64(pm[w * 16 + c] - m);
         l += f[w] * pl[w * 16 + c];
     }
 #pragma unroll
@@ -456,7 +466,7 @@ hipError_t launch_prefill_split(const __half *q, const SessTable *sess, int blk,
 __device__ __forceinline__ void merge_state(double &m, double &l, double *o, double m2, double l2, const double *o2,
                                             int n) {
     const double mm = fmax(m, m2);
-    const double fa = (m == -INFINITY) ? 0.0 : exp(m - mm), fb = (m2 == -INFINITY) ? 0.0 : exp(m2 - mm);
+    const double fa = (m == -INFINITY) ? 0.0 : exp_f64(m - mm), fb = (m2 == -INFINITY) ? 0.0 : exp_f64(m2 - mm);
     l = l * fa + l2 * fb;
     for (int e = 0; e < n; e++) o[e] = o[e] * fa + o2[e] * fb;
     m = mm;
@@ -527,8 +537,8 @@ __global__ void __launch_bounds__(64 * NW) k_attn_decode(const __half *__restric
             kv[it] = *(const v8h *)(Vc + (size_t)min(base + it * KPI + kslot, we - 1) * D + sub * 8);
         const double m_new = fmax(m_run, mb);                  // mb = -inf: no key of this lane group in the block
 
-        const double alpha = (m_run == -INFINITY) ? 0.0 : exp(m_run - m_new);
-        const double p_mine = (mb == -INFINITY) ? 0.0 : exp(sc_mine - m_new);   // exp(-inf) = 0 for keys past the end
+        const double alpha = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - m_new);
+        const double p_mine = (mb == -INFINITY) ? 0.0 : exp_f64(sc_mine - m_new);   // exp(-inf) = 0 for keys past the end
         double psum = p_mine;
 #pragma unroll
         for (int off = 1; off < LPK; off <<= 1) psum += __shfl_xor(psum, off);
@@ -591,7 +601,7 @@ __global__ void k_attn_combine(const SessTable *__restrict__ sess, int T, int nh
     for (int c = 0; c < nvalid; c++) m = fmax(m, pp[c * (D + 2)]);
     double l = 0.0, o = 0.0;
     for (int c = 0; c < nvalid; c++) {
-        const double wgt = exp(pp[c * (D + 2)] - m);
+        const double wgt = exp_f64(pp[c * (D + 2)] - m);
         l += wgt * pp[c * (D + 2) + 1];
         o += wgt * pp[c * (D + 2) + 2 + threadIdx.x];
     }

@@ -273,10 +273,37 @@ __device__ __forceinline__ float keep_f32(float v) {
 __device__ __forceinline__ __half decode_q8(const float *table, uint32_t code, float absmax) {
     return __float2half_rn(keep_f32(table[code] * absmax));
 }
-// tanh-form GeLU in fp64: 0.5 v (1 + tanh u) == v / (1 + exp(-2u))
+// e^x in fp64 to 0.8 units in the last place (the library's to 0.6) in 20 instructions without a branch: x = n ln 2 + r,
+// |r| <= 0.347, e^r = 1 + r + r^2 q(r) with q the degree-9 interpolation of (e^r - 1 - r) / r^2 in Chebyshev points
+// (relative error 1.6e-17).  0 below -745, finite (about 1e308) above 709.
+__device__ __forceinline__ double exp_f64(double x) {
+    constexpr double MAGIC = 6755399441055744.0;                    // 1.5 * 2^52: rounds to an integer, which sits in the low word
+    x = fmin(fmax(x, -800.0), 709.0);
+    const double t = fma(x, 0x1.71547652b82fep+0, MAGIC), n = t - MAGIC;
+    double r = fma(n, -0x1.62e42fef00000p-1, x);                    // n ln2_hi is exact
+    r = fma(n, -0x1.473de6af278edp-34, r);
+    double q = 0x1.af38ed3540c23p-26;
+    q = fma(q, r, 0x1.289186dc77ac4p-22);
+    q = fma(q, r, 0x1.71de0d8a3250fp-19);
+    q = fma(q, r, 0x1.a019b90ba6b3fp-16);
+    q = fma(q, r, 0x1.a01a01a7d1625p-13);
+    q = fma(q, r, 0x1.6c16c1788c5e4p-10);
+    q = fma(q, r, 0x1.1111111110994p-7);
+    q = fma(q, r, 0x1.5555555553d61p-5);
+    q = fma(q, r, 0x1.5555555555556p-3);
+    q = fma(q, r, 0x1.0000000000001p-1);
+    return __builtin_amdgcn_ldexp(fma(r * r, q, r) + 1.0, (int)(uint32_t)__double_as_longlong(t));
+}
+// tanh-form GeLU in fp64: 0.5 v (1 + tanh u) == v / (1 + exp(-2u)); the quotient from the reciprocal instruction, two
+// Newton steps and one correction by the remainder
 __device__ __forceinline__ double gelu_tanh(double v) {
     const double u = 0.7978845608028654 * (v + 0.044715 * v * v * v);
-    return v / (1.0 + exp(-2.0 * u));
+    const double d = 1.0 + exp_f64(-2.0 * u);
+    double y = __builtin_amdgcn_rcp(d);
+    y = fma(fma(-d, y, 1.0), y, y);
+    y = fma(fma(-d, y, 1.0), y, y);
+    const double q = v * y;
+    return fma(fma(-d, q, v), y, q);
 }
 // double -> fp16 with ONE rounding (to nearest even): the value is first rounded to odd at the 20 mantissa bits of
 // its high word (the low word only says whether anything lies below them), which is exact in fp32 and keeps enough
