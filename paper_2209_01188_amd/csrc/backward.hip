@@ -156,16 +156,19 @@ __global__ void __launch_bounds__(256) k_attn_bwd_prep(const float *__restrict__
 }
 
 // Transposed per-head copies for the attention backward: dst[s][h][dim][Tp] = src(s, h, row, dim), rows >= T zero.
-// mode 0: src is an [M, nh*D] activation matrix; mode 1: the keys of block blk in the sessions' caches.
+// One launch for the three of them, B workgroups along z each: queries and context gradients ([M, nh*D] activation
+// matrices) and the keys of block blk in the sessions' caches.
 template <int D>
-__global__ void __launch_bounds__(256) k_head_transpose(const __half *__restrict__ src, const SessTable *__restrict__ sess,
-                                                        int mode, int blk, int T, int Tp, int nh, __half *__restrict__ dst) {
+__global__ void __launch_bounds__(256) k_head_transpose(const __half *__restrict__ q, const __half *__restrict__ dO,
+                                                        const SessTable *__restrict__ sess, int blk, int B, int T, int Tp, int nh,
+                                                        __half *__restrict__ QT, __half *__restrict__ dOT, __half *__restrict__ KT) {
     constexpr int PN = D + 2;                                  // odd number of dwords per row: column reads spread over the banks
     __shared__ __half tile[32 * PN];
-    const int r0 = blockIdx.x * 32, h = blockIdx.y, s = blockIdx.z;
+    const int r0 = blockIdx.x * 32, h = blockIdx.y, which = blockIdx.z / B, s = blockIdx.z - which * B;
     const __half *base;
+    __half *dst = which == 0 ? QT : which == 1 ? dOT : KT;
     size_t stride;
-    if (mode == 0) { base = src + (size_t)s * T * nh * D + h * D; stride = (size_t)nh * D; }
+    if (which < 2) { base = (which ? dO : q) + (size_t)s * T * nh * D + h * D; stride = (size_t)nh * D; }
     else { base = sess->kv[s] + ((size_t)blk * 2 * nh + h) * sess->cap[s] * D; stride = D; }
     for (int i = threadIdx.x; i < 32 * D / 2; i += 256) {
         const int rr = i / (D / 2), c2 = (i - rr * (D / 2)) * 2;
@@ -396,10 +399,7 @@ template <int D>
 hipError_t attn_bwd_launch(const __half *q, const SessTable *sess, int blk, int B, int T, int Tp, int nh, const __half *dO,
                            __half *QT, __half *KT, __half *dOT, const float *lse, const float *Dv, __half *dqkv,
                            hipStream_t st) {
-    const dim3 gt(Tp / 32, nh, B);
-    k_head_transpose<D><<<gt, 256, 0, st>>>(q, sess, 0, blk, T, Tp, nh, QT);
-    k_head_transpose<D><<<gt, 256, 0, st>>>(nullptr, sess, 1, blk, T, Tp, nh, KT);
-    k_head_transpose<D><<<gt, 256, 0, st>>>(dO, sess, 0, blk, T, Tp, nh, dOT);
+    k_head_transpose<D><<<dim3(Tp / 32, nh, 3 * B), 256, 0, st>>>(q, dO, sess, blk, B, T, Tp, nh, QT, dOT, KT);
     const int grid = (B * nh + 7) / 8 * 8 * (((T + 63) / 64 + 1) / 2);
     k_attn_bwd<D, false><<<grid, 256, 0, st>>>(q, sess, blk, B, T, Tp, nh, dO, QT, KT, dOT, lse, Dv, dqkv);
     k_attn_bwd<D, true><<<grid, 256, 0, st>>>(q, sess, blk, B, T, Tp, nh, dO, QT, KT, dOT, lse, Dv, dqkv);

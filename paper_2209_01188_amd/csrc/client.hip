@@ -111,11 +111,6 @@ constexpr int LMD_CH = 4;                  // 64-column pieces per chunk
 constexpr uint32_t LMD_BIG = 0x57f8;       // fp16 bits of 127.5
 constexpr uint32_t LMD_SMALL = 0x33e0;     // fp16 bits of 0.246: below it three digits do, and lm_planes_small holds
 
-__device__ __forceinline__ uint32_t lm_pk_max(uint32_t a, uint32_t b) {      // of the two halves
-    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-    const us2 r = __builtin_elementwise_max(*(us2 *)&a, *(us2 *)&b);
-    return *(const uint32_t *)&r;
-}
 // three planes of four values below LMD_SMALL in magnitude (two words of two halves).  x * 2^24 + 2^23 + 0x408080 is
 // exact in fp32 and its low bytes are the digits plus 0x80, 0x80 and 0x40: one multiply-add straight from fp16
 // (conversions to and from integers run at a quarter of its rate), then byte permutations.
@@ -321,7 +316,7 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
 #pragma unroll
                     for (int p = 0; p < WN; p++)
 #pragma unroll
-                        for (int i = 0; i < 8; i++) mx = lm_pk_max(mx, (uint32_t)e[u][p][i >> 2][i & 3] & 0x7fff7fffu);
+                        for (int i = 0; i < 8; i++) mx = pk_max_u16(mx, (uint32_t)e[u][p][i >> 2][i & 3] & 0x7fff7fffu);
                     mx = max(mx & 0xffffu, mx >> 16);
                     const bool four = __any(mx >= LMD_SMALL);
                     v4i d[WN][4];

@@ -314,6 +314,20 @@ __device__ __forceinline__ __half d2h_rn(double v) {
     const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32) | min(lo, 1u);
     return __float2half_rn(keep_f32((float)__longlong_as_double((long long)((uint64_t)hi << 32))));
 }
+__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {     // of the two halves of a word
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    const us2 r = __builtin_elementwise_max(*(us2 *)&a, *(us2 *)&b);
+    return *(const uint32_t *)&r;
+}
+// smallest non-negative fp16 bit pattern whose value is >= theta (fp16 magnitudes order like their bits)
+inline uint32_t ps_theta_to_bits(float theta) {
+    if (!(theta > 0.0f)) return 0u;
+    _Float16 h = (_Float16)theta;          // round to nearest
+    unsigned short b;
+    memcpy(&b, &h, 2);
+    if ((float)h < theta) b++;             // next pattern up (0x7bff + 1 = 0x7c00 = +inf)
+    return b;
+}
 // int8 code of one activation/weight: fp32 product, round half to even, clamp
 __device__ __forceinline__ int q8(float x, float r) {
     float q = rintf(x * r);

@@ -60,7 +60,7 @@ template <int U>
 __device__ __forceinline__ void limb_x_tiles(const __half *__restrict__ X, int M, int K, int *__restrict__ count,
                                              const int *__restrict__ list, int8_t *__restrict__ xl, int n_out,
                                              int bid, int nblk) {
-    const int CT = (n_out + 63) >> 6, MTT = (M + 15) >> 4, lane = threadIdx.x, total = MTT * CT;
+    const int CT = (n_out + 63) >> 6, MTT = (M + 15) >> 4, lane = threadIdx.x & 63, total = MTT * CT;
     int need = 0;
     for (int item0 = bid; item0 < total; item0 += nblk * U) {
         int4 idx4[U][4];
@@ -128,7 +128,7 @@ __device__ __forceinline__ void limb_x_tiles(const __half *__restrict__ X, int M
 template <int U>
 __device__ __forceinline__ void digit_w_tiles(const LinearW &w, const int *__restrict__ list, int8_t *__restrict__ wd,
                                               int n_out, int bid, int nblk) {
-    const int CT = (n_out + 63) >> 6, NT = w.N >> 4, KT = w.K >> 6, lane = threadIdx.x, row = lane & 15;
+    const int CT = (n_out + 63) >> 6, NT = w.N >> 4, KT = w.K >> 6, lane = threadIdx.x & 63, row = lane & 15;
     const int total = NT * CT;
     const int8_t *__restrict__ wt = w.wt;
     for (int item0 = bid; item0 < total; item0 += nblk * U) {
@@ -218,16 +218,18 @@ struct GemmArgs {
 };
 
 // Both kinds of digit tiles in one launch (a launch costs as much as the work of a call with few tiles): the first
-// NBX workgroups cut the activations, the rest the weights.  Does nothing unless the call has more outlier columns
+// NBX waves cut the activations, the rest the weights.  Workgroups of four waves, which share nothing: a launch that
+// finds nothing to do costs by its number of workgroups.  Does nothing unless the call has more outlier columns
 // than the fp64 path takes.
 template <int U>
-__global__ void __launch_bounds__(64) k_digit_tiles(const __half *__restrict__ X, int M, LinearW w, int *__restrict__ count,
+__global__ void __launch_bounds__(256) k_digit_tiles(const __half *__restrict__ X, int M, LinearW w, int *__restrict__ count,
                                                       const int *__restrict__ list, int8_t *__restrict__ xl,
                                                       int8_t *__restrict__ wd, int NBX) {
     const int n_out = count[0];
     if (n_out <= PS_EXACT_OUTLIERS) return;
-    if ((int)blockIdx.x < NBX) limb_x_tiles<U>(X, M, w.K, count, list, xl, n_out, (int)blockIdx.x, NBX);
-    else digit_w_tiles<U>(w, list, wd, n_out, (int)blockIdx.x - NBX, (int)gridDim.x - NBX);
+    const int wv = (int)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (wv < NBX) limb_x_tiles<U>(X, M, w.K, count, list, xl, n_out, wv, NBX);
+    else digit_w_tiles<U>(w, list, wd, n_out, wv - NBX, (int)gridDim.x * 4 - NBX);
 }
 
 enum { GEMM_INT8 = 0, GEMM_F16 = 1, GEMM_DIGITS = 2 };
@@ -817,7 +819,7 @@ hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t 
     // The outlier-heavy case first (every kernel of it returns at once when the call has few outlier columns):
     // digit tiles of the activations and of the dequantized weights, the digit products (a second
     // launch for digit planes 4 and 5, which only activations of magnitude 127.5 and more have).
-    k_digit_tiles<2><<<2048 + 4096, 64, 0, st>>>(X, M, w, (int *)os.count, mo.list, mo.xl, mo.wd, 2048);
+    k_digit_tiles<2><<<(2048 + 4096) / 4, 256, 0, st>>>(X, M, w, (int *)os.count, mo.list, mo.xl, mo.wd, 2048);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int pg = 0; pg < 2; pg++) {

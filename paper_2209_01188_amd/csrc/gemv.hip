@@ -12,16 +12,9 @@
 
 namespace {
 
-typedef unsigned short us2 __attribute__((ext_vector_type(2)));
-
 __device__ __forceinline__ int byte_of(const v4i &w, int j) {
     int word = (j < 8) ? ((j < 4) ? w[0] : w[1]) : ((j < 12) ? w[2] : w[3]);
     return (int)(int8_t)((word >> ((j & 3) * 8)) & 0xff);
-}
-
-__device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b) {
-    us2 r = __builtin_elementwise_max(*(us2 *)&a, *(us2 *)&b);
-    return *(uint32_t *)&r;
 }
 
 struct RowIn {
@@ -223,7 +216,7 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
             }
             const uint32_t a0 = vals[i][0] & 0x7fff7fffu, a1 = vals[i][1] & 0x7fff7fffu;
             const uint32_t a2 = vals[i][2] & 0x7fff7fffu, a3 = vals[i][3] & 0x7fff7fffu;
-            const uint32_t cm = pk_max(pk_max(a0, a1), pk_max(a2, a3));
+            const uint32_t cm = pk_max_u16(pk_max_u16(a0, a1), pk_max_u16(a2, a3));
             const uint32_t cmax = max(cm & 0xffffu, cm >> 16);
             if (cmax >= in.theta_bits) {
                 uint32_t byte = 0;
@@ -411,23 +404,13 @@ hipError_t launch1(bool ln, const LinearW &w, const RowIn &in, const OutDesc &o,
     return launch2<U, 16>(ln, w, in, o, sess, st);
 }
 
-// smallest non-negative fp16 bit pattern whose value is >= theta
-uint32_t theta_to_bits(float theta) {
-    if (!(theta > 0.0f)) return 0u;
-    _Float16 h = (_Float16)theta;          // round to nearest
-    unsigned short b;
-    memcpy(&b, &h, 2);
-    if ((float)h < theta) b++;             // next pattern up (0x7bff + 1 = 0x7c00 = +inf)
-    return b;
-}
-
 }  // namespace
 
 hipError_t ps_gemv_row(const LinearW &w, const __half *x, const __half *ln_g, const __half *ln_b, float eps,
                        float theta, const RowDebug &dbg, const OutDesc &o, const SessTable *sess, const QuantIn *qin,
                        hipStream_t st) {
     RowIn in;
-    in.x = x; in.ln_g = ln_g; in.ln_b = ln_b; in.eps = eps; in.theta_bits = theta_to_bits(theta);
+    in.x = x; in.ln_g = ln_g; in.ln_b = ln_b; in.eps = eps; in.theta_bits = ps_theta_to_bits(theta);
     in.q8 = nullptr; in.q8_absmax = nullptr; in.q8_block = 1; in.q8_x_out = nullptr;
     if (qin) {
         if (!ln_g) return hipErrorInvalidValue;   // codes are only decoded in front of a LayerNorm

@@ -176,11 +176,27 @@ __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restric
 // are rounded in another order.  PER chunks of 8 columns per thread (H <= 2048 PER).  Q8: the rows arrive as 8-bit
 // codes, see k_layernorm_q8.
 template <int PER, bool Q8>
-__global__ void __launch_bounds__(256) k_layernorm_rows(const __half *__restrict__ x, QuantIn qin,
+__global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restrict__ x, QuantIn qin,
                                                         const __half *__restrict__ g, const __half *__restrict__ b,
                                                         float eps, int M, int H, __half *__restrict__ y,
-                                                        uint32_t *__restrict__ mask, float theta) {
+                                                        uint32_t *__restrict__ mask, uint32_t theta_bits) {
     constexpr int NT = 256;
+    // narrow rows: gain and bias stay in registers as fp64 over the rows of the workgroup, and so do a row's values over
+    // its three passes (conversions to fp64 take eight times as long as the operations on the values)
+    constexpr bool WIDE_REGS = PER <= 2;
+    constexpr int NE = WIDE_REGS ? PER * 8 : 1;
+    double gd[NE], bd[NE];
+    if constexpr (WIDE_REGS) {
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            const int k = (threadIdx.x + i * NT) * 8;
+            if (k < H) {
+                const v8h gv = *(const v8h_any *)(g + k), bv = *(const v8h_any *)(b + k);
+#pragma unroll
+                for (int e = 0; e < 8; e++) { gd[i * 8 + e] = (double)(float)gv[e]; bd[i * 8 + e] = (double)(float)bv[e]; }
+            }
+        }
+    }
     __shared__ double sm[NT / 64];
     __shared__ float table[Q8 ? 256 : 1];
     if constexpr (Q8) {
@@ -231,39 +247,68 @@ __global__ void __launch_bounds__(256) k_layernorm_rows(const __half *__restrict
             }
         }
         if (row + (int)gridDim.x < M) request(row + gridDim.x);
-        double s = 0.0;
+        double s = 0.0, xd[NE];
 #pragma unroll
         for (int i = 0; i < PER; i++) {
             if ((int)(threadIdx.x + i * NT) * 8 < H) {
 #pragma unroll
-                for (int e = 0; e < 8; e++) s += (double)(float)v[i][e];
+                for (int e = 0; e < 8; e++) {
+                    const double x1 = (double)(float)v[i][e];
+                    if constexpr (WIDE_REGS) xd[i * 8 + e] = x1;
+                    s += x1;
+                }
             }
         }
         const double mean = block_sum<NT / 64>(s, sm) / (double)H;
+        // wide rows: converted again in every pass (kept as fp64 they would not fit the registers)
+        auto forget = [&]() {
+            if constexpr (!WIDE_REGS)
+#pragma unroll
+                for (int i = 0; i < PER; i++) {
+                    v4i &w = *(v4i *)&v[i];
+                    asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]));
+                }
+        };
+        forget();
         double q = 0.0;
 #pragma unroll
         for (int i = 0; i < PER; i++) {
             if ((int)(threadIdx.x + i * NT) * 8 < H) {
 #pragma unroll
                 for (int e = 0; e < 8; e++) {
-                    const double a = (double)(float)v[i][e] - mean;
+                    double a;
+                    if constexpr (WIDE_REGS) a = xd[i * 8 + e] -= mean;
+                    else a = (double)(float)v[i][e] - mean;
                     q += a * a;
                 }
             }
         }
         const double inv = 1.0 / sqrt(block_sum<NT / 64>(q, sm) / (double)H + (double)eps);
+        forget();
 #pragma unroll
         for (int i = 0; i < PER; i++) {
             const int k = (threadIdx.x + i * NT) * 8;
             if (k < H) {
-                const v8h gv = *(const v8h_any *)(g + k), bv = *(const v8h_any *)(b + k);
                 __half out[8];
+                if constexpr (WIDE_REGS) {
 #pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    out[e] = d2h_rn(((double)(float)v[i][e] - mean) * inv * (double)(float)gv[e] + (double)(float)bv[e]);
-                    flags[i] |= (fabsf(__half2float(out[e])) >= theta ? 1u : 0u) << e;
+                    for (int e = 0; e < 8; e++) out[e] = d2h_rn(xd[i * 8 + e] * inv * gd[i * 8 + e] + bd[i * 8 + e]);
+                } else {
+                    const v8h gv = *(const v8h_any *)(g + k), bv = *(const v8h_any *)(b + k);
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        out[e] = d2h_rn(((double)(float)v[i][e] - mean) * inv * (double)(float)gv[e] + (double)(float)bv[e]);
                 }
-                *(v8h *)(y + row0 + k) = *(const v8h *)out;
+                const v4i ov = *(const v4i *)out;
+                *(v4i *)(y + row0 + k) = ov;
+                uint32_t m = 0;
+#pragma unroll
+                for (int e = 0; e < 4; e++) m = pk_max_u16(m, (uint32_t)ov[e] & 0x7fff7fffu);
+                if (max(m & 0xffffu, m >> 16) >= theta_bits) {
+#pragma unroll
+                    for (int e = 0; e < 8; e++)
+                        flags[i] |= ((((uint32_t)ov[e >> 1] >> ((e & 1) * 16)) & 0x7fffu) >= theta_bits ? 1u : 0u) << e;
+                }
             }
         }
     }
@@ -282,10 +327,11 @@ template <bool Q8>
 void launch_layernorm_rows(const __half *x, const QuantIn &qin, const __half *g, const __half *b, float eps, int M, int H,
                            __half *y, uint32_t *mask, float theta, hipStream_t st) {
     const int grid = M < LN_ROWS_GRID ? M : LN_ROWS_GRID;
-    if (H <= 2048) k_layernorm_rows<1, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
-    else if (H <= 4096) k_layernorm_rows<2, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
-    else if (H <= 8192) k_layernorm_rows<4, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
-    else k_layernorm_rows<8, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, theta);
+    const uint32_t tb = ps_theta_to_bits(theta);
+    if (H <= 2048) k_layernorm_rows<1, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, tb);
+    else if (H <= 4096) k_layernorm_rows<2, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, tb);
+    else if (H <= 8192) k_layernorm_rows<4, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, tb);
+    else k_layernorm_rows<8, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, tb);
 }
 
 // -------------------------------------------------- many rows: mask, then quantize
@@ -324,6 +370,64 @@ __device__ __forceinline__ void rowquant_prep(const OutlierPrep &pr, const uint3
 }
 __host__ inline int rowquant_grid(int rows) { return 8 * (((rows / 16 + 7) / 8) * 16); }
 
+// Arithmetic of the row quantizers on a chunk of 16 columns (8 words of two halves), written for few instructions: with
+// a conversion, a clamp and a mask test per element the quantizer of 4096 rows of 16384 spent 28 of its 54 us in the
+// vector ALU.  bits: the chunk's outlier columns (usually none).
+typedef uint32_t chunk_t[8];
+__device__ __forceinline__ uint32_t chunk_absmax(const chunk_t &w, uint32_t bits) {     // packed: one maximum per half
+    uint32_t m = 0;
+    if (bits == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; i++) m = pk_max_u16(m, w[i] & 0x7fff7fffu);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const uint32_t two = bits >> (2 * i);
+            m = pk_max_u16(m, w[i] & (((two & 1u) ? 0u : 0x7fffu) | ((two & 2u) ? 0u : 0x7fff0000u)));
+        }
+    }
+    return m;
+}
+// codes rint(fp32(x r)): the fp32 product straight from fp16 (a multiply-add with -0, which the compiler must not see
+// through), the rounding by an addition that leaves the integer in the low byte.  No clamp: |x| <= the row's maximum
+// s and r = fp32(127 / s) give |x r| <= 127.00002; codes of outlier columns are cleared.
+__device__ __forceinline__ v4i chunk_codes(const chunk_t &w, uint32_t bits, float r) {
+    float neg0 = -0.0f;
+    asm("" : "+v"(neg0));
+    v4i out;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        uint32_t t[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const unsigned short hb = (unsigned short)(w[2 * k + (e >> 1)] >> ((e & 1) * 16));
+            t[e] = __float_as_uint(fmaf(__half2float(*(const __half *)&hb), r, neg0) + 12582912.0f);
+        }
+        out[k] = (int)__builtin_amdgcn_perm(__builtin_amdgcn_perm(t[3], t[2], 0x0c0c0400), __builtin_amdgcn_perm(t[1], t[0], 0x0c0c0400), 0x05040100);
+    }
+    if (bits) {
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                if ((bits >> (4 * k + e)) & 1u) out[k] &= ~(0xff << (8 * e));
+    }
+    return out;
+}
+template <int NW>
+__device__ __forceinline__ float row_scale(uint32_t m, uint32_t *sm) {
+    m = max(m & 0xffffu, m >> 16);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = sm[0];
+#pragma unroll
+    for (int i = 1; i < NW; i++) m = max(m, sm[i]);
+    const unsigned short b = (unsigned short)m;
+    return __half2float(*(const __half *)&b);
+}
+
 // One workgroup per row of the 16-padded row range.  Row scale = absolute maximum over
 // non-outlier columns; codes go to the MFMA operand tile order (same tiling as the
 // weights, rows = tokens); padding rows are written as zeros.
@@ -332,7 +436,7 @@ __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict
                                                         int8_t *__restrict__ xq_tiled,
                                                         int8_t *__restrict__ xo_tiled, float *__restrict__ sx,
                                                         int8_t *__restrict__ xq_dbg, int rows, int grid, OutlierPrep pr) {
-    __shared__ float sm[4];
+    __shared__ uint32_t sm[4];
     __shared__ int list[4 * PS_EXACT_OUTLIERS];
     if ((int)blockIdx.x >= grid) {
         rowquant_prep<256>(pr, mask, X, M, grid, list);
@@ -350,31 +454,23 @@ __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict
         return;
     }
     const __half *xr = X + (size_t)t * K;
-    float m = 0.0f;
+    uint32_t m = 0;
     for (int c = threadIdx.x; c < nchunk; c += 256) {
-        const uint32_t bits = mask16[c];
-        v8h a = *(const v8h *)(xr + c * 16), b = *(const v8h *)(xr + c * 16 + 8);
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            if (!((bits >> j) & 1u)) m = fmaxf(m, fabsf((float)a[j]));
-            if (!((bits >> (j + 8)) & 1u)) m = fmaxf(m, fabsf((float)b[j]));
-        }
+        chunk_t w;
+        *(v4i *)w = *(const v4i *)(xr + c * 16);
+        *(v4i *)(w + 4) = *(const v4i *)(xr + c * 16 + 8);
+        m = pk_max_u16(m, chunk_absmax(w, mask16[c]));
     }
-    const float s = block_max<4>(m, sm);
+    const float s = row_scale<4>(m, sm);
     if (threadIdx.x == 0) sx[t] = s;
     const float r = s > 0.0f ? 127.0f / s : 0.0f;
     for (int c = threadIdx.x; c < nchunk; c += 256) {
         const uint32_t bits = mask16[c];
-        v8h a = *(const v8h *)(xr + c * 16), b = *(const v8h *)(xr + c * 16 + 8);
-        int q[16];
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            q[j] = ((bits >> j) & 1u) ? 0 : q8((float)a[j], r);
-            q[j + 8] = ((bits >> (j + 8)) & 1u) ? 0 : q8((float)b[j], r);
-        }
-        v4i o;
-#pragma unroll
-        for (int i = 0; i < 4; i++) o[i] = pack4(q[4 * i], q[4 * i + 1], q[4 * i + 2], q[4 * i + 3]);
+        const v8h a = *(const v8h *)(xr + c * 16), b = *(const v8h *)(xr + c * 16 + 8);
+        chunk_t w;
+        *(v8h *)w = a;
+        *(v8h *)(w + 4) = b;
+        const v4i o = chunk_codes(w, bits, r);
         const size_t slot = ((tile_row + (c >> 2)) * 64 + (c & 3) * 16 + (t & 15)) * 16;
         *(v4i *)(xq_tiled + slot) = o;
         if (xq_dbg) *(v4i *)(xq_dbg + (size_t)t * K + c * 16) = o;
@@ -408,7 +504,7 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
                                                              int8_t *__restrict__ xq_tiled,
                                                              int8_t *__restrict__ xo_tiled, float *__restrict__ sx,
                                                              int8_t *__restrict__ xq_dbg, int rows, int grid, OutlierPrep pr) {
-    __shared__ float sm[NT / 64];
+    __shared__ uint32_t sm[NT / 64];
     __shared__ int list[NT / 64 * PS_EXACT_OUTLIERS];
     if ((int)blockIdx.x >= grid) {
         rowquant_prep<NT>(pr, mask, X, M, grid, list);
@@ -437,33 +533,27 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
             bits[i] = mask16[c];
         }
     }
-    float m = 0.0f;
+    uint32_t m = 0;
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
         if ((int)(threadIdx.x + i * NT) < nchunk) {
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                if (!((bits[i] >> j) & 1u)) m = fmaxf(m, fabsf((float)a[i][j]));
-                if (!((bits[i] >> (j + 8)) & 1u)) m = fmaxf(m, fabsf((float)b[i][j]));
-            }
+            chunk_t w;
+            *(v8h *)w = a[i];
+            *(v8h *)(w + 4) = b[i];
+            m = pk_max_u16(m, chunk_absmax(w, bits[i]));
         }
     }
-    const float s = block_max<NT / 64>(m, sm);
+    const float s = row_scale<NT / 64>(m, sm);
     if (threadIdx.x == 0) sx[t] = s;
     const float r = s > 0.0f ? 127.0f / s : 0.0f;
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
         const int c = threadIdx.x + i * NT;
         if (c < nchunk) {
-            int q[16];
-#pragma unroll
-            for (int j = 0; j < 8; j++) {
-                q[j] = ((bits[i] >> j) & 1u) ? 0 : q8((float)a[i][j], r);
-                q[j + 8] = ((bits[i] >> (j + 8)) & 1u) ? 0 : q8((float)b[i][j], r);
-            }
-            v4i o;
-#pragma unroll
-            for (int k = 0; k < 4; k++) o[k] = pack4(q[4 * k], q[4 * k + 1], q[4 * k + 2], q[4 * k + 3]);
+            chunk_t w;
+            *(v8h *)w = a[i];
+            *(v8h *)(w + 4) = b[i];
+            const v4i o = chunk_codes(w, bits[i], r);
             const size_t slot = ((tile_row + (c >> 2)) * 64 + (c & 3) * 16 + (t & 15)) * 16;
             *(v4i *)(xq_tiled + slot) = o;
             if (xq_dbg) *(v4i *)(xq_dbg + (size_t)t * K + c * 16) = o;
@@ -720,7 +810,7 @@ hipError_t ps_copy_bytes(const void *src, void *dst, size_t n, hipStream_t st) {
 hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float eps, int M, int H, __half *y,
                         uint32_t *mask, float theta, hipStream_t st) {
     // few rows: more threads per row (latency), many rows: more rows in flight
-    if ((M >= 512 || H < 4096) && H % 8 == 0 && H <= 16384) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
+    if ((M >= 128 || H < 4096) && H % 8 == 0 && H <= 16384) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
     else if (H >= 4096 && H <= 16384) k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     else if (M <= 256 && H >= 4096) k_layernorm<1024><<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     else k_layernorm<256><<<M, 256, 0, st>>>(x, g, b, eps, H, y, mask, theta);
@@ -728,7 +818,7 @@ hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
                            int H, __half *y, uint32_t *mask, float theta, hipStream_t st) {
-    if ((M >= 512 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
+    if ((M >= 128 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
         launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, theta, st);
     else if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, theta);
     else k_layernorm_q8<256><<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, theta);

@@ -81,7 +81,8 @@ def test_attention_of_few_workgroups(d, first, T):
 # Attention of calls that fill the GPU: scores as int8 digit products for head_dim 64 and 128.  scale: QKV weights that
 # keep every query and key below 127.5 (digits), push single ones over it (the fp64 form for their tiles) and most of
 # them; T: one and several 64-query blocks per workgroup, an odd count of blocks; second call onto a filled cache.
-@pytest.mark.parametrize("d,nh,B,T", [(64, 8, 32, 17), (128, 4, 64, 20), (64, 16, 8, 140)])
+# the last two shapes make few workgroups and take the form whose waves split the keys
+@pytest.mark.parametrize("d,nh,B,T", [(64, 8, 32, 17), (128, 4, 64, 20), (64, 16, 8, 140), (128, 4, 3, 21), (64, 8, 2, 70)])
 @pytest.mark.parametrize("scale", [1.0, 40.0, 400.0])
 def test_attention_with_digit_scores(d, nh, B, T, scale):
     H = d * nh
