@@ -170,7 +170,7 @@ OutDesc plain_out(__half *y, int epilogue, const __half *resid) {
     return o;
 }
 
-// The blocks of the span on M = B*T rows whose session table already sits in the workspace.
+// The blocks of the span on M = B*T rows whose session table already sits in the workspace (ps_call_setup).
 // save == nullptr: intermediates live in the workspace.  Otherwise they are written where save says and
 // the up linear also stores the sum it feeds to GeLU.
 int forward_blocks(petals_span *sp, int M, int T, int max_keys, const __half *hidden_in, __half *hidden_out,
@@ -178,12 +178,11 @@ int forward_blocks(petals_span *sp, int M, int T, int max_keys, const __half *hi
     const petals_span_config &c = sp->cfg;
     Workspace &ws = sp->ws;
     const int H = c.hidden, nh = c.n_heads, d = H / nh;
-    // Multi-row calls: the outlier-column masks of all linears are cleared once; the kernel that writes a
+    // Multi-row calls: the outlier-column masks of all linears have been cleared with the call's table; the kernel that writes a
     // linear's input (LayerNorm, attention, the GeLU epilogue) flags the columns.  One-row calls detect
     // the outliers inside the fused kernel.
     const bool multi = M > 1;
     const float theta = c.outlier_threshold;
-    if (multi) HIP_TRY(ps_fill_u32(ws.masks, (size_t)c.n_blocks * 4 * ws.mask_words, 0u, st));
     // hidden states arriving as 8-bit codes: the first LayerNorm decodes them and leaves the fp16 rows in qin->x_out
     const __half *x = qin ? qin->x_out : hidden_in;
     for (int b = 0; b < c.n_blocks; b++) {
@@ -250,7 +249,7 @@ int run_call(petals_span *sp, petals_session *const *sessions, int32_t B, int32_
 
     Workspace &ws = sp->ws;
     const int M = B * T;
-    HIP_TRY(ps_set_table(tab, ws.table, st));
+    HIP_TRY(ps_call_setup(tab, ws.table, ws.masks, M > 1 ? (size_t)c.n_blocks * 4 * ws.mask_words : 0, st));
     QuantIn qin;
     if (qin_arg) {
         // the decoded rows live in the buffer that only the outputs of odd blocks use: block 0 reads them (LayerNorm,

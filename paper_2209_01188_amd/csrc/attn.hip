@@ -13,11 +13,15 @@ namespace {
 
 constexpr int ATTN_SPLIT_BELOW = 256;
 
-__global__ void k_set_table(SessTable t, SessTable *dst) {
-    // 64 threads copy the table word by word
-    const uint32_t *s = (const uint32_t *)&t;
-    uint32_t *d = (uint32_t *)dst;
-    for (int i = threadIdx.x; i < (int)(sizeof(SessTable) / 4); i += blockDim.x) d[i] = s[i];
+// Start of a call: workgroup 0 copies the table word by word, all of them clear the outlier masks (one launch: a launch
+// of its own costs 2 to 4.5 us whatever it does).
+__global__ void __launch_bounds__(256) k_call_setup(SessTable t, SessTable *dst, uint32_t *masks, size_t n_masks) {
+    if (blockIdx.x == 0) {
+        const uint32_t *s = (const uint32_t *)&t;
+        uint32_t *d = (uint32_t *)dst;
+        for (int i = threadIdx.x; i < (int)(sizeof(SessTable) / 4); i += 256) d[i] = s[i];
+    }
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_masks; i += (size_t)gridDim.x * 256) masks[i] = 0u;
 }
 
 // N consecutive halves at an address aligned to min(16, 2 N) bytes
@@ -648,8 +652,9 @@ hipError_t attn_launch(const __half *q, const SessTable *sess, int blk, int M, i
 
 }  // namespace
 
-hipError_t ps_set_table(const SessTable &host_table, SessTable *dev_table, hipStream_t st) {
-    k_set_table<<<1, 64, 0, st>>>(host_table, dev_table);
+hipError_t ps_call_setup(const SessTable &host_table, SessTable *dev_table, uint32_t *masks, size_t n_masks, hipStream_t st) {
+    const size_t want = (n_masks + 255) / 256;
+    k_call_setup<<<(unsigned)(want < 1 ? 1 : want > 256 ? 256 : want), 256, 0, st>>>(host_table, dev_table, masks, n_masks);
     return hipGetLastError();
 }
 

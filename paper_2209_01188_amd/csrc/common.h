@@ -161,7 +161,8 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M);
 int ps_gemm_lds_ksplit(int N, int ktiles, int M);
 
 // attention of M = B*T query rows against the caches (new keys/values already appended)
-hipError_t ps_set_table(const SessTable &host_table, SessTable *dev_table, hipStream_t st);
+// the call's table, and (n_masks > 0) its outlier masks cleared
+hipError_t ps_call_setup(const SessTable &host_table, SessTable *dev_table, uint32_t *masks, size_t n_masks, hipStream_t st);
 #define PS_ATTN_MAX_SPLITS 16
 #define PS_ATTN_PARTIAL_SLOTS 8192   // (row, head, split) triples that may need a partial result
 // mask (may be null): outlier-column bits of ctx are ORed into it (|ctx| >= theta)
@@ -208,20 +209,50 @@ __device__ __forceinline__ void flag_outlier_bits(uint32_t *mask, int word, uint
 __device__ __forceinline__ void flag_outlier(uint32_t *mask, float theta, int k, __half v) {
     if (mask && fabsf(__half2float(v)) >= theta) flag_outlier_bits(mask, k >> 5, 1u << (k & 31));
 }
+// Wave-wide reductions on the data-parallel-primitive moves (a few clocks a step; an exchange through LDS takes some
+// sixty, and a row kernel of a few microseconds waits for six of them in a row): four shifted steps inside the rows of
+// 16 lanes, two row broadcasts, the result in lane 63.  All 64 lanes must be active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t old, uint32_t v) {     // lanes without a source keep `old`
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_move(float old, float v) {
+    return __uint_as_float(dpp_move<CTRL, ROWS>(__float_as_uint(old), __float_as_uint(v)));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double old, double v) {
+    const uint64_t o = (uint64_t)__double_as_longlong(old), u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = dpp_move<CTRL, ROWS>((uint32_t)o, (uint32_t)u), hi = dpp_move<CTRL, ROWS>((uint32_t)(o >> 32), (uint32_t)(u >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+__device__ __forceinline__ uint32_t lane63(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+__device__ __forceinline__ float lane63(float v) { return __uint_as_float(lane63(__float_as_uint(v))); }
+__device__ __forceinline__ double lane63(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    return __longlong_as_double((long long)((uint64_t)lane63((uint32_t)(u >> 32)) << 32 | lane63((uint32_t)u)));
+}
+template <typename T, typename OP>
+__device__ __forceinline__ T wave_reduce(T v, T none, OP op) {               // none: what a lane without a partner combines with
+    v = op(v, dpp_move<0x111, 0xf>(none, v));     // row_shr 1, 2, 4, 8
+    v = op(v, dpp_move<0x112, 0xf>(none, v));
+    v = op(v, dpp_move<0x114, 0xf>(none, v));
+    v = op(v, dpp_move<0x118, 0xf>(none, v));
+    v = op(v, dpp_move<0x142, 0xa>(none, v));     // row_bcast 15 into rows 1 and 3
+    v = op(v, dpp_move<0x143, 0xc>(none, v));     // row_bcast 31 into rows 2 and 3
+    return lane63(v);
+}
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    return wave_reduce(v, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+    return wave_reduce(v, 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
 }
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    return wave_reduce(v, 0.0f, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    return wave_reduce(v, 0.0, [](double a, double b) { return a + b; });
 }
 // workgroup reductions over NW waves; sm: NW floats of LDS; sums are added in a fixed order
 template <int NW>

@@ -232,8 +232,7 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
         }
         if (LN && i == (MAXCH - 1) / 2) request_point(std::integral_constant<int, 2>());   // halfway through the arithmetic
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mreg = max(mreg, (uint32_t)__shfl_xor((int)mreg, off));
+    mreg = wave_max(mreg);
     if (lane == 0) smi[wave] = (int)mreg;
     lds_barrier();
     request_point(std::integral_constant<int, LN ? 3 : 1>());

@@ -416,9 +416,7 @@ __device__ __forceinline__ v4i chunk_codes(const chunk_t &w, uint32_t bits, floa
 }
 template <int NW>
 __device__ __forceinline__ float row_scale(uint32_t m, uint32_t *sm) {
-    m = max(m & 0xffffu, m >> 16);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    m = wave_max(max(m & 0xffffu, m >> 16));
     if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
     __syncthreads();
     m = sm[0];
@@ -693,8 +691,7 @@ __global__ void __launch_bounds__(NT) k_hidden_quantize_wide(const __half *__res
     for (int i = 0; i < PER; i++)
 #pragma unroll
         for (int e = 0; e < 8; e++) mb = max(mb, ((uint32_t)xv[i][e >> 1] >> ((e & 1) * 16)) & 0x7fffu);   // fp16 magnitudes order like their bits
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, off));
+    mb = wave_max(mb);
     if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = mb;
     __syncthreads();
 #pragma unroll
