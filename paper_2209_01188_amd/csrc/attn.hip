@@ -5,6 +5,7 @@
 // session): k_attn_prefill on the fp64 matrix instruction; for the backward pass it can also store the
 // log of the softmax denominators and the context before its fp16 rounding.
 #include <mutex>
+#include <utility>
 
 #include "common.h"
 #include "digits.h"
@@ -266,8 +267,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
             }
 #pragma unroll
             for (int r = 0; r < 4; r++) mt = fmax(mt, sc[r]);
-            mt = fmax(mt, __shfl_xor(mt, 16));
-            mt = fmax(mt, __shfl_xor(mt, 32));
+            mt = swap_reduce<32>(swap_reduce<16>(mt, max_f64), max_f64);
             const double m_new = fmax(m_run, mt);
             if (__any(m_new > m_run)) {
                 const double alpha = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - m_new);
@@ -291,8 +291,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
         if (kt > 0) stash(kt - 1);                    // that buffer was last read before the previous barrier
         __syncthreads();
     }
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    l_run = swap_reduce<32>(swap_reduce<16>(l_run, add_f64), add_f64);
     // log of the softmax denominator, kept for the backward pass: [head][row of the call]
     if (lse && tq < T && g == 0) lse[(size_t)h * B * T + qrow] = (float)(m_run + log(l_run));
     if (tq < T) {
@@ -390,8 +389,7 @@ __global__ void __launch_bounds__(64 * NWK, 2) k_attn_prefill_split(const __half
             sc[r] = (kpos <= qpos && kpos <= last_key) ? S[r] - slope * (double)(qpos - kpos) : -INFINITY;
             mt = fmax(mt, sc[r]);
         }
-        mt = fmax(mt, __shfl_xor(mt, 16));
-        mt = fmax(mt, __shfl_xor(mt, 32));
+        mt = swap_reduce<32>(swap_reduce<16>(mt, max_f64), max_f64);
         const double m_new = fmax(m_run, mt);         // -infinity while this wave has seen no key of this query
         const double alpha = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - m_new);
         double p[4], psum = 0.0;
@@ -410,8 +408,7 @@ __global__ void __launch_bounds__(64 * NWK, 2) k_attn_prefill_split(const __half
             for (int b = 0; b < NB; b++)
                 O[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__half2float(vc[r][b]), p[r], O[b], 0, 0, 0);
     }
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    l_run = swap_reduce<32>(swap_reduce<16>(l_run, add_f64), add_f64);
     // states of the waves -> LDS; wave r < 4 finishes register r of every output block
 #pragma unroll
     for (int r = 0; r < 4; r++)
@@ -466,14 +463,9 @@ hipError_t launch_prefill_split(const __half *q, const SessTable *sess, int blk,
     return hipGetLastError();
 }
 
-// softmax state of a set of keys: running maximum m, sum l of exp(z - m), weighted value sum o
-__device__ __forceinline__ void merge_state(double &m, double &l, double *o, double m2, double l2, const double *o2,
-                                            int n) {
-    const double mm = fmax(m, m2);
-    const double fa = (m == -INFINITY) ? 0.0 : exp_f64(m - mm), fb = (m2 == -INFINITY) ? 0.0 : exp_f64(m2 - mm);
-    l = l * fa + l2 * fb;
-    for (int e = 0; e < n; e++) o[e] = o[e] * fa + o2[e] * fb;
-    m = mm;
+template <typename F, int... I>
+__device__ __forceinline__ void for_constants(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
 }
 
 // Decode (one query per session): every wave owns a contiguous slice of the key range and runs
@@ -529,8 +521,7 @@ __global__ void __launch_bounds__(64 * NW) k_attn_decode(const __half *__restric
             double dot = 0.0;
 #pragma unroll
             for (int e = 0; e < 8; e++) dot += qf[e] * (double)(float)kv[it][e];
-#pragma unroll
-            for (int off = 1; off < LPK; off <<= 1) dot += __shfl_xor(dot, off);
+            dot = group_reduce<LPK>(dot, add_f64);
             const double sc = (j < we) ? dot - slope * (double)(i - j) : -INFINITY;
             mb = fmax(mb, sc);
             if (sub == it) sc_mine = sc;                       // lane `sub` of a group exponentiates key `it`
@@ -543,30 +534,45 @@ __global__ void __launch_bounds__(64 * NW) k_attn_decode(const __half *__restric
 
         const double alpha = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - m_new);
         const double p_mine = (mb == -INFINITY) ? 0.0 : exp_f64(sc_mine - m_new);   // exp(-inf) = 0 for keys past the end
-        double psum = p_mine;
-#pragma unroll
-        for (int off = 1; off < LPK; off <<= 1) psum += __shfl_xor(psum, off);
+        const double psum = group_reduce<LPK>(p_mine, add_f64);
         if (mb != -INFINITY) {                                 // per lane group; no cross-lane traffic inside
             l_run = l_run * alpha + psum;
             m_run = m_new;
 #pragma unroll
             for (int e = 0; e < 8; e++) o[e] *= alpha;
         }
-#pragma unroll
-        for (int it = 0; it < NIT; it++) {
-            const double p = __shfl(p_mine, kslot * LPK + it);  // 0 for keys past the end
+        // the probability of key `it` is lane `it`'s of the group (0 for keys past the end)
+        auto add_value = [&](auto itc) {
+            constexpr int it = decltype(itc)::value;
+            double p;
+            if constexpr (LPK >= 8) p = group_bcast<LPK, it>(p_mine);
+            else p = __shfl(p_mine, kslot * LPK + it);
 #pragma unroll
             for (int e = 0; e < 8; e++) o[e] += p * (double)(float)kv[it][e];
-        }
+        };
+        for_constants(add_value, std::make_integer_sequence<int, NIT>());
     }
     // merge the lane groups of the wave (same dims, different keys)
+    // the wave's maximum first, then every group's sums scaled to it and added up
+    {
+        double mw = m_run;
 #pragma unroll
-    for (int off = LPK; off < 64; off <<= 1) {
-        const double m2 = __shfl_xor(m_run, off), l2 = __shfl_xor(l_run, off);
-        double o2[8];
+        for (int off = LPK; off < 16; off <<= 1) mw = fmax(mw, __shfl_xor(mw, off));
+        mw = swap_reduce<32>(swap_reduce<16>(mw, max_f64), max_f64);
+        const double f = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - mw);
+        m_run = mw;
+        l_run *= f;
 #pragma unroll
-        for (int e = 0; e < 8; e++) o2[e] = __shfl_xor(o[e], off);
-        merge_state(m_run, l_run, o, m2, l2, o2, 8);
+        for (int e = 0; e < 8; e++) o[e] *= f;
+#pragma unroll
+        for (int off = LPK; off < 16; off <<= 1) {
+            l_run += __shfl_xor(l_run, off);
+#pragma unroll
+            for (int e = 0; e < 8; e++) o[e] += __shfl_xor(o[e], off);
+        }
+        l_run = swap_reduce<32>(swap_reduce<16>(l_run, add_f64), add_f64);
+#pragma unroll
+        for (int e = 0; e < 8; e++) o[e] = swap_reduce<32>(swap_reduce<16>(o[e], add_f64), add_f64);
     }
     if (kslot == 0) {
         if (sub == 0) { red_m[wave] = m_run; red_l[wave] = l_run; }
@@ -575,10 +581,14 @@ __global__ void __launch_bounds__(64 * NW) k_attn_decode(const __half *__restric
     }
     __syncthreads();
     if (threadIdx.x < D) {
-        double m = red_m[0], l = red_l[0], ov = red_o[0][threadIdx.x];
-        for (int w2 = 1; w2 < NW; w2++) {
-            const double o2 = red_o[w2][threadIdx.x];
-            merge_state(m, l, &ov, red_m[w2], red_l[w2], &o2, 1);
+        double m = red_m[0], l = 0.0, ov = 0.0;
+#pragma unroll
+        for (int w2 = 1; w2 < NW; w2++) m = fmax(m, red_m[w2]);
+#pragma unroll
+        for (int w2 = 0; w2 < NW; w2++) {
+            const double f = (red_m[w2] == -INFINITY) ? 0.0 : exp_f64(red_m[w2] - m);
+            l += f * red_l[w2];
+            ov += f * red_o[w2][threadIdx.x];
         }
         if (nsplit == 1) {
             const __half hv = d2h_rn(ov / l);

@@ -254,6 +254,54 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ double wave_sum(double v) {
     return wave_reduce(v, 0.0, [](double a, double b) { return a + b; });
 }
+// The same within groups of GROUP (2, 4, 8, 16) neighbouring lanes, every lane getting the result: exchanges inside
+// quads, then mirrored halves and rows (which hold one value per half or row by then).
+template <int GROUP, typename T, typename OP>
+__device__ __forceinline__ T group_reduce(T v, OP op) {
+    if constexpr (GROUP >= 2) v = op(v, dpp_move<0xb1, 0xf>(v, v));          // quad_perm 1 0 3 2
+    if constexpr (GROUP >= 4) v = op(v, dpp_move<0x4e, 0xf>(v, v));          // quad_perm 2 3 0 1
+    if constexpr (GROUP >= 8) v = op(v, dpp_move<0x141, 0xf>(v, v));         // row_half_mirror
+    if constexpr (GROUP >= 16) v = op(v, dpp_move<0x140, 0xf>(v, v));        // row_mirror
+    return v;
+}
+// lane n of every group of GROUP (8 or 16) neighbouring lanes, n a constant
+template <int GROUP, int N>
+__device__ __forceinline__ double group_bcast(double v) {
+    static_assert(GROUP == 8 || GROUP == 16, "groups of half a row or a row");
+    const double a = dpp_move<0x150 + N, 0xf>(v, v);                         // row_newbcast
+    if constexpr (GROUP == 16) return a;
+    const double b = dpp_move<0x150 + N + 8, 0xf>(v, v);
+    return (threadIdx.x & 8) ? b : a;
+}
+// the value of the lane 16 or 32 lanes away (rows or halves of the wave swapped), for symmetric operations: returns
+// op(own, other) in every lane
+template <int DIST, typename OP>
+__device__ __forceinline__ double swap_reduce(double v, OP op) {
+    static_assert(DIST == 16 || DIST == 32, "row or half");
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+    uint32_t a[2], b[2];
+    if constexpr (DIST == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        a[0] = l[0]; a[1] = h[0]; b[0] = l[1]; b[1] = h[1];
+    } else {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        a[0] = l[0]; a[1] = h[0]; b[0] = l[1]; b[1] = h[1];
+    }
+    return op(__longlong_as_double((long long)((uint64_t)a[1] << 32 | a[0])), __longlong_as_double((long long)((uint64_t)b[1] << 32 | b[0])));
+}
+template <int DIST>
+__device__ __forceinline__ int swap_sum(int v) {
+    if constexpr (DIST == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+        return (int)(l[0] + l[1]);
+    } else {
+        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+        return (int)(l[0] + l[1]);
+    }
+}
+__device__ __forceinline__ double add_f64(double a, double b) { return a + b; }
+__device__ __forceinline__ double max_f64(double a, double b) { return fmax(a, b); }
 // workgroup reductions over NW waves; sm: NW floats of LDS; sums are added in a fixed order
 template <int NW>
 __device__ __forceinline__ float block_max(float v, float *sm) {

@@ -326,10 +326,8 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
                 if (bits) outl += outlier_group<LN>(w1, bits, in, kt * 64 + kg * 16, mean, inv, swd);
             }
         }
-        acc += __shfl_xor(acc, 16);
-        acc += __shfl_xor(acc, 32);
-        outl += __shfl_xor(outl, 16);
-        outl += __shfl_xor(outl, 32);
+        acc = swap_sum<32>(swap_sum<16>(acc));
+        outl = swap_reduce<32>(swap_reduce<16>(outl, add_f64), add_f64);
         int *ri = red_i + ((it & 1) * NG + grp) * 128;
         double *rf = red_f + ((it & 1) * NG + grp) * 128;
         if (lane < 16) { ri[tw * 16 + lane] = acc; rf[tw * 16 + lane] = outl; }
