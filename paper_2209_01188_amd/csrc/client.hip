@@ -866,18 +866,9 @@ __device__ __forceinline__ void block_topk_ordered(const uint32_t (&key)[NPT], u
         for (int i = 0; i < NPT; i++) {
             const bool in = ((valid >> i) & 1u) && (pass == 3 || (key[i] >> (shift + 8)) == prefix);
             const uint32_t bin = (key[i] >> shift) & 255u;
-            if (pass < 3) {                                  // few keys share the prefix by now
-                if (in) atomicAdd(&hist[bin], 1);
-                continue;
-            }
-            unsigned long long todo = __ballot(in);
-            while (todo) {                                   // high bytes crowd a few bins: lanes that hit the same one add once
-                const int first = __ffsll((long long)todo) - 1;
-                const uint32_t b0 = (uint32_t)__shfl((int)bin, first);
-                const unsigned long long same = __ballot(in && bin == b0);
-                if (lane == first) atomicAdd(&hist[b0], __popcll(same));
-                todo &= ~same;
-            }
+            // (the high bytes of logits crowd a few bins: 64 lanes on one LDS word still take fewer clocks than finding
+            // out by ballots which lanes share a bin)
+            if (in) atomicAdd(&hist[bin], 1);
         }
         __syncthreads();
         if (wave == 0) {

@@ -352,6 +352,17 @@ __device__ __forceinline__ float keep_f32(float v) {
 __device__ __forceinline__ __half decode_q8(const float *table, uint32_t code, float absmax) {
     return __float2half_rn(keep_f32(table[code] * absmax));
 }
+// 1 / sqrt(v) for normal v > 0: the instruction's estimate and two Newton steps, good to a rounding or two of fp64
+// (the library's sqrt and division are a chain of some 60 dependent instructions, which a one-row kernel waits for)
+__device__ __forceinline__ double rsqrt_f64(double v) {
+    double y = __builtin_amdgcn_rsq(v);
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const double e = fma(-v * y, y, 1.0);
+        y = fma(y * e, fma(0.375, e, 0.5), y);
+    }
+    return y;
+}
 // e^x in fp64 to 0.8 units in the last place (the library's to 0.6) in 20 instructions without a branch: x = n ln 2 + r,
 // |r| <= 0.347, e^r = 1 + r + r^2 q(r) with q the degree-9 interpolation of (e^r - 1 - r) / r^2 in Chebyshev points
 // (relative error 1.6e-17).  0 below -745, finite (about 1e308) above 709.

@@ -194,7 +194,7 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
 #pragma unroll
         for (int i = 0; i < NWV; i++) { s += smd[i]; q += smq[i]; }
         mean = s / (double)K;
-        inv = 1.0 / sqrt(fmax(q / (double)K - mean * mean, 0.0) + (double)in.eps);
+        inv = rsqrt_f64(fmax(q / (double)K - mean * mean, 0.0) + (double)in.eps);
     } else {
         lds_barrier();        // mask bytes cleared before anybody sets one
     }
