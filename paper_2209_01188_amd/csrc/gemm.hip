@@ -224,11 +224,12 @@ hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_til
 }  // namespace
 
 // Rough times in microseconds, fitted to measurements on BLOOM-560M-, 7B1- and 176B-shaped linears at 96 to 512
-// rows.  64-row passes: each streams the N*K weight bytes at about 3 TB/s (what the 64-row form reaches), 5 us per
-// launch, 20 us for the row kernels in front.  Output blocks: a 256 x 256 block walks K/64 stages of about 0.7 us
+// rows.  64 rows per workgroup: the N*K weight bytes stream once per 64 rows at about 3 TB/s (what that form reaches),
+// 20 us for the row kernels in front.  Output blocks: a 256 x 256 block walks K/64 stages of about 0.7 us
 // (0.45 us for the 256 x 128 blocks that ps_gemm_lds takes when the call has at most 128 rows or at most 128
-// blocks), 256 blocks at a time, never faster than the weights stream at 4 TB/s, behind about 45 us of row, outlier
-// and digit kernels that are launched whatever the data.
+// blocks, whose stages are shared out if there are few of them: 8 us more for adding up), 256 blocks at a time, never
+// faster than the weights stream at 4 TB/s, behind about 35 us of row and digit kernels that are launched whatever the
+// data (45 us when the outlier preparation was a launch of its own).
 // PETALS_SPAN_MIDSIZE=blocks / =chunks in the environment overrides the choice (tests run both ways).
 constexpr double BLOCKS_FIXED = 35.0;
 

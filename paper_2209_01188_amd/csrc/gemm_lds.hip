@@ -7,7 +7,7 @@
 // 4-slot LDS ring filled by asynchronous global->LDS copies.
 //
 // Outlier columns: up to PS_EXACT_OUTLIERS of them are added exactly in the epilogue (fp64 matrix
-// instruction on compacted operands, see k_outlier_prep).  More than that: the fp16 x fp16 product over the
+// instruction on compacted operands, see outlier_prep.h).  More than that: the fp16 x fp16 product over the
 // outlier columns is computed EXACTLY in integer arithmetic on the int8 matrix cores.  Every fp16 value
 // is an integer multiple of 2^-24, so an activation is x = 2^-24 * sum_j 256^j * L_j with balanced
 // 8-bit digits L_j (4 of them up to |x| < 127.5, at most 6); a dequantized weight of output row n,
@@ -789,7 +789,8 @@ GemmArgs gemm_args(const void *a_tiles, const void *b_tiles, int ktiles, int M, 
 }  // namespace
 
 // Workgroups that share the k-tiles of a 256 x 128 output block of a call that makes few blocks (a 351-row call on a
-// 4096 x 16384 linear: 48 blocks on 256 compute units, 110 us; split five ways SPLITUS): as many as fill the compute
+// 4096 x 16384 linear: 48 blocks on 256 compute units, 110 us; split five ways 32 us, and 9 us for
+// adding up): as many as fill the compute
 // units once, each with at least 16 k-tiles to walk.
 int ps_gemm_lds_ksplit(int N, int ktiles, int M) {
     const int blocks = ((N + 255) / 256) * ((M + 127) / 128);

@@ -79,7 +79,21 @@ constexpr int GEMV_GROUP = 512;      // 8 waves share one 16-row panel at a time
 // chunk per wave at a time: HBM delivers 16 waves x 4 KB per compute unit in about 2 us, and a wave that asks for
 // more than the memory pipeline takes on stalls at the request until earlier data has arrived - the preparation
 // then waits with it (all chunks requested at once: the preparation takes 2.5 to 5 us longer, nothing gained).
-template <int U, int MAXCH, bool LN, int NG, int NPF>
+// CW: consecutive columns a thread takes at a time (MAXCH times).  8 for wide rows; 4 and 2 where the row has fewer than
+// 8 columns per thread, so that all 8 waves share the preparation instead of two or four (24 blocks of K = 1024: a step of 658 -> 621 us).
+template <int CW>
+__device__ __forceinline__ void load_words(const __half *p, int (&w)[CW / 2]) {
+    if constexpr (CW == 8) *(v4i *)w = *(const v4i *)p;
+    else if constexpr (CW == 4) *(v2i *)w = *(const v2i *)p;
+    else w[0] = *(const int *)p;
+}
+template <int CW>
+__device__ __forceinline__ float word_half(const int (&w)[CW / 2], int e) {
+    const unsigned short hb = (unsigned short)((uint32_t)w[e >> 1] >> ((e & 1) * 16));
+    return __half2float(*(const __half *)&hb);
+}
+
+template <int U, int MAXCH, bool LN, int NG, int NPF, int CW>
 __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn in, OutDesc o,
                                                              const SessTable *__restrict__ sess, int panels_per_wg,
                                                              int panels_extra) {
@@ -87,7 +101,7 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ double smd[NWV], smq[NWV];
     __shared__ int smi[NWV];
-    const int K = w.K, KT = K >> 6, nch8 = K >> 3;
+    const int K = w.K, KT = K >> 6, nch8 = K / CW;
     int8_t *xs = (int8_t *)lds;                               // K codes
     uint8_t *m8 = (uint8_t *)(lds + K);                       // K/8 mask bytes = K/16 group masks
     int *red_i = (int *)(lds + K + K / 8);                    // [2 parities][NG groups][8 waves][16]
@@ -103,34 +117,38 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
     const int nchunks = KT / U;
 
     // 1. the row (with LayerNorm also the gain and the bias): requested first, kept in registers
-    v8h xr[LN ? MAXCH : 1], gr[LN ? MAXCH : 1], br[LN ? MAXCH : 1];
-    v4i vals[MAXCH];
+    int xr[LN ? MAXCH : 1][CW / 2], gr[LN ? MAXCH : 1][CW / 2], br[LN ? MAXCH : 1][CW / 2];
+    int vals[MAXCH][CW / 2];
     if (LN) {
 #pragma unroll
         for (int i = 0; i < MAXCH; i++) {
             const int c = threadIdx.x + GEMV_THREADS * i;
             if (c < nch8) {
-                if (in.q8) {                        // uniform over the grid; the 8 columns share a codec block
-                    const uint2 qq = *(const uint2 *)(in.q8 + c * 8);
-                    const float am = in.q8_absmax[(c * 8) / in.q8_block];
-                    __half dec[8];
+                if (in.q8) {                        // uniform over the grid; the CW columns share a codec block
+                    uint32_t qq[2] = {0u, 0u};
+                    if constexpr (CW == 8) *(uint2 *)qq = *(const uint2 *)(in.q8 + c * CW);
+                    else if constexpr (CW == 4) qq[0] = *(const uint32_t *)(in.q8 + c * CW);
+                    else qq[0] = *(const uint16_t *)(in.q8 + c * CW);
+                    const float am = in.q8_absmax[(c * CW) / in.q8_block];
 #pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        dec[e] = decode_q8(d_code_table.code, ((e < 4 ? qq.x : qq.y) >> ((e & 3) * 8)) & 255u, am);
-                    xr[i] = *(const v8h *)dec;
-                    if (first) *(v8h *)(in.q8_x_out + c * 8) = xr[i];
+                    for (int e = 0; e < CW; e += 2) {
+                        const __half d0 = decode_q8(d_code_table.code, (qq[e >> 2] >> ((e & 3) * 8)) & 255u, am);
+                        const __half d1 = decode_q8(d_code_table.code, (qq[e >> 2] >> ((e & 3) * 8 + 8)) & 255u, am);
+                        xr[i][e >> 1] = (int)((uint32_t)__half_as_ushort(d0) | (uint32_t)__half_as_ushort(d1) << 16);
+                        if (first) *(int *)(in.q8_x_out + c * CW + e) = xr[i][e >> 1];
+                    }
                 } else {
-                    xr[i] = *(const v8h *)(in.x + c * 8);
+                    load_words<CW>(in.x + c * CW, xr[i]);
                 }
-                gr[i] = *(const v8h *)(in.ln_g + c * 8);
-                br[i] = *(const v8h *)(in.ln_b + c * 8);
+                load_words<CW>(in.ln_g + c * CW, gr[i]);
+                load_words<CW>(in.ln_b + c * CW, br[i]);
             }
         }
     } else {
 #pragma unroll
         for (int i = 0; i < MAXCH; i++) {
             const int c = threadIdx.x + GEMV_THREADS * i;
-            if (c < nch8) vals[i] = *(const v4i *)(in.x + c * 8);
+            if (c < nch8) load_words<CW>(in.x + c * CW, vals[i]);
         }
     }
     // A compute unit serves its waves' requests in order and takes on only so many ahead of the data (a wave that
@@ -182,7 +200,7 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
         for (int i = 0; i < MAXCH; i++) {
             if (threadIdx.x + GEMV_THREADS * i < nch8) {
 #pragma unroll
-                for (int e = 0; e < 8; e++) { const double a = (double)(float)xr[i][e]; s += a; q = fma(a, a, q); }
+                for (int e = 0; e < CW; e++) { const double a = (double)word_half<CW>(xr[i], e); s += a; q = fma(a, a, q); }
             }
         }
         s = wave_sum(s);
@@ -200,32 +218,37 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
     }
 
     // detect + absolute maximum over regular columns, 8 columns per register quad
-    uint32_t mreg = 0;
+    uint32_t mreg = 0, obits[MAXCH];
 #pragma unroll
     for (int i = 0; i < MAXCH; i++) {
         const int c = threadIdx.x + GEMV_THREADS * i;
         if (c < nch8) {
             if (LN) {
-                const v8h v = xr[i], gg = gr[i], bb = br[i];
-                __half out[8];
+                __half out[CW];
 #pragma unroll
-                for (int e = 0; e < 8; e++)
-                    out[e] = d2h_rn(((double)(float)v[e] - mean) * inv * (double)(float)gg[e] + (double)(float)bb[e]);
-                vals[i] = *(const v4i *)out;
-                if (first && in.a_out) *(v4i *)(in.a_out + c * 8) = vals[i];
+                for (int e = 0; e < CW; e++)
+                    out[e] = d2h_rn(((double)word_half<CW>(xr[i], e) - mean) * inv * (double)word_half<CW>(gr[i], e) + (double)word_half<CW>(br[i], e));
+#pragma unroll
+                for (int e = 0; e < CW; e += 2) {
+                    vals[i][e >> 1] = (int)((uint32_t)__half_as_ushort(out[e]) | (uint32_t)__half_as_ushort(out[e + 1]) << 16);
+                    if (first && in.a_out) *(int *)(in.a_out + c * CW + e) = vals[i][e >> 1];
+                }
             }
-            const uint32_t a0 = vals[i][0] & 0x7fff7fffu, a1 = vals[i][1] & 0x7fff7fffu;
-            const uint32_t a2 = vals[i][2] & 0x7fff7fffu, a3 = vals[i][3] & 0x7fff7fffu;
-            const uint32_t cm = pk_max_u16(pk_max_u16(a0, a1), pk_max_u16(a2, a3));
+            uint32_t cm = 0;
+#pragma unroll
+            for (int e = 0; e < CW / 2; e++) cm = pk_max_u16(cm, (uint32_t)vals[i][e] & 0x7fff7fffu);
             const uint32_t cmax = max(cm & 0xffffu, cm >> 16);
+            obits[i] = 0;
             if (cmax >= in.theta_bits) {
                 uint32_t byte = 0;
 #pragma unroll
-                for (int e = 0; e < 8; e++) {
+                for (int e = 0; e < CW; e++) {
                     const uint32_t a = ((uint32_t)vals[i][e >> 1] >> ((e & 1) * 16)) & 0x7fffu;
                     if (a >= in.theta_bits) byte |= 1u << e; else mreg = max(mreg, a);
                 }
-                m8[c] = (uint8_t)byte;
+                obits[i] = byte;
+                if constexpr (CW == 8) m8[c] = (uint8_t)byte;
+                else atomicOr((uint32_t *)m8 + (c * CW >> 5), byte << (c * CW & 31));
             } else {
                 mreg = max(mreg, cmax);
             }
@@ -245,28 +268,22 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
     for (int i = 0; i < MAXCH; i++) {
         const int c = threadIdx.x + GEMV_THREADS * i;
         if (c < nch8) {
-            const uint32_t byte = m8[c];          // set above by this same thread (0 from the initial clear)
-            // all 8 codes first, straight-line; the codes of outlier columns are then cleared byte by byte in the
+            // all codes first, straight-line; the codes of outlier columns are then cleared byte by byte in the
             // packed words (a test per element compiles to a branch per element, and a chunk with outlier
             // columns is rare)
-            int q[8];
+            int q[CW];
 #pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const unsigned short hb = (unsigned short)((uint32_t)vals[i][e >> 1] >> ((e & 1) * 16));
-                q[e] = q8(__half2float(*(const __half *)&hb), r);
-            }
-            v2i o2 = {pack4(q[0], q[1], q[2], q[3]), pack4(q[4], q[5], q[6], q[7])};
-            if (byte) {
-                uint32_t keep0 = 0xffffffffu, keep1 = 0xffffffffu;
+            for (int e = 0; e < CW; e++) q[e] = q8(word_half<CW>(vals[i], e), r);
+            uint32_t o2[2] = {0u, 0u};
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    keep0 &= ~(((byte >> e) & 1u) * (0xffu << (8 * e)));
-                    keep1 &= ~(((byte >> (4 + e)) & 1u) * (0xffu << (8 * e)));
-                }
-                o2[0] &= (int)keep0;
-                o2[1] &= (int)keep1;
+            for (int e = 0; e < CW; e++) o2[e >> 2] |= (uint32_t)(q[e] & 0xff) << (8 * (e & 3));
+            if (obits[i]) {
+#pragma unroll
+                for (int e = 0; e < CW; e++) o2[e >> 2] &= ~(((obits[i] >> e) & 1u) * (0xffu << (8 * (e & 3))));
             }
-            *(v2i *)(xs + c * 8) = o2;
+            if constexpr (CW == 8) *(uint2 *)(xs + c * 8) = *(const uint2 *)o2;
+            else if constexpr (CW == 4) *(uint32_t *)(xs + c * 4) = o2[0];
+            else *(uint16_t *)(xs + c * 2) = (uint16_t)o2[0];
         }
         if (!LN && i == (MAXCH - 1) / 2) request_point(std::integral_constant<int, 2>());  // halfway through the quantization
     }
@@ -342,10 +359,10 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
     }
 }
 
-template <int U, int MAXCH, int NG, int NPF>
+template <int U, int MAXCH, int NG, int NPF, int CW>
 hipError_t launch4(bool ln, const LinearW &w, const RowIn &in, const OutDesc &o, const SessTable *sess, int G, int per,
                    int extra, size_t base, size_t lds, size_t budget, hipStream_t st) {
-    auto kern = ln ? k_gemv_row<U, MAXCH, true, NG, NPF> : k_gemv_row<U, MAXCH, false, NG, NPF>;
+    auto kern = ln ? k_gemv_row<U, MAXCH, true, NG, NPF, CW> : k_gemv_row<U, MAXCH, false, NG, NPF, CW>;
     if (base > 64 * 1024) {
         static std::mutex attr_lock;
         static bool attr_set[2] = {false, false};
@@ -360,7 +377,7 @@ hipError_t launch4(bool ln, const LinearW &w, const RowIn &in, const OutDesc &o,
     return hipGetLastError();
 }
 
-template <int U, int MAXCH, int NG>
+template <int U, int MAXCH, int NG, int CW = 8>
 hipError_t launch3(bool ln, const LinearW &w, const RowIn &in, const OutDesc &o, const SessTable *sess, hipStream_t st) {
     const size_t base = ((size_t)w.K + w.K / 8 + 256 * 12 * NG + 15) & ~(size_t)15;
     // staging for the weight chunks requested before the row is prepared: up to two chunks per wave, as far as every
@@ -370,7 +387,7 @@ hipError_t launch3(bool ln, const LinearW &w, const RowIn &in, const OutDesc &o,
     const int nchunks = w.K / 64 / U;
     int npf = base + per_chunk <= budget ? (int)min((size_t)2, (budget - base) / per_chunk) : 0;
     if (!ln) npf = min(npf, 1);                         // without LayerNorm there are two request points, with it three
-    npf = max(0, min(npf, nchunks / 8 - 2));            // every wave's chunks tw + 8 k, k <= npf + 1, must exist
+    npf = CW < 8 ? 0 : max(0, min(npf, nchunks / 8 - 2));   // every wave's chunks tw + 8 k, k <= npf + 1, must exist
     const size_t lds = base + npf * per_chunk;
     // one resident round: at most 1024 threads' worth of workgroups per compute unit twice over (512 groups of
     // 8 waves); prefer a split of the panels without remainder
@@ -380,9 +397,11 @@ hipError_t launch3(bool ln, const LinearW &w, const RowIn &in, const OutDesc &o,
         if (units % cand == 0) { G = cand; break; }
     const int per = panels / G, extra = panels % G;
     if (lds > budget) return hipErrorInvalidValue;      // K <= 65536 (base at most 86 KB) always fits
-    if (npf == 2) return launch4<U, MAXCH, NG, 2>(ln, w, in, o, sess, G, per, extra, base, lds, budget, st);
-    if (npf == 1) return launch4<U, MAXCH, NG, 1>(ln, w, in, o, sess, G, per, extra, base, lds, budget, st);
-    return launch4<U, MAXCH, NG, 0>(ln, w, in, o, sess, G, per, extra, base, lds, budget, st);
+    if constexpr (CW == 8) {
+        if (npf == 2) return launch4<U, MAXCH, NG, 2, CW>(ln, w, in, o, sess, G, per, extra, base, lds, budget, st);
+        if (npf == 1) return launch4<U, MAXCH, NG, 1, CW>(ln, w, in, o, sess, G, per, extra, base, lds, budget, st);
+    }
+    return launch4<U, MAXCH, NG, 0, CW>(ln, w, in, o, sess, G, per, extra, base, lds, budget, st);
 }
 
 template <int U, int MAXCH>
@@ -396,6 +415,8 @@ hipError_t launch2(bool ln, const LinearW &w, const RowIn &in, const OutDesc &o,
 template <int U>
 hipError_t launch1(bool ln, const LinearW &w, const RowIn &in, const OutDesc &o, const SessTable *sess, hipStream_t st) {
     const int per_thread = (w.K / 8 + GEMV_GROUP - 1) / GEMV_GROUP;   // 8-column chunks a thread of an 8-wave workgroup holds in registers
+    if (w.K <= 2 * GEMV_GROUP) return launch3<U, 1, 1, 2>(ln, w, in, o, sess, st);
+    if (w.K <= 4 * GEMV_GROUP) return launch3<U, 1, 1, 4>(ln, w, in, o, sess, st);
     if (per_thread <= 1) return launch2<U, 1>(ln, w, in, o, sess, st);
     if (per_thread <= 4) return launch2<U, 4>(ln, w, in, o, sess, st);
     return launch2<U, 16>(ln, w, in, o, sess, st);

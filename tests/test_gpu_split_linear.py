@@ -1,0 +1,47 @@
+"""Prefill-size linears whose output makes few blocks: the contraction is split over workgroups and a second kernel adds
+the partial sums and finishes the outputs.  Bit for bit against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import oracle  # noqa: E402
+from paper_2209_01188_amd import binding, synth  # noqa: E402
+from tests.gpu_util import DEV, midsize, to_dev, to_np  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+# ffn: 32 k-tiles (the smallest that is split), an odd count in uneven shares, eight shares; M: edges of the row tiles and
+# of the 128-row blocks, and rows beyond the mid-size range; n_out: no outlier columns, the fp64 path's edges (0, 5, 64),
+# the digit products, and every column (no int8 part at all)
+@pytest.mark.parametrize("ffn", [2048, 2112, 8192])
+@pytest.mark.parametrize("M,n_out,epilogue", [(65, 0, 0), (128, 5, 2), (129, 64, 1), (351, 65, 2), (640, 7, 0), (200, -1, 2)])
+def test_split_contraction(ffn, M, n_out, epilogue):
+    H, nh = 192, 3
+    cfg = synth.SpanConfig("split", 1, H, nh, 1, M, 1, 1, (20.0, 40.0), ffn + M, ffn=ffn)
+    osp = oracle.Span(1, H, nh, ffn, 1e-5, 6.0)
+    gsp = binding.Span(1, H, nh, ffn, M, 1e-5, 6.0, DEV)
+    p = synth.block_params(cfg, 0)
+    osp.load_block(0, p)
+    gsp.load_block(0, p)
+    r = np.random.default_rng(ffn * 7 + M)
+    X = np.clip(r.standard_normal((M, ffn)), -5.9, 5.9)
+    cols = np.arange(ffn) if n_out < 0 else r.choice(ffn, n_out, replace=False)
+    X[r.integers(0, M, len(cols)), cols] = r.uniform(6.0, 30.0, len(cols)) * r.choice([-1, 1], len(cols))
+    X = X.astype(np.float16)
+    resid = (r.standard_normal((M, H)) * 4).astype(np.float16) if epilogue == 2 else None
+    wq, sw = osp.get_weight(0, 3)
+    Y, dbg = oracle.linear(X, wq, sw, p["b_down"], 6.0, epilogue, resid, want_debug=True)
+    assert dbg["mask"].sum() == len(cols)
+    with midsize("blocks"):
+        out = gsp.debug_linear(0, 3, to_dev(X), epilogue, None if resid is None else to_dev(resid))
+        torch.cuda.synchronize()
+    assert np.array_equal(to_np(out["mask"]), dbg["mask"]) and np.array_equal(to_np(out["xq"]), dbg["xq"])
+    assert np.array_equal(to_np(out["sx"]).view(np.uint32), dbg["sx"].view(np.uint32))
+    assert np.array_equal(to_np(out["acc"]), dbg["acc"])
+    assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
+    gsp.close()
+    osp.destroy()
