@@ -264,6 +264,8 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
     const unsigned short sb = (unsigned short)mreg;
     const float s_x = __half2float(*(const __half *)&sb);
     const float r = s_x > 0.0f ? 127.0f / s_x : 0.0f;
+    float neg0 = -0.0f;
+    asm("" : "+v"(neg0));
 #pragma unroll
     for (int i = 0; i < MAXCH; i++) {
         const int c = threadIdx.x + GEMV_THREADS * i;
@@ -271,12 +273,17 @@ __global__ void __launch_bounds__(GEMV_GROUP * NG) k_gemv_row(LinearW w, RowIn i
             // all codes first, straight-line; the codes of outlier columns are then cleared byte by byte in the
             // packed words (a test per element compiles to a branch per element, and a chunk with outlier
             // columns is rare)
-            int q[CW];
+            // (fp32 product straight from fp16 by a multiply-add with -0, rounded by an addition that leaves the integer
+            // in the low byte; |x r| <= 127.00002 for regular columns)
+            uint32_t t[CW], o2[2] = {0u, 0u};
 #pragma unroll
-            for (int e = 0; e < CW; e++) q[e] = q8(word_half<CW>(vals[i], e), r);
-            uint32_t o2[2] = {0u, 0u};
+            for (int e = 0; e < CW; e++) t[e] = __float_as_uint(fmaf(word_half<CW>(vals[i], e), r, neg0) + 12582912.0f);
 #pragma unroll
-            for (int e = 0; e < CW; e++) o2[e >> 2] |= (uint32_t)(q[e] & 0xff) << (8 * (e & 3));
+            for (int e = 0; e < CW; e += 4) {
+                const uint32_t lo = __builtin_amdgcn_perm(t[e + 1], t[e], 0x0c0c0400);
+                if constexpr (CW == 2) o2[0] = lo;
+                else o2[e >> 2] = __builtin_amdgcn_perm(__builtin_amdgcn_perm(t[(e + 3) % CW], t[(e + 2) % CW], 0x0c0c0400), lo, 0x05040100);
+            }
             if (obits[i]) {
 #pragma unroll
                 for (int e = 0; e < CW; e++) o2[e >> 2] &= ~(((obits[i] >> e) & 1u) * (0xffu << (8 * (e & 3))));
