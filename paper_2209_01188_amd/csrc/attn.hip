@@ -639,8 +639,10 @@ hipError_t attn_launch(const __half *q, const SessTable *sess, int blk, int M, i
     if (T > 1 || lse) {   // the matrix-core kernel also covers T = 1; it is the one that can report the denominators
         const int B = M / T;
         // Few workgroups of the shared-tile form (64 to 128 queries each): 16-query workgroups that split the keys.
-        // The line: one workgroup of the shared form per compute unit (128 tokens, 16 heads of 64: 33 -> 8 us; 3 x 117 tokens, 32 heads of 128: 94 -> 40 us;
-        // at 256 workgroups and more the shared conversions win).
+        // The line: one workgroup of the shared form per compute unit.  Below it the split wins (128 tokens, 16 heads of 64:
+        // 33 -> 8 us; 3 x 117 tokens, 32 heads of 128, mean of a first and a second call: 73 -> 34 us), from it on the
+        // shared conversions do (one block's prefill call of 512-token prompts, 32 heads: 2 prompts 446 us shared, 466
+        // split; 4 prompts 730 and 799).
         if (B * nh * (((T + 63) / 64 + 1) / 2) < ATTN_SPLIT_BELOW) {
             if (max_keys > 512 && B * nh * ((T + 15) / 16) <= 256)
                 return launch_prefill_split<D, 8>(q, sess, blk, B, T, nh, ctx, mask, theta, lse, ctx32, st);

@@ -806,8 +806,10 @@ hipError_t ps_copy_bytes(const void *src, void *dst, size_t n, hipStream_t st) {
 }
 hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float eps, int M, int H, __half *y,
                         uint32_t *mask, float theta, hipStream_t st) {
-    // few rows: more threads per row (latency), many rows: more rows in flight
-    if ((M >= 128 || H < 4096) && H % 8 == 0 && H <= 16384) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
+    // few rows: more threads per row (latency), many rows: more rows in flight (prefill calls of a 4096-wide block, two
+    // LayerNorms each: 140 rows 188 us with 1024 threads per row, 199 with several rows per 256 threads; 351 rows 244
+    // and 242: the line lies between).  Narrower rows would otherwise take 256 threads per row and flag row by row.
+    if ((M >= 256 || H < 4096) && H % 8 == 0 && H <= 16384) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
     else if (H >= 4096 && H <= 16384) k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     else if (M <= 256 && H >= 4096) k_layernorm<1024><<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     else k_layernorm<256><<<M, 256, 0, st>>>(x, g, b, eps, H, y, mask, theta);
@@ -815,7 +817,8 @@ hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
                            int H, __half *y, uint32_t *mask, float theta, hipStream_t st) {
-    if ((M >= 128 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
+    // the line of ps_layernorm (measured there, on fp16 rows)
+    if ((M >= 256 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
         launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, theta, st);
     else if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, theta);
     else k_layernorm_q8<256><<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, theta);

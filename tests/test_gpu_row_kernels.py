@@ -14,10 +14,10 @@ from tests.gpu_util import DEV, build_pair, hidden_close, to_dev, to_np  # noqa:
 pytestmark = pytest.mark.gpu
 
 
-# rows: the smallest call of this form, one row per workgroup or several, a last round of few rows; hidden: every
+# rows: the last call of the other form and the smallest of this one, one row per workgroup or several, a last round of few rows; hidden: every
 # register-chunk count and its edges
-@pytest.mark.parametrize("M,H,nh", [(512, 64, 4), (1023, 1024, 16), (1025, 2048, 16), (2049, 192, 3), (513, 4096, 32),
-                                    (520, 4160, 65), (700, 8192, 64), (515, 8256, 129), (513, 16384, 128)])
+@pytest.mark.parametrize("M,H,nh", [(512, 64, 4), (1023, 1024, 16), (1025, 2048, 16), (2049, 192, 3), (255, 4096, 32),
+                                    (256, 4096, 32), (513, 4096, 32), (520, 4160, 65), (700, 8192, 64), (515, 8256, 129), (513, 16384, 128)])
 def test_layernorm_of_many_rows(M, H, nh):
     r = np.random.default_rng(M + H)
     span = binding.Span(1, H, nh, 64, M, device=DEV)
