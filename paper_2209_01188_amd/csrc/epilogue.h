@@ -73,11 +73,12 @@ __device__ __forceinline__ void emit_output4(const OutDesc &o, const SessTable *
     *(v2i *)dst = *(const v2i *)out;
 }
 
-// derivative of the tanh-form GeLU (backward pass); tanh u = 1 - 2 / (1 + e^2u) on the fp32 exponential and reciprocal
-// instructions (1.5e-7 absolute; the library's tanhf is some forty instructions with branches)
+// derivative of the tanh-form GeLU (backward pass).  The library's tanhf: 1 - 2 / (1 + e^2u) on the exponential and
+// reciprocal instructions is shorter, but near -1 it is wrong by several units in the last place, which the factor
+// p (1 - tanh^2) carries into the derivative (2e-6 at p = -5; with tanhf 6e-7).
 __device__ __forceinline__ float gelu_tanh_grad(float p) {
     const float c0 = 0.7978845608028654f, c1 = 0.044715f;
-    const float t = 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(2.885390081777927f * c0 * (p + c1 * p * p * p)));
+    const float t = tanhf(c0 * (p + c1 * p * p * p));
     return 0.5f * (1.0f + t) + 0.5f * p * (1.0f - t * t) * c0 * (1.0f + 3.0f * c1 * p * p);
 }
 

@@ -273,3 +273,34 @@ def test_backward_full_size_call_is_deterministic_linear_and_keeps_the_prefill_o
         assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
     finally:
         gsp.close()
+
+
+def test_gelu_derivative_is_as_good_as_an_fp32_tanh():
+    """GeLU' where it nearly vanishes, so that fp16 storage resolves its fp32 error.  Unit weight matrices, a zero input
+    and no attention branch: pre-activation = up bias exactly, and a gradient with one entry per row comes out as
+    dx[row, i != j] = -dpre[row, j] / (H sqrt(eps)) with dpre = fp16(dy GeLU'(p_j)).  Bound: a tanh within one unit in
+    the last place below one (2^-24), times its weight in the formula, a few fp32 roundings of the rest, two fp16 ones."""
+    H = T = 64
+    eps, dy = 1e-5, 2048.0
+    span = binding.Span(1, H, 4, H, T, eps, 6.0, DEV)
+    eye, zero = torch.eye(H, device=DEV), torch.zeros(H, dtype=torch.float16, device=DEV)
+    p = dict(w_qkv=torch.zeros((3 * H, H), device=DEV), w_dense=torch.zeros((H, H), device=DEV), w_up=eye, w_down=eye,
+             b_qkv=torch.zeros(3 * H, dtype=torch.float16, device=DEV), b_dense=zero, b_down=zero,
+             ln1_g=zero + 1, ln1_b=zero, ln2_g=zero + 1, ln2_b=zero)
+    pre = np.arange(np.float16(-6.0).view(np.uint16) - np.float16(-4.1875).view(np.uint16), dtype=np.uint16)
+    pre = (np.float16(-4.1875).view(np.uint16) + pre).view(np.float16)
+    pre = pre[: pre.size // H * H]
+    x, g = torch.zeros((1, T, H), dtype=torch.float16, device=DEV), torch.zeros((1, T, H), dtype=torch.float16, device=DEV)
+    g[0, torch.arange(T), torch.arange(T)] = dy
+    got = []
+    for part in pre.reshape(-1, H):
+        span.load_block(0, dict(p, b_up=to_dev(part)))
+        dx = to_np(span.backward(x, g, want_output=False)[1])[0].astype(np.float64)
+        got.append(np.where(np.arange(H) == 0, dx[:, 1], dx[:, 0]) * -(H * np.sqrt(eps)) / dy)
+    span.close()
+    P = pre.astype(np.float64)
+    t = np.tanh(ob._C0 * (P + ob._C1 * P ** 3))
+    weight = np.abs(0.5 - P * t * ob._C0 * (1.0 + 3.0 * ob._C1 * P * P))
+    err = np.abs(np.concatenate(got) - ob.gelu_grad(P))
+    bound = 2.0 ** -24 * weight + 2.0 ** -22 * np.abs(ob.gelu_grad(P)) + 2.0 ** -10 * (np.abs(ob.gelu_grad(P)) + 2.0 ** -24 * weight) + 2.0 ** -24 / dy
+    assert (err <= bound).all(), (err / bound).max()
