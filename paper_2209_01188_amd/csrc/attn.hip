@@ -533,14 +533,13 @@ __global__ void __launch_bounds__(64 * NW) k_attn_decode(const __half *__restric
         const double m_new = fmax(m_run, mb);                  // mb = -inf: no key of this lane group in the block
 
         const double alpha = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - m_new);
-        const double p_mine = (mb == -INFINITY) ? 0.0 : exp_f64(sc_mine - m_new);   // exp(-inf) = 0 for keys past the end
-        const double psum = group_reduce<LPK>(p_mine, add_f64);
-        if (mb != -INFINITY) {                                 // per lane group; no cross-lane traffic inside
-            l_run = l_run * alpha + psum;
-            m_run = m_new;
+        // keys past the end: 0 (also where m_new is still -infinity).  Not decided on mb, which skips NaN scores: a NaN
+        // has to reach the sums
+        const double p_mine = (sc_mine == -INFINITY) ? 0.0 : exp_f64(sc_mine - m_new);
+        l_run = l_run * alpha + group_reduce<LPK>(p_mine, add_f64);     // per lane group; no other cross-lane traffic inside
+        m_run = m_new;
 #pragma unroll
-            for (int e = 0; e < 8; e++) o[e] *= alpha;
-        }
+        for (int e = 0; e < 8; e++) o[e] *= alpha;
         // the probability of key `it` is lane `it`'s of the group (0 for keys past the end)
         auto add_value = [&](auto itc) {
             constexpr int it = decltype(itc)::value;

@@ -365,10 +365,11 @@ __device__ __forceinline__ double rsqrt_f64(double v) {
 }
 // e^x in fp64 to 0.8 units in the last place (the library's to 0.6) in 20 instructions without a branch: x = n ln 2 + r,
 // |r| <= 0.347, e^r = 1 + r + r^2 q(r) with q the degree-9 interpolation of (e^r - 1 - r) / r^2 in Chebyshev points
-// (relative error 1.6e-17).  0 below -745, finite (about 1e308) above 709.
+// (relative error 1.6e-17).  For x <= 709; 0 below -745 and for -infinity; NaN stays NaN (the clamp is a comparison:
+// fmax would turn a NaN into the bound, and a key whose score is NaN would silently drop out of a softmax).
 __device__ __forceinline__ double exp_f64(double x) {
     constexpr double MAGIC = 6755399441055744.0;                    // 1.5 * 2^52: rounds to an integer, which sits in the low word
-    x = fmin(fmax(x, -800.0), 709.0);
+    x = x < -800.0 ? -800.0 : x;
     const double t = fma(x, 0x1.71547652b82fep+0, MAGIC), n = t - MAGIC;
     double r = fma(n, -0x1.62e42fef00000p-1, x);                    // n ln2_hi is exact
     r = fma(n, -0x1.473de6af278edp-34, r);
@@ -388,7 +389,7 @@ __device__ __forceinline__ double exp_f64(double x) {
 // Newton steps and one correction by the remainder
 __device__ __forceinline__ double gelu_tanh(double v) {
     const double u = 0.7978845608028654 * (v + 0.044715 * v * v * v);
-    const double d = 1.0 + exp_f64(-2.0 * u);
+    const double d = 1.0 + exp_f64(fmin(-2.0 * u, 709.0));           // a NaN comes back in through v
     double y = __builtin_amdgcn_rcp(d);
     y = fma(fma(-d, y, 1.0), y, y);
     y = fma(fma(-d, y, 1.0), y, y);

@@ -1,0 +1,39 @@
+"""Values that overflowed: what one session's infinities and NaN become, and that they stay with that session."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2209_01188_amd import binding, synth  # noqa: E402
+from tests.gpu_util import DEV, to_dev, to_np  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _span(H, nh, rows, ffn=256, seed=3):
+    cfg = synth.SpanConfig("nonfinite", 1, H, nh, 1, 1, 1, 1, (20.0, 40.0), seed, ffn=ffn)
+    span = binding.Span(1, H, nh, ffn, rows, 1e-5, 6.0, DEV)
+    span.load_block(0, synth.block_params(cfg, 0))
+    return span
+
+
+# Attention, one cached key whose score is NaN beside a finite value row.  T = 1: the key range in one workgroup of 4
+# waves (a lane group whose only key it is), of 8 waves, and split over workgroups.  T > 1: the form whose waves split
+# the keys with 4 and 8 waves, and the one with shared tiles.
+@pytest.mark.parametrize("d", [16, 64, 128])
+@pytest.mark.parametrize("B,L,T,at", [(2, 3, 1, 0), (2, 3, 1, 2), (2, 300, 1, 7), (2, 1000, 1, 999), (2, 9, 5, 4), (2, 610, 3, 0), (64, 20, 2, 11)])
+def test_a_key_with_a_nan_score_is_not_left_out(d, B, L, T, at):
+    nh, r = 4, np.random.default_rng(d + L + T)
+    span = _span(nh * d, nh, B * T)
+    sessions = [span.open_session(L + T) for _ in range(B)]
+    for i, s in enumerate(sessions):
+        kv = r.standard_normal((2, nh, L, d)).astype(np.float16)
+        if i == 0:
+            kv[0, 1, at, 3] = np.nan
+        s.import_kv(0, to_dev(kv))
+    x = to_dev(r.standard_normal((B, T, nh * d)).astype(np.float16))
+    y = to_np(span.prefill(sessions, x) if T > 1 else span.decode_step(sessions, x))
+    assert np.isnan(y[0]).all() and np.isfinite(y[1:]).all()
+    span.close()
