@@ -394,7 +394,7 @@ __device__ __forceinline__ double gelu_tanh(double v) {
     y = fma(fma(-d, y, 1.0), y, y);
     y = fma(fma(-d, y, 1.0), y, y);
     const double q = v * y;
-    return fma(fma(-d, q, v), y, q);
+    return q == (double)INFINITY ? q : fma(fma(-d, q, v), y, q);     // GeLU(+infinity): there the remainder would be NaN
 }
 // double -> fp16 with ONE rounding (to nearest even): the value is first rounded to odd at the 20 mantissa bits of
 // its high word (the low word only says whether anything lies below them), which is exact in fp32 and keeps enough

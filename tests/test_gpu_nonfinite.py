@@ -7,7 +7,7 @@ if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
 from paper_2209_01188_amd import binding, synth  # noqa: E402
-from tests.gpu_util import DEV, to_dev, to_np  # noqa: E402
+from tests.gpu_util import DEV, midsize, to_dev, to_np  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -36,4 +36,22 @@ def test_a_key_with_a_nan_score_is_not_left_out(d, B, L, T, at):
     x = to_dev(r.standard_normal((B, T, nh * d)).astype(np.float16))
     y = to_np(span.prefill(sessions, x) if T > 1 else span.decode_step(sessions, x))
     assert np.isnan(y[0]).all() and np.isfinite(y[1:]).all()
+    span.close()
+
+
+# GeLU behind the up linear, one row, batched decode and both prefill forms (64 rows per workgroup; output blocks, there
+# also with the contraction split): an infinite outlier value times a positive weight is +infinity, GeLU of it too.
+@pytest.mark.parametrize("M,H,ffn,form", [(1, 64, 256, None), (8, 64, 256, None), (100, 64, 256, "chunks"), (100, 64, 256, "blocks"), (70, 2048, 256, "blocks")])
+def test_gelu_of_infinity(M, H, ffn, form):
+    span = _span(H, max(4, H // 64), M, ffn)
+    wq = to_np(span.export_weight(0, 2)[0])
+    x = torch.zeros((M, H), dtype=torch.float16, device=DEV)
+    x[M // 2, 5] = float("inf")
+    with midsize(form):
+        plain = to_np(span.debug_linear(0, 2, x)["y"])
+        y = to_np(span.debug_linear(0, 2, x, binding.EPILOGUE_GELU)["y"])
+    up = wq[:, 5] > 0
+    assert (plain[M // 2, up] == np.inf).all() and (y[M // 2, up] == np.inf).all()
+    rest = np.delete(y, M // 2, 0)
+    assert np.isfinite(rest).all()
     span.close()
