@@ -13,6 +13,9 @@
 namespace {
 
 constexpr int ATTN_SPLIT_BELOW = 256;
+// Where the running maximum of k_attn_prefill starts: below every score but finite, so that a masked score (-infinity)
+// minus the maximum is -infinity, whose exponential is 0, also before the first visible key - no test per key.
+constexpr double ATTN_LOWEST = -1e300;
 
 // Start of a call: workgroup 0 copies the table word by word, all of them clear the outlier masks (one launch: a launch
 // of its own costs 2 to 4.5 us whatever it does).
@@ -159,7 +162,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
     v4d O[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) O[b] = (v4d){0.0, 0.0, 0.0, 0.0};
-    double m_run = -INFINITY, l_run = 0.0;
+    double m_run = ATTN_LOWEST, l_run = 0.0;
 
     // key tiles this wave needs (none if its queries lie beyond T) and the workgroup's last wave needs
     const int nkt_w = qt * 16 < T ? min(L + qt * 16 + 15, last_key) / 16 + 1 : 0;
@@ -270,7 +273,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
             mt = swap_reduce<32>(swap_reduce<16>(mt, max_f64), max_f64);
             const double m_new = fmax(m_run, mt);
             if (__any(m_new > m_run)) {
-                const double alpha = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - m_new);
+                const double alpha = exp_f64(m_run - m_new);
                 l_run *= alpha;
 #pragma unroll
                 for (int b = 0; b < NB; b++) O[b] *= alpha;
@@ -279,7 +282,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_prefill(const __half *__restric
             double p[4];
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                p[r] = (sc[r] == -INFINITY) ? 0.0 : exp_f64(sc[r] - m_run);
+                p[r] = exp_f64(sc[r] - m_run);
                 l_run += p[r];                        // per lane group; the groups are added at the end
             }
 #pragma unroll

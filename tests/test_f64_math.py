@@ -1,0 +1,74 @@
+"""The fp64 functions of csrc/f64math.h, compiled for the CPU and compared with 64-bit-mantissa arithmetic: errors in
+units in the last place of the result, no larger than those of the library forms they stand in for, and the special
+values.  The hardware's estimates are played by the exact value with a relative error of 2^-22 at most."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2209_01188_amd", "csrc")
+
+PROGRAM = r"""
+#include <cmath>
+#include <cstdio>
+#include <cstdint>
+#include <random>
+typedef long double ld;
+static std::mt19937_64 gen(11);
+static double uniform(double a, double b) { return std::uniform_real_distribution<double>(a, b)(gen); }
+static double rough(ld v) { return (double)(v * (1 + (ld)uniform(-0x1p-22, 0x1p-22))); }
+static double rsq_estimate(double v) { return rough(1 / sqrtl((ld)v)); }
+static double rcp_estimate(double v) { return rough(1 / (ld)v); }
+#define __device__
+#define __forceinline__ inline
+#define __builtin_amdgcn_rsq rsq_estimate
+#define __builtin_amdgcn_rcp rcp_estimate
+#define __builtin_amdgcn_ldexp ldexp
+using std::fma; using std::fmin;
+#include "f64math.h"
+static double ulps(double got, ld want) { int e; frexpl(want, &e); return (double)fabsl(((ld)got - want) / ldexpl(1, e - 53)); }
+static ld gelu_exact(double v) { const ld u = 0.7978845608028654L * (v + 0.044715L * v * v * v); return v / (1 + expl(-2 * u)); }
+static double gelu_library(double v) { const double u = 0.7978845608028654 * (v + 0.044715 * v * v * v); return v / (1.0 + exp(-2.0 * u)); }
+int main() {
+    double e = 0, r = 0, rl = 0, g = 0, gl = 0;
+    const double from[] = {-1.0, -40.0, -700.0};
+    for (double lo : from)
+        for (int i = 0; i < 3000000; i++) { const double x = uniform(lo, lo < -600 ? 709 : 0); e = fmax(e, ulps(exp_f64(x), expl(x))); }
+    for (int i = 0; i < 3000000; i++) {
+        const double v = ldexp(uniform(1, 2), (int)uniform(-20, 40));
+        r = fmax(r, ulps(rsqrt_f64(v), 1 / sqrtl(v)));
+        rl = fmax(rl, ulps(1.0 / sqrt(v), 1 / sqrtl(v)));
+        const double w = uniform(-6, 6);
+        g = fmax(g, ulps(gelu_tanh(w), gelu_exact(w)));
+        gl = fmax(gl, ulps(gelu_library(w), gelu_exact(w)));
+    }
+    printf("exp %.4f rsqrt %.4f library %.4f gelu %.4f library %.4f\n", e, r, rl, g, gl);
+    printf("special %d %d %d %d %d %d %d %d\n", std::isnan(exp_f64(NAN)), exp_f64(-INFINITY) == 0.0, exp_f64(-1e300) == 0.0, exp_f64(0.0) == 1.0,
+           std::isfinite(exp_f64(709.0)), std::isnan(gelu_tanh(NAN)), gelu_tanh(INFINITY) == INFINITY, fabs(gelu_tanh(-65504.0)) < 1e-100);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lines(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("needs g++")
+    d = tmp_path_factory.mktemp("f64")
+    (d / "t.cpp").write_text(PROGRAM)
+    subprocess.run([cxx, "-O2", "-mfma", "-ffp-contract=off", "-std=c++17", "-Wno-unknown-pragmas", "-I", CSRC, "-o", str(d / "t"), str(d / "t.cpp")], check=True)
+    return subprocess.run([str(d / "t")], check=True, capture_output=True, text=True).stdout.split("\n")
+
+
+def test_errors_are_no_larger_than_those_of_the_library_forms(lines):
+    w = lines[0].split()
+    exp, rsqrt, rsqrt_library, gelu, gelu_library = (float(w[i]) for i in (1, 3, 5, 7, 9))
+    print(lines[0])
+    assert exp <= 0.76      # the GPU library's reaches 0.88 (torch.exp of 7e7 doubles in [-700, 700])
+    assert rsqrt <= rsqrt_library
+    assert gelu <= gelu_library * 1.02      # both dominated by the rounding of u; the maximum is over other samples
+
+
+def test_special_values(lines):
+    assert lines[1].split()[1:] == ["1"] * 8, lines[1]
