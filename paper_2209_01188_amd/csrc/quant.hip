@@ -306,8 +306,10 @@ __global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restr
                 for (int e = 0; e < 4; e++) m = pk_max_u16(m, (uint32_t)ov[e] & 0x7fff7fffu);
                 if (max(m & 0xffffu, m >> 16) >= theta_bits) {
 #pragma unroll
-                    for (int e = 0; e < 8; e++)
-                        flags[i] |= ((((uint32_t)ov[e >> 1] >> ((e & 1) * 16)) & 0x7fffu) >= theta_bits ? 1u : 0u) << e;
+                    for (int e = 0; e < 8; e++) {      // NaN (bits above infinity's) is no outlier: a row that overflowed
+                        const uint32_t b = ((uint32_t)ov[e >> 1] >> ((e & 1) * 16)) & 0x7fffu;   // would flag every column
+                        flags[i] |= (b >= theta_bits && b <= 0x7c00u ? 1u : 0u) << e;              // of the other rows
+                    }
                 }
             }
         }

@@ -55,3 +55,35 @@ def test_gelu_of_infinity(M, H, ffn, form):
     rest = np.delete(y, M // 2, 0)
     assert np.isfinite(rest).all()
     span.close()
+
+
+# One session's row that overflowed (NaN after the first LayerNorm), beside healthy sessions: these get the bits they get
+# beside a row of zeros - above all no column becomes an outlier column because of it - and the row itself stays NaN.
+# Every LayerNorm form: several rows per workgroup (narrow rows; 256 rows on), one row per workgroup; fp16 rows and codes.
+@pytest.mark.parametrize("B,T,H,nh,form", [(8, 1, 1024, 16, None), (3, 2, 64, 4, None), (8, 1, 4096, 32, None), (5, 60, 256, 4, "chunks"),
+                                           (5, 60, 256, 4, "blocks"), (4, 70, 4096, 32, None)])
+@pytest.mark.parametrize("codes", [False, True])
+def test_a_row_that_overflowed_stays_with_its_session(B, T, H, nh, form, codes):
+    span = _span(H, nh, B * T, 512)
+    cfg = synth.SpanConfig("nonfinite", 1, H, nh, B, T, 1, 2, (20.0, 40.0), 9, ffn=512)
+    x = to_dev(synth.hidden_states(cfg, 0, B, T))
+    x[1] = 0
+    bad = x.clone()
+    bad[1, 0, 7] = float("inf")
+    n, block = x.numel(), 64
+    q, am = torch.empty(n, dtype=torch.uint8, device=DEV), torch.empty(n // block, device=DEV)
+    binding.petals_hidden_quantize(x, block, q, am)
+    am_bad = am.clone()
+    am_bad[T * H // block] = float("nan")
+    out, counts = [], []
+    for i in range(2):
+        sessions = [span.open_session(T) for _ in range(B)]
+        with midsize(form):
+            y = span.prefill_q8(sessions, T, q, am_bad if i else am, block) if codes else span.prefill(sessions, bad if i else x)
+        out.append(to_np(y))
+        counts.append(to_np(span.outlier_counts()).tolist())
+    assert counts[0] == counts[1]
+    rest = [0] + list(range(2, B))
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0][rest].view(np.uint16), out[1][rest].view(np.uint16))
+    assert np.isnan(out[1][1, 0]).all()
+    span.close()
