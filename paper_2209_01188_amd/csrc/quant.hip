@@ -701,9 +701,23 @@ __global__ void __launch_bounds__(NT) k_hidden_quantize_wide(const __half *__res
     const unsigned short ab = (unsigned short)mb;
     float a = __half2float(*(const __half *)&ab);
     const bool finite = mb < 0x7c00u;
-    if (!finite) {                                             // infinities and NaN: the largest of the numbers, as fmaxf has it
-        a = 0.0f;
-        for (int k = 0; k < len; k++) a = fmaxf(a, fabsf(__half2float(xb[k])));
+    if (!finite) {                                             // (the whole workgroup) NaN does not count, as in fmaxf
+        mb = 0;
+#pragma unroll
+        for (int i = 0; i < PER; i++)
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const uint32_t b = ((uint32_t)xv[i][e >> 1] >> ((e & 1) * 16)) & 0x7fffu;
+                mb = max(mb, b <= 0x7c00u ? b : 0u);
+            }
+        mb = wave_max(mb);
+        __syncthreads();                                       // the first maxima have been read
+        if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = mb;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NT / 64; w++) mb = max(mb, s_max[w]);
+        const unsigned short nb = (unsigned short)mb;
+        a = __half2float(*(const __half *)&nb);
     }
     if (threadIdx.x == 0) absmax[blockIdx.x] = a;
     const float r = a > 0.0f ? 1.0f / a : 0.0f;

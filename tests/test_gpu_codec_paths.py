@@ -56,3 +56,47 @@ def test_codec_every_fp16_value():
         y = np.where(np.abs(x.astype(np.float64)) <= top, x, np.float16(0)).astype(np.float16)
         y[::64] = np.float16(top)
         _roundtrip(y, 64, 0)
+
+
+@pytest.mark.parametrize("block", [64, 1024, 4096, 8192, 16384])
+def test_codec_of_infinities_and_nan(block):
+    """Blocks that hold them: aligned and odd addresses give the same codes and maxima, the largest number counts."""
+    r = np.random.default_rng(block)
+    n = 5 * block + 40
+    x = r.standard_normal(n).astype(np.float16)
+    x[3], x[block + 5], x[2 * block - 1] = np.inf, np.nan, -np.nan
+    x[2 * block:3 * block] = np.nan
+    x[3 * block + 1], x[3 * block + 2] = np.nan, -np.inf
+    x[n - 1] = np.nan
+    out = []
+    for shift in (0, 1):
+        xd, qd = _shifted(n, torch.float16, shift), _shifted(n, torch.uint8, shift)
+        xd.copy_(torch.from_numpy(x))
+        amd = torch.empty(6, dtype=torch.float32, device=DEV)
+        binding.petals_hidden_quantize(xd, block, qd, amd)
+        out.append((to_np(qd), to_np(amd)))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    want = [np.fmax.reduce(np.abs(x[i * block:(i + 1) * block]).astype(np.float32), initial=0.0) for i in range(6)]
+    assert np.array_equal(out[0][1], np.array(want, np.float32))
+
+
+def test_codec_of_infinities_takes_as_long_as_of_numbers():
+    block, n = 16384, 512 * 16384
+    x = torch.randn(n, device=DEV).to(torch.float16)
+    q, am = torch.empty(n, dtype=torch.uint8, device=DEV), torch.empty(n // block, device=DEV)
+
+    def time_of_one():
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                binding.petals_hidden_quantize(x, block, q, am)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) / 5)
+        return best
+
+    numbers = time_of_one()
+    x[::block] = float("inf")
+    assert time_of_one() < 4.0 * numbers      # a walk through the block by every thread: a hundred times as long
