@@ -4,6 +4,7 @@
 #include <stdarg.h>
 #include <string.h>
 
+#include <mutex>
 #include <new>
 
 #include "../../include/petals_client.h"
@@ -17,6 +18,7 @@ namespace {
 constexpr int LM_THREADS = 1024;           // 16 waves: enough 16-byte loads in flight for one workgroup per compute unit
 constexpr int LM_WAVES = LM_THREADS / 64;
 constexpr int LM_GROUPS = 256;             // workgroups of the LM head = partial results per row
+constexpr int LM_MAX_HIDDEN = 16384;
 constexpr int LM_MAX_ROWS = 32;            // rows of hidden states multiplied per pass over the matrix (matrix-core form)
 
 // One workgroup per token: gather the embedding row, LayerNorm in fp64, store fp16.
@@ -1003,7 +1005,6 @@ struct petals_client {
     int *flag;          // [LM_MAX_ROWS]
     SegStat *seg;       // [max_rows_per_call][segments of the vocabulary]: per-segment results of the sampler
     Cand *cand;         // [max_rows_per_call][segments][SAMPLE_KMAX]: per-segment candidates of top-k sampling
-    bool lds_attr_set;
 };
 
 namespace {
@@ -1011,7 +1012,7 @@ int check_client_config(const petals_client_config *c) {
     if (!c) return ps_fail(PETALS_ERR_INVALID_ARG, "config is null");
     if (c->vocab < 1 || c->hidden < 1 || c->max_rows_per_call < 1)
         return ps_fail(PETALS_ERR_INVALID_ARG, "config fields must be positive");
-    if (c->hidden % 64 || c->hidden > 16384) return ps_fail(PETALS_ERR_UNSUPPORTED, "hidden must be a multiple of 64, at most 16384");
+    if (c->hidden % 64 || c->hidden > LM_MAX_HIDDEN) return ps_fail(PETALS_ERR_UNSUPPORTED, "hidden must be a multiple of 64, at most 16384");
     if (!(c->ln_eps > 0.0f)) return ps_fail(PETALS_ERR_INVALID_ARG, "ln_eps must be positive");
     return PETALS_OK;
 }
@@ -1048,7 +1049,6 @@ int petals_client_create(const petals_client_config *cfg, const petals_client_pa
     c->seg = (SegStat *)((uint8_t *)c->flag + align_up(sizeof(int) * LM_MAX_ROWS));
     c->cand = (Cand *)((uint8_t *)c->seg + align_up(sizeof(SegStat) * (size_t)cfg->max_rows_per_call *
                                                      ((cfg->vocab + SAMPLE_SEG - 1) / SAMPLE_SEG)));
-    c->lds_attr_set = false;
     *out = c;
     return PETALS_OK;
 }
@@ -1089,9 +1089,14 @@ int petals_client_lm_head(petals_client *c, const void *hidden_in, int32_t M, fl
         // one row: the matrix streams at 6.6 TB/s past one fp64 multiply-add per value
         HIP_TRY(ps_layernorm(x, lng, lnb, c->cfg.ln_eps, 1, H, c->a, nullptr, 0.0f, st));
         const size_t lds = (size_t)H * 8;
-        if (!c->lds_attr_set) {
-            HIP_TRY(hipFuncSetAttribute((const void *)k_lm_head, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            c->lds_attr_set = true;
+        {   // the limit belongs to the function, for all clients of the process: set once, to the widest row there is
+            static std::mutex attr_lock;
+            static bool attr_set = false;
+            std::lock_guard<std::mutex> hold(attr_lock);
+            if (!attr_set) {
+                HIP_TRY(hipFuncSetAttribute((const void *)k_lm_head, hipFuncAttributeMaxDynamicSharedMemorySize, LM_MAX_HIDDEN * 8));
+                attr_set = true;
+            }
         }
         const int groups = min(LM_GROUPS, (V + LM_WAVES - 1) / LM_WAVES);
         k_lm_head<<<groups, LM_THREADS, lds, st>>>(c->a, E, V, H, logits_out, c->partial);

@@ -71,3 +71,21 @@ def test_lm_head_takes_rows_at_any_address():
     a = cl.lm_head(x, want_logits=True)[1]
     assert torch.equal(a, cl.lm_head(shifted.view(M, H), want_logits=True)[1])
     cl.close()
+
+
+def test_one_row_calls_of_clients_of_different_widths_alternate():
+    """The one-row form keeps its row in local memory, whose limit is set for the function, not for the client."""
+    r = np.random.default_rng(8)
+    V, clients = 300, []
+    for H in (16384, 64, 9216):
+        E = _matrix("embedding", r, V, H)
+        one, zero = np.ones(H, np.float16), np.zeros(H, np.float16)
+        x = r.standard_normal((1, H)).astype(np.float16)
+        want = oracle.layernorm(x, one, zero).astype(np.float64) @ E.astype(np.float64).T
+        clients.append((binding.Client(to_dev(E), to_dev(one), to_dev(zero), to_dev(one), to_dev(zero), max_rows=1), to_dev(x), want))
+    for i in (0, 1, 0, 2, 1, 2, 0):
+        cl, x, want = clients[i]
+        got = cl.lm_head(x, want_logits=True)[1].cpu().numpy()
+        assert (np.abs(got - want) <= 2.0 ** -23 * np.abs(want) + 1e-10).all(), i
+    for cl, _, _ in clients:
+        cl.close()
