@@ -100,15 +100,18 @@ __global__ void __launch_bounds__(LM_THREADS) k_lm_head(const __half *__restrict
 // once per logit - a few roundings of 2^-53 instead of one per column.  What was slow before: 16 fp64 matrix
 // instructions (64 clocks each) per 16 x 16 x 64 products against 16 int8 ones (16 clocks; 12 where the matrix tile
 // stays below 0.246, as embeddings do), and the passes over the matrix: up to four rows per pass with the hidden rows
-// as fp64 in LDS.  250880 x 4096, 8 rows: two passes of 560 us before, 380 us
-// now (5.4 TB/s; 450 us with every workgroup starting at column 0, the digit arithmetic and the matrix instructions
-// taken out change nothing: the 16 rows' separate 64-byte pieces are what is left, contiguous reads would take 335).
+// as fp64 in LDS.  250880 x 4096, 8 rows: a call of 1080 us in two passes before, 398 us now (5.2 TB/s; every workgroup
+// starting at column 0 costs another 64 us, the digit arithmetic and the matrix instructions taken out change nothing: the
+// 16 rows' separate 64-byte pieces are what is left, contiguous reads take 45 us less).
 //
 // The matrix is streamed once per 32 hidden rows: a wave owns WN tiles of 16 matrix rows (A operand) and walks their
 // columns 64 at a time; lane (row l%16, group l/16) holds columns 8 g .. +8 and 32 + 8 g .. +8 of the 64 as fp16, a
 // chunk of CH such pieces in flight in registers, and cuts them into digit planes itself (5 instructions per value).  The hidden rows' digits (k_lm_prepare) go through LDS, shared by the 8 waves, one
-// barrier per chunk.  A tile with a value of 127.5 or more in magnitude (or a NaN), and every tile if a hidden row
-// has one, is done again on the fp64 matrix instruction, where nothing bounds the values.
+// barrier per chunk.  Hidden values of 127.5 and more (a feature that dominates its row) have two digits more: a 64-column
+// piece in which any row has one is read a second time, for its products with digits 4 and 5 (one such feature, 250880 x
+// 4096, 8 rows: a call of 398 us becomes 408, all columns 816; with the whole product on the fp64 instruction instead,
+// 1000).  A tile of the matrix with a value of 127.5 or more, and every tile if a hidden row holds an infinity or NaN, is
+// done again on the fp64 matrix instruction, where nothing bounds the values.
 constexpr int LMD_CH = 4;                  // 64-column pieces per chunk
 constexpr uint32_t LMD_BIG = 0x57f8;       // fp16 bits of 127.5
 constexpr uint32_t LMD_SMALL = 0x33e0;     // fp16 bits of 0.246: below it three digits do, and lm_planes_small holds
@@ -143,16 +146,36 @@ __device__ __forceinline__ void lm_planes(const uint32_t (&u)[4], int (&p)[4]) {
     p[3] = (int)__builtin_amdgcn_perm(d, c, 0x07060302);
 }
 
-// LayerNorm of one hidden row per workgroup: the fp16 row to a (what the fp64 form reads), its digit planes to
-// dig[(kt * 4 + plane) * MT + row tile][lane][16 bytes], flag[row] = 1 if four digits do not cover it.  Rows beyond
-// `rows` (up to the end of the row tile) get zero digits.
+// digits 0 to 3 of a finite value of 127.5 or more in magnitude, and its digits 4 and 5: x = low + 256 y, low in
+// [-128.5, 127.5) and a multiple of 1/16, |y| <= 256
+__device__ __forceinline__ uint32_t lm_digits_wide(float f, int &d4, int &d5) {
+    const float y = floorf(fmaf(f, 0.00390625f, 0.501953125f));
+    d4 = (((int)y + 128) & 255) - 128;
+    d5 = ((int)y - d4) >> 8;
+    return (((uint32_t)(int)(fmaf(y, -256.0f, f) * 16.0f) << 20) + 0x80808080u) ^ 0x80808080u;
+}
+
+// What k_lm_prepare says of a hidden row: whether it holds an infinity or NaN, and the 64-column pieces with a value that
+// needs digits 4 and 5.
+constexpr int LM_PIECE_WORDS = LM_MAX_HIDDEN / 64 / 32;
+struct LmRow {
+    int nonfinite;
+    uint32_t wide[LM_PIECE_WORDS];
+};
+
+// LayerNorm of one hidden row per workgroup: the fp16 row to a (what the fp64 form reads), its digit planes 0 to 3 to
+// dig[(kt * 4 + plane) * MT + row tile][lane][16 bytes], planes 4 and 5 to dig2[(kt * 2 + plane - 4) * MT + row tile].
+// Rows beyond `rows` (up to the end of the row tile) get zero digits.
 template <int PER>
 __global__ void __launch_bounds__(512) k_lm_prepare(const __half *__restrict__ x, const __half *__restrict__ g,
                                                     const __half *__restrict__ b, float eps, int rows, int H, int MT,
-                                                    __half *__restrict__ a, uint8_t *__restrict__ dig, int *__restrict__ flag) {
+                                                    __half *__restrict__ a, uint8_t *__restrict__ dig, uint8_t *__restrict__ dig2,
+                                                    LmRow *__restrict__ info) {
     constexpr int NT = 512;
     __shared__ double sm[NT / 64];
-    __shared__ float smf[NT / 64];
+    __shared__ LmRow here;
+    if (threadIdx.x < sizeof(LmRow) / 4) ((uint32_t *)&here)[threadIdx.x] = 0u;
+    __syncthreads();
     const int t = blockIdx.x, mt = t >> 4, row = t & 15;
     const __half *xr = x + (size_t)t * H;
     const bool live = t < rows;
@@ -181,35 +204,46 @@ __global__ void __launch_bounds__(512) k_lm_prepare(const __half *__restrict__ x
         }
         inv = 1.0 / sqrt(block_sum<NT / 64>(q, sm) / (double)H + (double)eps);
     }
-    bool big = false;
 #pragma unroll
     for (int i = 0; i < PER; i++) {
         const int k = (threadIdx.x + i * NT) * 8;
         if (k < H) {
+            // columns 64 kt + 32 h + 8 g .. +8: bytes 8 h .. +8 of lane (g, row)
+            const int kt = k >> 6, h = (k >> 5) & 1, gg = (k >> 3) & 3;
             __half out[8];
             int lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
+            uint32_t up[2][2] = {{0u, 0u}, {0u, 0u}};            // digits 4 and 5, packed like the planes
             if (live) {
                 const v8h gv = *(const v8h_any *)(g + k), bv = *(const v8h_any *)(b + k);
                 uint32_t u[2][4];
 #pragma unroll
                 for (int e = 0; e < 8; e++) {
                     out[e] = d2h_rn(((double)(float)v[i][e] - mean) * inv * (double)(float)gv[e] + (double)(float)bv[e]);
-                    big |= (__half_as_ushort(out[e]) & 0x7fffu) >= LMD_BIG;
                     u[e >> 2][e & 3] = lm_digits(__half2float(out[e]));
+                    const uint32_t bits = __half_as_ushort(out[e]) & 0x7fffu;
+                    if (bits >= LMD_BIG) {                       // rare
+                        int d4, d5;
+                        u[e >> 2][e & 3] = lm_digits_wide(__half2float(out[e]), d4, d5);
+                        up[0][e >> 2] |= (uint32_t)(d4 & 255) << (8 * (e & 3));
+                        up[1][e >> 2] |= (uint32_t)(d5 & 255) << (8 * (e & 3));
+                        if (bits >= 0x7c00u) here.nonfinite = 1;
+                        atomicOr(&here.wide[kt >> 5], 1u << (kt & 31));
+                    }
                 }
                 *(v8h *)(a + (size_t)t * H + k) = *(const v8h *)out;
                 lm_planes(u[0], lo);
                 lm_planes(u[1], hi);
             }
-            // columns 64 kt + 32 h + 8 g .. +8: bytes 8 h .. +8 of lane (g, row)
-            const int kt = k >> 6, h = (k >> 5) & 1, gg = (k >> 3) & 3;
 #pragma unroll
             for (int pl = 0; pl < 4; pl++)
                 *(v2i *)(dig + (((size_t)(kt * 4 + pl) * MT + mt) * 64 + gg * 16 + row) * 16 + h * 8) = (v2i){lo[pl], hi[pl]};
+#pragma unroll
+            for (int pl = 0; pl < 2; pl++)
+                *(v2i *)(dig2 + (((size_t)(kt * 2 + pl) * MT + mt) * 64 + gg * 16 + row) * 16 + h * 8) = (v2i){(int)up[pl][0], (int)up[pl][1]};
         }
     }
-    const float any = block_max<NT / 64>(big ? 1.0f : 0.0f, smf);
-    if (threadIdx.x == 0) flag[t] = any > 0.0f ? 1 : 0;
+    __syncthreads();
+    if (threadIdx.x < sizeof(LmRow) / 4) ((uint32_t *)&info[t])[threadIdx.x] = ((const uint32_t *)&here)[threadIdx.x];
 }
 
 // the fp64 form of one wave's products: 16 matrix rows x MT tiles of 16 hidden rows.  Lane (row l%16, group l/16)
@@ -236,7 +270,8 @@ __device__ __forceinline__ void lm_tile_f64(const __half *__restrict__ er, const
 
 template <int WN, int MT>
 __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restrict__ a, const uint8_t *__restrict__ dig,
-                                                           const int *__restrict__ flag, int rows, const __half *__restrict__ E,
+                                                           const uint8_t *__restrict__ dig2, const LmRow *__restrict__ info, int rows,
+                                                           const __half *__restrict__ E,
                                                            int V, int H, float *__restrict__ logits, Best *__restrict__ partial) {
     constexpr int CH = LMD_CH, CHUNK = CH * 4 * MT * 1024, SR = CHUNK / (512 * 16);
     __shared__ __align__(16) unsigned char stage[2][CHUNK];
@@ -244,7 +279,16 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int KT = H >> 6, nch = (KT + CH - 1) / CH, ntiles = (V + 15) >> 4;
     const size_t dig_last = (size_t)KT * 4 * MT * 1024 - 16;
-    const bool all_f64 = __syncthreads_or(threadIdx.x < (unsigned)rows ? flag[threadIdx.x] : 0);
+    __shared__ uint32_t wide[LM_PIECE_WORDS];                // pieces of any row with digits 4 and 5
+    if (threadIdx.x < LM_PIECE_WORDS) {
+        uint32_t w = 0;
+        for (int t = 0; t < rows; t++) w |= info[t].wide[threadIdx.x];
+        wide[threadIdx.x] = w;
+    }
+    const bool all_f64 = __syncthreads_or(threadIdx.x < (unsigned)rows ? info[threadIdx.x].nonfinite : 0);
+    bool any_wide = false;
+#pragma unroll
+    for (int i = 0; i < LM_PIECE_WORDS; i++) any_wide |= wide[i] != 0u;
     const bool wide_store = logits && V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
     Best best[MT];
 #pragma unroll
@@ -293,13 +337,13 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
         const int vt0 = (grp * 8 + wave) * WN;
         const __half *en[WN];
         row_ptrs(grp + gridDim.x, en);
-        v4i acc[WN][MT][7];
+        v4i acc[WN][MT][9];
 #pragma unroll
         for (int p = 0; p < WN; p++)
 #pragma unroll
             for (int j = 0; j < MT; j++)
 #pragma unroll
-                for (int s = 0; s < 7; s++) acc[p][j][s] = (v4i){0, 0, 0, 0};
+                for (int s = 0; s < 9; s++) acc[p][j][s] = (v4i){0, 0, 0, 0};
         bool slow = all_f64;
         if (!all_f64) {
             int ch = rot;
@@ -378,6 +422,41 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                 store_s(buf ^ 1);
                 ch = ch_next;
             }
+            if (any_wide) {                                  // digits 4 and 5 of the hidden rows, piece by piece
+                for (int wi = 0; wi < LM_PIECE_WORDS; wi++)
+                    for (uint32_t left = __builtin_amdgcn_readfirstlane(wide[wi]); left; left &= left - 1u) {
+                        const int kt = wi * 32 + __ffs((int)left) - 1;
+#pragma unroll
+                        for (int p = 0; p < WN; p++) {
+                            v4i d[4];
+#pragma unroll
+                            for (int h = 0; h < 2; h++) {
+                                const v4i w = *(const v4i *)(er[p] + (size_t)kt * 64 + h * 32);
+#pragma unroll
+                                for (int q = 0; q < 2; q++) {
+                                    const uint32_t w0 = (uint32_t)w[2 * q], w1 = (uint32_t)w[2 * q + 1];
+                                    const uint32_t hb[4] = {w0 & 0xffffu, w0 >> 16, w1 & 0xffffu, w1 >> 16};
+                                    uint32_t dw[4];
+                                    int pl[4];
+#pragma unroll
+                                    for (int i = 0; i < 4; i++) dw[i] = lm_digits(__half2float(__ushort_as_half((unsigned short)hb[i])));
+                                    lm_planes(dw, pl);
+#pragma unroll
+                                    for (int i = 0; i < 4; i++) d[i][2 * h + q] = pl[i];
+                                }
+                            }
+#pragma unroll
+                            for (int j = 0; j < 2; j++)
+#pragma unroll
+                                for (int m = 0; m < MT; m++) {
+                                    const v4i xb = *(const v4i *)(dig2 + ((size_t)(kt * 2 + j) * MT + m) * 1024 + lane * 16);
+#pragma unroll
+                                    for (int i = 0; i < 4; i++)
+                                        acc[p][m][4 + i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[i], xb, acc[p][m][4 + i + j], 0, 0, 0);
+                                }
+                        }
+                    }
+            }
         }
 #pragma unroll
         for (int p = 0; p < WN; p++) {
@@ -390,9 +469,9 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                 for (int j = 0; j < MT; j++)
 #pragma unroll
                     for (int r = 0; r < 4; r++) {
-                        double t = (double)acc[p][j][6][r];
+                        double t = (double)acc[p][j][8][r];
 #pragma unroll
-                        for (int s = 5; s >= 0; s--) t = t * 256.0 + (double)acc[p][j][s][r];
+                        for (int s = 7; s >= 0; s--) t = t * 256.0 + (double)acc[p][j][s][r];
                         val[j][r] = t * 0x1p-48;
                     }
             }
@@ -1001,8 +1080,8 @@ struct petals_client {
     petals_client_params p;
     __half *a;          // LayerNorm output of the rows of one lm_head call
     Best *partial;      // [LM_MAX_ROWS][LM_GROUPS]
-    uint8_t *dig;       // digit planes of up to LM_MAX_ROWS hidden rows: [H / 64][4][row tiles][1024]
-    int *flag;          // [LM_MAX_ROWS]
+    uint8_t *dig, *dig2;   // digit planes of up to LM_MAX_ROWS hidden rows: [H / 64][4 and 2][row tiles][1024]
+    LmRow *info;           // [LM_MAX_ROWS]
     SegStat *seg;       // [max_rows_per_call][segments of the vocabulary]: per-segment results of the sampler
     Cand *cand;         // [max_rows_per_call][segments][SAMPLE_KMAX]: per-segment candidates of top-k sampling
 };
@@ -1024,7 +1103,7 @@ int petals_client_workspace_bytes(const petals_client_config *cfg, size_t *bytes
     if (!bytes) return ps_fail(PETALS_ERR_INVALID_ARG, "null pointer");
     if (int rc = check_client_config(cfg)) return rc;
     *bytes = align_up((size_t)cfg->max_rows_per_call * cfg->hidden * 2) + align_up(sizeof(Best) * LM_MAX_ROWS * LM_GROUPS) +
-             align_up((size_t)4 * LM_MAX_ROWS * cfg->hidden) + align_up(sizeof(int) * LM_MAX_ROWS) +
+             align_up((size_t)6 * LM_MAX_ROWS * cfg->hidden) + align_up(sizeof(LmRow) * LM_MAX_ROWS) +
              align_up(sizeof(SegStat) * (size_t)cfg->max_rows_per_call * ((cfg->vocab + SAMPLE_SEG - 1) / SAMPLE_SEG)) +
              align_up(sizeof(Cand) * SAMPLE_KMAX * (size_t)cfg->max_rows_per_call * ((cfg->vocab + SAMPLE_SEG - 1) / SAMPLE_SEG));
     return PETALS_OK;
@@ -1045,8 +1124,9 @@ int petals_client_create(const petals_client_config *cfg, const petals_client_pa
     c->a = (__half *)dev_workspace;
     c->partial = (Best *)((uint8_t *)dev_workspace + align_up((size_t)cfg->max_rows_per_call * cfg->hidden * 2));
     c->dig = (uint8_t *)c->partial + align_up(sizeof(Best) * LM_MAX_ROWS * LM_GROUPS);
-    c->flag = (int *)(c->dig + align_up((size_t)4 * LM_MAX_ROWS * cfg->hidden));
-    c->seg = (SegStat *)((uint8_t *)c->flag + align_up(sizeof(int) * LM_MAX_ROWS));
+    c->dig2 = c->dig + (size_t)4 * LM_MAX_ROWS * cfg->hidden;
+    c->info = (LmRow *)(c->dig + align_up((size_t)6 * LM_MAX_ROWS * cfg->hidden));
+    c->seg = (SegStat *)((uint8_t *)c->info + align_up(sizeof(LmRow) * LM_MAX_ROWS));
     c->cand = (Cand *)((uint8_t *)c->seg + align_up(sizeof(SegStat) * (size_t)cfg->max_rows_per_call *
                                                      ((cfg->vocab + SAMPLE_SEG - 1) / SAMPLE_SEG)));
     *out = c;
@@ -1116,12 +1196,12 @@ int petals_client_lm_head(petals_client *c, const void *hidden_in, int32_t M, fl
         // up to 16 rows: two matrix tiles per wave (the digits read from LDS then serve both) once that leaves every
         // compute unit a workgroup of 8 waves; with 17 to 32 rows two tiles need more registers than there are
         const int wn = mt == 1 && ntiles >= 256 * 16 ? 2 : 1, groups = min(LM_GROUPS, (ntiles + 8 * wn - 1) / (8 * wn));
-        if (H <= 4096) k_lm_prepare<1><<<16 * mt, 512, 0, st>>>(xr, lng, lnb, c->cfg.ln_eps, rows, H, mt, a, c->dig, c->flag);
-        else k_lm_prepare<4><<<16 * mt, 512, 0, st>>>(xr, lng, lnb, c->cfg.ln_eps, rows, H, mt, a, c->dig, c->flag);
+        if (H <= 4096) k_lm_prepare<1><<<16 * mt, 512, 0, st>>>(xr, lng, lnb, c->cfg.ln_eps, rows, H, mt, a, c->dig, c->dig2, c->info);
+        else k_lm_prepare<4><<<16 * mt, 512, 0, st>>>(xr, lng, lnb, c->cfg.ln_eps, rows, H, mt, a, c->dig, c->dig2, c->info);
         HIP_TRY(hipGetLastError());
-        if (wn == 2) k_lm_head_digits<2, 1><<<groups, 512, 0, st>>>(a, c->dig, c->flag, rows, E, V, H, lg, c->partial);
-        else if (mt == 2) k_lm_head_digits<1, 2><<<groups, 512, 0, st>>>(a, c->dig, c->flag, rows, E, V, H, lg, c->partial);
-        else k_lm_head_digits<1, 1><<<groups, 512, 0, st>>>(a, c->dig, c->flag, rows, E, V, H, lg, c->partial);
+        if (wn == 2) k_lm_head_digits<2, 1><<<groups, 512, 0, st>>>(a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial);
+        else if (mt == 2) k_lm_head_digits<1, 2><<<groups, 512, 0, st>>>(a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial);
+        else k_lm_head_digits<1, 1><<<groups, 512, 0, st>>>(a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial);
         HIP_TRY(hipGetLastError());
         if (next_token_out) {
             k_lm_pick<<<rows, 64, 0, st>>>(c->partial, groups, next_token_out + m0);

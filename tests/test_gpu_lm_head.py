@@ -59,6 +59,71 @@ def test_lm_head_of_several_rows(V, H, M, kind):
     cl.close()
 
 
+def _check(E, gain, bias, x, finite=True):
+    V, (M, H) = E.shape[0], x.shape
+    cl = binding.Client(to_dev(E), to_dev(gain), to_dev(bias), to_dev(gain), to_dev(bias), max_rows=M)
+    logits = cl.lm_head(to_dev(x), want_logits=True)[1].cpu().numpy()
+    cl.close()
+    a = oracle.layernorm(x, gain, bias).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        want = a @ E.astype(np.float64).T
+    if not finite:
+        assert np.array_equal(np.isnan(logits), np.isnan(want)) and np.array_equal(logits[np.isinf(want)], want[np.isinf(want)])
+        return
+    bound = 2.0 ** -24 * np.abs(want) + 2.0 ** -50 * (np.abs(a) @ np.abs(E.astype(np.float64)).T)
+    assert (np.abs(logits - want) <= bound).all()
+
+
+# Hidden values that need digits 4 and 5: a gain of zero and the value as bias put them into chosen columns - every
+# fp16 value near the edges of the digits, the ends of the range, any finite value; one column, columns of several
+# pieces (the first and last one of a piece and of the row), all columns; beside matrix pieces of three and four digits.
+@pytest.mark.parametrize("V,H,M", [(33, 64, 2), (1002, 640, 16), (1000, 4160, 17), (66000, 128, 5), (80, 16384, 2)])
+@pytest.mark.parametrize("where", ["one", "several", "all"])
+@pytest.mark.parametrize("kind", ["embedding", "four digits' edge"])
+def test_lm_head_of_hidden_values_beyond_four_digits(V, H, M, where, kind):
+    r = np.random.default_rng(V + H + M)
+    E = _matrix(kind, r, V, H)
+    gain, bias = r.normal(1.0, 0.1, H).astype(np.float16), r.normal(0.0, 0.1, H).astype(np.float16)
+    edge = np.concatenate([np.arange(0x57f0, 0x5810), np.arange(0x5bf0, 0x5c10), [0x77f8, 0x77f7, 0x7bfe, 0x7bff]]).astype(np.uint16)
+    values = np.concatenate([edge, edge | 0x8000, r.integers(0, 0x7c00, 64).astype(np.uint16)]).view(np.float16)
+    cols = {"one": [H - 1], "several": sorted({0, 63, H // 2, (H - 1) // 64 * 64, H - 1}), "all": list(range(H))}[where]
+    gain[cols] = 0
+    bias[cols] = r.permutation(np.resize(values, max(len(cols), values.size)))[:len(cols)]
+    _check(E, gain, bias, (r.standard_normal((M, H)) * 2.0).astype(np.float16))
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_lm_head_of_a_nonfinite_hidden_value(value):
+    r = np.random.default_rng(6)
+    V, H, M = 700, 192, 3
+    gain, bias = np.ones(H, np.float16), np.zeros(H, np.float16)
+    gain[70], bias[70], bias[3] = 0, value, 300.0
+    _check(_matrix("embedding", r, V, H), gain, bias, r.standard_normal((M, H)).astype(np.float16), finite=False)
+
+
+def test_a_dominant_feature_does_not_slow_the_lm_head_down():
+    """One LayerNorm output of 127.5 or more costs one more look at its 64 columns, not another form of the product."""
+    V, H, M = 100000, 4096, 4
+    E = (torch.randn(V, H, device="cuda") * 0.02).to(torch.float16)
+    zero, x = torch.zeros(H, dtype=torch.float16, device="cuda"), torch.randn(M, H, device="cuda").to(torch.float16)
+    best = []
+    for gain in (1.0, 500.0):
+        g = zero + 1
+        g[100] = gain
+        cl = binding.Client(E, g, zero, g, zero, max_rows=M)
+        best.append(float("inf"))
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                cl.lm_head(x, want_logits=True)
+            b.record()
+            b.synchronize()
+            best[-1] = min(best[-1], a.elapsed_time(b) / 4)
+        cl.close()
+    assert best[1] < 1.4 * best[0], best       # 2.4 times as long when the fp64 form took over
+
+
 def test_lm_head_takes_rows_at_any_address():
     r = np.random.default_rng(5)
     V, H, M = 500, 128, 6
