@@ -223,13 +223,23 @@ hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_til
 
 }  // namespace
 
-// Rough times in microseconds, fitted to measurements on BLOOM-560M-, 7B1- and 176B-shaped linears at 96 to 512
-// rows.  64 rows per workgroup: the N*K weight bytes stream once per 64 rows at about 3 TB/s (what that form reaches),
-// 20 us for the row kernels in front.  Output blocks: a 256 x 256 block walks K/64 stages of about 0.7 us
+// panels of 16 output rows per workgroup of ps_gemm: as many as still leave about one workgroup per compute unit
+static int gemm_panels_per_wg(int N) {
+    const int panels = N / 16;
+    return (panels % 4 == 0 && panels / 4 >= 224) ? 4 : (panels % 2 == 0 && panels / 2 >= 224) ? 2 : 1;
+}
+
+// Rough times in microseconds of a linear with its row kernels, fitted to both forms measured on the four linears of
+// blocks 1024 to 14336 wide at 65 to 512 rows (468 points; the choice is then never worse than 7 % and 0.1 % on average).
+// 64 rows per workgroup: workgroups of one or two panels, one to a compute unit, in rounds of 256 that each walk the K/64
+// tiles (3.4 us + 0.095 per tile with one panel, 5 us + 0.123 with two), 14 us for the row kernels in front.  All rows go
+// in one launch: charged by 64 rows, as when each 64 were a launch, narrow outputs went to the blocks too early (1024 x
+// 1024 at 320 rows: 24 us in this form, 36 in blocks).
+// Output blocks: a 256 x 256 block walks K/64 stages of about 0.7 us
 // (0.45 us for the 256 x 128 blocks that ps_gemm_lds takes when the call has at most 128 rows or at most 128
 // blocks, whose stages are shared out if there are few of them: 8 us more for adding up), 256 blocks at a time, never
 // faster than the weights stream at 4 TB/s, behind about 35 us of row and digit kernels that are launched whatever the
-// data (45 us when the outlier preparation was a launch of its own).
+// data.
 // PETALS_SPAN_MIDSIZE=blocks / =chunks in the environment overrides the choice (tests run both ways).
 constexpr double BLOCKS_FIXED = 35.0;
 
@@ -239,8 +249,9 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
         if (!strcmp(force, "blocks")) return false;
         if (!strcmp(force, "chunks")) return true;
     }
-    const double passes = (M + 63) / 64, bytes = (double)w.N * w.K;
-    const double t_chunks = 20.0 + passes * (bytes / 3.0e6 + 5.0);
+    const int wn = gemm_panels_per_wg(w.N) > 1 ? 2 : 1, groups = w.N / 16 / wn * ((M + 63) / 64);
+    const double bytes = (double)w.N * w.K, tiles = w.K / 64;
+    const double t_chunks = 14.0 + (groups + 255) / 256 * (wn == 2 ? 5.0 + 0.123 * tiles : 3.4 + 0.095 * tiles);
     double blocks = (double)((w.N + 255) / 256) * ((M + 255) / 256), stage = 0.7;
     int split = 1;
     if (M <= 128 || blocks * 2 <= 256) {
@@ -254,9 +265,7 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
 
 hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,
                    const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, hipStream_t st) {
-    // panels per workgroup: as many as still leave about one workgroup per compute unit
-    const int panels = w.N / 16;
-    const int wn = (panels % 4 == 0 && panels / 4 >= 224) ? 4 : (panels % 2 == 0 && panels / 2 >= 224) ? 2 : 1;
+    const int panels = w.N / 16, wn = gemm_panels_per_wg(w.N);
 #define PS_GEMM_CASE(WN_, MT_, UK_) return launch<WN_, MT_, UK_>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, st)
     if (M <= 16) {
         // one panel per workgroup (narrow outputs): 16 waves split the k-tiles, twice the weight bytes in flight per

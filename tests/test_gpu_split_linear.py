@@ -45,3 +45,31 @@ def test_split_contraction(ffn, M, n_out, epilogue):
     assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
     gsp.close()
     osp.destroy()
+
+
+# Which form a call of 65 to 512 rows takes: the estimate behind the choice must not miss the faster one by much.
+@pytest.mark.parametrize("H,nh,which,M", [(1024, 16, 1, 320), (1024, 16, 3, 448), (1536, 12, 1, 257), (2048, 16, 3, 160), (4096, 32, 0, 320), (4096, 32, 2, 512)])
+def test_the_faster_form_is_chosen(H, nh, which, M):
+    span = binding.Span(1, H, nh, 4 * H, M, device=DEV)
+    p = {n: torch.randn(s, device=DEV) * 0.02 for n, s in (("w_qkv", (3 * H, H)), ("w_dense", (H, H)), ("w_up", (4 * H, H)), ("w_down", (H, 4 * H)))}
+    p.update({n: torch.zeros(s, dtype=torch.float16, device=DEV) for n, s in
+              (("b_qkv", 3 * H), ("b_dense", H), ("b_up", 4 * H), ("b_down", H), ("ln1_g", H), ("ln1_b", H), ("ln2_g", H), ("ln2_b", H))})
+    span.load_block(0, p)
+    N, K = span.shapes(which)
+    x = torch.randn(M, K, device=DEV)
+    x[:, :4] *= 30
+    x, y, times = x.to(torch.float16), torch.empty((M, N), dtype=torch.float16, device=DEV), {}
+    for form in ("chunks", "blocks", None):
+        times[form] = float("inf")
+        with midsize(form):
+            for _ in range(4):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                torch.cuda._sleep(2000000)           # the calls queue up behind it: their time on the device, not the host's
+                a.record()
+                for _ in range(10):
+                    binding.petals_debug_linear(span.handle, 0, which, x, binding.EPILOGUE_NONE, None, None, None, None, None, y)
+                b.record()
+                b.synchronize()
+                times[form] = min(times[form], a.elapsed_time(b) / 10)
+    span.close()
+    assert times[None] <= 1.15 * min(times["chunks"], times["blocks"]), times
