@@ -155,11 +155,12 @@ __device__ __forceinline__ uint32_t lm_digits_wide(float f, int &d4, int &d5) {
     return (((uint32_t)(int)(fmaf(y, -256.0f, f) * 16.0f) << 20) + 0x80808080u) ^ 0x80808080u;
 }
 
-// What k_lm_prepare says of a hidden row: whether it holds an infinity or NaN, and the 64-column pieces with a value that
-// needs digits 4 and 5.
+// What k_lm_prepare says of a hidden row: whether it holds an infinity or NaN, whether any value needs digits 4 and 5, and
+// the 64-column pieces with such values.
 constexpr int LM_PIECE_WORDS = LM_MAX_HIDDEN / 64 / 32;
+enum { LM_NONFINITE = 1, LM_WIDE = 2 };
 struct LmRow {
-    int nonfinite;
+    int flags;
     uint32_t wide[LM_PIECE_WORDS];
 };
 
@@ -226,7 +227,7 @@ __global__ void __launch_bounds__(512) k_lm_prepare(const __half *__restrict__ x
                         u[e >> 2][e & 3] = lm_digits_wide(__half2float(out[e]), d4, d5);
                         up[0][e >> 2] |= (uint32_t)(d4 & 255) << (8 * (e & 3));
                         up[1][e >> 2] |= (uint32_t)(d5 & 255) << (8 * (e & 3));
-                        if (bits >= 0x7c00u) here.nonfinite = 1;
+                        atomicOr(&here.flags, bits >= 0x7c00u ? LM_NONFINITE : LM_WIDE);
                         atomicOr(&here.wide[kt >> 5], 1u << (kt & 31));
                     }
                 }
@@ -280,15 +281,16 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
     const int KT = H >> 6, nch = (KT + CH - 1) / CH, ntiles = (V + 15) >> 4;
     const size_t dig_last = (size_t)KT * 4 * MT * 1024 - 16;
     __shared__ uint32_t wide[LM_PIECE_WORDS];                // pieces of any row with digits 4 and 5
-    if (threadIdx.x < LM_PIECE_WORDS) {
-        uint32_t w = 0;
-        for (int t = 0; t < rows; t++) w |= info[t].wide[threadIdx.x];
-        wide[threadIdx.x] = w;
+    const int flags = lane < rows ? info[lane].flags : 0;    // (every wave by itself: no barrier in front of the first requests)
+    const bool all_f64 = __any(flags & LM_NONFINITE), any_wide = __any(flags & LM_WIDE);
+    if (any_wide) {                                          // rare; the same in all waves
+        if (threadIdx.x < LM_PIECE_WORDS) {
+            uint32_t w = 0;
+            for (int t = 0; t < rows; t++) w |= info[t].wide[threadIdx.x];
+            wide[threadIdx.x] = w;
+        }
+        __syncthreads();
     }
-    const bool all_f64 = __syncthreads_or(threadIdx.x < (unsigned)rows ? info[threadIdx.x].nonfinite : 0);
-    bool any_wide = false;
-#pragma unroll
-    for (int i = 0; i < LM_PIECE_WORDS; i++) any_wide |= wide[i] != 0u;
     const bool wide_store = logits && V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
     Best best[MT];
 #pragma unroll
