@@ -13,13 +13,22 @@ from tests.gpu_util import to_dev  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
-KINDS = ["embedding", "three digits' edge", "four digits' edge", "one large tile", "large hidden rows", "tiny"]
+KINDS = ["embedding", "three digits' edge", "both branches", "four digits' edge", "one large tile", "large hidden rows", "tiny"]
+SMALL = 0x33e0               # fp16 bits from which on a 16 x 64 piece of the matrix takes four digits
 
 
 def _matrix(kind, r, V, H):
     E = r.standard_normal((V, H)) * 0.02
-    if kind == "three digits' edge":
-        E = r.uniform(-0.4985, 0.4985, (V, H))
+    if kind in ("three digits' edge", "both branches"):
+        # the whole range of three digits, its largest values in some rows and in the first and last column
+        top = np.array([SMALL - 1], np.uint16).view(np.float16)[0]
+        E = np.clip(r.uniform(-0.2461, 0.2461, (V, H)), -float(top), float(top)).astype(np.float16)
+        E[:: 3, 0], E[1:: 3, 0], E[:: 2, H - 1], E[1:: 2, H - 1], E[V // 2] = top, -top, -top, top, top
+        E[V // 3] = -top
+        assert (np.abs(E).view(np.uint16) < SMALL).all()
+        if kind == "both branches":          # one value in every seventh row and third piece takes its piece to four digits
+            E[:: 7, 5:: 192] = np.array([SMALL], np.uint16).view(np.float16)[0]
+        return E
     elif kind == "four digits' edge":
         E = r.uniform(-127.4, 127.4, (V, H))
         E[::7] *= 1e-3
