@@ -64,30 +64,9 @@ __global__ void k_copy_bytes(const uint8_t *__restrict__ s, uint8_t *__restrict_
 
 // -------------------------------------------------------------- LayerNorm
 
-template <int NT>
-__global__ void __launch_bounds__(NT) k_layernorm(const __half *__restrict__ x, const __half *__restrict__ g,
-                                                  const __half *__restrict__ b, float eps, int H,
-                                                  __half *__restrict__ y, uint32_t *__restrict__ mask,
-                                                  float theta) {
-    __shared__ double sm[NT / 64];
-    const __half *xr = x + (size_t)blockIdx.x * H;
-    __half *yr = y + (size_t)blockIdx.x * H;
-    double mean, inv;
-    row_moments<NT>(xr, H, sm, mean, inv, (double)eps);
-    for (int k = threadIdx.x * 2; k < H; k += NT * 2) {
-        const __half2 o = ln_affine(*(const __half2 *)(xr + k), *(const __half2 *)(g + k),
-                                    *(const __half2 *)(b + k), mean, inv);
-        *(__half2 *)(yr + k) = o;
-        if (mask) {
-            const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
-            flag_outlier_bits(mask, k >> 5, bits << (k & 31));
-        }
-    }
-}
-
-// Rows that arrive as blockwise 8-bit codes: every thread decodes the elements it will normalise (same
-// assignment of elements to threads as k_layernorm), stores them as the fp16 row the residual reads later, and
-// goes on as k_layernorm does on that row.
+// One workgroup per row that arrives as blockwise 8-bit codes: every thread decodes the elements it will normalise, stores
+// them as the fp16 row the residual reads later, and normalises that row (1024 threads: the sums of k_layernorm_wide, in
+// the same order).
 static __device__ const CodeTable d_code_table = ps_make_code_table();
 
 template <int NT>
@@ -120,9 +99,8 @@ __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *
     }
 }
 
-// The same with the row held in registers (4096 <= H <= 16384: at most 8 pairs per thread of 1024), so the
-// row is read from memory once instead of three times.  Same assignment of elements to threads and same
-// reduction order as k_layernorm: identical results.
+// One workgroup per fp16 row, held in registers (H <= 16384: at most 8 pairs per thread of 1024) and so read from memory
+// once instead of three times.
 __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restrict__ x, const __half *__restrict__ g,
                                                          const __half *__restrict__ b, float eps, int H,
                                                          __half *__restrict__ y, uint32_t *__restrict__ mask,
@@ -172,7 +150,7 @@ __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restric
 // and the outlier columns of all its rows are flagged ONCE, at the end.  (One workgroup per row sent every row's
 // flags to the same few words of the mask: an outlier feature is one in every row, another XCD's bits are not seen
 // in this one's L2, and the memory takes 7 ns per access to one address - 4096 rows of 4096 with four outlier
-// columns: 58 us, without any 28 us.)  The elements a thread sums differ from the kernels above, i.e. the fp64 sums
+// columns: 58 us, without any 28 us.)  The elements a thread sums differ from the kernel above, i.e. the fp64 sums
 // are rounded in another order.  PER chunks of 8 columns per thread (H <= 2048 PER).  Q8: the rows arrive as 8-bit
 // codes, see k_layernorm_q8.
 template <int PER, bool Q8>
@@ -624,7 +602,7 @@ __global__ void __launch_bounds__(1024) k_hidden_quantize(const __half *__restri
 // the quotients by the block's maximum are the IEEE ones from one reciprocal (q = x r corrected by the exact
 // remainder: three instructions); and the midpoints below a quotient are counted with ONE comparison: quotients
 // are binned by sign, exponent and 6 mantissa bits, no bin holds more than one midpoint, and a table says how many
-// lie below each bin.  29.4 M values (2048 rows of 14336) into codes and back: 163 -> 56 us with the wide
+// lie below each bin.  29.4 M values (2048 rows of 14336) into codes and back: 163 -> 42 us with the wide
 // dequantizer below (92 us of it were the binary search over the 255 midpoints with two 2-byte reads of every value,
 // 66 us one 2-byte store and one 64-bit division per value).  128 threads cover blocks
 // of up to 1024 values, 512 with 1, 2 or 4 chunks blocks of up to 4096, 8192 and 16384.
@@ -824,11 +802,11 @@ hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float
                         uint32_t *mask, float theta, hipStream_t st) {
     // few rows: more threads per row (latency), many rows: more rows in flight (prefill calls of a 4096-wide block, two
     // LayerNorms each: 140 rows 188 us with 1024 threads per row, 199 with several rows per 256 threads; 351 rows 244
-    // and 242: the line lies between).  Narrower rows would otherwise take 256 threads per row and flag row by row.
-    if ((M >= 256 || H < 4096) && H % 8 == 0 && H <= 16384) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
-    else if (H >= 4096 && H <= 16384) k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
-    else if (M <= 256 && H >= 4096) k_layernorm<1024><<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
-    else k_layernorm<256><<<M, 256, 0, st>>>(x, g, b, eps, H, y, mask, theta);
+    // and 242: the line lies between).  Rows below 4096 columns, of which 1024 threads would hold two pairs each or fewer,
+    // always take 256 threads.
+    if (H % 8 || H > 16384) return hipErrorInvalidValue;       // span and client take multiples of 64 up to 16384
+    if (M >= 256 || H < 4096) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
+    else k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
     return hipGetLastError();
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
