@@ -96,7 +96,7 @@ __global__ void __launch_bounds__(LM_THREADS) k_lm_head(const __half *__restrict
 // Several rows of hidden states at once, exactly, on the int8 matrix instruction.  Every fp16 value is an integer
 // multiple of 2^-24, so with balanced 8-bit digits x = 2^-24 sum_j 256^j d_j, d_j in [-128, 127], four digits cover
 // |x| < 127.5.  A product of two such values is the sum over the digit pairs (i, j) of 256^(i + j) d_i d_j: the pairs
-// with the same i + j share an int32 accumulator (at most 4 * 2^14 * 16384 = 2^30), and the seven sums meet in fp64
+// with the same i + j share an int32 accumulator (at most 4 * 2^14 * 16384 = 2^30), and the seven sums (nine, see below) meet in fp64
 // once per logit - a few roundings of 2^-53 instead of one per column.  What was slow before: 16 fp64 matrix
 // instructions (64 clocks each) per 16 x 16 x 64 products against 16 int8 ones (16 clocks; 12 where the matrix tile
 // stays below 0.246, as embeddings do), and the passes over the matrix: up to four rows per pass with the hidden rows
