@@ -31,6 +31,7 @@
 namespace {
 
 constexpr int STRIP = 4;       // m-blocks per rasterization strip
+constexpr int PS_KSPLIT_MAX = 8;   // workgroups that share one output block's contraction, at most
 
 // ---------------------------------------------------------------------------------------------
 // outlier column list and fp16 gathers (only do work when the call has > PS_EXACT_OUTLIERS)
@@ -206,10 +207,7 @@ struct GemmArgs {
     // of the next product's token-side operand (16 x 32 tiles, rows beyond M zero)
     const __half *gelu_pre;   // [M, N] fp16, or null
     __half *tile_out;
-    // digit product only: plane_group 0 takes digit planes 0..3 of the activations and stores the product,
-    // 1 takes planes 4.. (present only when some outlier value reaches 127.5 in magnitude) and adds to it
-    int plane_group;
-    double *od;               // [M, N] fp64: the product over the outlier columns
+    double *od;               // digit product only: [M, N] fp64, the product over the outlier columns
     // int8 product with EPI_PARTIAL only: the k-tiles are shared out over ksplit workgroups per output block, each of
     // which stores its raw sums to part[split][weight panel][token tile][lane]; k_split_finish adds and finishes them
     int ksplit;
@@ -279,11 +277,28 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     const int rem = ord - strip * STRIP * nb_n, sw_this = min(STRIP, nb_m - strip * STRIP);
     const int bn = rem / sw_this, bm = strip * STRIP + rem % sw_this;
 
+    // Digit product: planes 0..3 first, then, only when some outlier value reaches 127.5 in magnitude, planes 4.. as a
+    // second pass over the same block, which adds to what the first one stored (as a launch of its own the second pass
+    // cost every linear 2.4 us of finding nothing to do).  Everything that depends on the thread is worked out again in
+    // each pass: kept over the loop it cost 18 spilled registers.
+    const int groups = DIG ? (os.count[1] + 3) >> 2 : 1;
+#pragma unroll 1
+    for (int pg = 0; pg < groups; pg++) {
+    int tid = threadIdx.x;
+    if constexpr (DIG) {
+        asm volatile("" : "+v"(tid));
+        if (pg) {                                             // every wave is done with the slots of the first pass
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+    }
     const int M = ga.M, N = ga.N, NT = N >> 4, MTT = (M + 15) >> 4;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, row = lane & 15, kg = lane >> 4;
+    // (the wave's number as a scalar: six to eight fewer registers, but the digit product's schedule gets slower by it, 29.0
+    // against 29.3 ms for a prefill call of 8 x 512 tokens of a 14336-wide block)
+    const int wave = DIG ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, row = lane & 15, kg = lane >> 4;
     const int wn = wave / WVM, wm = wave % WVM;
     const int nt0 = (ga.nb_n0 + bn) * BN, mt0 = bm * BM;
-    if (DIG && ga.plane_group * 4 >= os.count[1]) return;     // no activation needs these digit planes
 
     // the stage tiles this wave copies: s = wave + NW*j; s < BN: weight tile, else token tile
     const unsigned char *src[LOADS];
@@ -296,7 +311,7 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
                 const int panel = min((bn * WVN + s / TN) * 4 + (s & 3), NT - 1);
                 src[j] = ga.a_tiles + ((size_t)((s % TN) / 4) * NT + panel) * KTILES * 1024 + lane * 16;
             } else {                         // slot: wave row t / 4 = token tile, plane t % 4 of the group
-                const int t = s - BN, plane = min(ga.plane_group * 4 + (t & 3), PS_X_DIGITS - 1);
+                const int t = s - BN, plane = min(pg * 4 + (t & 3), PS_X_DIGITS - 1);
                 src[j] = ga.b_tiles + ((size_t)plane * MTT + min(bm * WVM + t / TM, MTT - 1)) * KTILES * 1024 + lane * 16;
             }
         } else {
@@ -440,7 +455,7 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
         // sum_k x * Wd = u_n * 2^-24 * (m_n * sum_j 256^j A_code[j] + sum_j 256^j A_rem[j]), taken in fp64 from the top
         // plane down: exact below 2^53, i.e. up to the last step, and good to 1 part in 2^53 after it.
         const int tt = bm * WVM + wm, t = tt * 16 + row;
-        const int live = min(4, os.count[1] - ga.plane_group * 4);       // planes 6, 7 do not exist
+        const int live = min(4, os.count[1] - pg * 4);       // planes 6, 7 do not exist
         if (tt < MTT) {                                                  // wave-uniform
 #pragma unroll
             for (int p = 0; p < 4; p++) {
@@ -463,11 +478,11 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
                     float a;
                     int E, m;
                     digit_scale(sv[r], a, E, m);
-                    res[r] = ldexp((double)m * tc + tr, E - 34 + 32 * ga.plane_group);   // u = 2^(E-10), activations in units of 2^-24
+                    res[r] = ldexp((double)m * tc + tr, E - 34 + 32 * pg);   // u = 2^(E-10), activations in units of 2^-24
                 }
                 if (t < M) {
                     double *dst = ga.od + (size_t)t * N + n0;
-                    if (ga.plane_group) res += *(const v4d *)dst;
+                    if (pg) res += *(const v4d *)dst;
                     *(v4d *)dst = res;
                 }
             }
@@ -675,6 +690,7 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
                 atomicOr(&o.next_mask[word], col_flag[threadIdx.x]);
         }
     }
+    }   // digit plane groups
 }
 
 // Second half of a split contraction: one wave per 16 x 16 output tile adds the partial sums, the outlier part and the
@@ -794,7 +810,7 @@ GemmArgs gemm_args(const void *a_tiles, const void *b_tiles, int ktiles, int M, 
 // units once, each with at least 16 k-tiles to walk.
 int ps_gemm_lds_ksplit(int N, int ktiles, int M) {
     const int blocks = ((N + 255) / 256) * ((M + 127) / 128);
-    return max(1, min(min(256 / blocks, ktiles / 16), 8));
+    return max(1, min(min(256 / blocks, ktiles / 16), PS_KSPLIT_MAX));
 }
 
 hipError_t ps_gemm_f16_tiles(const __half *feat_tiles, const __half *tok_tiles, int ktiles, int M, int n_feat,
@@ -818,20 +834,16 @@ hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t 
                        int M, const OutlierSet &os, const ManyOutliers &mo, const OutDesc &o, const SessTable *sess,
                        hipStream_t st) {
     // The outlier-heavy case first (every kernel of it returns at once when the call has few outlier columns):
-    // digit tiles of the activations and of the dequantized weights, the digit products (a second
-    // launch for digit planes 4 and 5, which only activations of magnitude 127.5 and more have).
+    // digit tiles of the activations and of the dequantized weights, the digit products.
     k_digit_tiles<2><<<(2048 + 4096) / 4, 256, 0, st>>>(X, M, w, (int *)os.count, mo.list, mo.xl, mo.wd, 2048);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    for (int pg = 0; pg < 2; pg++) {
-        GemmArgs gd = gemm_args(mo.wd, mo.xl, 0, M, w.N);
-        gd.plane_group = pg;
-        gd.od = mo.od;
-        gd.nb_n = (w.N / 16 + 7) / 8;            // 8 panels and 4 token tiles per block (times 2 digits, 4 planes)
-        gd.nb_m = ((M + 15) / 16 + 3) / 4;
-        e = launch_one<GEMM_DIGITS, 4>(gd, w, sx, os, nullptr, o, sess, st);
-        if (e != hipSuccess) return e;
-    }
+    GemmArgs gd = gemm_args(mo.wd, mo.xl, 0, M, w.N);
+    gd.od = mo.od;
+    gd.nb_n = (w.N / 16 + 7) / 8;                // 8 panels and 4 token tiles per block (times 2 digits, 4 planes)
+    gd.nb_m = ((M + 15) / 16 + 3) / 4;
+    e = launch_one<GEMM_DIGITS, 4>(gd, w, sx, os, nullptr, o, sess, st);
+    if (e != hipSuccess) return e;
     GemmArgs gi = gemm_args(w.wt, xq_tiled, w.K / 64, M, w.N);
     gi.part = (v4i *)mo.wd;                  // the digit tiles have been read when the int8 product starts
     return launch_lds<GEMM_INT8>(gi, w, sx, os, mo.od, o, sess, st, mo.wd_bytes);
