@@ -70,7 +70,10 @@ Workspace carve(const petals_span_config &c, uint8_t *base) {
     w.xo = (int8_t *)take((Mp < PS_CHUNKED_ROWS_MAX ? Mp : PS_CHUNKED_ROWS_MAX) * Kmax);   // outlier values of calls that take the batched-decode kernel
     w.sx = (float *)take(Mp * 4);
     w.mask_words = (Kmax + 63) / 64 * 2;
-    w.masks = (uint32_t *)take((size_t)c.n_blocks * 4 * w.mask_words * 4);
+    // calls of more than 64 rows: the LayerNorms flag outlier columns in bytes, right behind the masks (cleared with them)
+    const size_t mask_bytes = (size_t)c.n_blocks * 4 * w.mask_words * 4;
+    w.masks = (uint32_t *)take(mask_bytes + (M > 64 ? (size_t)c.n_blocks * 2 * H : 0));
+    w.flags = w.masks && M > 64 ? (uint8_t *)w.masks + mask_bytes : nullptr;
     w.partials = (double *)take((size_t)PS_ATTN_PARTIAL_SLOTS * (128 + 2) * 8);
     w.ocount = (int *)take(256);
     const size_t Nmax = 3 * H > F ? 3 * H : F;
@@ -120,9 +123,10 @@ namespace {
 // X is the input of the LayerNorm that precedes the linear (fused on the one-row path, a kernel of its own
 // writing ws.a otherwise).  debug: copy the integer intermediates out (one-row path: into ws.xq/mask/ws.sx).
 // mask_ready (multi-row calls without LayerNorm): the kernel that wrote X has already flagged the outlier
-// columns in mask; with a LayerNorm the mask must arrive cleared and the LayerNorm kernel flags them.
+// columns in mask; with a LayerNorm the mask must arrive cleared and the LayerNorm kernel flags them - in calls of more
+// than 64 rows in flags, cleared as well, from which the row quantizer writes the mask.
 int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, const __half *ln_g, const __half *ln_b, int M,
-               uint32_t *mask, bool mask_ready, const OutDesc &o, int8_t *xq_dbg, bool debug, hipStream_t st,
+               uint32_t *mask, uint8_t *flags, bool mask_ready, const OutDesc &o, int8_t *xq_dbg, bool debug, hipStream_t st,
                const QuantIn *qin = nullptr) {
     Workspace &ws = sp->ws;
     const petals_span_config &c = sp->cfg;
@@ -136,8 +140,9 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
     } else {
         if (!mask_ready) HIP_TRY(ps_fill_u32(mask, ws.mask_words, 0u, st));
         if (ln_g) {
-            if (qin) HIP_TRY(ps_layernorm_q8(*qin, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, theta, st));
-            else HIP_TRY(ps_layernorm(X, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, theta, st));
+            if (M <= 64) flags = nullptr;
+            if (qin) HIP_TRY(ps_layernorm_q8(*qin, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, flags, theta, st));
+            else HIP_TRY(ps_layernorm(X, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, flags, theta, st));
             X = ws.a;
         } else if (!mask_ready) {
             HIP_TRY(ps_colmask(X, M, w.K, theta, mask, st));
@@ -147,7 +152,7 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
         const bool chunks = ps_gemm_prefers_chunks(w, M);
         const bool small = M <= 64 || chunks;
         const OutlierPrep prep = {w, small ? nullptr : ws.ocount, ws.wd64, ws.x64, ws.many.list};
-        HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ws.xq, small ? ws.xo : nullptr, ws.sx, xq_dbg, prep, st));
+        HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ln_g ? flags : nullptr, ws.xq, small ? ws.xo : nullptr, ws.sx, xq_dbg, prep, st));
         const OutlierSet os = {ws.ocount, ws.wd64, ws.x64};
         const bool pr = sp->prof.begin(PETALS_PROFILE_GEMM, which, st);
         if (small) {
@@ -190,10 +195,11 @@ int forward_blocks(petals_span *sp, int M, int T, int max_keys, const __half *hi
         __half *xout = (b == c.n_blocks - 1) ? hidden_out : (save ? save->x[b + 1] : ((b & 1) ? ws.xb : ws.xa));
         __half *qb = save ? save->q[b] : ws.q, *ctxb = ws.ctx, *x1b = save ? save->x1[b] : ws.x1;
         uint32_t *mk = ws.masks + (size_t)b * 4 * ws.mask_words;
+        uint8_t *fl = ws.flags ? ws.flags + (size_t)b * 2 * H : nullptr;
         OutDesc oq = plain_out(qb, PETALS_EPILOGUE_NONE, nullptr);
         oq.scatter = 1; oq.T = T; oq.nh = nh; oq.d = d; oq.blk = b;
         // LayerNorm 1 -> fused QKV (queries to qb, keys/values appended to the caches)
-        if (int rc = run_linear(sp, 0, W.lin[0], x, W.ln1g, W.ln1b, M, mk, multi, oq, nullptr, false, st,
+        if (int rc = run_linear(sp, 0, W.lin[0], x, W.ln1g, W.ln1b, M, mk, fl, multi, oq, nullptr, false, st,
                                 b == 0 ? qin : nullptr)) return rc;
         {
             const bool pr = sp->prof.begin(PETALS_PROFILE_ATTENTION, -1, st);
@@ -203,16 +209,16 @@ int forward_blocks(petals_span *sp, int M, int T, int max_keys, const __half *hi
             sp->prof.end(pr, st);
         }
         // dense + residual
-        if (int rc = run_linear(sp, 1, W.lin[1], ctxb, nullptr, nullptr, M, mk + ws.mask_words, multi,
+        if (int rc = run_linear(sp, 1, W.lin[1], ctxb, nullptr, nullptr, M, mk + ws.mask_words, nullptr, multi,
                                 plain_out(x1b, PETALS_EPILOGUE_RESIDUAL, x), nullptr, false, st)) return rc;
         // LayerNorm 2 -> up + GeLU -> down + residual
         OutDesc ou = plain_out(ws.g, PETALS_EPILOGUE_GELU, nullptr);
         if (multi) { ou.next_mask = mk + 3 * ws.mask_words; ou.next_theta = theta; }
         if (save) ou.pre_out = save->pre[b];
-        if (int rc = run_linear(sp, 2, W.lin[2], x1b, W.ln2g, W.ln2b, M, mk + 2 * ws.mask_words, multi, ou, nullptr,
-                                false, st)) return rc;
+        if (int rc = run_linear(sp, 2, W.lin[2], x1b, W.ln2g, W.ln2b, M, mk + 2 * ws.mask_words, fl ? fl + H : nullptr, multi, ou,
+                                nullptr, false, st)) return rc;
         if (!xout) break;    // backward pass without a caller for the output: nothing reads the last block's result
-        if (int rc = run_linear(sp, 3, W.lin[3], ws.g, nullptr, nullptr, M, mk + 3 * ws.mask_words, multi,
+        if (int rc = run_linear(sp, 3, W.lin[3], ws.g, nullptr, nullptr, M, mk + 3 * ws.mask_words, nullptr, multi,
                                 plain_out(xout, PETALS_EPILOGUE_RESIDUAL, x1b), nullptr, false, st)) return rc;
         x = xout;
     }
@@ -249,7 +255,7 @@ int run_call(petals_span *sp, petals_session *const *sessions, int32_t B, int32_
 
     Workspace &ws = sp->ws;
     const int M = B * T;
-    HIP_TRY(ps_call_setup(tab, ws.table, ws.masks, M > 1 ? (size_t)c.n_blocks * 4 * ws.mask_words : 0, st));
+    HIP_TRY(ps_call_setup(tab, ws.table, ws.masks, ps_mask_clear_words(c, ws, M), st));
     QuantIn qin;
     if (qin_arg) {
         // the decoded rows live in the buffer that only the outputs of odd blocks use: block 0 reads them (LayerNorm,
@@ -555,7 +561,7 @@ int petals_debug_linear(petals_span *sp, int32_t block, int32_t which, const voi
     OutDesc o = plain_out(yy, epilogue, (const __half *)resid);
     o.acc_out = acc;
     uint32_t *mk = ws.masks;
-    if (int rc = run_linear(sp, which, L, (const __half *)x, nullptr, nullptr, M, mk, false, o, xq, true, st)) return rc;
+    if (int rc = run_linear(sp, which, L, (const __half *)x, nullptr, nullptr, M, mk, nullptr, false, o, xq, true, st)) return rc;
     if (sx) HIP_TRY(ps_copy_bytes(ws.sx, sx, (size_t)M * 4, st));
     if (outlier_mask) HIP_TRY(ps_mask_to_bytes(mk, L.K, outlier_mask, st));
     return PETALS_OK;
@@ -576,8 +582,9 @@ int petals_debug_layernorm(petals_span *sp, int32_t block, int32_t which, const 
     const LinearW &L = W.lin[which ? 2 : 0];
     uint32_t *mk = ws.masks;
     if (M > 1) HIP_TRY(ps_fill_u32(mk, ws.mask_words, 0u, st));
+    if (M > 64) HIP_TRY(ps_fill_u32((uint32_t *)ws.flags, (size_t)c.hidden / 4, 0u, st));
     if (int rc = run_linear(sp, which ? 2 : 0, L, (const __half *)x, which ? W.ln2g : W.ln1g, which ? W.ln2b : W.ln1b, M, mk,
-                            M > 1, plain_out(ws.g, PETALS_EPILOGUE_NONE, nullptr), xq, true, st)) return rc;
+                            ws.flags, M > 1, plain_out(ws.g, PETALS_EPILOGUE_NONE, nullptr), xq, true, st)) return rc;
     HIP_TRY(ps_copy_bytes(ws.a, y, (size_t)M * c.hidden * 2, st));
     if (sx) HIP_TRY(ps_copy_bytes(ws.sx, sx, (size_t)M * 4, st));
     if (outlier_mask) HIP_TRY(ps_mask_to_bytes(mk, L.K, outlier_mask, st));

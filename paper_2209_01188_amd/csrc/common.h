@@ -106,20 +106,22 @@ hipError_t ps_quantize_weight(const float *W, int N, int K, int8_t *wt, float *s
 hipError_t ps_untile_weight(const int8_t *wt, int N, int K, int8_t *wq_rowmajor, hipStream_t st);
 hipError_t ps_fill_u32(uint32_t *p, size_t n, uint32_t v, hipStream_t st);
 hipError_t ps_copy_bytes(const void *src, void *dst, size_t n, hipStream_t st);
-// mask (may be null): outlier-column bits of y are ORed into it (|y| >= theta)
+// mask (may be null): outlier-column bits of y are ORed into it (|y| >= theta); flags (null, or instead of mask, zeroed):
+// one byte per column, set to 1 where a row reaches theta
 hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float eps, int M, int H,
-                        __half *y, uint32_t *mask, float theta, hipStream_t st);
+                        __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st);
 // LayerNorm of rows that arrive as 8-bit codes (also writes the decoded rows to qin.x_out)
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
-                           int H, __half *y, uint32_t *mask, float theta, hipStream_t st);
+                           int H, __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st);
 hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask, hipStream_t st);
-// M rows -> tiled int8 codes (rows padded to 16 with zeros), row scales; mask given
+// M rows -> tiled int8 codes (rows padded to 16 with zeros), row scales; mask given, or (flags not null) given as one byte
+// per column and then written to mask
 // xo_tiled (may be null): same tile order, 16 bytes per (token, 16-column group) = the fp16 values of the
 // group's first 8 outlier columns in ascending order; groups without outliers are not written
 // pr (pr.count may be null): the linear's outlier columns are counted and, if they are few, compacted in the same launch
 struct OutlierPrep;
-hipError_t ps_rowquant_tiled(const __half *X, int M, int K, const uint32_t *mask, int8_t *xq_tiled, int8_t *xo_tiled,
-                             float *sx, int8_t *xq_rowmajor_dbg, const OutlierPrep &pr, hipStream_t st);
+hipError_t ps_rowquant_tiled(const __half *X, int M, int K, uint32_t *mask, const uint8_t *flags, int8_t *xq_tiled,
+                             int8_t *xo_tiled, float *sx, int8_t *xq_rowmajor_dbg, const OutlierPrep &pr, hipStream_t st);
 hipError_t ps_mask_to_bytes(const uint32_t *mask, int K, uint8_t *out, hipStream_t st);
 hipError_t ps_mask_count(const uint32_t *masks, int n_masks, int words, int32_t *out, hipStream_t st);
 
@@ -210,6 +212,26 @@ __device__ __forceinline__ void flag_outlier_bits(uint32_t *mask, int word, uint
 }
 __device__ __forceinline__ void flag_outlier(uint32_t *mask, float theta, int k, __half v) {
     if (mask && fabsf(__half2float(v)) >= theta) flag_outlier_bits(mask, k >> 5, 1u << (k & 31));
+}
+// The same for the LayerNorms of calls of more than 64 rows, with a byte per column: an outlier feature is one in every
+// row, and the memory takes 7 ns per atomic on one address (351 rows of 4096 with four outlier columns: 10.1 us, 5.1
+// with bytes).  Plain stores of a 1 need no order, meet in the XCD's own L2, and L2s write back only the bytes that were
+// written.
+__device__ __forceinline__ void flag_outlier_bytes(uint8_t *flags, int k, uint32_t bits) {
+    while (bits) {
+        flags[k + __ffs(bits) - 1] = 1;
+        bits &= bits - 1;
+    }
+}
+// 16 such bytes as bits
+__device__ __forceinline__ uint32_t flag_bits16(const v4i &f) {
+    const uint32_t lo = __builtin_amdgcn_udot4((uint32_t)f[1], 0x80402010u, __builtin_amdgcn_udot4((uint32_t)f[0], 0x08040201u, 0u, false), false);
+    const uint32_t hi = __builtin_amdgcn_udot4((uint32_t)f[3], 0x80402010u, __builtin_amdgcn_udot4((uint32_t)f[2], 0x08040201u, 0u, false), false);
+    return lo | hi << 8;
+}
+// the outlier bits of columns 16 c .. 16 c + 15, from flags if there are any
+__device__ __forceinline__ uint32_t chunk_outliers(const uint32_t *mask, const uint8_t *flags, int c) {
+    return flags ? flag_bits16(*(const v4i *)(flags + (size_t)c * 16)) : ((const uint16_t *)mask)[c];
 }
 // Wave-wide reductions on the data-parallel-primitive moves (a few clocks a step; an exchange through LDS takes some
 // sixty, and a row kernel of a few microseconds waits for six of them in a row): four shifted steps inside the rows of

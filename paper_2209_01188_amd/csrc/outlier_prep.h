@@ -16,44 +16,63 @@ __host__ __device__ inline int outlier_prep_items(const OutlierPrep &p, int M) {
 // Counts the outlier columns and, when there are at most PS_EXACT_OUTLIERS, gathers their
 // dequantized weights (items [0, N/16)) and activations (the rest) as doubles in matrix-instruction lane order.
 // Every wave rebuilds the short column list from the bit mask itself.  list: PS_EXACT_OUTLIERS ints of LDS of this wave.
-__device__ __forceinline__ void outlier_prep_wave(const OutlierPrep &pr, const uint32_t *__restrict__ mask,
+__device__ __forceinline__ void outlier_prep_wave(const OutlierPrep &pr, const uint32_t *__restrict__ mask, const uint8_t *__restrict__ flags,
                                                   const __half *__restrict__ X, int M, int item, int *list) {
     const LinearW &w = pr.w;
-    const int K = w.K, KT = K >> 6, nwords = K >> 5, lane = threadIdx.x & 63;
-    const int wpt = (nwords + 63) / 64, w0 = min(nwords, lane * wpt), w1 = min(nwords, w0 + wpt);
-    int cnt = 0;
-    for (int i = w0; i < w1; i++) cnt += __popc(mask[i]);
-    int incl = cnt;
+    // 16 columns per lane and step: groups of 1024 consecutive columns per wave, at most 64 of them (K <= 65536)
+    const int K = w.K, KT = K >> 6, nchunk = K >> 4, lane = threadIdx.x & 63;
+    auto chunk = [&](int c) -> uint32_t { return c < nchunk ? chunk_outliers(mask, flags, c) : 0u; };
+    const auto sum = [](uint32_t a, uint32_t b) { return a + b; };
+    uint32_t cnt = 0, before = 0;          // outlier columns in all groups, and in those in front of group `item`
+    uint64_t used = 0;                     // groups that hold any
+    for (int g0 = 0; g0 * 64 < nchunk; g0 += 8) {
+        uint32_t b[8];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(incl, off);
-        if (lane >= off) incl += v;
-    }
-    const int total = __shfl(incl, 63);
-    if (item == 0 && lane == 0) { pr.count[0] = total; pr.count[1] = 4; }   // [1]: digit planes, raised by k_digit_tiles
-    if (total > PS_EXACT_OUTLIERS && item == 0 && pr.full_list) {
-        // more columns than the fp64 path takes: item 0 leaves their ascending list for the digit products,
-        // padded with -1 up to the next multiple of 64
-        int at = incl - cnt;
-        for (int i = w0; i < w1; i++) {
-            uint32_t b = mask[i];
-            while (b) {
-                const int j = __ffs(b) - 1;
-                b &= b - 1;
-                pr.full_list[at++] = i * 32 + j;
-            }
+        for (int i = 0; i < 8; i++) b[i] = chunk((g0 + i) * 64 + lane);     // all requested before the first is looked at
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            cnt += __popc(b[i]);
+            if (g0 + i < item) before += __popc(b[i]);
+            used |= (uint64_t)(__ballot(b[i] != 0) != 0) << (g0 + i);
         }
-        const int padded = (total + 63) & ~63;
-        for (int i = total + lane; i < padded; i += 64) pr.full_list[i] = -1;
     }
-    if (total == 0 || total > PS_EXACT_OUTLIERS) return;
-    int pos = incl - cnt;
-    for (int i = w0; i < w1; i++) {
-        uint32_t b = mask[i];
+    const int total = (int)wave_reduce(cnt, 0u, sum);
+    if (item == 0 && lane == 0) { pr.count[0] = total; pr.count[1] = 4; }   // [1]: digit planes, raised by k_digit_tiles
+    const auto lanes_before = [&](uint32_t b) {     // of this lane's columns in its group
+        const int n = __popc(b);
+        int incl = n;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(incl, off);
+            if (lane >= off) incl += v;
+        }
+        return incl - n;
+    };
+    if (total > PS_EXACT_OUTLIERS) {
+        // more columns than the fp64 path takes: their ascending list for the digit products, each group's part by the wave
+        // of that number, padded with -1 up to the next multiple of 64.  (The whole list by one wave was what this launch
+        // waited for: 200 rows of 32768 with 500 outlier columns 17 us.)
+        if (item * 64 >= nchunk || !pr.full_list) return;
+        uint32_t b = chunk(item * 64 + lane);
+        int at = (int)wave_reduce(before, 0u, sum) + lanes_before(b);
         while (b) {
-            const int j = __ffs(b) - 1;
+            pr.full_list[at++] = (item * 64 + lane) * 16 + __ffs(b) - 1;
             b &= b - 1;
-            list[pos++] = i * 32 + j;
+        }
+        if (item == 0)
+            for (int i = total + lane; i < ((total + 63) & ~63); i += 64) pr.full_list[i] = -1;
+        return;
+    }
+    if (total == 0) return;
+    int base = 0;
+    for (; used; used &= used - 1) {
+        const int c = (__ffsll((unsigned long long)used) - 1) * 64 + lane;
+        uint32_t b = chunk(c);
+        int at = base + lanes_before(b);
+        base += (int)wave_reduce((uint32_t)__popc(b), 0u, sum);
+        while (b) {
+            list[at++] = c * 16 + __ffs(b) - 1;
+            b &= b - 1;
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -72,7 +72,8 @@ static __device__ const CodeTable d_code_table = ps_make_code_table();
 template <int NT>
 __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *__restrict__ g,
                                                      const __half *__restrict__ b, float eps, int H,
-                                                     __half *__restrict__ y, uint32_t *__restrict__ mask, float theta) {
+                                                     __half *__restrict__ y, uint32_t *__restrict__ mask,
+                                                     uint8_t *__restrict__ flags, float theta) {
     __shared__ double sm[NT / 64];
     __shared__ float table[256];
     for (int i = threadIdx.x; i < 256; i += NT) table[i] = d_code_table.code[i];
@@ -92,10 +93,9 @@ __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *
         const __half2 o = ln_affine(*(const __half2 *)(xr + k), *(const __half2 *)(g + k),
                                     *(const __half2 *)(b + k), mean, inv);
         *(__half2 *)(yr + k) = o;
-        if (mask) {
-            const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
-            flag_outlier_bits(mask, k >> 5, bits << (k & 31));
-        }
+        const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
+        if (flags) flag_outlier_bytes(flags, k, bits);
+        else if (mask) flag_outlier_bits(mask, k >> 5, bits << (k & 31));
     }
 }
 
@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *
 __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restrict__ x, const __half *__restrict__ g,
                                                          const __half *__restrict__ b, float eps, int H,
                                                          __half *__restrict__ y, uint32_t *__restrict__ mask,
-                                                         float theta) {
+                                                         uint8_t *__restrict__ flags, float theta) {
     constexpr int NT = 1024, PER = 8;
     __shared__ double sm[NT / 64];
     const __half *xr = x + (size_t)blockIdx.x * H;
@@ -137,10 +137,9 @@ __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restric
         if (k < H) {
             const __half2 o = ln_affine(v[i], *(const __half2 *)(g + k), *(const __half2 *)(b + k), mean, inv);
             *(__half2 *)(yr + k) = o;
-            if (mask) {
-                const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
-                flag_outlier_bits(mask, k >> 5, bits << (k & 31));
-            }
+            const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
+            if (flags) flag_outlier_bytes(flags, k, bits);
+            else if (mask) flag_outlier_bits(mask, k >> 5, bits << (k & 31));
         }
     }
 }
@@ -157,7 +156,7 @@ template <int PER, bool Q8>
 __global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restrict__ x, QuantIn qin,
                                                         const __half *__restrict__ g, const __half *__restrict__ b,
                                                         float eps, int M, int H, __half *__restrict__ y,
-                                                        uint32_t *__restrict__ mask, uint32_t theta_bits) {
+                                                        uint32_t *__restrict__ mask, uint8_t *__restrict__ cols, uint32_t theta_bits) {
     constexpr int NT = 256;
     // narrow rows: gain and bias stay in registers as fp64 over the rows of the workgroup, and so do a row's values over
     // its three passes (conversions to fp64 take eight times as long as the operations on the values)
@@ -292,11 +291,13 @@ __global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restr
             }
         }
     }
-    if (mask) {
+    if (mask || cols) {
 #pragma unroll
         for (int i = 0; i < PER; i++) {
             const int k = (threadIdx.x + i * NT) * 8;
-            if (k < H) flag_outlier_bits(mask, k >> 5, flags[i] << (k & 31));
+            if (k >= H) continue;
+            if (cols) flag_outlier_bytes(cols, k, flags[i]);
+            else flag_outlier_bits(mask, k >> 5, flags[i] << (k & 31));
         }
     }
 }
@@ -305,13 +306,13 @@ constexpr int LN_ROWS_GRID = 1024;
 
 template <bool Q8>
 void launch_layernorm_rows(const __half *x, const QuantIn &qin, const __half *g, const __half *b, float eps, int M, int H,
-                           __half *y, uint32_t *mask, float theta, hipStream_t st) {
+                           __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
     const int grid = M < LN_ROWS_GRID ? M : LN_ROWS_GRID;
     const uint32_t tb = ps_theta_to_bits(theta);
-    if (H <= 2048) k_layernorm_rows<1, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, tb);
-    else if (H <= 4096) k_layernorm_rows<2, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, tb);
-    else if (H <= 8192) k_layernorm_rows<4, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, tb);
-    else k_layernorm_rows<8, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, tb);
+    if (H <= 2048) k_layernorm_rows<1, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
+    else if (H <= 4096) k_layernorm_rows<2, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
+    else if (H <= 8192) k_layernorm_rows<4, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
+    else k_layernorm_rows<8, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
 }
 
 // -------------------------------------------------- many rows: mask, then quantize
@@ -343,10 +344,10 @@ __device__ __forceinline__ int rowquant_row(int grid) {
     return ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
 }
 template <int NT>
-__device__ __forceinline__ void rowquant_prep(const OutlierPrep &pr, const uint32_t *mask, const __half *X, int M, int grid,
-                                              int *list) {
+__device__ __forceinline__ void rowquant_prep(const OutlierPrep &pr, const uint32_t *mask, const uint8_t *flags, const __half *X,
+                                              int M, int grid, int *list) {
     const int wave = threadIdx.x >> 6, item = ((int)blockIdx.x - grid) * (NT / 64) + wave;
-    if (item < outlier_prep_items(pr, M)) outlier_prep_wave(pr, mask, X, M, item, list + wave * PS_EXACT_OUTLIERS);
+    if (item < outlier_prep_items(pr, M)) outlier_prep_wave(pr, mask, flags, X, M, item, list + wave * PS_EXACT_OUTLIERS);
 }
 __host__ inline int rowquant_grid(int rows) { return 8 * (((rows / 16 + 7) / 8) * 16); }
 
@@ -410,19 +411,18 @@ __device__ __forceinline__ float row_scale(uint32_t m, uint32_t *sm) {
 // non-outlier columns; codes go to the MFMA operand tile order (same tiling as the
 // weights, rows = tokens); padding rows are written as zeros.
 __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict__ X, int M, int K,
-                                                        const uint32_t *__restrict__ mask,
+                                                        uint32_t *__restrict__ mask, const uint8_t *__restrict__ flags,
                                                         int8_t *__restrict__ xq_tiled,
                                                         int8_t *__restrict__ xo_tiled, float *__restrict__ sx,
                                                         int8_t *__restrict__ xq_dbg, int rows, int grid, OutlierPrep pr) {
     __shared__ uint32_t sm[4];
     __shared__ int list[4 * PS_EXACT_OUTLIERS];
     if ((int)blockIdx.x >= grid) {
-        rowquant_prep<256>(pr, mask, X, M, grid, list);
+        rowquant_prep<256>(pr, mask, flags, X, M, grid, list);
         return;
     }
     const int t = rowquant_row(grid), KT = K >> 6, nchunk = K >> 4;
     if (t >= rows) return;
-    const uint16_t *mask16 = (const uint16_t *)mask;
     const size_t tile_row = (size_t)(t >> 4) * KT;
     if (t >= M) {
         for (int c = threadIdx.x; c < nchunk; c += 256) {
@@ -437,13 +437,15 @@ __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict
         chunk_t w;
         *(v4i *)w = *(const v4i *)(xr + c * 16);
         *(v4i *)(w + 4) = *(const v4i *)(xr + c * 16 + 8);
-        m = pk_max_u16(m, chunk_absmax(w, mask16[c]));
+        const uint32_t bits = chunk_outliers(mask, flags, c);
+        if (flags && t == 0) ((uint16_t *)mask)[c] = (uint16_t)bits;      // for the kernels that read bits
+        m = pk_max_u16(m, chunk_absmax(w, bits));
     }
     const float s = row_scale<4>(m, sm);
     if (threadIdx.x == 0) sx[t] = s;
     const float r = s > 0.0f ? 127.0f / s : 0.0f;
     for (int c = threadIdx.x; c < nchunk; c += 256) {
-        const uint32_t bits = mask16[c];
+        const uint32_t bits = chunk_outliers(mask, flags, c);
         const v8h a = *(const v8h *)(xr + c * 16), b = *(const v8h *)(xr + c * 16 + 8);
         chunk_t w;
         *(v8h *)w = a;
@@ -478,19 +480,18 @@ __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict
 // for calls of many rows, 256 threads per row put four times as many rows on a compute unit.
 template <int NT, int CPT>
 __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__restrict__ X, int M, int K,
-                                                             const uint32_t *__restrict__ mask,
+                                                             uint32_t *__restrict__ mask, const uint8_t *__restrict__ flags,
                                                              int8_t *__restrict__ xq_tiled,
                                                              int8_t *__restrict__ xo_tiled, float *__restrict__ sx,
                                                              int8_t *__restrict__ xq_dbg, int rows, int grid, OutlierPrep pr) {
     __shared__ uint32_t sm[NT / 64];
     __shared__ int list[NT / 64 * PS_EXACT_OUTLIERS];
     if ((int)blockIdx.x >= grid) {
-        rowquant_prep<NT>(pr, mask, X, M, grid, list);
+        rowquant_prep<NT>(pr, mask, flags, X, M, grid, list);
         return;
     }
     const int t = rowquant_row(grid), KT = K >> 6, nchunk = K >> 4;
     if (t >= rows) return;
-    const uint16_t *mask16 = (const uint16_t *)mask;
     const size_t tile_row = (size_t)(t >> 4) * KT;
     if (t >= M) {
         for (int c = threadIdx.x; c < nchunk; c += NT) {
@@ -508,7 +509,8 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
         if (c < nchunk) {
             a[i] = *(const v8h *)(xr + c * 16);
             b[i] = *(const v8h *)(xr + c * 16 + 8);
-            bits[i] = mask16[c];
+            bits[i] = chunk_outliers(mask, flags, c);
+            if (flags && t == 0) ((uint16_t *)mask)[c] = (uint16_t)bits[i];   // for the kernels that read bits
         }
     }
     uint32_t m = 0;
@@ -799,23 +801,23 @@ hipError_t ps_copy_bytes(const void *src, void *dst, size_t n, hipStream_t st) {
     return hipGetLastError();
 }
 hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float eps, int M, int H, __half *y,
-                        uint32_t *mask, float theta, hipStream_t st) {
+                        uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
     // few rows: more threads per row (latency), many rows: more rows in flight (prefill calls of a 4096-wide block, two
     // LayerNorms each: 140 rows 188 us with 1024 threads per row, 199 with several rows per 256 threads; 351 rows 244
     // and 242: the line lies between).  Rows below 4096 columns, of which 1024 threads would hold two pairs each or fewer,
     // always take 256 threads.
     if (H % 8 || H > 16384) return hipErrorInvalidValue;       // span and client take multiples of 64 up to 16384
-    if (M >= 256 || H < 4096) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, theta, st);
-    else k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, theta);
+    if (M >= 256 || H < 4096) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, flags, theta, st);
+    else k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, flags, theta);
     return hipGetLastError();
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
-                           int H, __half *y, uint32_t *mask, float theta, hipStream_t st) {
+                           int H, __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
     // the line of ps_layernorm (measured there, on fp16 rows)
     if ((M >= 256 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
-        launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, theta, st);
-    else if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, theta);
-    else k_layernorm_q8<256><<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, theta);
+        launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, flags, theta, st);
+    else if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
+    else k_layernorm_q8<256><<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
     return hipGetLastError();
 }
 hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask, hipStream_t st) {
@@ -823,15 +825,15 @@ hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask
     k_colmask<<<grid, 256, 0, st>>>(X, M, K, theta, mask);
     return hipGetLastError();
 }
-hipError_t ps_rowquant_tiled(const __half *X, int M, int K, const uint32_t *mask, int8_t *xq_tiled, int8_t *xo_tiled,
-                             float *sx, int8_t *xq_dbg, const OutlierPrep &pr, hipStream_t st) {
+hipError_t ps_rowquant_tiled(const __half *X, int M, int K, uint32_t *mask, const uint8_t *flags, int8_t *xq_tiled,
+                             int8_t *xo_tiled, float *sx, int8_t *xq_dbg, const OutlierPrep &pr, hipStream_t st) {
     const int rows = (M + 15) / 16 * 16, grid = rowquant_grid(rows), items = outlier_prep_items(pr, M);
     if (K >= 4096 && K <= 16384 && M >= 512)   // many rows: four times as many rows in flight per compute unit
-        k_rowquant_tiled_wide<256, 4><<<grid + (items + 3) / 4, 256, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
+        k_rowquant_tiled_wide<256, 4><<<grid + (items + 3) / 4, 256, 0, st>>>(X, M, K, mask, flags, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
     else if (K >= 4096 && K <= 65536)          // wide rows: 1024 threads keep the row in registers, one pass over X
-        k_rowquant_tiled_wide<1024, 4><<<grid + (items + 15) / 16, 1024, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
+        k_rowquant_tiled_wide<1024, 4><<<grid + (items + 15) / 16, 1024, 0, st>>>(X, M, K, mask, flags, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
     else
-        k_rowquant_tiled<<<grid + (items + 3) / 4, 256, 0, st>>>(X, M, K, mask, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
+        k_rowquant_tiled<<<grid + (items + 3) / 4, 256, 0, st>>>(X, M, K, mask, flags, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
     return hipGetLastError();
 }
 hipError_t ps_mask_count(const uint32_t *masks, int n_masks, int words, int32_t *out, hipStream_t st) {

@@ -21,6 +21,7 @@ struct Workspace {
     int8_t *xo;         // outlier values per (token, 16-column group) of calls of at most 64 rows
     float *sx;
     uint32_t *masks;    // [n_blocks][4][mask_words]
+    uint8_t *flags;     // [n_blocks][2][hidden], right behind masks: outlier columns of the LayerNorms' outputs, one byte each (spans that take more than 64 rows)
     double *partials;
     int *ocount;
     double *wd64, *x64;
@@ -75,6 +76,10 @@ struct SaveSet {
     std::vector<float *> lse, ctx32;
 };
 
+// what a call of M rows clears first: nothing, the masks, or the masks and the flags behind them
+inline size_t ps_mask_clear_words(const petals_span_config &c, const Workspace &ws, int M) {
+    return M <= 1 ? 0 : (size_t)c.n_blocks * 4 * ws.mask_words + (M > 64 ? (size_t)c.n_blocks * 2 * c.hidden / 4 : 0);
+}
 // N and K of linear `which` (0 qkv, 1 dense, 2 up, 3 down)
 void ps_linear_dims(const petals_span_config &c, int which, int *N, int *K);
 int ps_check_config(const petals_span_config *c);

@@ -37,6 +37,40 @@ def test_layernorm_of_many_rows(M, H, nh):
     span.close()
 
 
+# rows: the last call whose LayerNorm flags outlier columns as bits and the first that takes bytes, both LayerNorm forms;
+# columns: none, the most of the fp64 path, one more (a list in memory), all; hidden: one group of 1024 columns and a piece
+@pytest.mark.parametrize("M", [64, 65, 300])
+@pytest.mark.parametrize("H,nh,n_out", [(1088, 17, 0), (1088, 17, 64), (4160, 65, 65), (1088, 17, 1088), (4160, 65, 2100)])
+def test_outlier_columns_of_a_layernorm_reach_the_linear(M, H, nh, n_out):
+    """The gain makes n_out columns outliers; the mask and the up linear's output are those of the oracle."""
+    r = np.random.default_rng(M + H + n_out)
+    cols = np.sort(r.choice(H, n_out, replace=False))
+    if 0 < n_out < H:
+        cols[-1] = H - 1                                       # the very last column
+        cols = np.unique(cols)
+    cfg = synth.SpanConfig("flags", 2, H, nh, 1, M, 1, 1, (20.0, 40.0), 4)
+    osp, span, params = build_pair(cfg, max_rows=M)
+    # block 0 leaves its rows to block 1, whose second LayerNorm is looked at: flags are those of block and LayerNorm
+    gain = np.full(H, 0.5, np.float16)
+    gain[cols] = 30.0
+    p = dict(params[1], ln2_g=gain, ln2_b=np.zeros(H, np.float16))
+    span.load_block(1, {k: to_dev(v) for k, v in p.items()})
+    x = np.clip(r.standard_normal((M, H)), -4.0, 4.0).astype(np.float16)
+    got = span.debug_layernorm(1, 1, to_dev(x), want_quantized=True)
+    ref = oracle.layernorm(x, gain, np.zeros(H, np.float16))
+    out = (np.abs(ref.astype(np.float32)) >= 6.0).any(0)
+    assert out.sum() == len(cols)
+    assert np.array_equal(to_np(got["y"]).view(np.uint16), ref.view(np.uint16))
+    assert np.array_equal(to_np(got["mask"]).astype(bool), out)
+    wq, sw = osp.get_weight(1, 2)
+    Y, dbg = oracle.linear(ref, wq, sw, params[1]["b_up"], 6.0, 1, want_debug=True)
+    assert np.array_equal(to_np(got["xq"]), dbg["xq"]) and np.array_equal(to_np(got["sx"]).view(np.uint32), dbg["sx"].view(np.uint32))
+    lin = span.debug_linear(1, 2, to_dev(ref), 1)
+    assert np.array_equal(to_np(lin["acc"]), dbg["acc"])
+    hidden_close(to_np(lin["y"]), Y, "up linear behind the LayerNorm")
+    span.close(); osp.destroy()
+
+
 @pytest.mark.parametrize("B,T,H,block", [(2, 256, 64, 64), (3, 171, 192, 4096), (1, 1025, 128, 1024)])
 def test_codes_of_many_rows_as_span_input(B, T, H, block):
     cfg = synth.SpanConfig("rows", 2, H, H // 32, B, T, 1, 1, (20.0, 40.0), 7)
