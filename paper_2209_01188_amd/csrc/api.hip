@@ -52,7 +52,8 @@ size_t block_weight_bytes(const petals_span_config &c) {
     return b + 4 * ps_align_up((size_t)c.hidden * 2);
 }
 
-Workspace carve(const petals_span_config &c, uint8_t *base) {
+// with_digits: room for ps_gemm_digits (calls of 17 to 64 rows of wide spans; without it they take ps_gemm alone)
+Workspace carve(const petals_span_config &c, uint8_t *base, bool with_digits = true) {
     Workspace w;
     const size_t M = (size_t)c.max_rows_per_call, Mp = (M + 15) / 16 * 16, H = c.hidden, F = c.ffn;
     const size_t Kmax = F > H ? F : H;
@@ -88,6 +89,17 @@ Workspace carve(const petals_span_config &c, uint8_t *base) {
         w.many.wd_bytes = 2 * (NKmax + 64 * Nmax);
         w.many.wd = (int8_t *)take(w.many.wd_bytes);
         w.many.od = (double *)take(Mp * Nmax * 8);
+    }
+    w.digits = DigitCall{};
+    w.xd = nullptr;
+    const size_t rows = Mp < 64 ? Mp : 64;
+    if (with_digits && ps_gemm_digits_applies((int)H, (int)H, (int)rows)) {
+        const size_t halves = PS_DIGIT_SPLITS * 2 * (H / 32) * 16 * 64;
+        w.xd = (int8_t *)take(rows * Kmax * 4);
+        w.digits.part = (double *)take(halves * 8);
+        w.digits.part_acc = (int *)take(halves * 4);
+        w.digits.xd = w.xd;
+        w.digits.rowstate = w.ocount;
     }
     w.total = off;
     return w;
@@ -152,11 +164,15 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
         const bool chunks = ps_gemm_prefers_chunks(w, M);
         const bool small = M <= 64 || chunks;
         const OutlierPrep prep = {w, small ? nullptr : ws.ocount, ws.wd64, ws.x64, ws.many.list};
-        HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ln_g ? flags : nullptr, ws.xq, small ? ws.xo : nullptr, ws.sx, xq_dbg, prep, st));
+        // (a LayerNorm's output has few outlier columns: only the inputs that attention and GeLU write go for digits)
+        const bool digits = !ln_g && ws.xd && w.N == c.hidden && ps_gemm_digits_applies(w.N, w.K, M);
+        const RowDigits rd = {digits ? ws.xd : nullptr, ws.ocount};
+        HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ln_g ? flags : nullptr, ws.xq, small ? ws.xo : nullptr, ws.sx, xq_dbg, prep, rd, st));
         const OutlierSet os = {ws.ocount, ws.wd64, ws.x64};
         const bool pr = sp->prof.begin(PETALS_PROFILE_GEMM, which, st);
         if (small) {
-            HIP_TRY(ps_gemm(w, ws.xq, ws.xo, mask, X, ws.sx, M, o, ws.table, st));
+            if (digits) HIP_TRY(ps_gemm_digits(w, ws.xq, ws.digits, M, st));
+            HIP_TRY(ps_gemm(w, ws.xq, ws.xo, mask, X, ws.sx, M, o, ws.table, digits ? ws.digits : DigitCall{}, st));
         } else {
             HIP_TRY(ps_gemm_lds(w, ws.xq, mask, X, ws.sx, M, os, ws.many, o, ws.table, st));
         }
@@ -485,7 +501,7 @@ int petals_span_decode_step_static(petals_span *sp, petals_session *const *sessi
     // the intermediates of a B-row step, laid out like a workspace sized for exactly B rows
     petals_span_config c = sp->cfg;
     c.max_rows_per_call = B;
-    const size_t need = carve(c, nullptr).total;
+    const size_t need = carve(c, nullptr, false).total;
     if (need > PS_STATIC_SCRATCH_BYTES)
         return fail(PETALS_ERR_CAPACITY, "a step of %d rows of this span needs %zu bytes of scratch memory, the static buffer holds %zu",
                     B, need, (size_t)PS_STATIC_SCRATCH_BYTES);
@@ -494,7 +510,7 @@ int petals_span_decode_step_static(petals_span *sp, petals_session *const *sessi
     // the span's kernels take every intermediate buffer from sp->ws: point it at the static memory for this call
     const Workspace own = sp->ws;
     const int own_rows = sp->cfg.max_rows_per_call;
-    sp->ws = carve(c, (uint8_t *)base);
+    sp->ws = carve(c, (uint8_t *)base, false);
     sp->cfg.max_rows_per_call = B;
     const int rc = run_call(sp, sessions, B, 1, hidden_in, hidden_out, (hipStream_t)stream);
     sp->ws = own;

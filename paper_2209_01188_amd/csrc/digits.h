@@ -30,3 +30,17 @@ __device__ __forceinline__ void digit_planes4(const __half (&x)[4], int (&p)[4])
     p[2] = (int)(__builtin_amdgcn_perm(d, c, 0x05040100) ^ 0x80808080u);
     p[3] = (int)(__builtin_amdgcn_perm(d, c, 0x07060302) ^ 0x80808080u);
 }
+
+// Scale of the digit form of output row n's dequantized weights: a = sw / 127 (fp32, as everywhere),
+// E = its binary exponent (not below fp16's smallest normal one), so that every fp16(code * a) is a
+// multiple of u = 2^(E - 10); m = a / u rounded to an integer (0 is possible for a row whose scale is
+// below fp16's subnormal spacing; its products can still round up to a few u).  False for a zero row.
+__device__ __forceinline__ bool digit_scale(float sw, float &a, int &E, int &m) {
+    a = sw / 127.0f;
+    E = -14;
+    m = 0;
+    if (!(a > 0.0f) || !(a < 1.0e30f)) return false;
+    E = max(ilogbf(a), -14);
+    m = (int)rintf(ldexpf(a, 10 - E));
+    return true;
+}

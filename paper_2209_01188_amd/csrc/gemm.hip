@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "digits.h"
 #include "epilogue.h"
 
 namespace {
@@ -23,6 +24,58 @@ __device__ __forceinline__ float half_of8(const v4i &x, int r) {   // r-th of th
     return __half2float(__ushort_as_half((unsigned short)((word >> ((r & 1) * 16)) & 0xffff)));
 }
 
+struct NoDigits {};
+template <bool DIG>
+auto digit_arg(const DigitCall &dc) {
+    if constexpr (DIG) return dc;
+    else return NoDigits{};
+}
+
+// The rest of a call that k_gemm_digits has summed: one wave per 4 x 2 output rows and 32 tokens adds the splits and
+// goes through the linear's tail.
+__device__ __forceinline__ void finish_digits(const LinearW &w, const uint32_t *__restrict__ mask, const __half *__restrict__ X,
+                                              const float *__restrict__ sx, int M, const OutDesc &o,
+                                              const SessTable *__restrict__ sess, const DigitCall &dc) {
+    const int lane = threadIdx.x & 63, pairs = w.N >> 5, K = w.K, KT = K >> 6;
+    const int items = pairs * 4 * ((M + 31) >> 5), stride = gridDim.x * (blockDim.x >> 6);
+    for (int item = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); item < items; item += stride) {
+        const int q = item & 3, hp = item >> 2, half = hp / pairs, pair = hp - half * pairs;     // uniform in the wave
+        const int t = half * 32 + (lane & 31), n0 = pair * 32 + 8 * q + 4 * (lane >> 5);
+        const size_t at = (((size_t)half * pairs + pair) * 16 + 4 * q) * 64 + lane, split = (size_t)2 * pairs * 16 * 64;
+        const float4 s4 = *(const float4 *)(w.sw + n0);
+        const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
+        v4i acc = {0, 0, 0, 0};
+        v4d od = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int sp = 0; sp < PS_DIGIT_SPLITS; sp++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                od[r] += dc.part[sp * split + at + r * 64];
+                acc[r] += dc.part_acc[sp * split + at + r * 64];
+            }
+        if (t >= M) continue;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            float a;
+            int E, m;
+            digit_scale(sv[r], a, E, m);
+            od[r] = ldexp(od[r], E - 34);                  // u = 2^(E-10), activations in units of 2^-24
+            if (!(sv[r] <= 65504.0f)) {
+                // some |Wd| of this row may overflow fp16: column by column, infinities and all
+                od[r] = 0.0;
+                const int n = n0 + r;
+                for (int kw = 0; kw < K >> 5; kw++)
+                    for (uint32_t b = mask[kw]; b; b &= b - 1) {
+                        const int k = kw * 32 + __ffs(b) - 1;
+                        const int code = w.wt[((size_t)(n >> 4) * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + (n & 15)) * 16 + (k & 15)];
+                        od[r] += (double)__half2float(X[(size_t)t * K + k]) * (double)dequant_w16(code, sv[r] / 127.0f);
+                    }
+            }
+        }
+        emit_output4(o, sess, w.N, t, n0, acc, od, sx[t] / 127.0f, w.sw, w.bias);
+    }
+}
+
 // One workgroup = WVK waves on WN consecutive 16-row weight panels; wave wk takes chunks of UK
 // consecutive k-tiles (chunk c = wk, wk + WVK, ...) for MT token tiles of 16 rows, so a token tile
 // fetched once meets WN weight tiles.  Weights are the A operand (lane l: row l%16, 16 codes of
@@ -32,11 +85,18 @@ __device__ __forceinline__ float half_of8(const v4i &x, int r) {   // r-th of th
 // group's first 8 outlier columns (written by ps_rowquant_tiled); a group with more takes the rest
 // from X.  The waves' partial sums meet in LDS once; up to four waves finish the (panel, token tile)
 // pairs.
-template <int WN, int MT, int UK, int WVK>
+template <int WN, int MT, int UK, int WVK, bool DIG>
 __global__ void __launch_bounds__(64 * WVK)
 k_gemm(LinearW w, const int8_t *__restrict__ xq_tiled, const int8_t *__restrict__ xo_tiled,
        const uint32_t *__restrict__ mask, const __half *__restrict__ X, const float *__restrict__ sx, int M,
-       OutDesc o, const SessTable *__restrict__ sess) {
+       OutDesc o, const SessTable *__restrict__ sess, typename std::conditional<DIG, DigitCall, NoDigits>::type dc) {
+    if constexpr (DIG) {                             // (at most 64 rows)
+        const int l = threadIdx.x & 63;
+        if (!__ballot(l < M && dc.rowstate[l] != PS_ROWS_IN_DIGITS)) {
+            finish_digits(w, mask, X, sx, M, o, sess, dc);
+            return;
+        }
+    }
     const int K = w.K, KT = K >> 6, N = w.N;
     if (gridDim.y > 1) {
         // a call of more than 64 rows: blockIdx.y takes rows 64 y .. +64 of it
@@ -203,12 +263,12 @@ k_gemm(LinearW w, const int8_t *__restrict__ xq_tiled, const int8_t *__restrict_
     }
 }
 
-template <int WN, int MT, int UK, int WVK = 8>
+template <int WN, int MT, int UK, int WVK = 8, bool DIG = false>
 hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,
-                  const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, hipStream_t st) {
+                  const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, const DigitCall &dc, hipStream_t st) {
     constexpr int G = WN * MT, NPP = G < 4 ? G : 4;
     const size_t lds = (size_t)WVK * NPP * 64 * (16 + 32);   // up to 96 KB
-    auto kern = k_gemm<WN, MT, UK, WVK>;
+    auto kern = k_gemm<WN, MT, UK, WVK, DIG>;
     static std::mutex attr_lock;
     static bool attr_set = false;
     std::lock_guard<std::mutex> hold(attr_lock);
@@ -217,7 +277,7 @@ hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_til
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    k_gemm<WN, MT, UK, WVK><<<dim3(w.N / (16 * WN), (M + 63) / 64), 64 * WVK, lds, st>>>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess);
+    kern<<<dim3(w.N / (16 * WN), (M + 63) / 64), 64 * WVK, lds, st>>>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, digit_arg<DIG>(dc));
     return hipGetLastError();
 }
 
@@ -264,19 +324,25 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
 }
 
 hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,
-                   const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, hipStream_t st) {
+                   const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, const DigitCall &dc, hipStream_t st) {
     const int panels = w.N / 16, wn = gemm_panels_per_wg(w.N);
-#define PS_GEMM_CASE(WN_, MT_, UK_) return launch<WN_, MT_, UK_>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, st)
+#define PS_GEMM_CASE(WN_, MT_, UK_) return launch<WN_, MT_, UK_>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st)
     if (M <= 16) {
         // one panel per workgroup (narrow outputs): 16 waves split the k-tiles, twice the weight bytes in flight per
         // compute unit (C3, 8 rows: down 2.85 -> 3.2 TB/s, dense 1.5 -> 1.65 TB/s; with 2 panels 16 waves are slower)
-        if (wn == 1 && w.K >= 4096) return launch<1, 1, 2, 16>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, st);
+        if (wn == 1 && w.K >= 4096) return launch<1, 1, 2, 16>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
         // small matrices (C3: 50-67 MB, 13-16 us per launch) do better with two workgroups per compute unit and
         // short chunks (up 3.5 -> 3.8, QKV 3.2 -> 3.25 TB/s); large ones with four panels per workgroup
         if (wn == 4 && panels / 4 < 448 && (size_t)w.N * w.K <= ((size_t)1 << 27)) PS_GEMM_CASE(2, 1, 2);
         if (wn == 4) PS_GEMM_CASE(4, 1, 2);
         if (wn == 2) PS_GEMM_CASE(2, 1, 1);
         PS_GEMM_CASE(1, 1, 4);
+    }
+    if (dc.xd) {
+        if (!ps_gemm_digits_applies(w.N, w.K, M)) return hipErrorInvalidValue;
+        if (M > 32) return launch<2, 4, 1, 8, true>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
+        if (wn == 4) return launch<4, 2, 1, 8, true>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
+        return launch<2, 2, 2, 8, true>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
     }
     if (M <= 32) {
         if (wn == 4) PS_GEMM_CASE(4, 2, 1);

@@ -26,6 +26,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "digits.h"
 #include "epilogue.h"
 
 namespace {
@@ -35,20 +36,6 @@ constexpr int PS_KSPLIT_MAX = 8;   // workgroups that share one output block's c
 
 // ---------------------------------------------------------------------------------------------
 // outlier column list and fp16 gathers (only do work when the call has > PS_EXACT_OUTLIERS)
-
-// Scale of the digit form of output row n's dequantized weights: a = sw / 127 (fp32, as everywhere),
-// E = its binary exponent (not below fp16's smallest normal one), so that every fp16(code * a) is a
-// multiple of u = 2^(E - 10); m = a / u rounded to an integer (0 is possible for a row whose scale is
-// below fp16's subnormal spacing; its products can still round up to a few u).  False for a zero row.
-__device__ __forceinline__ bool digit_scale(float sw, float &a, int &E, int &m) {
-    a = sw / 127.0f;
-    E = -14;
-    m = 0;
-    if (!(a > 0.0f) || !(a < 1.0e30f)) return false;
-    E = max(ilogbf(a), -14);
-    m = (int)rintf(ldexpf(a, 10 - E));
-    return true;
-}
 
 // Digit tiles of the outlier columns, in the int8 operand order (16 rows x 64 compacted columns = 1024 bytes,
 // lane l owns row l%16 and columns (l/16)*16 .. +16).  One wave per tile; the grid is fixed and strides over the

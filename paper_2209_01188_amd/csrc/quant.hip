@@ -2,6 +2,7 @@
 // streaming tile order, LayerNorm, outlier-column detection, row-wise int8
 // quantization of activations, the blockwise 8-bit hidden-state codec, cache copies.
 #include "common.h"
+#include "digits.h"
 #include "outlier_prep.h"
 #include "rowops.h"
 
@@ -407,9 +408,21 @@ __device__ __forceinline__ float row_scale(uint32_t m, uint32_t *sm) {
     return __half2float(*(const __half *)&b);
 }
 
+// Where the outlier columns come from: the mask, or (LayerNorm outputs of calls of more than 64 rows) FLAGS.  A template
+// argument: a test per chunk puts a branch between its loads, and the compiler waits for all of them where its ends meet.
+enum { ROWS_MASK = 0, ROWS_DIGITS = 1, ROWS_FLAGS = 2 };
+template <int MODE>
+__device__ __forceinline__ uint32_t row_chunk_outliers(uint32_t *mask, const uint8_t *flags, int c, int t) {
+    if constexpr (MODE != ROWS_FLAGS) return ((const uint16_t *)mask)[c];
+    const uint32_t bits = flag_bits16(*(const v4i *)(flags + (size_t)c * 16));
+    if (t == 0) ((uint16_t *)mask)[c] = (uint16_t)bits;                  // for the kernels that read bits
+    return bits;
+}
+
 // One workgroup per row of the 16-padded row range.  Row scale = absolute maximum over
 // non-outlier columns; codes go to the MFMA operand tile order (same tiling as the
 // weights, rows = tokens); padding rows are written as zeros.
+template <int MODE>
 __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict__ X, int M, int K,
                                                         uint32_t *__restrict__ mask, const uint8_t *__restrict__ flags,
                                                         int8_t *__restrict__ xq_tiled,
@@ -437,15 +450,14 @@ __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict
         chunk_t w;
         *(v4i *)w = *(const v4i *)(xr + c * 16);
         *(v4i *)(w + 4) = *(const v4i *)(xr + c * 16 + 8);
-        const uint32_t bits = chunk_outliers(mask, flags, c);
-        if (flags && t == 0) ((uint16_t *)mask)[c] = (uint16_t)bits;      // for the kernels that read bits
+        const uint32_t bits = row_chunk_outliers<MODE>(mask, flags, c, t);
         m = pk_max_u16(m, chunk_absmax(w, bits));
     }
     const float s = row_scale<4>(m, sm);
     if (threadIdx.x == 0) sx[t] = s;
     const float r = s > 0.0f ? 127.0f / s : 0.0f;
     for (int c = threadIdx.x; c < nchunk; c += 256) {
-        const uint32_t bits = chunk_outliers(mask, flags, c);
+        const uint32_t bits = row_chunk_outliers<MODE>(mask, flags, c, t);
         const v8h a = *(const v8h *)(xr + c * 16), b = *(const v8h *)(xr + c * 16 + 8);
         chunk_t w;
         *(v8h *)w = a;
@@ -478,13 +490,19 @@ __global__ void __launch_bounds__(256) k_rowquant_tiled(const __half *__restrict
 // columns in registers between the absolute-maximum pass and the quantization, so X is read once;
 // for calls of few rows, where the latency of the loads is the whole cost, this halves it (1024 threads);
 // for calls of many rows, 256 threads per row put four times as many rows on a compute unit.
-template <int NT, int CPT>
+// ROWS_DIGITS: also counts the outlier columns, and if they are more than one in 16 writes the row's outlier values as
+// digits, zero in regular columns.  (14336 x 57344, 32 rows, digits against fp64 form: one column in 12 304 and 357 us, one
+// in 4 300 and 623; the fp64 form at one in 16 305, one in 32 250; at 64 rows 539 and 605, 550 and 1105, 528, 430.)
+template <int NT, int CPT, int MODE>
 __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__restrict__ X, int M, int K,
                                                              uint32_t *__restrict__ mask, const uint8_t *__restrict__ flags,
                                                              int8_t *__restrict__ xq_tiled,
                                                              int8_t *__restrict__ xo_tiled, float *__restrict__ sx,
-                                                             int8_t *__restrict__ xq_dbg, int rows, int grid, OutlierPrep pr) {
-    __shared__ uint32_t sm[NT / 64];
+                                                             int8_t *__restrict__ xq_dbg, int rows, int grid, OutlierPrep pr,
+                                                             RowDigits rd) {
+    constexpr bool DIGITS = MODE == ROWS_DIGITS;
+    __shared__ uint32_t sm[NT / 64], smc[DIGITS ? NT / 64 : 1];
+    __shared__ int big;
     __shared__ int list[NT / 64 * PS_EXACT_OUTLIERS];
     if ((int)blockIdx.x >= grid) {
         rowquant_prep<NT>(pr, mask, flags, X, M, grid, list);
@@ -509,11 +527,10 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
         if (c < nchunk) {
             a[i] = *(const v8h *)(xr + c * 16);
             b[i] = *(const v8h *)(xr + c * 16 + 8);
-            bits[i] = chunk_outliers(mask, flags, c);
-            if (flags && t == 0) ((uint16_t *)mask)[c] = (uint16_t)bits[i];   // for the kernels that read bits
+            bits[i] = row_chunk_outliers<MODE>(mask, flags, c, t);
         }
     }
-    uint32_t m = 0;
+    uint32_t m = 0, n_out = 0;
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
         if ((int)(threadIdx.x + i * NT) < nchunk) {
@@ -521,9 +538,22 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
             *(v8h *)w = a[i];
             *(v8h *)(w + 4) = b[i];
             m = pk_max_u16(m, chunk_absmax(w, bits[i]));
+            if constexpr (DIGITS) n_out += __popc(bits[i]);
         }
     }
+    if constexpr (DIGITS) {
+        n_out = wave_reduce(n_out, 0u, [](uint32_t a, uint32_t b) { return a + b; });
+        if ((threadIdx.x & 63) == 0) smc[threadIdx.x >> 6] = n_out;
+        if (threadIdx.x == 0) big = 0;
+    }
     const float s = row_scale<NT / 64>(m, sm);
+    bool digits = false;
+    if constexpr (DIGITS) {
+        n_out = 0;
+#pragma unroll
+        for (int i = 0; i < NT / 64; i++) n_out += smc[i];
+        digits = n_out * 16 > (uint32_t)K;
+    }
     if (threadIdx.x == 0) sx[t] = s;
     const float r = s > 0.0f ? 127.0f / s : 0.0f;
 #pragma unroll
@@ -537,6 +567,28 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
             const size_t slot = ((tile_row + (c >> 2)) * 64 + (c & 3) * 16 + (t & 15)) * 16;
             *(v4i *)(xq_tiled + slot) = o;
             if (xq_dbg) *(v4i *)(xq_dbg + (size_t)t * K + c * 16) = o;
+            if (DIGITS && digits) {
+                __half v[16];
+                uint32_t am = 0;
+#pragma unroll
+                for (int e = 0; e < 8; e++) {
+                    const uint32_t two = bits[i] >> (2 * e), h = w[e] & (((two & 1u) ? 0xffffu : 0u) | ((two & 2u) ? 0xffff0000u : 0u));
+                    am = pk_max_u16(am, h & 0x7fff7fffu);
+                    *(uint32_t *)(v + 2 * e) = h;
+                }
+                if (max(am & 0xffffu, am >> 16) >= DIGITS_BIG) big = 1;
+                v4i pl[4];
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    int p4[4];
+                    digit_planes4(*(const __half(*)[4])(v + 4 * q), p4);
+#pragma unroll
+                    for (int d = 0; d < 4; d++) pl[d][q] = p4[d];
+                }
+                int8_t *to = rd.xd + (tile_row + (c >> 2)) * 4096 + ((c & 3) * 16 + (t & 15)) * 16;
+#pragma unroll
+                for (int d = 0; d < 4; d++) *(v4i *)(to + d * 1024) = pl[d];
+            }
             if (xo_tiled && bits[i]) {   // the group's first 8 outlier values, ascending column order
                 v8h ov;
                 uint32_t rest = bits[i];
@@ -555,6 +607,10 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
                 *(v8h *)(xo_tiled + slot) = ov;
             }
         }
+    }
+    if constexpr (DIGITS) {              // a value that takes more than four digits (or is none): the fp64 form for the call
+        __syncthreads();
+        if (threadIdx.x == 0) rd.rowstate[t] = digits && !big ? PS_ROWS_IN_DIGITS : 0;
     }
 }
 
@@ -826,14 +882,25 @@ hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask
     return hipGetLastError();
 }
 hipError_t ps_rowquant_tiled(const __half *X, int M, int K, uint32_t *mask, const uint8_t *flags, int8_t *xq_tiled,
-                             int8_t *xo_tiled, float *sx, int8_t *xq_dbg, const OutlierPrep &pr, hipStream_t st) {
+                             int8_t *xo_tiled, float *sx, int8_t *xq_dbg, const OutlierPrep &pr, const RowDigits &rd,
+                             hipStream_t st) {
     const int rows = (M + 15) / 16 * 16, grid = rowquant_grid(rows), items = outlier_prep_items(pr, M);
-    if (K >= 4096 && K <= 16384 && M >= 512)   // many rows: four times as many rows in flight per compute unit
-        k_rowquant_tiled_wide<256, 4><<<grid + (items + 3) / 4, 256, 0, st>>>(X, M, K, mask, flags, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
-    else if (K >= 4096 && K <= 65536)          // wide rows: 1024 threads keep the row in registers, one pass over X
-        k_rowquant_tiled_wide<1024, 4><<<grid + (items + 15) / 16, 1024, 0, st>>>(X, M, K, mask, flags, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
-    else
-        k_rowquant_tiled<<<grid + (items + 3) / 4, 256, 0, st>>>(X, M, K, mask, flags, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
+    const int extra4 = (items + 3) / 4, extra16 = (items + 15) / 16;
+#define PS_ROWS(NT_, MODE_) k_rowquant_tiled_wide<NT_, 4, MODE_><<<grid + (NT_ == 256 ? extra4 : extra16), NT_, 0, st>>>(X, M, K, mask, flags, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr, rd)
+    if (rd.xd) {
+        if (K < 4096 || K > 65536 || flags) return hipErrorInvalidValue;
+        PS_ROWS(1024, ROWS_DIGITS);
+    } else if (K >= 4096 && K <= 16384 && M >= 512) {   // many rows: four times as many rows in flight per compute unit
+        if (flags) PS_ROWS(256, ROWS_FLAGS);
+        else PS_ROWS(256, ROWS_MASK);
+    } else if (K >= 4096 && K <= 65536) {               // wide rows: 1024 threads keep the row in registers, one pass over X
+        if (flags) PS_ROWS(1024, ROWS_FLAGS);
+        else PS_ROWS(1024, ROWS_MASK);
+    } else {
+        auto kern = flags ? k_rowquant_tiled<ROWS_FLAGS> : k_rowquant_tiled<ROWS_MASK>;
+        kern<<<grid + extra4, 256, 0, st>>>(X, M, K, mask, flags, xq_tiled, xo_tiled, sx, xq_dbg, rows, grid, pr);
+    }
+#undef PS_ROWS
     return hipGetLastError();
 }
 hipError_t ps_mask_count(const uint32_t *masks, int n_masks, int words, int32_t *out, hipStream_t st) {
