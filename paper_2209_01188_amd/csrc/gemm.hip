@@ -289,19 +289,34 @@ static int gemm_panels_per_wg(int N) {
     return (panels % 4 == 0 && panels / 4 >= 224) ? 4 : (panels % 2 == 0 && panels / 2 >= 224) ? 2 : 1;
 }
 
+// Microseconds of the 64-rows-per-workgroup form without its row kernels, and whether four waves per workgroup do better than
+// eight.  Eight: one workgroup to a compute unit (registers, and local memory for the sums to meet in), in rounds of 256 that
+// each walk the K/64 tiles in 3.4 us + 0.095 per tile with one panel, 5 us + 0.123 with two; four: two to a unit, rounds of
+// 512 in 4 us + 0.18 per tile and 8 us + 0.22.  So four wherever eight would leave a second round nearly empty (128 rows:
+// 3072 x 1024 with its row kernels 23.1 -> 20.5 us, 9216 x 3072 at 192 rows 55.3 -> 45.5, 16384 x 4096 at 64 rows 39.4 -> 34.9),
+// eight in single rounds (1024 x 4096 at 128 rows: 21.8 against 24.8) and where their rounds come out even (24576 x 8192 at
+// 64 rows: 75 against 81).
+static double gemm_rows64_us(const LinearW &w, int M, int wn, bool &four) {
+    const int groups = w.N / 16 / wn * ((M + 63) / 64);
+    const double tiles = w.K / 64;
+    const double t8 = (groups + 255) / 256 * (wn == 2 ? 5.0 + 0.123 * tiles : 3.4 + 0.095 * tiles);
+    const double t4 = (groups + 511) / 512 * (wn == 2 ? 8.0 + 0.22 * tiles : 4.0 + 0.18 * tiles);
+    four = t4 < t8;
+    return fmin(t4, t8);
+}
+
 // Rough times in microseconds of a linear with its row kernels, fitted to both forms measured on the four linears of
-// blocks 1024 to 14336 wide at 65 to 512 rows (468 points; the choice is then never worse than 7 % and 0.1 % on average).
-// 64 rows per workgroup: workgroups of one or two panels, one to a compute unit, in rounds of 256 that each walk the K/64
-// tiles (3.4 us + 0.095 per tile with one panel, 5 us + 0.123 with two), 14 us for the row kernels in front.  All rows go
-// in one launch: charged by 64 rows, as when each 64 were a launch, narrow outputs went to the blocks too early (1024 x
-// 1024 at 320 rows: 24 us in this form, 36 in blocks).
+// blocks 1024 to 14336 wide at 65 to 512 rows (468 points; the choice is then never worse than 5 % and 0.05 % on average).
+// 64 rows per workgroup: see above, 14 us for the row kernels in front.  All rows go in one launch: charged by 64 rows, as
+// when each 64 were a launch, narrow outputs went to the blocks too early (1024 x 1024 at 320 rows: 24 us in this form, 36 in
+// blocks).
 // Output blocks: a 256 x 256 block walks K/64 stages of about 0.7 us
 // (0.45 us for the 256 x 128 blocks that ps_gemm_lds takes when the call has at most 128 rows or at most 128
 // blocks, whose stages are shared out if there are few of them: 8 us more for adding up), 256 blocks at a time, never
-// faster than the weights stream at 4 TB/s, behind about 35 us of row and digit kernels that are launched whatever the
+// faster than the weights stream at 4 TB/s, behind about 32 us of row and digit kernels that are launched whatever the
 // data.
 // PETALS_SPAN_MIDSIZE=blocks / =chunks in the environment overrides the choice (tests run both ways).
-constexpr double BLOCKS_FIXED = 35.0;
+constexpr double BLOCKS_FIXED = 32.0;
 
 bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
     if (M <= 64 || M > PS_CHUNKED_ROWS_MAX) return false;
@@ -309,9 +324,9 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
         if (!strcmp(force, "blocks")) return false;
         if (!strcmp(force, "chunks")) return true;
     }
-    const int wn = gemm_panels_per_wg(w.N) > 1 ? 2 : 1, groups = w.N / 16 / wn * ((M + 63) / 64);
-    const double bytes = (double)w.N * w.K, tiles = w.K / 64;
-    const double t_chunks = 14.0 + (groups + 255) / 256 * (wn == 2 ? 5.0 + 0.123 * tiles : 3.4 + 0.095 * tiles);
+    bool four;
+    const double bytes = (double)w.N * w.K;
+    const double t_chunks = 14.0 + gemm_rows64_us(w, M, gemm_panels_per_wg(w.N) > 1 ? 2 : 1, four);
     double blocks = (double)((w.N + 255) / 256) * ((M + 255) / 256), stage = 0.7;
     int split = 1;
     if (M <= 128 || blocks * 2 <= 256) {
@@ -350,7 +365,11 @@ hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_ti
         PS_GEMM_CASE(1, 2, 2);
     }
     if (M <= PS_CHUNKED_ROWS_MAX) {   // more than 64 rows: 64 per workgroup, see the kernel
+        bool four;
+        gemm_rows64_us(w, M, wn >= 2 ? 2 : 1, four);
+        if (wn >= 2 && four) return launch<2, 4, 1, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
         if (wn >= 2) PS_GEMM_CASE(2, 4, 1);
+        if (four) return launch<1, 4, 1, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
         PS_GEMM_CASE(1, 4, 1);
     }
 #undef PS_GEMM_CASE

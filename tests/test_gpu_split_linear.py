@@ -9,7 +9,7 @@ if not torch.cuda.is_available():
 
 import oracle  # noqa: E402
 from paper_2209_01188_amd import binding, synth  # noqa: E402
-from tests.gpu_util import DEV, midsize, to_dev, to_np  # noqa: E402
+from tests.gpu_util import DEV, build_pair, midsize, to_dev, to_np  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -41,6 +41,29 @@ def test_split_contraction(ffn, M, n_out, epilogue):
         torch.cuda.synchronize()
     assert np.array_equal(to_np(out["mask"]), dbg["mask"]) and np.array_equal(to_np(out["xq"]), dbg["xq"])
     assert np.array_equal(to_np(out["sx"]).view(np.uint32), dbg["sx"].view(np.uint32))
+    assert np.array_equal(to_np(out["acc"]), dbg["acc"])
+    assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
+    gsp.close()
+    osp.destroy()
+
+
+# 64 rows per workgroup with four waves (more than 256 workgroups, both panel counts) and with eight (the first of each):
+# ragged rows and k-tile counts below, at and above the waves, outlier columns in the last tile
+@pytest.mark.parametrize("ffn,hidden,nh", [(7232, 192, 3), (3136, 320, 5)])
+@pytest.mark.parametrize("M", [33, 64, 65, 130, 200, 500])
+def test_four_waves_per_workgroup(ffn, hidden, nh, M):
+    cfg = synth.SpanConfig("waves", 1, hidden, nh, 1, M, 1, 1, (20.0, 40.0), 3, ffn=ffn)
+    osp, gsp, params = build_pair(cfg, max_rows=M)
+    r = np.random.default_rng(M + ffn)
+    X = np.clip(r.standard_normal((M, hidden)) * 2, -5.9, 5.9)
+    X[r.integers(0, M, 20), r.choice(hidden, 20, replace=False)] = 9.0
+    X[M - 1, hidden - 1] = -40.0
+    X = X.astype(np.float16)
+    wq, sw = osp.get_weight(0, 2)
+    Y, dbg = oracle.linear(X, wq, sw, params[0]["b_up"], 6.0, 1, want_debug=True)
+    with midsize("chunks"):
+        out = gsp.debug_linear(0, 2, to_dev(X), 1)
+        torch.cuda.synchronize()
     assert np.array_equal(to_np(out["acc"]), dbg["acc"])
     assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
     gsp.close()
