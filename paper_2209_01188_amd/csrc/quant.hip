@@ -70,7 +70,7 @@ __global__ void k_copy_bytes(const uint8_t *__restrict__ s, uint8_t *__restrict_
 // the same order).
 static __device__ const CodeTable d_code_table = ps_make_code_table();
 
-template <int NT>
+template <int NT, bool FLAGS>
 __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *__restrict__ g,
                                                      const __half *__restrict__ b, float eps, int H,
                                                      __half *__restrict__ y, uint32_t *__restrict__ mask,
@@ -95,13 +95,14 @@ __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *
                                     *(const __half2 *)(b + k), mean, inv);
         *(__half2 *)(yr + k) = o;
         const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
-        if (flags) flag_outlier_bytes(flags, k, bits);
+        if constexpr (FLAGS) flag_outlier_bytes(flags, k, bits);
         else if (mask) flag_outlier_bits(mask, k >> 5, bits << (k & 31));
     }
 }
 
 // One workgroup per fp16 row, held in registers (H <= 16384: at most 8 pairs per thread of 1024) and so read from memory
 // once instead of three times.
+template <bool FLAGS>
 __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restrict__ x, const __half *__restrict__ g,
                                                          const __half *__restrict__ b, float eps, int H,
                                                          __half *__restrict__ y, uint32_t *__restrict__ mask,
@@ -139,7 +140,7 @@ __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restric
             const __half2 o = ln_affine(v[i], *(const __half2 *)(g + k), *(const __half2 *)(b + k), mean, inv);
             *(__half2 *)(yr + k) = o;
             const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
-            if (flags) flag_outlier_bytes(flags, k, bits);
+            if constexpr (FLAGS) flag_outlier_bytes(flags, k, bits);
             else if (mask) flag_outlier_bits(mask, k >> 5, bits << (k & 31));
         }
     }
@@ -864,7 +865,7 @@ hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float
     // always take 256 threads.
     if (H % 8 || H > 16384) return hipErrorInvalidValue;       // span and client take multiples of 64 up to 16384
     if (M >= 256 || H < 4096) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, flags, theta, st);
-    else k_layernorm_wide<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, flags, theta);
+    else (flags ? k_layernorm_wide<true> : k_layernorm_wide<false>)<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, flags, theta);
     return hipGetLastError();
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
@@ -872,8 +873,8 @@ hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b,
     // the line of ps_layernorm (measured there, on fp16 rows)
     if ((M >= 256 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
         launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, flags, theta, st);
-    else if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
-    else k_layernorm_q8<256><<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
+    else if (M <= 256 && H >= 4096) (flags ? k_layernorm_q8<1024, true> : k_layernorm_q8<1024, false>)<<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
+    else (flags ? k_layernorm_q8<256, true> : k_layernorm_q8<256, false>)<<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
     return hipGetLastError();
 }
 hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask, hipStream_t st) {
