@@ -304,17 +304,18 @@ __global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restr
     }
 }
 
-constexpr int LN_ROWS_GRID = 1024;
+// Workgroups that are resident at once (256 units, waves per SIMD by the kernel's registers): a grid of 1024 with room for
+// 768 ran the last 256 alone.
+constexpr int LN_ROWS_GRID[4] = {256 * 5, 256 * 3, 256 * 4, 256 * 3};   // PER = 1, 2, 4, 8
 
 template <bool Q8>
 void launch_layernorm_rows(const __half *x, const QuantIn &qin, const __half *g, const __half *b, float eps, int M, int H,
                            __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
-    const int grid = M < LN_ROWS_GRID ? M : LN_ROWS_GRID;
+    const int v = H <= 2048 ? 0 : H <= 4096 ? 1 : H <= 8192 ? 2 : 3;
+    const int grid = M < LN_ROWS_GRID[v] ? M : LN_ROWS_GRID[v];
     const uint32_t tb = ps_theta_to_bits(theta);
-    if (H <= 2048) k_layernorm_rows<1, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
-    else if (H <= 4096) k_layernorm_rows<2, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
-    else if (H <= 8192) k_layernorm_rows<4, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
-    else k_layernorm_rows<8, Q8><<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
+    auto kern = v == 0 ? k_layernorm_rows<1, Q8> : v == 1 ? k_layernorm_rows<2, Q8> : v == 2 ? k_layernorm_rows<4, Q8> : k_layernorm_rows<8, Q8>;
+    kern<<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
 }
 
 // -------------------------------------------------- many rows: mask, then quantize
