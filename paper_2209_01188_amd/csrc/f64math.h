@@ -39,14 +39,32 @@ __device__ __forceinline__ double exp_f64(double x) {
     const double h = 1.0 + rh, l = fma(n, -0x1.473de6af278edp-34, (1.0 - h) + rh);
     return __builtin_amdgcn_ldexp(h + fma(r * r, q, l), (int)(unsigned)__builtin_bit_cast(unsigned long long, t));
 }
-// tanh-form GeLU in fp64: 0.5 v (1 + tanh u) == v / (1 + exp(-2u)); the quotient from the reciprocal instruction, two
-// Newton steps and one correction by the remainder
+// tanh-form GeLU in fp64: 0.5 v (1 + tanh u) == v / (1 + exp(-2u)), in some 30 instructions of its own (on exp_f64 41; a
+// prefill call's up linear spends a fifth of its time on them): -2 u / ln 2 straight from v (-1.5957... / ln 2 as a sum of two
+// numbers, and that times 0.044715), 2^y as 2^n 2^f with the degree-10 interpolation of (2^f - 1) / f in Chebyshev points, the quotient from the
+// reciprocal instruction, one cubic step and one correction by the remainder.  No larger an error than with exp_f64 (both
+// have that of the argument's rounding).  NaN gets lost in the clamps and comes back in through v in the remainder;
+// +infinity is kept out of the quotient, where its remainder would be NaN, and comes back in there too.
 __device__ __forceinline__ double gelu_tanh(double v) {
-    const double u = 0.7978845608028654 * (v + 0.044715 * v * v * v);
-    const double d = 1.0 + exp_f64(fmin(-2.0 * u, 709.0));           // a NaN comes back in through v
-    double y = __builtin_amdgcn_rcp(d);
-    y = fma(fma(-d, y, 1.0), y, y);
-    y = fma(fma(-d, y, 1.0), y, y);
-    const double q = v * y;
-    return q == (double)INFINITY ? q : fma(fma(-d, q, v), y, q);     // GeLU(+infinity): there the remainder would be NaN
+    constexpr double MAGIC = 6755399441055744.0;
+    const double t = v * v;
+    const double y = fmin(fmax(fma(v, fma(t, -0x1.a5a7cf7572a98p-4, -0x1.26aec21bce75ap+1), v * 0x1.85892a664356cp-53), -1100.0), 1000.0);
+    const double k = y + MAGIC, f = y - (k - MAGIC);
+    double q = 0x1.e9d3fe3952179p-32;
+    q = fma(q, f, 0x1.e6063f7217bc6p-28);
+    q = fma(q, f, 0x1.b524fae627834p-24);
+    q = fma(q, f, 0x1.62bfd47773353p-20);
+    q = fma(q, f, 0x1.ffcbfc670dcd4p-17);
+    q = fma(q, f, 0x1.430913096fd9fp-13);
+    q = fma(q, f, 0x1.5d87fe78a5276p-10);
+    q = fma(q, f, 0x1.3b2ab6fba1ddap-7);
+    q = fma(q, f, 0x1.c6b08d704a0c2p-5);
+    q = fma(q, f, 0x1.ebfbdff82c598p-3);
+    q = fma(q, f, 0x1.62e42fefa39efp-1);
+    const double d = 1.0 + __builtin_amdgcn_ldexp(fma(q, f, 1.0), (int)(unsigned)__builtin_bit_cast(unsigned long long, k));
+    double r = __builtin_amdgcn_rcp(d);
+    const double h = fma(-d, r, 1.0);
+    r = fma(r, fma(h, h, h), r);
+    const double g = fmin(v, 1e300) * r;
+    return fma(fma(-d, g, v), r, g);
 }

@@ -25,7 +25,7 @@ static double rcp_estimate(double v) { return rough(1 / (ld)v); }
 #define __builtin_amdgcn_rsq rsq_estimate
 #define __builtin_amdgcn_rcp rcp_estimate
 #define __builtin_amdgcn_ldexp ldexp
-using std::fma; using std::fmin;
+using std::fma; using std::fmin; using std::fmax;
 #include "f64math.h"
 static double ulps(double got, ld want) { int e; frexpl(want, &e); return (double)fabsl(((ld)got - want) / ldexpl(1, e - 53)); }
 static ld gelu_exact(double v) { const ld u = 0.7978845608028654L * (v + 0.044715L * v * v * v); return v / (1 + expl(-2 * u)); }
