@@ -44,3 +44,30 @@ __device__ __forceinline__ bool digit_scale(float sw, float &a, int &E, int &m) 
     m = (int)rintf(ldexpf(a, 10 - E));
     return true;
 }
+
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+// The remainders of 16 codes of one output row: r = Wd / u - m code with Wd = fp16(fp32(code a)), exact in fp16: |r| <= 127
+// in units of u, and adding 1536 u leaves r in the low byte.  For a <= 515 (no Wd overflows); mu = m u = fp16(a).
+// Bytes become floats as code + 128, which the multiply-add takes off again with the one rounding of the product itself.
+__device__ __forceinline__ v4i digit_remainders(const v4i &codes, float a, _Float16 mu, _Float16 magic) {
+    const float a128 = -128.0f * a;
+    v4i out;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const uint32_t b = (uint32_t)codes[q] ^ 0x80808080u;
+        uint32_t t[2];
+#pragma unroll
+        for (int p = 0; p < 2; p++) {
+            const float f0 = (float)((b >> (16 * p)) & 255u), f1 = (float)((b >> (16 * p + 8)) & 255u);
+            float w0 = fmaf(f0, a, a128), w1 = fmaf(f1, a, a128);
+            asm("" : "+v"(w0), "+v"(w1));      // two roundings, fp32 and fp16, as everywhere
+            const uint32_t biased = __builtin_amdgcn_perm(0x64646464u, b, p ? 0x04030402u : 0x04010400u);    // 1024 + code + 128
+            const v2h c = *(const v2h *)&biased - (v2h){(_Float16)1152.0f, (_Float16)1152.0f}, wd = {(_Float16)w0, (_Float16)w1};
+            v2h r = __builtin_elementwise_fma(c, (v2h){(_Float16)-mu, (_Float16)-mu}, wd);
+            r += (v2h){magic, magic};
+            t[p] = *(const uint32_t *)&r;
+        }
+        out[q] = (int)__builtin_amdgcn_perm(t[1], t[0], 0x06040200);
+    }
+    return out;
+}

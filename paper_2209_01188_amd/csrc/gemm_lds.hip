@@ -37,145 +37,184 @@ constexpr int PS_KSPLIT_MAX = 8;   // workgroups that share one output block's c
 // ---------------------------------------------------------------------------------------------
 // outlier column list and fp16 gathers (only do work when the call has > PS_EXACT_OUTLIERS)
 
-// Digit tiles of the outlier columns, in the int8 operand order (16 rows x 64 compacted columns = 1024 bytes,
-// lane l owns row l%16 and columns (l/16)*16 .. +16).  One wave per tile; the grid is fixed and strides over the
-// tiles the call actually has, U tiles at a time: all list entries first, then all sources, then the stores.
+// Digit tiles of the outlier columns, in the int8 operand order (16 rows x 64 compacted columns = 1024 bytes, lane l owns row
+// l%16 and columns (l/16)*16 .. +16), one wave per tile or run of tiles.
 //
-// Activations: digit j of token tile mt, column tile ct at ((j * MTT + mt) * CT + ct) * 1024.  All
-// PS_X_DIGITS digit planes are written; count[1] receives the number of planes that hold anything (at
-// least 4), which is what the product walks.
-template <int U>
-__device__ __forceinline__ void limb_x_tiles(const __half *__restrict__ X, int M, int K, int *__restrict__ count,
-                                             const int *__restrict__ list, int8_t *__restrict__ xl, int n_out,
-                                             int bid, int nblk) {
-    const int CT = (n_out + 63) >> 6, MTT = (M + 15) >> 4, lane = threadIdx.x & 63, total = MTT * CT;
-    int need = 0;
-    for (int item0 = bid; item0 < total; item0 += nblk * U) {
-        int4 idx4[U][4];
-        int tt[U];
+// Activations: digit j of token tile mt, column tile ct at ((j * MTT + mt) * CT + ct) * 1024.  All PS_X_DIGITS digit planes
+// are written; count[1] receives the number of planes that hold anything (at least 4), which is what the product walks.
+// Weights: digit 0 (the int8 codes) of panel nt, column tile ct at ((nt) * CT + ct) * 1024, digit 1 (the remainders) at
+// ((NT + nt) * CT + ct) * 1024.
+__device__ __forceinline__ void store_x_digits(__half (&x)[16], bool live, int8_t *__restrict__ xl, size_t plane, size_t tile, int &need) {
+    const int lane = threadIdx.x & 63;
+    bool big = false;
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int item = min(item0 + u * nblk, total - 1);
-            const int mt = item / CT, ct = item - mt * CT;
-            tt[u] = mt * 16 + (lane & 15);
-            const int4 *lp = (const int4 *)(list + ct * 64 + (lane >> 4) * 16);
+    for (int e = 0; e < 16; e++) {
+        uint32_t b = __half_as_ushort(x[e]);
+        if (!live || (b & 0x7fffu) >= 0x7c00u) b = 0;               // not a number / infinite: unspecified, stay defined
+        big |= (b & 0x7fffu) >= DIGITS_BIG;
+        x[e] = __ushort_as_half((unsigned short)b);
+    }
+    v4i dig[PS_X_DIGITS];
 #pragma unroll
-            for (int q = 0; q < 4; q++) idx4[u][q] = lp[q];
+    for (int p = 0; p < PS_X_DIGITS; p++) dig[p] = (v4i){0, 0, 0, 0};
+    if (!__any(big)) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            int p4[4];
+            digit_planes4(*(const __half(*)[4])(x + 4 * q), p4);
+#pragma unroll
+            for (int p = 0; p < 4; p++) dig[p][q] = p4[p];
         }
-        __half xv[U][16];
+    } else {                                                        // values that take more than four digits: in 64 bits
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const __half *row = X + (size_t)min(tt[u], M - 1) * K;
+        for (int e = 0; e < 16; e++) {
+            long long I = (long long)((double)__half2float(x[e]) * 16777216.0);     // exact: every fp16 value is a multiple of 2^-24
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const int id[4] = {idx4[u][q].x, idx4[u][q].y, idx4[u][q].z, idx4[u][q].w};
-#pragma unroll
-                for (int e = 0; e < 4; e++) xv[u][q * 4 + e] = row[max(id[e], 0)];       // always in bounds
+            for (int p = 0; p < PS_X_DIGITS; p++) {
+                const int d = (int)((I + 128) & 255) - 128;         // balanced digit in [-128, 127]
+                I = (I - d) >> 8;
+                dig[p][e >> 2] |= (d & 0xff) << (8 * (e & 3));
+                if (d != 0) need = max(need, p + 1);
             }
+            __builtin_amdgcn_sched_barrier(0);                      // one after the other: side by side they take 90 registers
         }
+    }
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int item = item0 + u * nblk;
-            if (item >= total) continue;                                   // wave-uniform
-            const int mt = item / CT, ct = item - mt * CT;
-            int dig[PS_X_DIGITS][4];
+    for (int p = 0; p < PS_X_DIGITS; p++) *(v4i *)(xl + ((p * plane + tile) * 64 + lane) * 16) = dig[p];
+}
+__device__ __forceinline__ void store_w_digits(const v4i &codes, float sw, int8_t *__restrict__ wd, size_t plane, size_t tile) {
+    const int lane = threadIdx.x & 63;
+    float a;
+    int E, m;
+    const bool scaled = digit_scale(sw, a, E, m);
+    v4i rem = digit_remainders(codes, a, (_Float16)a, (_Float16)ldexpf(1.5f, E));
+    if (!(sw <= 65504.0f)) {                                        // some weight of the row may overflow fp16: those count as their codes
 #pragma unroll
-            for (int j = 0; j < PS_X_DIGITS; j++)
+        for (int q = 0; q < 4; q++) {
+            rem[q] = 0;
 #pragma unroll
-                for (int q = 0; q < 4; q++) dig[j][q] = 0;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const int id[4] = {idx4[u][q].x, idx4[u][q].y, idx4[u][q].z, idx4[u][q].w};
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const bool live = tt[u] < M && id[e] >= 0;
-                    float f = live ? __half2float(xv[u][q * 4 + e]) : 0.0f;
-                    if (!(fabsf(f) <= 65504.0f)) f = 0.0f;                 // not a number / infinite: unspecified, stay defined
-                    long long I = (long long)((double)f * 16777216.0);     // exact: every fp16 value is a multiple of 2^-24
-#pragma unroll
-                    for (int j = 0; j < PS_X_DIGITS; j++) {
-                        const int d = (int)((I + 128) & 255) - 128;        // balanced digit in [-128, 127]
-                        I = (I - d) >> 8;
-                        dig[j][q] |= (d & 0xff) << (8 * e);
-                        if (d != 0) need = max(need, j + 1);
-                    }
+            for (int e = 0; e < 4; e++) {
+                const int c = (int)(int8_t)(codes[q] >> (8 * e));
+                int r = 0;
+                if (scaled) {
+                    const float v = dequant_w16(c, a);
+                    if (fabsf(v) <= 65504.0f) r = (int)ldexpf(v, 10 - E) - m * c;
                 }
-            }
-#pragma unroll
-            for (int j = 0; j < PS_X_DIGITS; j++) {
-                const v4i o = {dig[j][0], dig[j][1], dig[j][2], dig[j][3]};
-                *(v4i *)(xl + ((((size_t)j * MTT + mt) * CT + ct) * 64 + lane) * 16) = o;
+                rem[q] |= (min(max(r, -128), 127) & 0xff) << (8 * e);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
-    if (need > 4) atomicMax(count + 1, need);
+    *(v4i *)(wd + (tile * 64 + lane) * 16) = codes;
+    *(v4i *)(wd + ((plane + tile) * 64 + lane) * 16) = rem;
 }
 
-// Weights: digit 0 (the int8 codes) of panel nt, column tile ct at ((nt) * CT + ct) * 1024, digit 1 (the
-// remainders) at ((NT + nt) * CT + ct) * 1024.
-template <int U>
-__device__ __forceinline__ void digit_w_tiles(const LinearW &w, const int *__restrict__ list, int8_t *__restrict__ wd,
-                                              int n_out, int bid, int nblk) {
-    const int CT = (n_out + 63) >> 6, NT = w.N >> 4, KT = w.K >> 6, lane = threadIdx.x & 63, row = lane & 15;
-    const int total = NT * CT;
-    const int8_t *__restrict__ wt = w.wt;
-    for (int item0 = bid; item0 < total; item0 += nblk * U) {
-        int4 idx4[U][4];
-        int nts[U];
-        float swr[U];
+// Few outlier columns among many: each column of the tile is fetched by itself.
+__device__ __forceinline__ void digit_tiles_gathered(const __half *__restrict__ X, int M, const LinearW &w, const int *__restrict__ list,
+                                                     int8_t *__restrict__ xl, int8_t *__restrict__ wd, int n_out, bool tokens,
+                                                     int bid, int nblk, int &need) {
+    const int CT = (n_out + 63) >> 6, NT = w.N >> 4, MTT = (M + 15) >> 4, KT = w.K >> 6, lane = threadIdx.x & 63, row = lane & 15;
+    const int rows = tokens ? MTT : NT;
+    for (int item = bid; item < rows * CT; item += nblk) {
+        const int rt = item / CT, ct = item - rt * CT;
+        int id[16];
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int item = min(item0 + u * nblk, total - 1);
-            const int nt = item / CT, ct = item - nt * CT;
-            nts[u] = nt;
-            const int4 *lp = (const int4 *)(list + ct * 64 + (lane >> 4) * 16);
+        for (int q = 0; q < 4; q++) *(int4 *)(id + 4 * q) = ((const int4 *)(list + ct * 64 + (lane >> 4) * 16))[q];
+        if (tokens) {
+            const int t = rt * 16 + row;
+            const __half *xr = X + (size_t)min(t, M - 1) * w.K;
+            __half x[16];
 #pragma unroll
-            for (int q = 0; q < 4; q++) idx4[u][q] = lp[q];
-            swr[u] = w.sw[nt * 16 + row];
+            for (int e = 0; e < 16; e++) x[e] = xr[max(id[e], 0)];                  // always in bounds
+#pragma unroll
+            for (int e = 0; e < 16; e++)
+                if (id[e] < 0) x[e] = __ushort_as_half(0);
+            store_x_digits(x, t < M, xl, (size_t)MTT * CT, (size_t)rt * CT + ct, need);
+        } else {
+            int c[16];
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                const int k = max(id[e], 0);
+                c[e] = w.wt[((size_t)rt * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + row) * 16 + (k & 15)];
+            }
+            v4i codes;
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                codes[q] = pack4(id[4 * q] < 0 ? 0 : c[4 * q], id[4 * q + 1] < 0 ? 0 : c[4 * q + 1], id[4 * q + 2] < 0 ? 0 : c[4 * q + 2], id[4 * q + 3] < 0 ? 0 : c[4 * q + 3]);
+            store_w_digits(codes, w.sw[rt * 16 + row], wd, (size_t)NT * CT, (size_t)rt * CT + ct);
         }
-        int code[U][16];
+    }
+}
+
+// Many: a wave makes up to DT_TILES consecutive tiles of one row tile at a time.  It reads the source columns as they lie (a
+// lane 16 columns of a row, DT_AHEAD k-tiles at once: with one it waits for each in turn) and drops the outlier ones into its
+// piece of LDS in the order of the tiles.  12 k of 14336 and 35 k of 57344 columns at 4096 rows: 1.22 ms for both linears, 4 GB;
+// column by column with 64-bit digit arithmetic per element 1.70.  From one column in four on: with few of them most of what
+// is read would be dropped (200 rows, 400 of 32768 columns: a call of 460 us takes 689).
+constexpr int DT_TILES = 4, DT_AHEAD = 8;
+
+// Rows of type T (int8 codes in tiles, fp16 row-major): the outlier columns of ranks [r0, r0 + 64 DT_TILES) into
+// st[tile][lane][16], zero where there is none.  load(kt, v): this lane's 16 columns of k-tile kt.
+template <typename T, typename LOAD>
+__device__ __forceinline__ void compact_columns(const uint64_t *__restrict__ mask64, const int *__restrict__ list, int n_out, int r0,
+                                                T *__restrict__ st, LOAD load) {
+    const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
+    const int k0 = list[r0], kt1 = list[min(n_out, r0 + 64 * DT_TILES) - 1] >> 6;   // uniform; ascending
 #pragma unroll
-        for (int u = 0; u < U; u++) {
+    for (int i = 0; i < DT_TILES * (int)sizeof(T); i++) ((v4i *)st)[i * 64 + lane] = (v4i){0, 0, 0, 0};
+    int base = -__popcll(mask64[k0 >> 6] & ((1ull << (k0 & 63)) - 1));              // rank of the k-tile's first outlier, from r0
+    for (int kt = k0 >> 6; kt <= kt1; kt += DT_AHEAD) {
+        uint64_t bits[DT_AHEAD];
+        T v[DT_AHEAD][16];
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const int id[4] = {idx4[u][q].x, idx4[u][q].y, idx4[u][q].z, idx4[u][q].w};
+        for (int u = 0; u < DT_AHEAD; u++) {
+            bits[u] = kt + u <= kt1 ? mask64[kt + u] : 0;
+            load(min(kt + u, kt1), v[u]);
+        }
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const int k = max(id[e], 0);
-                    const int c = wt[((size_t)nts[u] * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + row) * 16 + (k & 15)];
-                    code[u][q * 4 + e] = id[e] >= 0 ? c : 0;
+        for (int u = 0; u < DT_AHEAD; u++) {
+            const uint32_t mine = (uint32_t)(bits[u] >> (16 * g)) & 0xffffu;
+            int pos = base + __popcll(bits[u] & ((1ull << (16 * g)) - 1));
+#pragma unroll
+            for (int e = 0; e < 16; e++) {
+                if ((mine >> e) & 1u) {
+                    if ((uint32_t)pos < 64u * DT_TILES) st[((pos >> 6) * 64 + row + 16 * ((pos >> 4) & 3)) * 16 + (pos & 15)] = v[u][e];
+                    pos++;
                 }
             }
+            base += __popcll(bits[u]);
         }
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int item = item0 + u * nblk;
-            if (item >= total) continue;                                   // wave-uniform
-            const int ct = item - nts[u] * CT;
-            float a;
-            int E, m;
-            const bool scaled = digit_scale(swr[u], a, E, m);
-            v4i oc, orr;
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                int pc = 0, pr = 0;
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const int c = code[u][q * 4 + e];
-                    int r = 0;
-                    if (scaled) {
-                        const float v = dequant_w16(c, a);                 // the fp16 weight, as a float
-                        if (fabsf(v) <= 65504.0f) r = (int)ldexpf(v, 10 - E) - m * c;   // exact: v is a multiple of 2^(E-10)
-                    }
-                    r = min(max(r, -128), 127);                            // |r| <= 127 always holds; stay defined regardless
-                    pc |= (c & 0xff) << (8 * e);
-                    pr |= (r & 0xff) << (8 * e);
-                }
-                oc[q] = pc;
-                orr[q] = pr;
+    }
+}
+
+__device__ __forceinline__ void digit_tiles_compacted(const __half *__restrict__ X, int M, const LinearW &w, const uint64_t *__restrict__ mask64,
+                                                      const int *__restrict__ list, int8_t *__restrict__ xl, int8_t *__restrict__ wd,
+                                                      int n_out, bool tokens, __half *st, int bid, int nblk, int &need) {
+    const int CT = (n_out + 63) >> 6, NT = w.N >> 4, MTT = (M + 15) >> 4, KT = w.K >> 6, K = w.K, lane = threadIdx.x & 63;
+    const int ranges = (CT + DT_TILES - 1) / DT_TILES, rows = tokens ? MTT : NT;
+    for (int item = bid; item < rows * ranges; item += nblk) {
+        const int rt = item / ranges, ct0 = (item - rt * ranges) * DT_TILES;
+        if (tokens) {
+            const int t = rt * 16 + (lane & 15);
+            const __half *row = X + (size_t)min(t, M - 1) * K + (lane >> 4) * 16;
+            compact_columns<__half>(mask64, list, n_out, ct0 * 64, st, [&](int kt, __half *v) {
+                *(v8h *)v = *(const v8h *)(row + (size_t)kt * 64);
+                *(v8h *)(v + 8) = *(const v8h *)(row + (size_t)kt * 64 + 8);
+            });
+            for (int j = 0; j < DT_TILES && ct0 + j < CT; j++) {
+                __half x[16];
+                *(v8h *)x = *(const v8h *)(st + (j * 64 + lane) * 16);
+                *(v8h *)(x + 8) = *(const v8h *)(st + (j * 64 + lane) * 16 + 8);
+                store_x_digits(x, t < M, xl, (size_t)MTT * CT, (size_t)rt * CT + ct0 + j, need);
             }
-            *(v4i *)(wd + (((size_t)nts[u] * CT + ct) * 64 + lane) * 16) = oc;
-            *(v4i *)(wd + (((size_t)(NT + nts[u]) * CT + ct) * 64 + lane) * 16) = orr;
+        } else {
+            const int8_t *panel = w.wt + (size_t)rt * KT * 1024 + lane * 16;
+            int8_t *st8 = (int8_t *)st;
+            compact_columns<int8_t>(mask64, list, n_out, ct0 * 64, st8, [&](int kt, int8_t *v) {
+                *(v4i *)v = *(const v4i *)(panel + (size_t)kt * 1024);
+            });
+            for (int j = 0; j < DT_TILES && ct0 + j < CT; j++)
+                store_w_digits(*(const v4i *)(st8 + (j * 64 + lane) * 16), w.sw[rt * 16 + (lane & 15)], wd, (size_t)NT * CT, (size_t)rt * CT + ct0 + j);
         }
     }
 }
@@ -202,19 +241,22 @@ struct GemmArgs {
     float *f32_out;           // plain fp16 product: [M, N] fp32 result
 };
 
-// Both kinds of digit tiles in one launch (a launch costs as much as the work of a call with few tiles): the first
-// NBX waves cut the activations, the rest the weights.  Workgroups of four waves, which share nothing: a launch that
-// finds nothing to do costs by its number of workgroups.  Does nothing unless the call has more outlier columns
-// than the fp64 path takes.
-template <int U>
-__global__ void __launch_bounds__(256) k_digit_tiles(const __half *__restrict__ X, int M, LinearW w, int *__restrict__ count,
-                                                      const int *__restrict__ list, int8_t *__restrict__ xl,
-                                                      int8_t *__restrict__ wd, int NBX) {
+// Both kinds of digit tiles in one launch (a launch costs as much as the work of a call with few tiles): the first NBX waves
+// cut the activations, the rest the weights.  Workgroups of four waves, which share nothing: a launch that finds nothing to
+// do costs by its number of workgroups.  Does nothing unless the call has more outlier columns than the fp64 path takes.
+__global__ void __launch_bounds__(256) k_digit_tiles(const __half *__restrict__ X, int M, LinearW w, const uint32_t *__restrict__ mask,
+                                                      int *__restrict__ count, const int *__restrict__ list,
+                                                      int8_t *__restrict__ xl, int8_t *__restrict__ wd, int NBX) {
+    __shared__ __align__(16) __half stage[4][DT_TILES * 64 * 16];
     const int n_out = count[0];
     if (n_out <= PS_EXACT_OUTLIERS) return;
-    const int wv = (int)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (wv < NBX) limb_x_tiles<U>(X, M, w.K, count, list, xl, n_out, wv, NBX);
-    else digit_w_tiles<U>(w, list, wd, n_out, wv - NBX, (int)gridDim.x * 4 - NBX);
+    const int wave = threadIdx.x >> 6, wv = (int)blockIdx.x * 4 + wave;
+    const bool tokens = wv < NBX;
+    const int bid = tokens ? wv : wv - NBX, nblk = tokens ? NBX : (int)gridDim.x * 4 - NBX;
+    int need = 0;
+    if (n_out >= w.K >> 2) digit_tiles_compacted(X, M, w, (const uint64_t *)mask, list, xl, wd, n_out, tokens, stage[wave], bid, nblk, need);
+    else digit_tiles_gathered(X, M, w, list, xl, wd, n_out, tokens, bid, nblk, need);
+    if (need > 4) atomicMax(count + 1, need);
 }
 
 enum { GEMM_INT8 = 0, GEMM_F16 = 1, GEMM_DIGITS = 2 };
@@ -822,7 +864,8 @@ hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t 
                        hipStream_t st) {
     // The outlier-heavy case first (every kernel of it returns at once when the call has few outlier columns):
     // digit tiles of the activations and of the dequantized weights, the digit products.
-    k_digit_tiles<2><<<(2048 + 4096) / 4, 256, 0, st>>>(X, M, w, (int *)os.count, mo.list, mo.xl, mo.wd, 2048);
+    // (768 workgroups: those that are resident at once; twice as many cost a call that has nothing to cut 0.3 us more)
+    k_digit_tiles<<<768, 256, 0, st>>>(X, M, w, mask, (int *)os.count, mo.list, mo.xl, mo.wd, 1024);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     GemmArgs gd = gemm_args(mo.wd, mo.xl, 0, M, w.N);

@@ -96,3 +96,30 @@ def test_the_faster_form_is_chosen(H, nh, which, M):
                 times[form] = min(times[form], a.elapsed_time(b) / 10)
     span.close()
     assert times[None] <= 1.2 * min(times["chunks"], times["blocks"]), times
+
+
+# Digit tiles of the outlier columns: column by column below one in four, in runs from there on (the line on either side, all
+# but one, all); values of five digits in one tile, rows of the last token tile missing
+@pytest.mark.parametrize("n_out", [271, 272, 1000, 1087, 1088])
+@pytest.mark.parametrize("big", [False, True])
+def test_digit_tiles_of_many_columns(n_out, big):
+    M, hidden, nh = 203, 1088, 17
+    cfg = synth.SpanConfig("tiles", 1, hidden, nh, 1, M, 1, 1, (20.0, 40.0), 5, ffn=192)
+    osp, gsp, params = build_pair(cfg, max_rows=M)
+    r = np.random.default_rng(n_out)
+    X = np.clip(r.standard_normal((M, hidden)), -5.9, 5.9) * 2.0 ** r.integers(-18, 1, (M, hidden))
+    cols = r.choice(hidden, n_out, replace=False)
+    X[r.integers(0, M, n_out), cols] = r.uniform(6.0, 127.0, n_out)
+    if big:
+        X[M - 1, cols[-1]] = -3000.0
+    X = X.astype(np.float16)
+    wq, sw = osp.get_weight(0, 1)
+    resid = r.standard_normal((M, hidden)).astype(np.float16)
+    Y, dbg = oracle.linear(X, wq, sw, params[0]["b_dense"], 6.0, 2, resid, want_debug=True)
+    assert dbg["mask"].sum() == n_out
+    with midsize("blocks"):
+        out = gsp.debug_linear(0, 1, to_dev(X), 2, to_dev(resid))
+        torch.cuda.synchronize()
+    assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
+    gsp.close()
+    osp.destroy()
