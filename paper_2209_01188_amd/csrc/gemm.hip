@@ -342,16 +342,29 @@ hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_ti
                    const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, const DigitCall &dc, hipStream_t st) {
     const int panels = w.N / 16, wn = gemm_panels_per_wg(w.N);
 #define PS_GEMM_CASE(WN_, MT_, UK_) return launch<WN_, MT_, UK_>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st)
+    // Up to 32 rows: four waves per workgroup, two workgroups to a compute unit, where eight (one to a unit by their
+    // registers) would leave half of the last round's units idle (2, 3 or 4 panels per workgroup, QKV of blocks 2048 to 8192
+    // wide at 24 rows 19.0 -> 17.5, 28.4 -> 26.4, 56.2 -> 52.1 us); not where that round is fuller (43008 x 14336: 123
+    // against 139).
+    const int wgs = panels / wn, rest = wgs % 256;
+    const bool four32 = wgs > 256 && rest > 0 && rest <= 128;
+#define PS_GEMM_CASE4(WN_, MT_, UK_) \
+    do { \
+        if (four32) return launch<WN_, MT_, UK_, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st); \
+        PS_GEMM_CASE(WN_, MT_, UK_); \
+    } while (0)
     if (M <= 16) {
         // one panel per workgroup (narrow outputs): 16 waves split the k-tiles, twice the weight bytes in flight per
         // compute unit (C3, 8 rows: down 2.85 -> 3.2 TB/s, dense 1.5 -> 1.65 TB/s; with 2 panels 16 waves are slower)
+        // - eight where a second round of 16 waves would be mostly empty (8 rows: 5120 x 5120 21.6 -> 18.8 us, 6144 x 24576 51.1 -> 49.0)
+        if (wn == 1 && w.K >= 4096 && four32) return launch<1, 1, 2, 8>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
         if (wn == 1 && w.K >= 4096) return launch<1, 1, 2, 16>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
         // small matrices (C3: 50-67 MB, 13-16 us per launch) do better with two workgroups per compute unit and
         // short chunks (up 3.5 -> 3.8, QKV 3.2 -> 3.25 TB/s); large ones with four panels per workgroup
         if (wn == 4 && panels / 4 < 448 && (size_t)w.N * w.K <= ((size_t)1 << 27)) PS_GEMM_CASE(2, 1, 2);
-        if (wn == 4) PS_GEMM_CASE(4, 1, 2);
+        if (wn == 4) PS_GEMM_CASE4(4, 1, 2);
         if (wn == 2) PS_GEMM_CASE(2, 1, 1);
-        PS_GEMM_CASE(1, 1, 4);
+        PS_GEMM_CASE4(1, 1, 4);
     }
     if (dc.xd) {
         if (!ps_gemm_digits_applies(w.N, w.K, M)) return hipErrorInvalidValue;
@@ -360,9 +373,9 @@ hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_ti
         return launch<2, 2, 2, 8, true>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
     }
     if (M <= 32) {
-        if (wn == 4) PS_GEMM_CASE(4, 2, 1);
-        if (wn == 2) PS_GEMM_CASE(2, 2, 2);
-        PS_GEMM_CASE(1, 2, 2);
+        if (wn == 4) PS_GEMM_CASE4(4, 2, 1);
+        if (wn == 2) PS_GEMM_CASE4(2, 2, 2);
+        PS_GEMM_CASE4(1, 2, 2);
     }
     if (M <= PS_CHUNKED_ROWS_MAX) {   // more than 64 rows: 64 per workgroup, see the kernel
         bool four;
@@ -372,6 +385,7 @@ hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_ti
         if (four) return launch<1, 4, 1, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
         PS_GEMM_CASE(1, 4, 1);
     }
+#undef PS_GEMM_CASE4
 #undef PS_GEMM_CASE
     return hipErrorInvalidValue;   // larger calls belong to ps_gemm_lds
 }

@@ -47,10 +47,11 @@ def test_split_contraction(ffn, M, n_out, epilogue):
     osp.destroy()
 
 
-# 64 rows per workgroup with four waves (more than 256 workgroups, both panel counts) and with eight (the first of each):
-# ragged rows and k-tile counts below, at and above the waves, outlier columns in the last tile
-@pytest.mark.parametrize("ffn,hidden,nh", [(7232, 192, 3), (3136, 320, 5)])
-@pytest.mark.parametrize("M", [33, 64, 65, 130, 200, 500])
+# Four waves per workgroup: 64 rows per workgroup (more than 256 workgroups, one and two panels; the smallest calls still take
+# eight) and up to 32 rows where the last of several rounds of 256 workgroups is half empty (one, two and four panels); ragged
+# rows, k-tile counts below, at and above the waves, outlier columns in the last tile
+@pytest.mark.parametrize("ffn,hidden,nh,M", [(f, h, n, M) for f, h, n in ((7232, 192, 3), (3136, 320, 5)) for M in (33, 64, 65, 130, 200, 500)] +
+                         [(f, h, n, M) for f, h, n in ((16448, 192, 3), (8256, 320, 5), (4160, 192, 3)) for M in (2, 16, 17, 32)] + [(4160, 4096, 32, 16)])
 def test_four_waves_per_workgroup(ffn, hidden, nh, M):
     cfg = synth.SpanConfig("waves", 1, hidden, nh, 1, M, 1, 1, (20.0, 40.0), 3, ffn=ffn)
     osp, gsp, params = build_pair(cfg, max_rows=M)
