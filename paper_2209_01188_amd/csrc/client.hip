@@ -117,8 +117,8 @@ constexpr uint32_t LMD_BIG = 0x57f8;       // fp16 bits of 127.5
 constexpr uint32_t LMD_SMALL = 0x33e0;     // fp16 bits of 0.246: below it three digits do, and lm_planes_small holds
 
 // three planes of four values below LMD_SMALL in magnitude (two words of two halves).  x * 2^24 + 2^23 + 0x408080 is
-// exact in fp32 and its low bytes are the digits plus 0x80, 0x80 and 0x40: one multiply-add straight from fp16
-// (conversions to and from integers run at a quarter of its rate), then byte permutations.
+// exact in fp32 and its low bytes are the digits plus 0x80, 0x80 and 0x40: one multiply-add straight from fp16,
+// then byte permutations.
 __device__ __forceinline__ void lm_planes_small(uint32_t w0, uint32_t w1, int (&p)[4]) {
     const uint32_t hb[4] = {w0 & 0xffffu, w0 >> 16, w1 & 0xffffu, w1 >> 16};
     uint32_t u[4];

@@ -10,8 +10,8 @@ constexpr uint32_t DIGITS_BIG = 0x57f8;    // fp16 bits of 127.5: from here on f
 // The digit planes of four values below 127.5 in magnitude, one word per plane (byte k = value k).
 // x * 256 rounded to an integer (up to a lower half in [-32896, 32639], which is what two balanced digits hold: the
 // addend moves the rounding boundary by a little over 2^-9) carries the upper two digits, the exact rest times 2^24
-// the lower two; both sit, plus 0x8080, in the low bytes of an fp32 sum.  Multiply-adds run at the full rate;
-// conversions to and from integers at a quarter of it.
+// the lower two; both sit, plus 0x8080, in the low bytes of an fp32 sum.  (Fewer instructions than by conversion to integers and
+// shifts; each runs at the same rate, conversions included.)
 __device__ __forceinline__ void digit_planes4(const __half (&x)[4], int (&p)[4]) {
     constexpr float M = 8388608.0f + 0x8080;
     uint32_t t[4], u[4];

@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restr
                                                         uint32_t *__restrict__ mask, uint8_t *__restrict__ cols, uint32_t theta_bits) {
     constexpr int NT = 256;
     // narrow rows: gain and bias stay in registers as fp64 over the rows of the workgroup, and so do a row's values over
-    // its three passes (conversions to fp64 take eight times as long as the operations on the values)
+    // its three passes (two conversions each, where a pass has one to three operations on a value)
     constexpr bool WIDE_REGS = PER <= 2;
     constexpr int NE = WIDE_REGS ? PER * 8 : 1;
     double gd[NE], bd[NE];
