@@ -10,11 +10,15 @@ struct OutlierPrep {
     double *wd64, *x64;
     int *full_list;
 };
-// waves of work: one per 16 output rows, one per 16 tokens
-__host__ __device__ inline int outlier_prep_items(const OutlierPrep &p, int M) { return p.count ? p.w.N / 16 + (M + 15) / 16 : 0; }
+// waves of work: one per 16 output rows and one per 16 tokens, and no fewer than the list has groups of 1024 columns (an
+// output of 64 rows has four panels, its 65536 columns 64 groups)
+__host__ __device__ inline int outlier_prep_items(const OutlierPrep &p, int M) {
+    const int gathers = p.w.N / 16 + (M + 15) / 16, groups = (p.w.K + 1023) / 1024;
+    return !p.count ? 0 : gathers > groups ? gathers : groups;
+}
 
 // Counts the outlier columns and, when there are at most PS_EXACT_OUTLIERS, gathers their
-// dequantized weights (items [0, N/16)) and activations (the rest) as doubles in matrix-instruction lane order.
+// dequantized weights (items [0, N/16)) and activations (the next ceil(M/16)) as doubles in matrix-instruction lane order.
 // Every wave rebuilds the short column list from the bit mask itself.  list: PS_EXACT_OUTLIERS ints of LDS of this wave.
 __device__ __forceinline__ void outlier_prep_wave(const OutlierPrep &pr, const uint32_t *__restrict__ mask, const uint8_t *__restrict__ flags,
                                                   const __half *__restrict__ X, int M, int item, int *list) {
@@ -63,7 +67,7 @@ __device__ __forceinline__ void outlier_prep_wave(const OutlierPrep &pr, const u
             for (int i = total + lane; i < ((total + 63) & ~63); i += 64) pr.full_list[i] = -1;
         return;
     }
-    if (total == 0) return;
+    if (total == 0 || item >= (w.N >> 4) + ((M + 15) >> 4)) return;
     int base = 0;
     for (; used; used &= used - 1) {
         const int c = (__ffsll((unsigned long long)used) - 1) * 64 + lane;

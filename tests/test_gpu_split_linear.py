@@ -124,3 +124,34 @@ def test_digit_tiles_of_many_columns(n_out, big):
     assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
     gsp.close()
     osp.destroy()
+
+
+# Outputs so narrow that the preparation has fewer waves of gathers than the column list has groups of 1024 (12, 37 and 61 for
+# 64), and just as many as it needs (65)
+@pytest.mark.parametrize("hidden,nh,M", [(64, 1, 128), (64, 1, 513), (896, 7, 65), (960, 15, 65)])
+@pytest.mark.parametrize("n_out", [65, 700, 20000])
+def test_column_list_of_wide_inputs_and_narrow_outputs(hidden, nh, M, n_out):
+    F = 65536
+    sp = binding.Span(1, hidden, nh, F, M, 1e-5, 6.0, DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M)
+    p = dict(w_qkv=torch.zeros((3 * hidden, hidden), device=DEV), w_dense=torch.zeros((hidden, hidden), device=DEV),
+             w_up=torch.zeros((F, hidden), device=DEV), w_down=torch.empty((hidden, F), device=DEV).normal_(0.0, 0.02, generator=g))
+    for n, s in (("b_qkv", 3 * hidden), ("b_dense", hidden), ("b_up", F), ("b_down", hidden), ("ln1_g", hidden), ("ln1_b", hidden), ("ln2_g", hidden), ("ln2_b", hidden)):
+        p[n] = torch.zeros(s, dtype=torch.float16, device=DEV)
+    sp.load_block(0, p)
+    r = np.random.default_rng(n_out)
+    X = np.clip(r.standard_normal((M, F), dtype=np.float32), -5.9, 5.9)
+    cols = np.unique(np.concatenate([r.choice(F - 1024, n_out - 3, replace=False), [F - 1024, F - 500, F - 1]]))   # and the last group
+    X[r.integers(0, M, len(cols)), cols] = r.uniform(6.0, 100.0, len(cols))
+    X = X.astype(np.float16)
+    with midsize("blocks"):
+        out = sp.debug_linear(0, 3, to_dev(X), 0)
+        torch.cuda.synchronize()
+    wq, sw = sp.export_weight(0, 3)
+    rows = np.unique(np.concatenate([np.arange(16), r.integers(0, hidden, 16), [hidden - 1]]))
+    Y, dbg = oracle.linear(X, to_np(wq)[rows], to_np(sw)[rows], np.zeros(len(rows), np.float16), 6.0, 0, None, want_debug=True)
+    assert dbg["mask"].sum() == len(cols)
+    assert np.array_equal(to_np(out["acc"])[:, rows], dbg["acc"])
+    assert np.array_equal(to_np(out["y"])[:, rows].view(np.uint16), Y.view(np.uint16))
+    sp.close()
