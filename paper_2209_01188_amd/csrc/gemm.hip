@@ -343,11 +343,13 @@ hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_ti
     const int panels = w.N / 16, wn = gemm_panels_per_wg(w.N);
 #define PS_GEMM_CASE(WN_, MT_, UK_) return launch<WN_, MT_, UK_>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st)
     // Up to 32 rows: four waves per workgroup, two workgroups to a compute unit, where eight (one to a unit by their
-    // registers) would leave half of the last round's units idle (2, 3 or 4 panels per workgroup, QKV of blocks 2048 to 8192
-    // wide at 24 rows 19.0 -> 17.5, 28.4 -> 26.4, 56.2 -> 52.1 us); not where that round is fuller (43008 x 14336: 123
-    // against 139).
-    const int wgs = panels / wn, rest = wgs % 256;
-    const bool four32 = wgs > 256 && rest > 0 && rest <= 128;
+    // registers) would leave at least half of the units idle in the last of an odd number of rounds of 256 (2, 3 or 4 panels per
+    // workgroup, QKV of blocks 2048 to 8192 wide at 24 rows 19.0 -> 17.5, 28.4 -> 26.4, 56.2 -> 52.1 us; 57344 x 12288 8 % less).
+    // Not where that round is fuller (43008 x 14336: 123 against 139), nor with an even number of rounds: rounds of 512 end with
+    // a nearly empty one themselves (40960 x 10240 at 8 rows 82 against 95, QKV of a 12288-wide block at 24 rows 105 against 118;
+    // only inputs of less than some 3000 columns gain there, 4 to 18 %, and no block's up or QKV linear has them).
+    const int wgs = panels / wn, rest = (wgs - 1) % 512 + 1;
+    const bool four32 = rest > 256 && rest <= 384;
 #define PS_GEMM_CASE4(WN_, MT_, UK_) \
     do { \
         if (four32) return launch<WN_, MT_, UK_, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st); \

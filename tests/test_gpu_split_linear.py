@@ -155,3 +155,36 @@ def test_column_list_of_wide_inputs_and_narrow_outputs(hidden, nh, M, n_out):
     assert np.array_equal(to_np(out["acc"])[:, rows], dbg["acc"])
     assert np.array_equal(to_np(out["y"])[:, rows].view(np.uint16), Y.view(np.uint16))
     sp.close()
+
+
+# Up to 32 rows, outputs of 513 to 640 workgroups of four panels: with a little larger output each takes the other form, which
+# must not be the faster one.
+@pytest.mark.parametrize("H,nh,small,large,M", [(10240, 80, 40960, 41984, 8), (12288, 96, 36864, 41984, 24)])
+def test_a_smaller_output_is_no_slower(H, nh, small, large, M):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(H)
+    times = []
+    for F in (small, large):
+        span = binding.Span(1, H, nh, F, M, device=DEV)
+        p = dict(w_qkv=torch.zeros((3 * H, H), device=DEV), w_dense=torch.zeros((H, H), device=DEV), w_down=torch.zeros((H, F), device=DEV),
+                 w_up=torch.empty((F, H), device=DEV).normal_(0.0, 0.02, generator=g))
+        for n, s in (("b_qkv", 3 * H), ("b_dense", H), ("b_up", F), ("b_down", H), ("ln1_g", H), ("ln1_b", H), ("ln2_g", H), ("ln2_b", H)):
+            p[n] = torch.zeros(s, dtype=torch.float16, device=DEV)
+        span.load_block(0, p)
+        del p
+        X = torch.empty((M, H), device=DEV).normal_(generator=g).clamp_(-5.0, 5.0).half()
+        y = torch.empty((M, F), dtype=torch.float16, device=DEV)
+        best = 1e9
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda._sleep(1000000)
+            a.record()
+            for _ in range(10):
+                binding.petals_debug_linear(span.handle, 0, 2, X, 0, None, None, None, None, None, y)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) / 10)
+        times.append(best)
+        span.close()
+        torch.cuda.empty_cache()
+    assert times[0] <= 1.03 * times[1], times
