@@ -109,112 +109,97 @@ __device__ __forceinline__ void store_w_digits(const v4i &codes, float sw, int8_
     *(v4i *)(wd + ((plane + tile) * 64 + lane) * 16) = rem;
 }
 
-// Few outlier columns among many: each column of the tile is fetched by itself.
-__device__ __forceinline__ void digit_tiles_gathered(const __half *__restrict__ X, int M, const LinearW &w, const int *__restrict__ list,
-                                                     int8_t *__restrict__ xl, int8_t *__restrict__ wd, int n_out, bool tokens,
-                                                     int bid, int nblk, int &need) {
-    const int CT = (n_out + 63) >> 6, NT = w.N >> 4, MTT = (M + 15) >> 4, KT = w.K >> 6, lane = threadIdx.x & 63, row = lane & 15;
-    const int rows = tokens ? MTT : NT;
-    for (int item = bid; item < rows * CT; item += nblk) {
-        const int rt = item / CT, ct = item - rt * CT;
+// One column at a time.  The weights always: 64 columns of a panel's codes lie within a few cache lines, which the lanes share
+// (a linear of 65 rows at half of its columns, 14336 x 57344, 4096 x 16384 and 16384 x 4096: 1007, 175 and 117 us; with the
+// codes compacted as below 1228, 201 and 141; at three quarters 1426, 231 and 144 against 1422, 240 and 150; only with nearly
+// all columns of the largest it is 1 to 4 % behind).
+__device__ __forceinline__ void weight_digits(const LinearW &w, const int *__restrict__ list, int8_t *__restrict__ wd, int n_out, int bid, int nblk) {
+    const int CT = (n_out + 63) >> 6, NT = w.N >> 4, KT = w.K >> 6, lane = threadIdx.x & 63, row = lane & 15;
+    for (int item = bid; item < NT * CT; item += nblk) {
+        const int nt = item / CT, ct = item - nt * CT;
+        int id[16], c[16];
+#pragma unroll
+        for (int q = 0; q < 4; q++) *(int4 *)(id + 4 * q) = ((const int4 *)(list + ct * 64 + (lane >> 4) * 16))[q];
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int k = max(id[e], 0);
+            c[e] = w.wt[((size_t)nt * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + row) * 16 + (k & 15)];
+        }
+        v4i codes;
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            codes[q] = pack4(id[4 * q] < 0 ? 0 : c[4 * q], id[4 * q + 1] < 0 ? 0 : c[4 * q + 1], id[4 * q + 2] < 0 ? 0 : c[4 * q + 2], id[4 * q + 3] < 0 ? 0 : c[4 * q + 3]);
+        store_w_digits(codes, w.sw[nt * 16 + row], wd, (size_t)NT * CT, (size_t)nt * CT + ct);
+    }
+}
+__device__ __forceinline__ void token_digits_gathered(const __half *__restrict__ X, int M, int K, const int *__restrict__ list,
+                                                      int8_t *__restrict__ xl, int n_out, int bid, int nblk, int &need) {
+    const int CT = (n_out + 63) >> 6, MTT = (M + 15) >> 4, lane = threadIdx.x & 63;
+    for (int item = bid; item < MTT * CT; item += nblk) {
+        const int mt = item / CT, ct = item - mt * CT, t = mt * 16 + (lane & 15);
         int id[16];
 #pragma unroll
         for (int q = 0; q < 4; q++) *(int4 *)(id + 4 * q) = ((const int4 *)(list + ct * 64 + (lane >> 4) * 16))[q];
-        if (tokens) {
-            const int t = rt * 16 + row;
-            const __half *xr = X + (size_t)min(t, M - 1) * w.K;
-            __half x[16];
+        const __half *xr = X + (size_t)min(t, M - 1) * K;
+        __half x[16];
 #pragma unroll
-            for (int e = 0; e < 16; e++) x[e] = xr[max(id[e], 0)];                  // always in bounds
+        for (int e = 0; e < 16; e++) x[e] = xr[max(id[e], 0)];                  // always in bounds
 #pragma unroll
-            for (int e = 0; e < 16; e++)
-                if (id[e] < 0) x[e] = __ushort_as_half(0);
-            store_x_digits(x, t < M, xl, (size_t)MTT * CT, (size_t)rt * CT + ct, need);
-        } else {
-            int c[16];
-#pragma unroll
-            for (int e = 0; e < 16; e++) {
-                const int k = max(id[e], 0);
-                c[e] = w.wt[((size_t)rt * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + row) * 16 + (k & 15)];
-            }
-            v4i codes;
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                codes[q] = pack4(id[4 * q] < 0 ? 0 : c[4 * q], id[4 * q + 1] < 0 ? 0 : c[4 * q + 1], id[4 * q + 2] < 0 ? 0 : c[4 * q + 2], id[4 * q + 3] < 0 ? 0 : c[4 * q + 3]);
-            store_w_digits(codes, w.sw[rt * 16 + row], wd, (size_t)NT * CT, (size_t)rt * CT + ct);
-        }
+        for (int e = 0; e < 16; e++)
+            if (id[e] < 0) x[e] = __ushort_as_half(0);
+        store_x_digits(x, t < M, xl, (size_t)MTT * CT, (size_t)mt * CT + ct, need);
     }
 }
 
-// Many: a wave makes up to DT_TILES consecutive tiles of one row tile at a time.  It reads the source columns as they lie (a
-// lane 16 columns of a row, DT_AHEAD k-tiles at once: with one it waits for each in turn) and drops the outlier ones into its
-// piece of LDS in the order of the tiles.  12 k of 14336 and 35 k of 57344 columns at 4096 rows: 1.22 ms for both linears, 4 GB;
-// column by column with 64-bit digit arithmetic per element 1.70.  From one column in four on: with few of them most of what
-// is read would be dropped (200 rows, 400 of 32768 columns: a call of 460 us takes 689).
+// Most columns: a wave makes up to DT_TILES consecutive tiles of one row tile at a time.  It reads the rows as they lie (a lane
+// 16 columns, DT_AHEAD k-tiles at once: with one it waits for each in turn) and drops the outlier columns into its piece of
+// LDS in the order of the tiles.  From four columns in seven on: there the columns of DT_TILES tiles lie within DT_AHEAD
+// k-tiles (1024 x 16384 at 8192 rows with half of the columns 974 us by column and 999 this way, with five in eight 1115 and
+// 1049; 200 rows with 400 of 32768 columns 460 and 689).
 constexpr int DT_TILES = 4, DT_AHEAD = 8;
 
-// Rows of type T (int8 codes in tiles, fp16 row-major): the outlier columns of ranks [r0, r0 + 64 DT_TILES) into
-// st[tile][lane][16], zero where there is none.  load(kt, v): this lane's 16 columns of k-tile kt.
-template <typename T, typename LOAD>
-__device__ __forceinline__ void compact_columns(const uint64_t *__restrict__ mask64, const int *__restrict__ list, int n_out, int r0,
-                                                T *__restrict__ st, LOAD load) {
-    const int lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
-    const int k0 = list[r0], kt1 = list[min(n_out, r0 + 64 * DT_TILES) - 1] >> 6;   // uniform; ascending
+__device__ __forceinline__ void token_digits_compacted(const __half *__restrict__ X, int M, int K, const uint64_t *__restrict__ mask64,
+                                                       const int *__restrict__ list, int8_t *__restrict__ xl, int n_out, __half *st,
+                                                       int bid, int nblk, int &need) {
+    const int CT = (n_out + 63) >> 6, MTT = (M + 15) >> 4, lane = threadIdx.x & 63, row = lane & 15, g = lane >> 4;
+    const int ranges = (CT + DT_TILES - 1) / DT_TILES;
+    for (int item = bid; item < MTT * ranges; item += nblk) {
+        const int mt = item / ranges, ct0 = (item - mt * ranges) * DT_TILES, t = mt * 16 + row;
+        const __half *src = X + (size_t)min(t, M - 1) * K + g * 16;
+        // the outlier columns of ranks [64 ct0, 64 (ct0 + DT_TILES)) into st[tile][lane][16], zero where there is none
+        const int k0 = list[ct0 * 64], kt1 = list[min(n_out, (ct0 + DT_TILES) * 64) - 1] >> 6;   // uniform; ascending
 #pragma unroll
-    for (int i = 0; i < DT_TILES * (int)sizeof(T); i++) ((v4i *)st)[i * 64 + lane] = (v4i){0, 0, 0, 0};
-    int base = -__popcll(mask64[k0 >> 6] & ((1ull << (k0 & 63)) - 1));              // rank of the k-tile's first outlier, from r0
-    for (int kt = k0 >> 6; kt <= kt1; kt += DT_AHEAD) {
-        uint64_t bits[DT_AHEAD];
-        T v[DT_AHEAD][16];
+        for (int i = 0; i < DT_TILES * 2; i++) ((v4i *)st)[i * 64 + lane] = (v4i){0, 0, 0, 0};
+        int base = -__popcll(mask64[k0 >> 6] & ((1ull << (k0 & 63)) - 1));          // rank of the k-tile's first outlier, from 64 ct0
+        for (int kt = k0 >> 6; kt <= kt1; kt += DT_AHEAD) {
+            uint64_t bits[DT_AHEAD];
+            __half v[DT_AHEAD][16];
 #pragma unroll
-        for (int u = 0; u < DT_AHEAD; u++) {
-            bits[u] = kt + u <= kt1 ? mask64[kt + u] : 0;
-            load(min(kt + u, kt1), v[u]);
-        }
+            for (int u = 0; u < DT_AHEAD; u++) {
+                const __half *from = src + (size_t)min(kt + u, kt1) * 64;
+                bits[u] = kt + u <= kt1 ? mask64[kt + u] : 0;
+                *(v8h *)v[u] = *(const v8h *)from;
+                *(v8h *)(v[u] + 8) = *(const v8h *)(from + 8);
+            }
 #pragma unroll
-        for (int u = 0; u < DT_AHEAD; u++) {
-            const uint32_t mine = (uint32_t)(bits[u] >> (16 * g)) & 0xffffu;
-            int pos = base + __popcll(bits[u] & ((1ull << (16 * g)) - 1));
+            for (int u = 0; u < DT_AHEAD; u++) {
+                const uint32_t mine = (uint32_t)(bits[u] >> (16 * g)) & 0xffffu;
+                int pos = base + __popcll(bits[u] & ((1ull << (16 * g)) - 1));
 #pragma unroll
-            for (int e = 0; e < 16; e++) {
-                if ((mine >> e) & 1u) {
-                    if ((uint32_t)pos < 64u * DT_TILES) st[((pos >> 6) * 64 + row + 16 * ((pos >> 4) & 3)) * 16 + (pos & 15)] = v[u][e];
-                    pos++;
+                for (int e = 0; e < 16; e++) {
+                    if ((mine >> e) & 1u) {
+                        if ((uint32_t)pos < 64u * DT_TILES) st[((pos >> 6) * 64 + row + 16 * ((pos >> 4) & 3)) * 16 + (pos & 15)] = v[u][e];
+                        pos++;
+                    }
                 }
+                base += __popcll(bits[u]);
             }
-            base += __popcll(bits[u]);
         }
-    }
-}
-
-__device__ __forceinline__ void digit_tiles_compacted(const __half *__restrict__ X, int M, const LinearW &w, const uint64_t *__restrict__ mask64,
-                                                      const int *__restrict__ list, int8_t *__restrict__ xl, int8_t *__restrict__ wd,
-                                                      int n_out, bool tokens, __half *st, int bid, int nblk, int &need) {
-    const int CT = (n_out + 63) >> 6, NT = w.N >> 4, MTT = (M + 15) >> 4, KT = w.K >> 6, K = w.K, lane = threadIdx.x & 63;
-    const int ranges = (CT + DT_TILES - 1) / DT_TILES, rows = tokens ? MTT : NT;
-    for (int item = bid; item < rows * ranges; item += nblk) {
-        const int rt = item / ranges, ct0 = (item - rt * ranges) * DT_TILES;
-        if (tokens) {
-            const int t = rt * 16 + (lane & 15);
-            const __half *row = X + (size_t)min(t, M - 1) * K + (lane >> 4) * 16;
-            compact_columns<__half>(mask64, list, n_out, ct0 * 64, st, [&](int kt, __half *v) {
-                *(v8h *)v = *(const v8h *)(row + (size_t)kt * 64);
-                *(v8h *)(v + 8) = *(const v8h *)(row + (size_t)kt * 64 + 8);
-            });
-            for (int j = 0; j < DT_TILES && ct0 + j < CT; j++) {
-                __half x[16];
-                *(v8h *)x = *(const v8h *)(st + (j * 64 + lane) * 16);
-                *(v8h *)(x + 8) = *(const v8h *)(st + (j * 64 + lane) * 16 + 8);
-                store_x_digits(x, t < M, xl, (size_t)MTT * CT, (size_t)rt * CT + ct0 + j, need);
-            }
-        } else {
-            const int8_t *panel = w.wt + (size_t)rt * KT * 1024 + lane * 16;
-            int8_t *st8 = (int8_t *)st;
-            compact_columns<int8_t>(mask64, list, n_out, ct0 * 64, st8, [&](int kt, int8_t *v) {
-                *(v4i *)v = *(const v4i *)(panel + (size_t)kt * 1024);
-            });
-            for (int j = 0; j < DT_TILES && ct0 + j < CT; j++)
-                store_w_digits(*(const v4i *)(st8 + (j * 64 + lane) * 16), w.sw[rt * 16 + (lane & 15)], wd, (size_t)NT * CT, (size_t)rt * CT + ct0 + j);
+        for (int j = 0; j < DT_TILES && ct0 + j < CT; j++) {
+            __half x[16];
+            *(v8h *)x = *(const v8h *)(st + (j * 64 + lane) * 16);
+            *(v8h *)(x + 8) = *(const v8h *)(st + (j * 64 + lane) * 16 + 8);
+            store_x_digits(x, t < M, xl, (size_t)MTT * CT, (size_t)mt * CT + ct0 + j, need);
         }
     }
 }
@@ -251,11 +236,13 @@ __global__ void __launch_bounds__(256) k_digit_tiles(const __half *__restrict__ 
     const int n_out = count[0];
     if (n_out <= PS_EXACT_OUTLIERS) return;
     const int wave = threadIdx.x >> 6, wv = (int)blockIdx.x * 4 + wave;
-    const bool tokens = wv < NBX;
-    const int bid = tokens ? wv : wv - NBX, nblk = tokens ? NBX : (int)gridDim.x * 4 - NBX;
+    if (wv >= NBX) {
+        weight_digits(w, list, wd, n_out, wv - NBX, (int)gridDim.x * 4 - NBX);
+        return;
+    }
     int need = 0;
-    if (n_out >= w.K >> 2) digit_tiles_compacted(X, M, w, (const uint64_t *)mask, list, xl, wd, n_out, tokens, stage[wave], bid, nblk, need);
-    else digit_tiles_gathered(X, M, w, list, xl, wd, n_out, tokens, bid, nblk, need);
+    if (n_out * 7 >= w.K * 4) token_digits_compacted(X, M, w.K, (const uint64_t *)mask, list, xl, n_out, stage[wave], wv, NBX, need);
+    else token_digits_gathered(X, M, w.K, list, xl, n_out, wv, NBX, need);
     if (need > 4) atomicMax(count + 1, need);
 }
 

@@ -99,9 +99,9 @@ def test_the_faster_form_is_chosen(H, nh, which, M):
     assert times[None] <= 1.2 * min(times["chunks"], times["blocks"]), times
 
 
-# Digit tiles of the outlier columns: column by column below one in four, in runs from there on (the line on either side, all
-# but one, all); values of five digits in one tile, rows of the last token tile missing
-@pytest.mark.parametrize("n_out", [271, 272, 1000, 1087, 1088])
+# Digit tiles of the outlier columns: the rows' column by column below four in seven, in runs from there on (the line on either
+# side, all but one, all); values of five digits in one tile, rows of the last token tile missing
+@pytest.mark.parametrize("n_out", [271, 272, 621, 622, 1000, 1087, 1088])
 @pytest.mark.parametrize("big", [False, True])
 def test_digit_tiles_of_many_columns(n_out, big):
     M, hidden, nh = 203, 1088, 17
@@ -155,6 +155,40 @@ def test_column_list_of_wide_inputs_and_narrow_outputs(hidden, nh, M, n_out):
     assert np.array_equal(to_np(out["acc"])[:, rows], dbg["acc"])
     assert np.array_equal(to_np(out["y"])[:, rows].view(np.uint16), Y.view(np.uint16))
     sp.close()
+
+
+# Half of the columns are fewer than five in eight, and take less time (the products alone about 0.8 of it).
+def test_time_of_digit_tiles_grows_with_the_columns():
+    H, F, M = 4096, 16384, 65
+    g = torch.Generator(device=DEV)
+    g.manual_seed(H)
+    span = binding.Span(1, H, 32, F, M, device=DEV)
+    p = dict(w_qkv=torch.zeros((3 * H, H), device=DEV), w_dense=torch.zeros((H, H), device=DEV), w_up=torch.zeros((F, H), device=DEV),
+             w_down=torch.empty((H, F), device=DEV).normal_(0.0, 0.02, generator=g))
+    for n, s in (("b_qkv", 3 * H), ("b_dense", H), ("b_up", F), ("b_down", H), ("ln1_g", H), ("ln1_b", H), ("ln2_g", H), ("ln2_b", H)):
+        p[n] = torch.zeros(s, dtype=torch.float16, device=DEV)
+    span.load_block(0, p)
+    y = torch.empty((M, H), dtype=torch.float16, device=DEV)
+    times = []
+    with midsize("blocks"):
+        for n_out in (F // 2, F * 5 // 8):
+            X = torch.empty((M, F), device=DEV).normal_(generator=g).clamp_(-5.0, 5.0)
+            cols = torch.randperm(F, generator=g, device=DEV)[:n_out]
+            X[torch.randint(0, M, (n_out,), generator=g, device=DEV), cols] = 9.0
+            X = X.half()
+            best = 1e9
+            for _ in range(6):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                torch.cuda._sleep(1000000)
+                a.record()
+                for _ in range(6):
+                    binding.petals_debug_linear(span.handle, 0, 3, X, 0, None, None, None, None, None, y)
+                b.record()
+                b.synchronize()
+                best = min(best, a.elapsed_time(b) / 6)
+            times.append(best)
+    span.close()
+    assert times[0] <= 0.9 * times[1], times
 
 
 # Up to 32 rows, outputs of 513 to 640 workgroups of four panels: with a little larger output each takes the other form, which
