@@ -158,6 +158,13 @@ __device__ __forceinline__ void token_digits_gathered(const __half *__restrict__
 // 1049; 200 rows with 400 of 32768 columns 460 and 689).
 constexpr int DT_TILES = 4, DT_AHEAD = 8;
 
+// what the lanes of a wave have written to LDS is there for its other lanes
+__device__ __forceinline__ void wave_sync_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ void token_digits_compacted(const __half *__restrict__ X, int M, int K, const uint64_t *__restrict__ mask64,
                                                        const int *__restrict__ list, int8_t *__restrict__ xl, int n_out, __half *st,
                                                        int bid, int nblk, int &need) {
@@ -170,6 +177,7 @@ __device__ __forceinline__ void token_digits_compacted(const __half *__restrict_
         const int k0 = list[ct0 * 64], kt1 = list[min(n_out, (ct0 + DT_TILES) * 64) - 1] >> 6;   // uniform; ascending
 #pragma unroll
         for (int i = 0; i < DT_TILES * 2; i++) ((v4i *)st)[i * 64 + lane] = (v4i){0, 0, 0, 0};
+        wave_sync_lds();
         int base = -__popcll(mask64[k0 >> 6] & ((1ull << (k0 & 63)) - 1));          // rank of the k-tile's first outlier, from 64 ct0
         for (int kt = k0 >> 6; kt <= kt1; kt += DT_AHEAD) {
             uint64_t bits[DT_AHEAD];
@@ -195,12 +203,14 @@ __device__ __forceinline__ void token_digits_compacted(const __half *__restrict_
                 base += __popcll(bits[u]);
             }
         }
+        wave_sync_lds();
         for (int j = 0; j < DT_TILES && ct0 + j < CT; j++) {
             __half x[16];
             *(v8h *)x = *(const v8h *)(st + (j * 64 + lane) * 16);
             *(v8h *)(x + 8) = *(const v8h *)(st + (j * 64 + lane) * 16 + 8);
             store_x_digits(x, t < M, xl, (size_t)MTT * CT, (size_t)mt * CT + ct0 + j, need);
         }
+        wave_sync_lds();                 // read before the next item's zeros
     }
 }
 
