@@ -39,17 +39,21 @@ __device__ __forceinline__ double exp_f64(double x) {
     const double h = 1.0 + rh, l = fma(n, -0x1.473de6af278edp-34, (1.0 - h) + rh);
     return __builtin_amdgcn_ldexp(h + fma(r * r, q, l), (int)(unsigned)__builtin_bit_cast(unsigned long long, t));
 }
-// tanh-form GeLU in fp64: 0.5 v (1 + tanh u) == v / (1 + exp(-2u)), in some 30 instructions of its own (on exp_f64 41; a
-// prefill call's up linear spends a fifth of its time on them): -2 u / ln 2 straight from v (-1.5957... / ln 2 as a sum of two
-// numbers, and that times 0.044715), 2^y as 2^n 2^f with the degree-10 interpolation of (2^f - 1) / f in Chebyshev points, the quotient from the
-// reciprocal instruction, one cubic step and one correction by the remainder.  No larger an error than with exp_f64 (both
-// have that of the argument's rounding).  NaN gets lost in the clamps and comes back in through v in the remainder;
-// +infinity is kept out of the quotient, where its remainder would be NaN, and comes back in there too.
+// tanh-form GeLU in fp64: 0.5 v (1 + tanh u) == v / (1 + exp(-2u)), in some 32 instructions of its own (on exp_f64 41; a
+// prefill call's up linear spends a fifth of its time on them): y = -2 u / ln 2 straight from v (-1.5957... / ln 2 as a sum of
+// two numbers, and that times 0.044715), its last product with the part that rounding would drop, 2^y as 2^n 2^f with the
+// degree-10 interpolation of (2^f - 1) / f in Chebyshev points, the quotient from the reciprocal instruction, one cubic step and
+// one correction by the remainder.  Where 1 + tanh u nearly vanishes the rounding of the argument is what the error consists
+// of: on [-6, -5] up to 36 units in the last place of the function with these constants as doubles (44 with the square root of
+// 2 / pi itself); the form on exp_f64 45 and 51 as the compiler contracts it here, 57 and 61 uncontracted; without the dropped
+// part 56 and 63 either way.  Beyond +-20 the result is v, or less than 1e-250.  NaN gets lost in the clamps and comes back in
+// through v in the remainder; +infinity is kept out of the quotient, where its remainder would be NaN, and comes back in there
+// too.
 __device__ __forceinline__ double gelu_tanh(double v) {
     constexpr double MAGIC = 6755399441055744.0;
-    const double t = v * v;
-    const double y = fmin(fmax(fma(v, fma(t, -0x1.a5a7cf7572a98p-4, -0x1.26aec21bce75ap+1), v * 0x1.85892a664356cp-53), -1100.0), 1000.0);
-    const double k = y + MAGIC, f = y - (k - MAGIC);
+    const double c = fmin(fmax(v, -20.0), 20.0);
+    const double s = fma(c * c, -0x1.a5a7cf7572a98p-4, -0x1.26aec21bce75ap+1), y = c * s;
+    const double k = y + MAGIC, f = (y - (k - MAGIC)) + fma(c, 0x1.85892a664356cp-53, fma(c, s, -y));
     double q = 0x1.e9d3fe3952179p-32;
     q = fma(q, f, 0x1.e6063f7217bc6p-28);
     q = fma(q, f, 0x1.b524fae627834p-24);
