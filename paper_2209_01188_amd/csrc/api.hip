@@ -52,7 +52,7 @@ size_t block_weight_bytes(const petals_span_config &c) {
     return b + 4 * ps_align_up((size_t)c.hidden * 2);
 }
 
-// with_digits: room for ps_gemm_digits (calls of 17 to 64 rows of wide spans; without it they take ps_gemm alone)
+// with_digits: room for the digit form of ps_gemm (calls of 17 to 64 rows of wide spans; without it they take the fp64 form)
 Workspace carve(const petals_span_config &c, uint8_t *base, bool with_digits = true) {
     Workspace w;
     const size_t M = (size_t)c.max_rows_per_call, Mp = (M + 15) / 16 * 16, H = c.hidden, F = c.ffn;
@@ -100,6 +100,7 @@ Workspace carve(const petals_span_config &c, uint8_t *base, bool with_digits = t
         w.digits.part_acc = (int *)take(halves * 4);
         w.digits.xd = w.xd;
         w.digits.rowstate = w.ocount;
+        w.digits.done = (int *)take(PS_DIGIT_DONE * 4);
     }
     w.total = off;
     return w;
@@ -166,12 +167,11 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
         const OutlierPrep prep = {w, small ? nullptr : ws.ocount, ws.wd64, ws.x64, ws.many.list};
         // (a LayerNorm's output has few outlier columns: only the inputs that attention and GeLU write go for digits)
         const bool digits = !ln_g && ws.xd && w.N == c.hidden && ps_gemm_digits_applies(w.N, w.K, M);
-        const RowDigits rd = {digits ? ws.xd : nullptr, ws.ocount};
+        const RowDigits rd = {digits ? ws.xd : nullptr, ws.ocount, ws.digits.done};
         HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ln_g ? flags : nullptr, ws.xq, small ? ws.xo : nullptr, ws.sx, xq_dbg, prep, rd, st));
         const OutlierSet os = {ws.ocount, ws.wd64, ws.x64};
         const bool pr = sp->prof.begin(PETALS_PROFILE_GEMM, which, st);
         if (small) {
-            if (digits) HIP_TRY(ps_gemm_digits(w, ws.xq, ws.digits, M, st));
             HIP_TRY(ps_gemm(w, ws.xq, ws.xo, mask, X, ws.sx, M, o, ws.table, digits ? ws.digits : DigitCall{}, st));
         } else {
             HIP_TRY(ps_gemm_lds(w, ws.xq, mask, X, ws.sx, M, os, ws.many, o, ws.table, st));

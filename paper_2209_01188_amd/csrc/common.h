@@ -119,13 +119,14 @@ hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask
 // xo_tiled (may be null): same tile order, 16 bytes per (token, 16-column group) = the fp16 values of the
 // group's first 8 outlier columns in ascending order; groups without outliers are not written
 // pr (pr.count may be null): the linear's outlier columns are counted and, if they are few, compacted in the same launch
-// rd (rd.xd may be null): if the call has many outlier columns, their digits for ps_gemm_digits, and what became of each row
+// rd (rd.xd may be null): if the call has many outlier columns, their digits for ps_gemm, and what became of each row
 struct OutlierPrep;
 struct RowDigits {
     int8_t *xd;          // [ceil(M/16)][K/64][4 digits][1024], tiles in the order of xq_tiled
     int *rowstate;       // [M]
+    int *done;           // [PS_DIGIT_DONE], cleared
 };
-#define PS_ROWS_IN_DIGITS 1       // the row's digits are written; a call goes to ps_gemm_digits if all its rows say so
+#define PS_ROWS_IN_DIGITS 1       // the row's digits are written; a call is taken as digits if all its rows say so
 hipError_t ps_rowquant_tiled(const __half *X, int M, int K, uint32_t *mask, const uint8_t *flags, int8_t *xq_tiled,
                              int8_t *xo_tiled, float *sx, int8_t *xq_rowmajor_dbg, const OutlierPrep &pr, const RowDigits &rd,
                              hipStream_t st);
@@ -162,23 +163,22 @@ hipError_t ps_gemv_row(const LinearW &w, const __half *x, const __half *ln_g, co
 #define PS_CHUNKED_ROWS_MAX 512
 // batched-decode linear, 2 <= M <= PS_CHUNKED_ROWS_MAX rows, 64 per workgroup (int8 MFMA, outlier columns exactly on fp64 MFMA inside the
 // loop); xq_tiled and xo_tiled as written by ps_rowquant_tiled
-// dc (dc.xd may be null): finishes the call if ps_gemm_digits has taken it
+// dc (dc.xd may be null): for calls of 17 to 64 rows on wide matrices, whose outlier columns are then taken as digits if the row
+// quantizer has written them for all rows, see gemm_digits.h.  (That is known on the device only: both forms are in one launch.)
 struct DigitCall;
 hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,
                    const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, const DigitCall &dc,
                    hipStream_t st);
-// The same for 17 to 64 rows on wide matrices with many outlier columns, see gemm_digits.hip.  ps_gemm_digits and then
-// ps_gemm are launched, and the rows' state, known on the device only, decides whether the second finishes what the first
-// has summed or does all the work.
 #define PS_DIGIT_SPLITS 4         // workgroups that share the contraction
+#define PS_DIGIT_DONE 1024        // pieces of the output that they finish: 512 pairs of panels, for each half of the tokens
 struct DigitCall {
     const int8_t *xd;             // RowDigits
     const int *rowstate;
+    int *done;                    // [PS_DIGIT_DONE], cleared by the row quantizer: shares whose sums are in memory
     double *part;                 // [split][token half][pair of panels][16][64 lanes]: the outlier product in units of u_n 2^-24
     int *part_acc;                // the same of the regular columns' sums
 };
 bool ps_gemm_digits_applies(int N, int K, int M);
-hipError_t ps_gemm_digits(const LinearW &w, const int8_t *xq_tiled, const DigitCall &dc, int M, hipStream_t st);
 // Calls of more than 64 rows that are better served by ps_gemm, 64 rows per workgroup (the weights are streamed once
 // per 64 rows, with every compute unit busy) than by the 256 x 256 output blocks of ps_gemm_lds, which
 // leave most of the GPU idle when the call has few of them.  PS_CHUNKED_ROWS_MAX bounds such calls.

@@ -10,8 +10,8 @@
 #include <mutex>
 
 #include "common.h"
-#include "digits.h"
 #include "epilogue.h"
+#include "gemm_digits.h"
 
 namespace {
 
@@ -31,51 +31,6 @@ auto digit_arg(const DigitCall &dc) {
     else return NoDigits{};
 }
 
-// The rest of a call that k_gemm_digits has summed: one wave per 4 x 2 output rows and 32 tokens adds the splits and
-// goes through the linear's tail.
-__device__ __forceinline__ void finish_digits(const LinearW &w, const uint32_t *__restrict__ mask, const __half *__restrict__ X,
-                                              const float *__restrict__ sx, int M, const OutDesc &o,
-                                              const SessTable *__restrict__ sess, const DigitCall &dc) {
-    const int lane = threadIdx.x & 63, pairs = w.N >> 5, K = w.K, KT = K >> 6;
-    const int items = pairs * 4 * ((M + 31) >> 5), stride = gridDim.x * (blockDim.x >> 6);
-    for (int item = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); item < items; item += stride) {
-        const int q = item & 3, hp = item >> 2, half = hp / pairs, pair = hp - half * pairs;     // uniform in the wave
-        const int t = half * 32 + (lane & 31), n0 = pair * 32 + 8 * q + 4 * (lane >> 5);
-        const size_t at = (((size_t)half * pairs + pair) * 16 + 4 * q) * 64 + lane, split = (size_t)2 * pairs * 16 * 64;
-        const float4 s4 = *(const float4 *)(w.sw + n0);
-        const float sv[4] = {s4.x, s4.y, s4.z, s4.w};
-        v4i acc = {0, 0, 0, 0};
-        v4d od = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int sp = 0; sp < PS_DIGIT_SPLITS; sp++)
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                od[r] += dc.part[sp * split + at + r * 64];
-                acc[r] += dc.part_acc[sp * split + at + r * 64];
-            }
-        if (t >= M) continue;
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            float a;
-            int E, m;
-            digit_scale(sv[r], a, E, m);
-            od[r] = ldexp(od[r], E - 34);                  // u = 2^(E-10), activations in units of 2^-24
-            if (!(sv[r] <= 65504.0f)) {
-                // some |Wd| of this row may overflow fp16: column by column, infinities and all
-                od[r] = 0.0;
-                const int n = n0 + r;
-                for (int kw = 0; kw < K >> 5; kw++)
-                    for (uint32_t b = mask[kw]; b; b &= b - 1) {
-                        const int k = kw * 32 + __ffs(b) - 1;
-                        const int code = w.wt[((size_t)(n >> 4) * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + (n & 15)) * 16 + (k & 15)];
-                        od[r] += (double)__half2float(X[(size_t)t * K + k]) * (double)dequant_w16(code, sv[r] / 127.0f);
-                    }
-            }
-        }
-        emit_output4(o, sess, w.N, t, n0, acc, od, sx[t] / 127.0f, w.sw, w.bias);
-    }
-}
-
 // One workgroup = WVK waves on WN consecutive 16-row weight panels; wave wk takes chunks of UK
 // consecutive k-tiles (chunk c = wk, wk + WVK, ...) for MT token tiles of 16 rows, so a token tile
 // fetched once meets WN weight tiles.  Weights are the A operand (lane l: row l%16, 16 codes of
@@ -90,12 +45,14 @@ __global__ void __launch_bounds__(64 * WVK)
 k_gemm(LinearW w, const int8_t *__restrict__ xq_tiled, const int8_t *__restrict__ xo_tiled,
        const uint32_t *__restrict__ mask, const __half *__restrict__ X, const float *__restrict__ sx, int M,
        OutDesc o, const SessTable *__restrict__ sess, typename std::conditional<DIG, DigitCall, NoDigits>::type dc) {
+    extern __shared__ __align__(16) unsigned char lds[];
     if constexpr (DIG) {                             // (at most 64 rows)
         const int l = threadIdx.x & 63;
         if (!__ballot(l < M && dc.rowstate[l] != PS_ROWS_IN_DIGITS)) {
-            finish_digits(w, mask, X, sx, M, o, sess, dc);
+            digit_linear(w, xq_tiled, mask, X, sx, M, o, sess, dc, lds);
             return;
         }
+        if ((int)blockIdx.x * 16 * WN >= w.N) return;
     }
     const int K = w.K, KT = K >> 6, N = w.N;
     if (gridDim.y > 1) {
@@ -224,7 +181,6 @@ k_gemm(LinearW w, const int8_t *__restrict__ xq_tiled, const int8_t *__restrict_
     // The waves' partial sums meet in LDS, up to four (panel, token tile) pairs at a time; one wave per
     // pair adds them in wave order (the fp64 terms are exact products of fp16 values) and finishes it.
     constexpr int G = WN * MT, NPP = G < 4 ? G : 4;
-    extern __shared__ __align__(16) unsigned char lds[];
     v4i *ri = (v4i *)lds;                                             // [WVK][NPP][64]
     v4d *rf = (v4d *)(lds + (size_t)WVK * NPP * 64 * 16);             // [WVK][NPP][64]
 #pragma unroll
@@ -267,7 +223,9 @@ template <int WN, int MT, int UK, int WVK = 8, bool DIG = false>
 hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,
                   const __half *X, const float *sx, int M, const OutDesc &o, const SessTable *sess, const DigitCall &dc, hipStream_t st) {
     constexpr int G = WN * MT, NPP = G < 4 ? G : 4;
-    const size_t lds = (size_t)WVK * NPP * 64 * (16 + 32);   // up to 96 KB
+    constexpr size_t sums = (size_t)WVK * NPP * 64 * (16 + 32), ring = DIG ? DIGIT_SLOTS * 10 * 1024 : 0;
+    constexpr size_t lds = sums > ring ? sums : ring;        // up to 96 KB
+    const int wgs = w.N / (16 * WN), digit_wgs = DIG ? digit_grid_x(w.N, M) * PS_DIGIT_SPLITS : 0;
     auto kern = k_gemm<WN, MT, UK, WVK, DIG>;
     static std::mutex attr_lock;
     static bool attr_set = false;
@@ -277,11 +235,15 @@ hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_til
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    kern<<<dim3(w.N / (16 * WN), (M + 63) / 64), 64 * WVK, lds, st>>>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, digit_arg<DIG>(dc));
+    kern<<<dim3(wgs > digit_wgs ? wgs : digit_wgs, (M + 63) / 64), 64 * WVK, lds, st>>>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, digit_arg<DIG>(dc));
     return hipGetLastError();
 }
 
 }  // namespace
+
+// Narrower outputs belong to narrower blocks, whose activations hold few outliers; 16384 is the widest there is.  Up to 16
+// rows a column is rarely an outlier and the fp64 form's cost is half (one token tile).
+bool ps_gemm_digits_applies(int N, int K, int M) { return M > 16 && M <= 64 && N >= 12288 && N <= 16384 && K >= 4096; }
 
 // panels of 16 output rows per workgroup of ps_gemm: as many as still leave about one workgroup per compute unit
 static int gemm_panels_per_wg(int N) {

@@ -7,12 +7,14 @@
 // In gemm.hip every outlier column costs a 64-clock fp64 matrix instruction per panel and token tile (4 columns at a
 // time); here a 64-column tile costs eight 16-clock int8 instructions per token tile and 80 vector instructions for its
 // remainders, however many of its columns are outliers.
-#include "common.h"
+#pragma once
 #include "digits.h"
+#include "epilogue.h"
 
 namespace {
 
-constexpr int PAIRS = 8;              // waves of a workgroup, each with a pair of 16-row panels
+constexpr int DIGIT_PAIRS = 8;        // waves of a workgroup, each with a pair of 16-row panels
+constexpr int DIGIT_SLOTS = 6;        // of 10 KB of the LDS ring
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ v4i buffer_load16(const __amdgpu_buffer_rsrc_t r, int lane_offset, int offset) {
@@ -35,25 +37,35 @@ __device__ __forceinline__ void buffer_copy16(const __amdgpu_buffer_rsrc_t r, vo
 // replace and its remainders are worked out.
 // Tiles are 16 rows x 64 columns, see LinearW; lane l takes row l % 16 of panel (or token tile) (l / 16) % 2 and column
 // group l / 32 + 2 h for instruction h of a step.
-template <int NSLOT>
-__global__ void __launch_bounds__(64 * PAIRS, 2)
-k_gemm_digits(LinearW w, const int8_t *__restrict__ xq_tiled, DigitCall dc, int M) {
-    constexpr int TOK = 10, PD = NSLOT - 1, PW = 3, MORE = TOK - PAIRS;
-    extern __shared__ __align__(16) unsigned char lds[];
+// Of the PS_DIGIT_SPLITS waves that share a pair of panels, the one that gets there last adds the sums, always in the same
+// order, and goes through the linear's tail.  (While this form and the tails were launches of their own, a call that does not come
+// here paid 2 us for either: dense of a 14336-wide block with few outlier columns, 24 rows, 47.6 us in the fp64 form alone, 49.7
+// with them, 48.3 with all in one launch; with a third outlier columns 89.3 and 91.1 at 32 rows, 157 and 156 at 64.)  The sums
+// pass between compute units, most of them on other XCDs, by relaxed agent-scope atomics, which are written through and read
+// past the L2s, and every store has been acknowledged before the count goes up.  Plain stores with a release and an acquire
+// would do as well, for 10 us more per linear: each has its L2 written back or dropped as a whole.
+__host__ __device__ inline int digit_grid_x(int N, int M) {
+    const int wgs = (N / 32 + DIGIT_PAIRS - 1) / DIGIT_PAIRS;
+    return M > 32 ? (wgs + 7) / 8 * 16 : wgs;
+}
+__device__ __forceinline__ void digit_linear(const LinearW &w, const int8_t *__restrict__ xq_tiled, const uint32_t *__restrict__ mask,
+                                             const __half *__restrict__ X, const float *__restrict__ sx, int M, const OutDesc &o,
+                                             const SessTable *__restrict__ sess, const DigitCall &dc, unsigned char *lds) {
+    constexpr int NSLOT = DIGIT_SLOTS, PAIRS = DIGIT_PAIRS, TOK = 10, PD = NSLOT - 1, PW = 3, MORE = TOK - PAIRS;
     const int lane = threadIdx.x & 63;
-    if (__ballot(lane < M && dc.rowstate[lane] != PS_ROWS_IN_DIGITS)) return;      // the other form takes this call
     const int KT = w.K >> 6, pairs = w.N >> 5, MTT = (M + 15) >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // 33 rows and more: the two halves of the tokens in workgroups 8 apart, that is on one XCD, whose L2 then gives the
     // weights to the second one
-    int bx = blockIdx.x, half = 0;
+    const int share = (int)blockIdx.x / digit_grid_x(w.N, M);
+    int bx = (int)blockIdx.x - share * digit_grid_x(w.N, M), half = 0;
     if (M > 32) {
         half = (bx >> 3) & 1;
         bx = (bx >> 4) * 8 + (bx & 7);
     }
-    if (bx * PAIRS >= pairs) return;
+    if (share >= PS_DIGIT_SPLITS || bx * PAIRS >= pairs) return;
     const int pair = min(bx * PAIRS + wave, pairs - 1);
-    const int share = blockIdx.y, k_first = KT * share / PS_DIGIT_SPLITS, NS = KT * (share + 1) / PS_DIGIT_SPLITS - k_first;
+    const int k_first = KT * share / PS_DIGIT_SPLITS, NS = KT * (share + 1) / PS_DIGIT_SPLITS - k_first;
 
     // Buffer form of the requests: descriptor = the run of tiles, bounds-checked by the hardware, and no address arithmetic in
     // the vector unit; with the flat form of the copies the compiler waits for ALL requests wherever it waits for weights.
@@ -174,35 +186,73 @@ k_gemm_digits(LinearW w, const int8_t *__restrict__ xq_tiled, DigitCall dc, int 
     }
     multiply(wq[0], rem0, -1);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the copies beyond the end have landed, too
-    if (bx * PAIRS + wave >= pairs) return;
 
     // m sum_j 256^j A_code[j] + sum_j 256^j A_rem[j] in fp64 from the top digit down: exact below 2^53, i.e. up to the last
     // step.  Register 4 q + r of lane l is output row 8 q + 4 (l / 32) + r of the pair, token l % 32.
-    const size_t at = (((size_t)share * 2 + half) * pairs + pair) * 16 * 64 + lane;
+    if (bx * PAIRS + wave >= pairs) return;
+    const size_t at = ((size_t)half * pairs + pair) * 16 * 64 + lane, split = (size_t)2 * pairs * 16 * 64;
+    double own[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) {
         const int m1 = __shfl(m, 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3));      // lane n holds the scale of row n
         double tc = 0.0, tr = 0.0;
 #pragma unroll
         for (int d = 3; d >= 0; d--) { tc = tc * 256.0 + (double)ac[d][r]; tr = tr * 256.0 + (double)ar[d][r]; }
-        dc.part[at + r * 64] = fma((double)m1, tc, tr);
-        dc.part_acc[at + r * 64] = acc[r];
+        own[r] = fma((double)m1, tc, tr);
+        __hip_atomic_store(dc.part + share * split + at + r * 64, own[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(dc.part_acc + share * split + at + r * 64, acc[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // they are where everybody sees them
+    int before = 0;
+    if (lane == 0) before = __hip_atomic_fetch_add(dc.done + half * (PS_DIGIT_DONE / 2) + pair, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(before) != PS_DIGIT_SPLITS - 1) return;
+    asm volatile("" ::: "memory");                         // no load in front of the count
+    const int t = half * 32 + (lane & 31);
+    const float sw = w.sw[pair * 32 + (lane & 31)];
+    digit_scale(sw, a, E, m);
+    const bool overflow = __any(!(sw <= 65504.0f));        // some |Wd| of such a row may overflow fp16
+    int e[16];
+#pragma unroll
+    for (int r = 0; r < 16; r++) e[r] = __shfl(E, 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) - 34;    // u = 2^(E-10), activations in units of 2^-24
+    if (t >= M) return;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int n0 = pair * 32 + 8 * q + 4 * (lane >> 5);
+        v4i sum;
+        v4d od;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const size_t i = at + (4 * q + r) * 64;
+            const auto other = [&](int j) { return (j + (j >= share)) * split + i; };
+            const auto part = [&](int j) { return __hip_atomic_load(dc.part + other(j), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            const auto part_acc = [&](int j) { return __hip_atomic_load(dc.part_acc + other(j), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            static_assert(PS_DIGIT_SPLITS == 4, "");
+            const double p0 = part(0), p1 = part(1), p2 = part(2), p = own[4 * q + r];
+            sum[r] = acc[4 * q + r] + part_acc(0) + part_acc(1) + part_acc(2);
+            od[r] = share == 0 ? p : p0;               // in the order of the shares, its own in its place
+            od[r] += share == 0 ? p0 : share == 1 ? p : p1;
+            od[r] += share <= 1 ? p1 : share == 2 ? p : p2;
+            od[r] += share == 3 ? p : p2;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; r++) od[r] = __builtin_amdgcn_ldexp(od[r], e[4 * q + r]);
+        if (overflow) {                                    // column by column, infinities and all
+            for (int r = 0; r < 4; r++) {
+                const int n = n0 + r;
+                if (w.sw[n] <= 65504.0f) continue;
+                double v = 0.0;
+                for (int kw = 0; kw < w.K >> 5; kw++)
+                    for (uint32_t b = mask[kw]; b; b &= b - 1) {
+                        const int k = kw * 32 + __ffs(b) - 1;
+                        const int code = w.wt[((size_t)(n >> 4) * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + (n & 15)) * 16 + (k & 15)];
+                        v += (double)__half2float(X[(size_t)t * w.K + k]) * (double)dequant_w16(code, w.sw[n] / 127.0f);
+                    }
+#pragma unroll
+                for (int i = 0; i < 4; i++) od[i] = i == r ? v : od[i];
+            }
+        }
+        emit_output4(o, sess, w.N, t, n0, sum, od, sx[t] / 127.0f, w.sw, w.bias);
     }
 }
 
 }  // namespace
-
-// Narrower outputs belong to narrower blocks, whose activations hold few outliers, and would only pay for the launch that
-// finds nothing to do (a 10240-wide block, 18 rows: 461 -> 468 us); 16384 is the widest there is.  Up to 16 rows a column
-// is rarely an outlier and the fp64 form's cost is half (one token tile).
-bool ps_gemm_digits_applies(int N, int K, int M) { return M > 16 && M <= 64 && N >= 12288 && N <= 16384 && K >= 4096; }
-
-hipError_t ps_gemm_digits(const LinearW &w, const int8_t *xq_tiled, const DigitCall &dc, int M, hipStream_t st) {
-    if (!ps_gemm_digits_applies(w.N, w.K, M) || w.N % 64) return hipErrorInvalidValue;
-    constexpr int NSLOT = 6;
-    constexpr size_t bytes = (size_t)NSLOT * 10 * 1024;
-    auto kern = k_gemm_digits<NSLOT>;
-    const int wgs = (w.N / 32 + PAIRS - 1) / PAIRS;
-    kern<<<dim3(M > 32 ? (wgs + 7) / 8 * 16 : wgs, PS_DIGIT_SPLITS), 64 * PAIRS, bytes, st>>>(w, xq_tiled, dc, M);
-    return hipGetLastError();
-}

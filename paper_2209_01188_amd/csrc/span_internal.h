@@ -26,7 +26,7 @@ struct Workspace {
     int *ocount;
     double *wd64, *x64;
     ManyOutliers many;     // only carved when max_rows_per_call > 64
-    int8_t *xd;            // wide spans: digits of the outlier columns of calls of 17 to 64 rows, see ps_gemm_digits
+    int8_t *xd;            // wide spans: digits of the outlier columns of calls of 17 to 64 rows, see gemm_digits.h
     DigitCall digits;
     size_t mask_words;
     size_t total;

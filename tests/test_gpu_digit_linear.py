@@ -1,5 +1,5 @@
 """Linears of 17 to 64 rows on wide outputs whose input has many outlier columns: exact int8 digit products in the pass
-over the weights (gemm_digits.hip), against the oracle and, where the call falls back, against the same bits."""
+over the weights (gemm_digits.h), against the oracle and, where the call falls back, against the same bits."""
 import numpy as np
 import pytest
 
@@ -74,6 +74,37 @@ def test_linear_with_many_outlier_columns(span, M, share, kind):
     got = to_np(out["y"])[:, rows]
     same = got.view(np.uint16) == Y.view(np.uint16)
     assert same.all(), "%d of %d outputs differ, rows %s" % ((~same).sum(), same.size, rows[np.unique(np.argwhere(~same)[:, 1])][:8])
+
+
+@pytest.mark.parametrize("M", [17, 64])
+def test_every_call_adds_the_shares_in_the_same_order(span, M):
+    """The workgroup that finishes an output is another one from call to call; the sums and their order are not."""
+    F = span.shapes(3)[1]
+    x = to_dev(_input(M, F, F // 2, "", 5))
+    y = torch.empty((40, M, H), dtype=torch.float16, device=DEV)
+    for i in range(len(y)):
+        binding.petals_debug_linear(span.handle, 0, 3, x, 0, None, None, None, None, None, y[i])
+    assert (y.view(torch.int16) == y[0].view(torch.int16)).all()
+
+
+def test_calls_that_may_go_to_digits_are_no_more_launches(span):
+    """One row beyond the limit: most calls have few outlier columns, and a launch that finds nothing to do costs 2 us."""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    F, nodes = span.shapes(3)[1], []
+    for M in (16, 17):
+        x, y = to_dev(_input(M, F, 3, "", M)), torch.empty((M, H), dtype=torch.float16, device=DEV)
+        call = lambda: binding.petals_debug_linear(span.handle, 0, 3, x, 0, None, None, None, None, None, y)
+        call()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            call()
+        n = ctypes.c_size_t(0)
+        assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+        nodes.append(n.value)
+        del graph
+    assert nodes[0] == nodes[1] and nodes[0] >= 3, nodes
 
 
 def test_weights_that_overflow_fp16_as_in_the_other_form(span):
