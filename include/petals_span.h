@@ -159,8 +159,9 @@ int petals_span_decode_step(petals_span *span, petals_session *const *sessions, 
  * petals_span_decode_step for callers that cannot provide or allocate device memory at the time of the call
  * (code running under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same step,
  * same arguments, same results bit for bit, but every intermediate buffer lives in a fixed device array that
- * is part of the library image (32 MiB per GPU, held until the process ends) instead of the span's workspace.
- * The call allocates nothing, on the host or on the device.  A step whose intermediates do not fit
+ * is part of the library image (96 MiB per GPU, held until the process ends) instead of the span's workspace.
+ * The call allocates nothing, on the host or on the device.  A step whose intermediates do not fit the 32 MiB of
+ * them that are for these (the others are for exact sums over outlier columns, for which they always suffice)
  * (B * hidden of the order of a few hundred thousand; for BLOOM-176B-shaped blocks up to about 40 sessions)
  * returns PETALS_ERR_CAPACITY and changes nothing.  All spans of the process share the array of their GPU:
  * calls of this entry point that overlap in time on one GPU (different streams or threads) race; calls on one

@@ -17,8 +17,11 @@ thread_local char g_err[512] = "";
 
 // Scratch of petals_span_decode_step_static: device memory that belongs to the library image, so that the call
 // needs no workspace from anybody.  Every GPU the library runs on holds its own copy at its own address.
+// The first part bounds which steps fit; behind it there is room for the digit sums (see carve) of every step that does: 64 rows
+// of 65536 columns in four digits, the sums of 16384 outputs and their counters.
 #define PS_STATIC_SCRATCH_BYTES ((size_t)32 << 20)
-static __device__ __align__(256) unsigned char scratch[PS_STATIC_SCRATCH_BYTES];
+#define PS_STATIC_DIGIT_BYTES (((size_t)64 * 65536 * 4) + (size_t)PS_DIGIT_SPLITS * 64 * 16384 * 12 + PS_DIGIT_DONE * 4)
+static __device__ __align__(256) unsigned char scratch[PS_STATIC_SCRATCH_BYTES + PS_STATIC_DIGIT_BYTES];
 
 int ps_fail(int code, const char *fmt, ...) {
     va_list ap;
@@ -52,7 +55,7 @@ size_t block_weight_bytes(const petals_span_config &c) {
     return b + 4 * ps_align_up((size_t)c.hidden * 2);
 }
 
-// with_digits: room for the digit form of ps_gemm (calls of 17 to 64 rows of wide spans; without it they take the fp64 form)
+// with_digits: room for the digit form of ps_gemm (calls of 17 to 64 rows of wide spans), behind everything else
 Workspace carve(const petals_span_config &c, uint8_t *base, bool with_digits = true) {
     Workspace w;
     const size_t M = (size_t)c.max_rows_per_call, Mp = (M + 15) / 16 * 16, H = c.hidden, F = c.ffn;
@@ -507,10 +510,12 @@ int petals_span_decode_step_static(petals_span *sp, petals_session *const *sessi
                     B, need, (size_t)PS_STATIC_SCRATCH_BYTES);
     void *base = nullptr;
     if (int rc = static_scratch(&base)) return rc;
+    const size_t all = carve(c, nullptr).total;
+    if (all - need > PS_STATIC_DIGIT_BYTES) return fail(PETALS_ERR_CAPACITY, "%zu bytes of digit sums do not fit the static buffer", all - need);
     // the span's kernels take every intermediate buffer from sp->ws: point it at the static memory for this call
     const Workspace own = sp->ws;
     const int own_rows = sp->cfg.max_rows_per_call;
-    sp->ws = carve(c, (uint8_t *)base, false);
+    sp->ws = carve(c, (uint8_t *)base);
     sp->cfg.max_rows_per_call = B;
     const int rc = run_call(sp, sessions, B, 1, hidden_in, hidden_out, (hipStream_t)stream);
     sp->ws = own;

@@ -69,3 +69,42 @@ def test_static_decode_step_rejects_what_does_not_fit_and_leaves_sessions_alone(
         assert all(s.length == 0 for s in ses)
     finally:
         sp.close()
+
+
+@pytest.mark.parametrize("B", [17, 64])
+def test_static_decode_step_sums_outlier_columns_as_the_workspace_one_does(B):
+    """12288 columns, all of them outliers of the dense linear's input: large ones that cancel (the first row's in part) and
+    leave sums of tiny values, where another order of the additions shows in the last bits of fp16."""
+    H, nh, F, d = 12288, 96, 4096, 128
+    g = torch.Generator(device=DEV)
+    g.manual_seed(B)
+    sp = binding.Span(1, H, nh, F, 64, 1e-5, 6.0, DEV)
+    try:
+        k = torch.arange(H, device=DEV)
+        a, b = k[k % 2 == 0], k[k % 2 == 1]                  # context columns from column 0 and 1 of the LayerNorm
+        wv = torch.zeros((H, H), device=DEV)
+        wv[a, 0] = torch.where(a < H // 2, 1.0, -1.0)
+        wv[b, 1] = 0.08                                      # 6.3 in the first row, some 1e-7 in the others
+        w_qkv = torch.zeros((nh, 3, d, H), device=DEV)
+        w_qkv[:, 2] = wv.view(nh, d, H)
+        w_dense = torch.empty((H, H), device=DEV).normal_(0.0, 3000.0, generator=g)
+        w_dense[:, a[a < H // 2]] = w_dense[:, a[a < H // 2]].abs()      # sums beyond 2^53 of their smallest unit
+        w_dense[:, a[a >= H // 2]] = w_dense[:, a[a < H // 2]]
+        p = dict(w_qkv=w_qkv.view(3 * H, H), w_dense=w_dense, w_up=torch.zeros((F, H), device=DEV), w_down=torch.zeros((H, F), device=DEV))
+        for n, s in (("b_qkv", 3 * H), ("b_dense", H), ("b_up", F), ("b_down", H), ("ln1_g", H), ("ln1_b", H), ("ln2_g", H), ("ln2_b", H)):
+            p[n] = torch.zeros(s, dtype=torch.float16, device=DEV)
+        p["ln1_g"][:2] = 1.0
+        sp.load_block(0, p)
+        del p, wv, w_qkv, w_dense
+        x = torch.zeros((B, H), dtype=torch.float16, device=DEV)
+        x[:, 0] = 1.0
+        x[:, 1] = (torch.arange(B, device=DEV) % 2 + 1365).to(torch.float16) * 2.0 ** -24    # about the mean: next to nothing in the LayerNorm
+        x[0, 1] = 1.0
+        ref = sp.decode_step([sp.open_session(2) for _ in range(B)], x)
+        assert sp.outlier_counts()[0, 1] == H and (ref[:, 2:] != 0).float().mean() > 0.9
+        got = sp.decode_step_static([sp.open_session(2) for _ in range(B)], x)
+        torch.cuda.synchronize()
+        differ = (got.view(torch.int16) != ref.view(torch.int16)).sum().item()
+        assert differ == 0, "%d of %d" % (differ, ref.numel())
+    finally:
+        sp.close()
