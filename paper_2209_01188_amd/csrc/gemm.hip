@@ -241,8 +241,11 @@ hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_til
 
 }  // namespace
 
-// Narrower outputs belong to narrower blocks, whose activations hold few outliers; 16384 is the widest there is.  Up to 16
-// rows a column is rarely an outlier and the fp64 form's cost is half (one token tile).
+// Narrower outputs belong to narrower blocks, whose inputs hold few outlier columns in a trained model, and there the calls that
+// don't go to digits would pay for this form's registers and its eight waves (steps through two 10240-wide blocks with few outlier
+// columns, 17, 32, 48 and 64 rows: 784 -> 791, 795 -> 807, 926 -> 937, 1032 -> 1056 us; where one in six or more is one they would
+// gain: 929 -> 954, 1051 -> 972, 1680 -> 1435, 1924 -> 1524).  From 12288 on the former is 0 to 0.3 %, the latter up to a half.
+// 16384 is the widest there is.  Up to 16 rows a column is rarely an outlier and the fp64 form's cost is half (one token tile).
 bool ps_gemm_digits_applies(int N, int K, int M) { return M > 16 && M <= 64 && N >= 12288 && N <= 16384 && K >= 4096; }
 
 // panels of 16 output rows per workgroup of ps_gemm: as many as still leave about one workgroup per compute unit
