@@ -1,6 +1,8 @@
 // Elementwise / per-row kernels of the span library: weight quantization into the
 // streaming tile order, LayerNorm, outlier-column detection, row-wise int8
 // quantization of activations, the blockwise 8-bit hidden-state codec, cache copies.
+#include <atomic>
+
 #include "common.h"
 #include "digits.h"
 #include "outlier_prep.h"
@@ -304,18 +306,24 @@ __global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restr
     }
 }
 
-// Workgroups that are resident at once (256 units, waves per SIMD by the kernel's registers): a grid of 1024 with room for
-// 768 ran the last 256 alone.
-constexpr int LN_ROWS_GRID[4] = {256 * 5, 256 * 3, 256 * 4, 256 * 3};   // PER = 1, 2, 4, 8
-
 template <bool Q8>
-void launch_layernorm_rows(const __half *x, const QuantIn &qin, const __half *g, const __half *b, float eps, int M, int H,
-                           __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
+hipError_t launch_layernorm_rows(const __half *x, const QuantIn &qin, const __half *g, const __half *b, float eps, int M, int H,
+                                 __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
     const int v = H <= 2048 ? 0 : H <= 4096 ? 1 : H <= 8192 ? 2 : 3;
-    const int grid = M < LN_ROWS_GRID[v] ? M : LN_ROWS_GRID[v];
     const uint32_t tb = ps_theta_to_bits(theta);
     auto kern = v == 0 ? k_layernorm_rows<1, Q8> : v == 1 ? k_layernorm_rows<2, Q8> : v == 2 ? k_layernorm_rows<4, Q8> : k_layernorm_rows<8, Q8>;
-    kern<<<grid, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
+    // Workgroups that are resident at once on the 256 units, by the kernel's registers (5, 3, 4 and 3 to a unit as compiled now): a
+    // grid of 1024 with room for 768 ran the last 256 alone (4096 rows of 4096 22.6 us, 21.5 this way).
+    static std::atomic<int> resident[4];
+    int per_unit = resident[v].load(std::memory_order_relaxed);
+    if (!per_unit) {
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_unit, kern, 256, 0);
+        if (e != hipSuccess) return e;
+        if (per_unit < 1) return hipErrorInvalidConfiguration;
+        resident[v].store(per_unit, std::memory_order_relaxed);
+    }
+    kern<<<M < 256 * per_unit ? M : 256 * per_unit, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
+    return hipGetLastError();
 }
 
 // -------------------------------------------------- many rows: mask, then quantize
@@ -866,16 +874,16 @@ hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float
     // and 242: the line lies between).  Rows below 4096 columns, of which 1024 threads would hold two pairs each or fewer,
     // always take 256 threads.
     if (H % 8 || H > 16384) return hipErrorInvalidValue;       // span and client take multiples of 64 up to 16384
-    if (M >= 256 || H < 4096) launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, flags, theta, st);
-    else (flags ? k_layernorm_wide<true> : k_layernorm_wide<false>)<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, flags, theta);
+    if (M >= 256 || H < 4096) return launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, flags, theta, st);
+    (flags ? k_layernorm_wide<true> : k_layernorm_wide<false>)<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, flags, theta);
     return hipGetLastError();
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
                            int H, __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
     // the line of ps_layernorm (measured there, on fp16 rows)
     if ((M >= 256 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
-        launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, flags, theta, st);
-    else if (M <= 256 && H >= 4096) (flags ? k_layernorm_q8<1024, true> : k_layernorm_q8<1024, false>)<<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
+        return launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, flags, theta, st);
+    if (M <= 256 && H >= 4096) (flags ? k_layernorm_q8<1024, true> : k_layernorm_q8<1024, false>)<<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
     else (flags ? k_layernorm_q8<256, true> : k_layernorm_q8<256, false>)<<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
     return hipGetLastError();
 }
