@@ -555,6 +555,7 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
         n_out = wave_reduce(n_out, 0u, [](uint32_t a, uint32_t b) { return a + b; });
         if ((threadIdx.x & 63) == 0) smc[threadIdx.x >> 6] = n_out;
         if (threadIdx.x == 0) big = 0;
+        static_assert(NT >= PS_DIGIT_DONE, "one thread clears each counter");
         if (t == 0 && threadIdx.x < PS_DIGIT_DONE) rd.done[threadIdx.x] = 0;
     }
     const float s = row_scale<NT / 64>(m, sm);

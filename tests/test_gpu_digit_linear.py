@@ -76,6 +76,29 @@ def test_linear_with_many_outlier_columns(span, M, share, kind):
     assert same.all(), "%d of %d outputs differ, rows %s" % ((~same).sum(), same.size, rows[np.unique(np.argwhere(~same)[:, 1])][:8])
 
 
+def test_outputs_that_leave_waves_and_workgroups_over():
+    """12352 outputs: 386 pairs of panels, two of them in the last of 49 workgroups."""
+    N, F = 12352, 4096
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N)
+    sp = binding.Span(1, N, N // 64, F, 64, device=DEV)
+    p = dict(w_qkv=torch.zeros((3 * N, N), device=DEV), w_dense=torch.zeros((N, N), device=DEV), w_up=torch.zeros((F, N), device=DEV),
+             w_down=torch.empty((N, F), device=DEV).normal_(0.0, 0.02, generator=g))
+    for n, s in (("b_qkv", 3 * N), ("b_dense", N), ("b_up", F), ("b_down", N), ("ln1_g", N), ("ln1_b", N), ("ln2_g", N), ("ln2_b", N)):
+        p[n] = torch.zeros(s, dtype=torch.float16, device=DEV)
+    sp.load_block(0, p)
+    del p
+    wq, sw = (to_np(v) for v in sp.export_weight(0, 3))
+    rows = np.concatenate([np.arange(16), np.arange(N - 160, N)])
+    for M in (17, 32, 33, 64):
+        x = _input(M, F, F // 2, "", M)
+        out = sp.debug_linear(0, 3, to_dev(x))
+        Y, dbg = oracle.linear(x, wq[rows], sw[rows], np.zeros(len(rows), np.float16), 6.0, 0, None, want_debug=True)
+        assert np.array_equal(to_np(out["acc"])[:, rows], dbg["acc"]), M
+        assert np.array_equal(to_np(out["y"])[:, rows].view(np.uint16), Y.view(np.uint16)), M
+    sp.close()
+
+
 @pytest.mark.parametrize("M", [17, 64])
 def test_every_call_adds_the_shares_in_the_same_order(span, M):
     """The workgroup that finishes an output is another one from call to call; the sums and their order are not."""
