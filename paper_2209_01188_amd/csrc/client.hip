@@ -97,44 +97,53 @@ __global__ void __launch_bounds__(LM_THREADS) k_lm_head(const __half *__restrict
 // multiple of 2^-24, so with balanced 8-bit digits x = 2^-24 sum_j 256^j d_j, d_j in [-128, 127], four digits cover
 // |x| < 127.5.  A product of two such values is the sum over the digit pairs (i, j) of 256^(i + j) d_i d_j: the pairs
 // with the same i + j share an int32 accumulator (at most 4 * 2^14 * 16384 = 2^30), and the seven sums (nine, see below) meet in fp64
-// once per logit - a few roundings of 2^-53 instead of one per column.  What was slow before: 16 fp64 matrix
-// instructions (64 clocks each) per 16 x 16 x 64 products against 16 int8 ones (16 clocks; 12 where the matrix tile
-// stays below 0.246, as embeddings do), and the passes over the matrix: up to four rows per pass with the hidden rows
-// as fp64 in LDS.  250880 x 4096, 8 rows: a call of 1080 us in two passes before, 398 us now (5.2 TB/s; every workgroup
-// starting at column 0 costs another 64 us, the digit arithmetic and the matrix instructions taken out change nothing: the
-// 16 rows' separate 64-byte pieces are what is left, contiguous reads take 45 us less).
+// once per logit - a few roundings of 2^-53 instead of one per column.
 //
-// The matrix is streamed once per 32 hidden rows: a wave owns WN tiles of 16 matrix rows (A operand) and walks their
-// columns 64 at a time; lane (row l%16, group l/16) holds columns 8 g .. +8 and 32 + 8 g .. +8 of the 64 as fp16, a
-// chunk of CH such pieces in flight in registers, and cuts them into digit planes itself (5 instructions per value).  The hidden rows' digits (k_lm_prepare) go through LDS, shared by the 8 waves, one
-// barrier per chunk.  Hidden values of 127.5 and more (a feature that dominates its row) have two digits more: a 64-column
-// piece in which any row has one is read a second time, for its products with digits 4 and 5 (one such feature, 250880 x
-// 4096, 8 rows: a call of 398 us becomes 408, all columns 816; with the whole product on the fp64 instruction instead,
-// 1000).  A tile of the matrix with a value of 127.5 or more, and every tile if a hidden row holds an infinity or NaN, is
-// done again on the fp64 matrix instruction, where nothing bounds the values.
-constexpr int LMD_CH = 4;                  // 64-column pieces per chunk
-constexpr uint32_t LMD_BIG = 0x57f8;       // fp16 bits of 127.5
+// The matrix is streamed once per 32 hidden rows: a wave owns WN tiles of 16 matrix rows (A operand) and walks their columns
+// 64 at a time.  What bounds it are the bytes of the matrix, if the memory sees long pieces: with every lane loading its own
+// operands (16 rows x 64 bytes per instruction) 250880 x 4096 at 8 rows took 398 us a call, and the arithmetic taken out
+// changed nothing.  So the pieces are copied to LDS asynchronously, 256 consecutive bytes of a row at a time, and read
+// from there in operand order (360 us; then the arithmetic counts: without it 326).  The wave cuts its values into digits
+// itself, 13 instructions per four values and one per pair for the largest magnitude, two pieces of 64 columns in one
+// straight line so that the matrix unit has work beside that (342 us, 6.0 TB/s; 14336 columns at 2 rows 1440 -> 1155;
+// 17 to 32 rows, where a digit read from LDS meets one matrix tile only and products and arithmetic are the bound, 484 ->
+// 470).  Every workgroup starts at another chunk: from column 0 on all of them fall on a few memory channels (417 us).
+// Two matrix tiles per wave also for 17 to 32 rows: 75 spilled registers, 731 us.  The hidden rows' digits (k_lm_prepare)
+// go through LDS as well, shared by the 8 waves, one barrier per chunk.
+//
+// Hidden values of 127.5 and more (a feature that dominates its row) have two digits more: a 64-column
+// piece in which any row has one is read a second time, for its products with digits 4 and 5; with the whole product on the fp64
+// instruction instead one such feature made a call of 398 us one of 1000.  A tile of the matrix with a value of 127 or
+// more, and every tile if a hidden row holds an infinity or NaN, is done again on the fp64 matrix instruction, where nothing
+// bounds the values.
+constexpr int LMD_CH = 2;                  // 64-column pieces per chunk
+constexpr uint32_t LMD_BIG = 0x57f8;       // fp16 bits of 127.5: from here on a hidden value takes digits 4 and 5
+constexpr uint32_t LMD_BIG_E = 0x57f0;     // fp16 bits of 127: from here on a matrix value takes more than four digits (it is moved by 1/4)
 constexpr uint32_t LMD_SMALL = 0x33e0;     // fp16 bits of 0.246: below it three digits do, and lm_planes_small holds
+constexpr int LMD_SHIFT = 0x400000;        // 1/4 in units of 2^-24
 
-// three planes of four values below LMD_SMALL in magnitude (two words of two halves).  x * 2^24 + 2^23 + 0x408080 is
-// exact in fp32 and its low bytes are the digits plus 0x80, 0x80 and 0x40: one multiply-add straight from fp16,
+// Matrix values are cut into digits after 1/4 has been added, so that the third digit of a small one is positive and comes out of
+// the sum below as it is; what that adds to the products, 64 times the sums of the hidden rows' digits, is taken off again,
+// exactly, before the sums meet.
+// Three planes of four values below LMD_SMALL in magnitude (two words of two halves).  x * 2^24 + 2^23 + 0x408080 is
+// exact in fp32 and its low bytes are the digits of x + 1/4 plus 0x80, 0x80 and 0: one multiply-add straight from fp16,
 // then byte permutations.
 __device__ __forceinline__ void lm_planes_small(uint32_t w0, uint32_t w1, int (&p)[4]) {
     const uint32_t hb[4] = {w0 & 0xffffu, w0 >> 16, w1 & 0xffffu, w1 >> 16};
     uint32_t u[4];
 #pragma unroll
     for (int i = 0; i < 4; i++)
-        u[i] = __float_as_uint(fmaf(__half2float(__ushort_as_half((unsigned short)hb[i])), 16777216.0f, 8388608.0f + 0x408080));
+        u[i] = __float_as_uint(fmaf(__half2float(__ushort_as_half((unsigned short)hb[i])), 16777216.0f, 8388608.0f + (LMD_SHIFT + 0x8080)));
     const uint32_t a = __builtin_amdgcn_perm(u[1], u[0], 0x05010400), b = __builtin_amdgcn_perm(u[3], u[2], 0x05010400);
     const uint32_t c = __builtin_amdgcn_perm(u[1], u[0], 0x0c0c0602), d = __builtin_amdgcn_perm(u[3], u[2], 0x0c0c0602);
     p[0] = (int)(__builtin_amdgcn_perm(b, a, 0x05040100) ^ 0x80808080u);
     p[1] = (int)(__builtin_amdgcn_perm(b, a, 0x07060302) ^ 0x80808080u);
-    const uint32_t t = __builtin_amdgcn_perm(d, c, 0x05040100);            // bytes 0 .. 0x7f: the digits plus 0x40
-    p[2] = (int)(((t ^ 0x80808080u) - 0x40404040u) ^ 0x80808080u);
+    p[2] = (int)__builtin_amdgcn_perm(d, c, 0x05040100);                   // 1 .. 0x7f
 }
 
-__device__ __forceinline__ uint32_t lm_digits(float f) {       // bytes = the four digits (|f| < 127.5)
-    return ((uint32_t)(int)(f * 16777216.0f) + 0x80808080u) ^ 0x80808080u;
+template <int SHIFT = 0>
+__device__ __forceinline__ uint32_t lm_digits(float f) {       // bytes = the four digits of f (+ SHIFT * 2^-24), below 127.5 in magnitude
+    return ((uint32_t)(int)(f * 16777216.0f) + (0x80808080u + SHIFT)) ^ 0x80808080u;
 }
 // four values' digit words -> one word per plane (byte k = value k)
 __device__ __forceinline__ void lm_planes(const uint32_t (&u)[4], int (&p)[4]) {
@@ -155,13 +164,14 @@ __device__ __forceinline__ uint32_t lm_digits_wide(float f, int &d4, int &d5) {
     return (((uint32_t)(int)(fmaf(y, -256.0f, f) * 16.0f) << 20) + 0x80808080u) ^ 0x80808080u;
 }
 
-// What k_lm_prepare says of a hidden row: whether it holds an infinity or NaN, whether any value needs digits 4 and 5, and
-// the 64-column pieces with such values.
+// What k_lm_prepare says of a hidden row: whether it holds an infinity or NaN, whether any value needs digits 4 and 5,
+// the 64-column pieces with such values, and the sums of its digits.
 constexpr int LM_PIECE_WORDS = LM_MAX_HIDDEN / 64 / 32;
 enum { LM_NONFINITE = 1, LM_WIDE = 2 };
 struct LmRow {
     int flags;
     uint32_t wide[LM_PIECE_WORDS];
+    int sum[4];                // of the row's digits 0 to 3, plane by plane
 };
 
 // LayerNorm of one hidden row per workgroup: the fp16 row to a (what the fp64 form reads), its digit planes 0 to 3 to
@@ -182,6 +192,7 @@ __global__ void __launch_bounds__(512) k_lm_prepare(const __half *__restrict__ x
     const bool live = t < rows;
     v8h v[PER];
     double s = 0.0, q = 0.0, mean = 0.0, inv = 0.0;
+    int sum[4] = {0, 0, 0, 0};
     if (live) {
 #pragma unroll
         for (int i = 0; i < PER; i++) {
@@ -234,6 +245,9 @@ __global__ void __launch_bounds__(512) k_lm_prepare(const __half *__restrict__ x
                 *(v8h *)(a + (size_t)t * H + k) = *(const v8h *)out;
                 lm_planes(u[0], lo);
                 lm_planes(u[1], hi);
+#pragma unroll
+                for (int pl = 0; pl < 4; pl++)
+                    sum[pl] = __builtin_amdgcn_sdot4(hi[pl], 0x01010101, __builtin_amdgcn_sdot4(lo[pl], 0x01010101, sum[pl], false), false);
             }
 #pragma unroll
             for (int pl = 0; pl < 4; pl++)
@@ -242,6 +256,11 @@ __global__ void __launch_bounds__(512) k_lm_prepare(const __half *__restrict__ x
             for (int pl = 0; pl < 2; pl++)
                 *(v2i *)(dig2 + (((size_t)(kt * 2 + pl) * MT + mt) * 64 + gg * 16 + row) * 16 + h * 8) = (v2i){(int)up[pl][0], (int)up[pl][1]};
         }
+    }
+#pragma unroll
+    for (int pl = 0; pl < 4; pl++) {
+        const int w = (int)wave_sum((float)sum[pl]);          // at most 64 x 32 x 128: exact
+        if ((threadIdx.x & 63) == 0) atomicAdd(&here.sum[pl], w);
     }
     __syncthreads();
     if (threadIdx.x < sizeof(LmRow) / 4) ((uint32_t *)&info[t])[threadIdx.x] = ((const uint32_t *)&here)[threadIdx.x];
@@ -269,18 +288,41 @@ __device__ __forceinline__ void lm_tile_f64(const __half *__restrict__ er, const
     }
 }
 
+// LDS of k_lm_head_digits: per wave a ring of matrix pieces (16 WN rows x LMD_CH * 128 bytes each), then a ring of the hidden
+// rows' digits for as many pieces, shared by the workgroup.  64 to 128 KB of the matrix are in flight per compute unit.
+template <int WN, int MT>
+struct LmLds {
+    static constexpr int SLOT = WN * 16 * LMD_CH * 128, RING = WN == 2 ? 2 : 3;
+    static constexpr int DIGITS = LMD_CH * 4 * MT * 1024, BYTES = RING * (8 * SLOT + DIGITS);
+};
+
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ v2h lm_max_abs(v2h m, v2h x) {     // one instruction; NaN wins
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, x), -x);
+}
+// one asynchronous copy of 64 x 16 bytes to LDS, in the order of the lanes; zeros from `bytes` on
+template <int AUX>
+__device__ __forceinline__ void lm_copy16(const void *base, int bytes, unsigned char *to, uint32_t offset) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void *)base, 0, bytes, 0x00020000),
+                                             (__attribute__((address_space(3))) void *)to, 16, offset, 0, 0, AUX);
+}
+
 template <int WN, int MT>
 __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restrict__ a, const uint8_t *__restrict__ dig,
                                                            const uint8_t *__restrict__ dig2, const LmRow *__restrict__ info, int rows,
                                                            const __half *__restrict__ E,
                                                            int V, int H, float *__restrict__ logits, Best *__restrict__ partial) {
-    constexpr int CH = LMD_CH, CHUNK = CH * 4 * MT * 1024, SR = CHUNK / (512 * 16);
-    __shared__ __align__(16) unsigned char stage[2][CHUNK];
+    constexpr int CH = LMD_CH, RING = LmLds<WN, MT>::RING, SLOT = LmLds<WN, MT>::SLOT, DIGITS = LmLds<WN, MT>::DIGITS;
+    constexpr int NE = SLOT / 1024, ND = DIGITS / 8192;      // copies a wave asks for per chunk: matrix, digits
+    constexpr int SEGS = CH * 8, RPI = 64 / SEGS;            // 16-byte segments of a row in a slot, rows per copy
+    extern __shared__ __align__(16) unsigned char lds[];
     __shared__ Best wbest[8][MT * 16];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    unsigned char *ring = lds + wave * (RING * SLOT), *dstage = lds + 8 * RING * SLOT;
     const int KT = H >> 6, nch = (KT + CH - 1) / CH, ntiles = (V + 15) >> 4;
-    const size_t dig_last = (size_t)KT * 4 * MT * 1024 - 16;
     __shared__ uint32_t wide[LM_PIECE_WORDS];                // pieces of any row with digits 4 and 5
+    __shared__ int dsum[MT * 16][4];                         // 64 times the sums of the hidden rows' digits (read behind many barriers)
+    if (threadIdx.x < MT * 64) dsum[threadIdx.x >> 2][threadIdx.x & 3] = info[threadIdx.x >> 2].sum[threadIdx.x & 3] * (LMD_SHIFT >> 16);
     const int flags = lane < rows ? info[lane].flags : 0;    // (every wave by itself: no barrier in front of the first requests)
     const bool all_f64 = __any(flags & LM_NONFINITE), any_wide = __any(flags & LM_WIDE);
     if (any_wide) {                                          // rare; the same in all waves
@@ -296,49 +338,58 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
 #pragma unroll
     for (int j = 0; j < MT; j++) best[j] = Best{-INFINITY, 0x7fffffff};
 
-    // The pipeline runs through the rounds of a workgroup without draining: behind the last chunk of a round come the
-    // first chunk of the next one (rows clamped into the matrix) and the digits of chunk 0.  All its requests are
-    // unconditional: where two paths with different numbers of loads in flight meet, the compiler waits for all of them.
-    v4i e[CH][WN][2], sr[SR];
-    const __half *er[WN];
-    auto row_ptrs = [&](int grp, const __half *(&ptr)[WN]) {
+    // Copies: one takes RPI rows x SEGS segments of a slot, in the order of the lanes; segment s of row r lies at position
+    // s ^ (r & SEGS - 1) of the row, so that the 16 rows a lane group reads one segment of do not share banks.  Rows beyond
+    // the matrix and chunks beyond the last round are out of the descriptor's bounds and read as zeros, the columns behind a
+    // ragged last piece are not used.  (Offsets sit in the vector operand: the check against the bounds is sure to see them.)
+    uint32_t voff[NE];
 #pragma unroll
-        for (int p = 0; p < WN; p++) ptr[p] = E + (size_t)min(((grp * 8 + wave) * WN + p) * 16 + c, V - 1) * H + g * 8;
+    for (int j = 0; j < NE; j++) {
+        const int r = j * RPI + lane / SEGS;
+        voff[j] = (uint32_t)r * (uint32_t)(H * 2) + (((lane & (SEGS - 1)) ^ (r & (SEGS - 1))) << 4);
+    }
+    const __half *pbase = E;                                 // this wave's rows of the round that is being requested, and their bytes
+    int pbytes = 0;
+    auto rows_of = [&](int grp) {
+        const long long row0 = (long long)(grp * 8 + wave) * (WN * 16), left = grp * 8 * WN < ntiles ? (long long)V - row0 : 0;
+        pbase = E + (left > 0 ? row0 : 0) * H;
+        pbytes = left > 0 ? (int)min(left, (long long)WN * 16) * H * 2 : 0;
     };
-    auto load_e = [&](int u, const __half *const (&ptr)[WN], int kt) {
+    auto load_e = [&](int slot, int ch) {
 #pragma unroll
-        for (int p = 0; p < WN; p++) {
-            const __half *src = ptr[p] + (size_t)min(kt, KT - 1) * 64;
-            e[u][p][0] = __builtin_nontemporal_load((const v4i *)src);
-            e[u][p][1] = __builtin_nontemporal_load((const v4i *)(src + 32));
-        }
+        for (int j = 0; j < NE; j++)
+            lm_copy16<2 /* non-temporal */>(pbase, pbytes, ring + slot * SLOT + j * 1024, voff[j] + ch * (CH * 128));
     };
-    auto load_s = [&](int ch) {
+    auto load_d = [&](int buf, int ch) {
 #pragma unroll
-        for (int i = 0; i < SR; i++) {
-            const size_t off = (size_t)ch * CHUNK + i * 8192 + threadIdx.x * 16;
-            sr[i] = *(const v4i *)(dig + (off < dig_last ? off : dig_last));
-        }
-    };
-    auto store_s = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < SR; i++) *(v4i *)(stage[buf] + i * 8192 + threadIdx.x * 16) = sr[i];
+        for (int j = 0; j < ND; j++)
+            lm_copy16<0>(dig, KT * 4 * MT * 1024, dstage + buf * DIGITS + (wave + 8 * j) * 1024, ch * DIGITS + (wave + 8 * j) * 1024 + lane * 16);
     };
     // Every workgroup starts its rows at another chunk and wraps around: rows are a power of two or so of bytes apart,
     // and with all workgroups at the same column the requests of the whole device fall on a few memory channels.
     const int rot = (blockIdx.x >> 3) % nch;
-    int buf = 0;
-    row_ptrs(blockIdx.x, er);
+    // The ring runs through the rounds of a workgroup without draining.  (pg, pi, pch): round, index and chunk that the next
+    // request of matrix pieces is for, dch: the chunk of digits that is, slot: the place of the chunk at hand in both rings.
+    int pg = blockIdx.x, pi = 0, pch = rot, dch = rot, slot = 0;
+    rows_of(pg);
+    auto request = [&](int s) {
+        load_e(s, pch);
+        pch = pch + 1 == nch ? 0 : pch + 1;
+        if (++pi == nch) { pi = 0; pch = rot; pg += gridDim.x; rows_of(pg); }
+    };
+    auto request_digits = [&](int s) {
+        load_d(s, dch);
+        dch = dch + 1 == nch ? 0 : dch + 1;
+    };
     if (!all_f64) {
-        load_s(rot);
 #pragma unroll
-        for (int u = 0; u < CH; u++) load_e(u, er, rot * CH + u);
-        store_s(0);
+        for (int s = 0; s < RING; s++) {
+            if (s < RING - 1) request_digits(s);
+            request(s);
+        }
     }
     for (int grp = blockIdx.x; grp * 8 * WN < ntiles; grp += gridDim.x) {       // the same rounds for the whole workgroup
         const int vt0 = (grp * 8 + wave) * WN;
-        const __half *en[WN];
-        row_ptrs(grp + gridDim.x, en);
         v4i acc[WN][MT][9];
 #pragma unroll
         for (int p = 0; p < WN; p++)
@@ -349,36 +400,74 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
         bool slow = all_f64;
         if (!all_f64) {
             int ch = rot;
-            for (int i_ch = 0; i_ch < nch; i_ch++, buf ^= 1) {
-                const bool last = i_ch + 1 == nch;                       // then ch_next is rot again, of the next round
-                const int ch_next = ch + 1 == nch ? 0 : ch + 1;
-                const __half *nx[WN];
+            for (int i_ch = 0; i_ch < nch; i_ch++) {
+                // This chunk has landed: matrix pieces are asked for RING chunks ahead, digits RING - 1 (before the pieces of
+                // the same step), so behind this chunk's digits there are RING - 1 chunks' pieces and RING - 2 chunks' digits
+                // in flight.  Later stores only make the wait longer.
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NE + (RING - 2) * (NE + ND)) : "memory");
+                __builtin_amdgcn_s_barrier();    // ... in all waves, and everybody is done with the digits of the chunk before
+                asm volatile("" ::: "memory");
+                request_digits(slot == 0 ? RING - 1 : slot - 1);
+                v4i e[CH][WN][2];
 #pragma unroll
-                for (int p = 0; p < WN; p++) nx[p] = last ? en[p] : er[p];
-                load_s(ch_next);
-                lds_barrier();                   // this chunk's digits are there; everybody is done with the chunk before
-#pragma unroll
-                for (int u = 0; u < CH; u++) {
-                    const int kt = ch * CH + u;
-                    uint32_t mx = 0;                         // largest magnitude bits of this lane's values
+                for (int u = 0; u < CH; u++)
 #pragma unroll
                     for (int p = 0; p < WN; p++)
 #pragma unroll
-                        for (int i = 0; i < 8; i++) mx = pk_max_u16(mx, (uint32_t)e[u][p][i >> 2][i & 3] & 0x7fff7fffu);
-                    mx = max(mx & 0xffffu, mx >> 16);
-                    const bool four = __any(mx >= LMD_SMALL);
-                    v4i d[WN][4];
-                    if (!four) {
+                        for (int h = 0; h < 2; h++)
+                            e[u][p][h] = *(const v4i *)(ring + slot * SLOT + (p * 16 + c) * (CH * 128) + (((u * 8 + h * 4 + g) ^ ((p * 16 + c) & (SEGS - 1))) << 4));
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the slot is free again
+                request(slot);
+                const unsigned char *sb = dstage + slot * DIGITS + lane * 16;
+                v2h big[CH];                             // largest magnitudes of this lane's values (NaN if there is one)
+#pragma unroll
+                for (int u = 0; u < CH; u++) {
+                    big[u] = (v2h){(_Float16)0.0f, (_Float16)0.0f};
+#pragma unroll
+                    for (int p = 0; p < WN; p++)
+#pragma unroll
+                        for (int i = 0; i < 8; i++) {
+                            const int word = e[u][p][i >> 2][i & 3];
+                            big[u] = lm_max_abs(big[u], *(const v2h *)&word);
+                        }
+                }
+                static_assert(CH == 2, "pieces of a chunk");
+                const v2h both = lm_max_abs(big[0], big[1]);
+                const uint32_t bits = *(const uint32_t *)&both & 0x7fff7fffu;
+                const bool full = ch * CH + CH <= KT;
+                if (full && !__any(max(bits & 0xffffu, bits >> 16) >= LMD_SMALL)) {
+                    // nearly always: straight-line, so that one piece's arithmetic runs beside the other's products
+#pragma unroll
+                    for (int u = 0; u < CH; u++) {
+                        v4i d[WN][3];
 #pragma unroll
                         for (int p = 0; p < WN; p++)
 #pragma unroll
-                            for (int q = 0; q < 4; q++) {    // values 4 q .. +4 of this lane's 16
+                            for (int q = 0; q < 4; q++) {        // values 4 q .. +4 of this lane's 16
                                 int pl[4];
                                 lm_planes_small((uint32_t)e[u][p][q >> 1][2 * (q & 1)], (uint32_t)e[u][p][q >> 1][2 * (q & 1) + 1], pl);
 #pragma unroll
                                 for (int i = 0; i < 3; i++) d[p][i][q] = pl[i];
                             }
-                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; j++)
+#pragma unroll
+                            for (int m = 0; m < MT; m++) {
+                                const v4i xb = *(const v4i *)(sb + ((u * 4 + j) * MT + m) * 1024);
+#pragma unroll
+                                for (int i = 0; i < 3; i++)
+#pragma unroll
+                                    for (int p = 0; p < WN; p++)
+                                        acc[p][m][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[p][i], xb, acc[p][m][i + j], 0, 0, 0);
+                            }
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < CH; u++) {
+                        if (ch * CH + u >= KT) continue;         // ragged last chunk
+                        const uint32_t ub = *(const uint32_t *)&big[u] & 0x7fff7fffu;
+                        slow |= (bool)__any(max(ub & 0xffffu, ub >> 16) >= LMD_BIG_E);
+                        v4i d[WN][4];
 #pragma unroll
                         for (int p = 0; p < WN; p++)
 #pragma unroll
@@ -388,41 +477,26 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                                 uint32_t dw[4];
                                 int pl[4];
 #pragma unroll
-                                for (int i = 0; i < 4; i++) dw[i] = lm_digits(__half2float(__ushort_as_half((unsigned short)hb[i])));
+                                for (int i = 0; i < 4; i++) dw[i] = lm_digits<LMD_SHIFT>(__half2float(__ushort_as_half((unsigned short)hb[i])));
                                 lm_planes(dw, pl);
 #pragma unroll
                                 for (int i = 0; i < 4; i++) d[p][i][q] = pl[i];
                             }
-                        slow |= (bool)__any(mx >= LMD_BIG);
-                    }
-                    load_e(u, nx, ch_next * CH + u);              // the same piece of the next chunk
-                    if (kt >= KT) continue;                  // ragged last chunk
-                    const unsigned char *sb = stage[buf] + (size_t)u * 4 * MT * 1024 + lane * 16;
-#pragma unroll
-                    for (int j = 0; j < 4; j++)
-#pragma unroll
-                        for (int m = 0; m < MT; m++) {
-                            const v4i xb = *(const v4i *)(sb + (j * MT + m) * 1024);
-#pragma unroll
-                            for (int i = 0; i < 3; i++)
-#pragma unroll
-                                for (int p = 0; p < WN; p++)
-                                    acc[p][m][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[p][i], xb, acc[p][m][i + j], 0, 0, 0);
-                        }
-                    if (four) {
 #pragma unroll
                         for (int j = 0; j < 4; j++)
 #pragma unroll
                             for (int m = 0; m < MT; m++) {
-                                const v4i xb = *(const v4i *)(sb + (j * MT + m) * 1024);
+                                const v4i xb = *(const v4i *)(sb + ((u * 4 + j) * MT + m) * 1024);
 #pragma unroll
-                                for (int p = 0; p < WN; p++)
-                                    acc[p][m][3 + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[p][3], xb, acc[p][m][3 + j], 0, 0, 0);
+                                for (int i = 0; i < 4; i++)
+#pragma unroll
+                                    for (int p = 0; p < WN; p++)
+                                        acc[p][m][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[p][i], xb, acc[p][m][i + j], 0, 0, 0);
                             }
                     }
                 }
-                store_s(buf ^ 1);
-                ch = ch_next;
+                ch = ch + 1 == nch ? 0 : ch + 1;         // behind the last chunk comes the first of the next round
+                slot = slot + 1 == RING ? 0 : slot + 1;
             }
             if (any_wide) {                                  // digits 4 and 5 of the hidden rows, piece by piece
                 for (int wi = 0; wi < LM_PIECE_WORDS; wi++)
@@ -430,10 +504,11 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                         const int kt = wi * 32 + __ffs((int)left) - 1;
 #pragma unroll
                         for (int p = 0; p < WN; p++) {
+                            const __half *er = E + (size_t)min((vt0 + p) * 16 + c, V - 1) * H + g * 8;
                             v4i d[4];
 #pragma unroll
                             for (int h = 0; h < 2; h++) {
-                                const v4i w = *(const v4i *)(er[p] + (size_t)kt * 64 + h * 32);
+                                const v4i w = *(const v4i *)(er + (size_t)kt * 64 + h * 32);
 #pragma unroll
                                 for (int q = 0; q < 2; q++) {
                                     const uint32_t w0 = (uint32_t)w[2 * q], w1 = (uint32_t)w[2 * q + 1];
@@ -465,7 +540,7 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
             if (vt0 + p >= ntiles) continue;                 // wave-uniform
             v4d val[MT];
             if (slow) {
-                lm_tile_f64<MT>(er[p], a, rows, H, val);
+                lm_tile_f64<MT>(E + (size_t)min((vt0 + p) * 16 + c, V - 1) * H + g * 8, a, rows, H, val);
             } else {
 #pragma unroll
                 for (int j = 0; j < MT; j++)
@@ -473,7 +548,7 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                     for (int r = 0; r < 4; r++) {
                         double t = (double)acc[p][j][8][r];
 #pragma unroll
-                        for (int s = 7; s >= 0; s--) t = t * 256.0 + (double)acc[p][j][s][r];
+                        for (int s = 7; s >= 0; s--) t = t * 256.0 + (double)(acc[p][j][s][r] - (s >= 2 && s < 6 ? dsum[j * 16 + c][s - 2] : 0));
                         val[j][r] = t * 0x1p-48;
                     }
             }
@@ -494,9 +569,8 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                 }
             }
         }
-#pragma unroll
-        for (int p = 0; p < WN; p++) er[p] = en[p];
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // nothing may land in LDS after the workgroup's end
     // the four lane groups of a wave hold candidates of the same hidden rows, then the waves
 #pragma unroll
     for (int j = 0; j < MT; j++) {
@@ -514,6 +588,25 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
         for (int w2 = 1; w2 < 8; w2++) take_better(r, wbest[w2][threadIdx.x].v, wbest[w2][threadIdx.x].i);
         partial[threadIdx.x * LM_GROUPS + blockIdx.x] = r;
     }
+}
+
+template <int WN, int MT>
+hipError_t lm_head_digits(int groups, const __half *a, const uint8_t *dig, const uint8_t *dig2, const LmRow *info, int rows,
+                          const __half *E, int V, int H, float *logits, Best *partial, hipStream_t st) {
+    constexpr int lds = LmLds<WN, MT>::BYTES;
+    auto kern = k_lm_head_digits<WN, MT>;
+    static std::mutex attr_lock;
+    static bool attr_set = false;
+    {
+        std::lock_guard<std::mutex> hold(attr_lock);
+        if (!attr_set) {
+            hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    kern<<<groups, 512, lds, st>>>(a, dig, dig2, info, rows, E, V, H, logits, partial);
+    return hipGetLastError();
 }
 
 // the best of the workgroups' candidates of each hidden row
@@ -1201,10 +1294,10 @@ int petals_client_lm_head(petals_client *c, const void *hidden_in, int32_t M, fl
         if (H <= 4096) k_lm_prepare<1><<<16 * mt, 512, 0, st>>>(xr, lng, lnb, c->cfg.ln_eps, rows, H, mt, a, c->dig, c->dig2, c->info);
         else k_lm_prepare<4><<<16 * mt, 512, 0, st>>>(xr, lng, lnb, c->cfg.ln_eps, rows, H, mt, a, c->dig, c->dig2, c->info);
         HIP_TRY(hipGetLastError());
-        if (wn == 2) k_lm_head_digits<2, 1><<<groups, 512, 0, st>>>(a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial);
-        else if (mt == 2) k_lm_head_digits<1, 2><<<groups, 512, 0, st>>>(a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial);
-        else k_lm_head_digits<1, 1><<<groups, 512, 0, st>>>(a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial);
-        HIP_TRY(hipGetLastError());
+        hipError_t e = wn == 2   ? lm_head_digits<2, 1>(groups, a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial, st)
+                       : mt == 2 ? lm_head_digits<1, 2>(groups, a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial, st)
+                                 : lm_head_digits<1, 1>(groups, a, c->dig, c->dig2, c->info, rows, E, V, H, lg, c->partial, st);
+        HIP_TRY(e);
         if (next_token_out) {
             k_lm_pick<<<rows, 64, 0, st>>>(c->partial, groups, next_token_out + m0);
             HIP_TRY(hipGetLastError());

@@ -68,6 +68,18 @@ def test_lm_head_of_several_rows(V, H, M, kind):
     cl.close()
 
 
+# Matrix values are moved by 1/4 before they are cut: the last ones that four digits hold, and those behind them; chunks of 128
+# columns over several rounds of workgroups, one of the chunks ragged
+@pytest.mark.parametrize("value", [126.9375, -126.9375, 127.0, -127.0, 127.4375, -127.4375, -127.5, 128.0])
+@pytest.mark.parametrize("V,H,M", [(70003, 192, 3), (1000, 64, 17), (5000, 448, 9)])
+def test_lm_head_of_matrix_values_about_the_last_of_four_digits(V, H, M, value):
+    r = np.random.default_rng(V + H)
+    E = (r.standard_normal((V, H)) * 0.02).astype(np.float16)
+    E[V // 2, H - 1] = E[17, 0] = E[V - 1, 33] = value
+    x = (r.standard_normal((M, H)) * 2.0).astype(np.float16)
+    _check(E, np.ones(H, np.float16), np.zeros(H, np.float16), x)
+
+
 def _check(E, gain, bias, x, finite=True):
     V, (M, H) = E.shape[0], x.shape
     cl = binding.Client(to_dev(E), to_dev(gain), to_dev(bias), to_dev(gain), to_dev(bias), max_rows=M)
