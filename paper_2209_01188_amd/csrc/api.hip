@@ -105,6 +105,7 @@ Workspace carve(const petals_span_config &c, uint8_t *base, bool with_digits = t
         w.digits.rowstate = w.ocount;
         w.digits.done = (int *)take(PS_DIGIT_DONE * 4);
     }
+    w.step = ps_decode_row_applies((int)H, (int)F, (int)H / c.n_heads, c.n_blocks) ? (uint32_t *)take(PS_STEP_WORDS(H, F) * 4) : nullptr;
     w.total = off;
     return w;
 }
@@ -244,6 +245,30 @@ int forward_blocks(petals_span *sp, int M, int T, int max_keys, const __half *hi
     return PETALS_OK;
 }
 
+// All blocks of a narrow span on one row in one launch.  (A profiled call takes the separate launches, which it times.)
+int forward_row(petals_span *sp, int max_keys, const __half *hidden_in, __half *hidden_out, hipStream_t st, const QuantIn *qin) {
+    const petals_span_config &c = sp->cfg;
+    const BlockW &B = sp->blocks[0];
+    StepArgs s;
+    memset(&s, 0, sizeof(s));
+    for (int i = 0; i < 4; i++) s.lin[i] = B.lin[i];
+    s.ln1g = B.ln1g; s.ln1b = B.ln1b; s.ln2g = B.ln2g; s.ln2b = B.ln2b;
+    s.stride = block_weight_bytes(c);
+    s.n_blocks = c.n_blocks; s.H = c.hidden; s.F = c.ffn; s.nh = c.n_heads;
+    s.eps = c.ln_eps;
+    s.theta_bits = ps_theta_to_bits(c.outlier_threshold);
+    s.x = hidden_in;
+    if (qin) { s.q8 = qin->q; s.q8_absmax = qin->absmax; s.q8_block = qin->block; }
+    s.out = hidden_out;
+    s.sess = sp->ws.table;
+    s.words = sp->ws.step;
+    s.ticket = (int *)(s.words + (size_t)6 * c.hidden + c.ffn);
+    s.done = s.ticket + 64;
+    s.partials = sp->ws.partials;
+    HIP_TRY(ps_decode_row(s, c.hidden / c.n_heads, max_keys, st));
+    return PETALS_OK;
+}
+
 // Checks, session table, the blocks, session lengths: the body of every forward call.  Works on sp->ws.
 int run_call(petals_span *sp, petals_session *const *sessions, int32_t B, int32_t T, const void *hidden_in,
              void *hidden_out, hipStream_t st, const QuantIn *qin_arg = nullptr) {
@@ -274,7 +299,9 @@ int run_call(petals_span *sp, petals_session *const *sessions, int32_t B, int32_
 
     Workspace &ws = sp->ws;
     const int M = B * T;
-    HIP_TRY(ps_call_setup(tab, ws.table, ws.masks, ps_mask_clear_words(c, ws, M), st));
+    const bool row = M == 1 && ws.step && !sp->prof.on;
+    HIP_TRY(row ? ps_call_setup(tab, ws.table, ws.step, PS_STEP_WORDS(c.hidden, c.ffn), st)
+                : ps_call_setup(tab, ws.table, ws.masks, ps_mask_clear_words(c, ws, M), st));
     QuantIn qin;
     if (qin_arg) {
         // the decoded rows live in the buffer that only the outputs of odd blocks use: block 0 reads them (LayerNorm,
@@ -282,8 +309,9 @@ int run_call(petals_span *sp, petals_session *const *sessions, int32_t B, int32_
         qin = *qin_arg;
         qin.x_out = ws.xb;
     }
-    if (int rc = forward_blocks(sp, M, T, max_keys, (const __half *)hidden_in, (__half *)hidden_out, nullptr, st,
-                                qin_arg ? &qin : nullptr)) return rc;
+    if (int rc = row ? forward_row(sp, max_keys, (const __half *)hidden_in, (__half *)hidden_out, st, qin_arg)
+                     : forward_blocks(sp, M, T, max_keys, (const __half *)hidden_in, (__half *)hidden_out, nullptr, st,
+                                      qin_arg ? &qin : nullptr)) return rc;
     for (int s = 0; s < B; s++) sessions[s]->len += T;
     return PETALS_OK;
 }

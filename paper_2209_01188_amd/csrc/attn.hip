@@ -7,6 +7,7 @@
 #include <mutex>
 #include <utility>
 
+#include "attn_state.h"
 #include "common.h"
 #include "digits.h"
 
@@ -466,11 +467,6 @@ hipError_t launch_prefill_split(const __half *q, const SessTable *sess, int blk,
     return hipGetLastError();
 }
 
-template <typename F, int... I>
-__device__ __forceinline__ void for_constants(F f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>()), ...);
-}
-
 // Decode (one query per session): every wave owns a contiguous slice of the key range and runs
 // its own online softmax over 64-key blocks with no workgroup barrier in the loop.  Inside a
 // wave, head_dim/8 neighbouring lanes share a key (16 bytes of it each), so one load
@@ -554,44 +550,16 @@ __global__ void __launch_bounds__(64 * NW) k_attn_decode(const __half *__restric
         };
         for_constants(add_value, std::make_integer_sequence<int, NIT>());
     }
-    // merge the lane groups of the wave (same dims, different keys)
-    // the wave's maximum first, then every group's sums scaled to it and added up
-    {
-        double mw = m_run;
+    merge_wave<LPK>(m_run, l_run, o);
+    if (lane == 0) { red_m[wave] = m_run; red_l[wave] = l_run; }
 #pragma unroll
-        for (int off = LPK; off < 16; off <<= 1) mw = fmax(mw, __shfl_xor(mw, off));
-        mw = swap_reduce<32>(swap_reduce<16>(mw, max_f64), max_f64);
-        const double f = (m_run == -INFINITY) ? 0.0 : exp_f64(m_run - mw);
-        m_run = mw;
-        l_run *= f;
-#pragma unroll
-        for (int e = 0; e < 8; e++) o[e] *= f;
-#pragma unroll
-        for (int off = LPK; off < 16; off <<= 1) {
-            l_run += __shfl_xor(l_run, off);
-#pragma unroll
-            for (int e = 0; e < 8; e++) o[e] += __shfl_xor(o[e], off);
-        }
-        l_run = swap_reduce<32>(swap_reduce<16>(l_run, add_f64), add_f64);
-#pragma unroll
-        for (int e = 0; e < 8; e++) o[e] = swap_reduce<32>(swap_reduce<16>(o[e], add_f64), add_f64);
-    }
-    if (kslot == 0) {
-        if (sub == 0) { red_m[wave] = m_run; red_l[wave] = l_run; }
-#pragma unroll
-        for (int e = 0; e < 8; e++) red_o[wave][sub * 8 + e] = o[e];
-    }
+    for (int e = 0; e < (LPK + 7) / 8; e++) red_o[wave][merged_dim<LPK>(lane) + e] = o[e];
     __syncthreads();
-    if (threadIdx.x < D) {
-        double m = red_m[0], l = 0.0, ov = 0.0;
-#pragma unroll
-        for (int w2 = 1; w2 < NW; w2++) m = fmax(m, red_m[w2]);
-#pragma unroll
-        for (int w2 = 0; w2 < NW; w2++) {
-            const double f = (red_m[w2] == -INFINITY) ? 0.0 : exp_f64(red_m[w2] - m);
-            l += f * red_l[w2];
-            ov += f * red_o[w2][threadIdx.x];
-        }
+    // (with all lanes of the waves that hold a dim: the scales of the waves are exchanged between lanes)
+    if (wave * 64 < D) {
+        double m, l;
+        const double ov = merge_waves<NW, D>(red_m, red_l, red_o, lane, min((int)threadIdx.x, D - 1), m, l);
+        if (threadIdx.x >= D) return;
         if (nsplit == 1) {
             const __half hv = d2h_rn(ov / l);
             ctx[(size_t)s * H + h * D + threadIdx.x] = hv;

@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "f64math.h"
 
@@ -160,6 +161,31 @@ struct RowDebug {
 hipError_t ps_gemv_row(const LinearW &w, const __half *x, const __half *ln_g, const __half *ln_b, float eps,
                        float theta, const RowDebug &dbg, const OutDesc &o, const SessTable *sess, const QuantIn *qin,
                        hipStream_t st);
+// One token of one session through all blocks of a narrow span, one launch (decode_row.hip).  lin, ln*: block 0's; block b's lie
+// b * stride bytes further.
+struct StepArgs {
+    LinearW lin[4];
+    const __half *ln1g, *ln1b, *ln2g, *ln2b;
+    size_t stride;
+    int n_blocks, H, F, nh;
+    float eps;
+    uint32_t theta_bits;
+    const __half *x;             // input row, or (q8 not null) its codes
+    const uint8_t *q8;
+    const float *q8_absmax;
+    int q8_block;
+    __half *out;
+    const SessTable *sess;
+    uint32_t *words;             // [PS_STEP_WORDS(H, F)], cleared before the launch: rows on their way, then ticket and done
+    int *ticket;                 // next work item; [1] not zero: a workgroup has waited too long
+    int *done;                   // [PS_MAX_HEADS] key ranges that have been summed up
+    double *partials;
+    int ranges;                  // of keys per head (this and the next set by the launcher)
+    double inv_h;                // 1 / H
+};
+#define PS_STEP_WORDS(H, F) ((size_t)6 * (H) + (F) + 64 + PS_MAX_HEADS)
+bool ps_decode_row_applies(int H, int F, int d, int n_blocks);
+hipError_t ps_decode_row(const StepArgs &s, int d, int max_keys, hipStream_t st);
 #define PS_CHUNKED_ROWS_MAX 512
 // batched-decode linear, 2 <= M <= PS_CHUNKED_ROWS_MAX rows, 64 per workgroup (int8 MFMA, outlier columns exactly on fp64 MFMA inside the
 // loop); xq_tiled and xo_tiled as written by ps_rowquant_tiled
@@ -411,6 +437,10 @@ __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {     // 
     typedef unsigned short us2 __attribute__((ext_vector_type(2)));
     const us2 r = __builtin_elementwise_max(*(us2 *)&a, *(us2 *)&b);
     return *(const uint32_t *)&r;
+}
+template <typename F, int... I>
+__device__ __forceinline__ void for_constants(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
 }
 // smallest non-negative fp16 bit pattern whose value is >= theta (fp16 magnitudes order like their bits)
 inline uint32_t ps_theta_to_bits(float theta) {

@@ -28,6 +28,7 @@ struct Workspace {
     ManyOutliers many;     // only carved when max_rows_per_call > 64
     int8_t *xd;            // wide spans: digits of the outlier columns of calls of 17 to 64 rows, see gemm_digits.h
     DigitCall digits;
+    uint32_t *step;        // narrow spans: rows on their way between workgroups in a one-row step, see decode_row.hip
     size_t mask_words;
     size_t total;
 };
