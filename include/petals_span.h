@@ -294,6 +294,12 @@ int petals_debug_layernorm(petals_span *span, int32_t block, int32_t which, cons
  */
 int petals_debug_outlier_counts(petals_span *span, int32_t *counts, void *stream);
 
+/*
+ * For tests: how long, in ticks of the GPU's 100 MHz clock, a row of a LayerNorm waits for the outlier columns of the
+ * other rows of its call before it works them out by itself (10000 unless set; the results are the same).
+ */
+int petals_debug_norm_patience(petals_span *span, uint32_t ticks);
+
 /* Row-major int8 codes [N, K] and row scales [N] of a loaded linear (dev outputs). */
 int petals_debug_export_weight(petals_span *span, int32_t block, int32_t which, int8_t *wq,
                                float *sw, void *stream);

@@ -18,9 +18,10 @@ thread_local char g_err[512] = "";
 // Scratch of petals_span_decode_step_static: device memory that belongs to the library image, so that the call
 // needs no workspace from anybody.  Every GPU the library runs on holds its own copy at its own address.
 // The first part bounds which steps fit; behind it there is room for the digit sums (see carve) of every step that does: 64 rows
-// of 65536 columns in four digits, the sums of 16384 outputs and their counters.
+// of 65536 columns in four digits, the sums of 16384 outputs and their counters, the records of 64 rows of 16384 columns, the words of one row.
 #define PS_STATIC_SCRATCH_BYTES ((size_t)32 << 20)
-#define PS_STATIC_DIGIT_BYTES (((size_t)64 * 65536 * 4) + (size_t)PS_DIGIT_SPLITS * 64 * 16384 * 12 + PS_DIGIT_DONE * 4)
+#define PS_STATIC_DIGIT_BYTES (((size_t)64 * 65536 * 4) + (size_t)PS_DIGIT_SPLITS * 64 * 16384 * 12 + PS_DIGIT_DONE * 4 + \
+                               (size_t)64 * (PS_NORM_RECORD_WORDS * 4 + 16384 / 8) + ((size_t)1 << 20))
 static __device__ __align__(256) unsigned char scratch[PS_STATIC_SCRATCH_BYTES + PS_STATIC_DIGIT_BYTES];
 
 int ps_fail(int code, const char *fmt, ...) {
@@ -55,8 +56,9 @@ size_t block_weight_bytes(const petals_span_config &c) {
     return b + 4 * ps_align_up((size_t)c.hidden * 2);
 }
 
-// with_digits: room for the digit form of ps_gemm (calls of 17 to 64 rows of wide spans), behind everything else
-Workspace carve(const petals_span_config &c, uint8_t *base, bool with_digits = true) {
+// with_rest: what is behind everything else, room for the digit form of ps_gemm (calls of 17 to 64 rows of wide spans), for the
+// records of the LayerNorms and for the words of one row
+Workspace carve(const petals_span_config &c, uint8_t *base, bool with_rest = true) {
     Workspace w;
     const size_t M = (size_t)c.max_rows_per_call, Mp = (M + 15) / 16 * 16, H = c.hidden, F = c.ffn;
     const size_t Kmax = F > H ? F : H;
@@ -96,7 +98,7 @@ Workspace carve(const petals_span_config &c, uint8_t *base, bool with_digits = t
     w.digits = DigitCall{};
     w.xd = nullptr;
     const size_t rows = Mp < 64 ? Mp : 64;
-    if (with_digits && ps_gemm_digits_applies((int)H, (int)H, (int)rows)) {
+    if (with_rest && ps_gemm_digits_applies((int)H, (int)H, (int)rows)) {
         const size_t halves = PS_DIGIT_SPLITS * 2 * (H / 32) * 16 * 64;
         w.xd = (int8_t *)take(rows * Kmax * 4);
         w.digits.part = (double *)take(halves * 8);
@@ -105,7 +107,11 @@ Workspace carve(const petals_span_config &c, uint8_t *base, bool with_digits = t
         w.digits.rowstate = w.ocount;
         w.digits.done = (int *)take(PS_DIGIT_DONE * 4);
     }
-    w.step = ps_decode_row_applies((int)H, (int)F, (int)H / c.n_heads, c.n_blocks) ? (uint32_t *)take(PS_STEP_WORDS(H, F) * 4) : nullptr;
+    const size_t norm_rows = M < PS_NORM_ROWS_MAX ? M : PS_NORM_ROWS_MAX;
+    const bool records = with_rest && M > 1 && c.n_blocks * 4 < 65535;
+    w.records = records ? (uint64_t *)take(norm_rows * PS_NORM_RECORD_WORDS * 4) : nullptr;
+    w.record_masks = records ? (uint32_t *)take(norm_rows * H / 8) : nullptr;
+    w.step = with_rest && ps_decode_row_applies((int)H, (int)F, (int)H / c.n_heads, c.n_blocks) ? (uint32_t *)take(PS_STEP_WORDS(H, F) * 4) : nullptr;
     w.total = off;
     return w;
 }
@@ -155,8 +161,18 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
         HIP_TRY(ps_gemv_row(w, X, ln_g, ln_b, c.ln_eps, theta, dbg, o, ws.table, qin, st));
         sp->prof.end(pr, st);
     } else {
+        // calls of a few hundred rows whose output would be too few 256 x 256 blocks to fill the GPU go through
+        // the batched-decode kernel, 64 rows per workgroup (same outlier columns for all: those of the whole call)
+        const bool chunks = ps_gemm_prefers_chunks(w, M);
+        const bool small = M <= 64 || chunks;
+        // few rows: LayerNorm and row quantizer are one launch
+        const bool fused = ln_g && small && M <= PS_NORM_ROWS_MAX && ws.records;
         if (!mask_ready) HIP_TRY(ps_fill_u32(mask, ws.mask_words, 0u, st));
-        if (ln_g) {
+        if (fused) {
+            const NormExchange ex = {ws.records, ws.record_masks, (uint32_t)((mask - ws.masks) / ws.mask_words) + 1, sp->norm_patience};
+            HIP_TRY(ps_layernorm_codes(X, qin, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, ws.xq, ws.xo, ws.sx, xq_dbg, theta, ex, st));
+            X = ws.a;
+        } else if (ln_g) {
             if (M <= 64) flags = nullptr;
             if (qin) HIP_TRY(ps_layernorm_q8(*qin, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, flags, theta, st));
             else HIP_TRY(ps_layernorm(X, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, flags, theta, st));
@@ -164,15 +180,11 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
         } else if (!mask_ready) {
             HIP_TRY(ps_colmask(X, M, w.K, theta, mask, st));
         }
-        // calls of a few hundred rows whose output would be too few 256 x 256 blocks to fill the GPU go through
-        // the batched-decode kernel, 64 rows per workgroup (same outlier columns for all: those of the whole call)
-        const bool chunks = ps_gemm_prefers_chunks(w, M);
-        const bool small = M <= 64 || chunks;
         const OutlierPrep prep = {w, small ? nullptr : ws.ocount, ws.wd64, ws.x64, ws.many.list};
         // (a LayerNorm's output has few outlier columns: only the inputs that attention and GeLU write go for digits)
         const bool digits = !ln_g && ws.xd && w.N == c.hidden && ps_gemm_digits_applies(w.N, w.K, M);
         const RowDigits rd = {digits ? ws.xd : nullptr, ws.ocount, ws.digits.done};
-        HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ln_g ? flags : nullptr, ws.xq, small ? ws.xo : nullptr, ws.sx, xq_dbg, prep, rd, st));
+        if (!fused) HIP_TRY(ps_rowquant_tiled(X, M, w.K, mask, ln_g ? flags : nullptr, ws.xq, small ? ws.xo : nullptr, ws.sx, xq_dbg, prep, rd, st));
         const OutlierSet os = {ws.ocount, ws.wd64, ws.x64};
         const bool pr = sp->prof.begin(PETALS_PROFILE_GEMM, which, st);
         if (small) {
@@ -300,8 +312,8 @@ int run_call(petals_span *sp, petals_session *const *sessions, int32_t B, int32_
     Workspace &ws = sp->ws;
     const int M = B * T;
     const bool row = M == 1 && ws.step && !sp->prof.on;
-    HIP_TRY(row ? ps_call_setup(tab, ws.table, ws.step, PS_STEP_WORDS(c.hidden, c.ffn), st)
-                : ps_call_setup(tab, ws.table, ws.masks, ps_mask_clear_words(c, ws, M), st));
+    HIP_TRY(row ? ps_call_setup(tab, ws.table, nullptr, 0, ws.step, PS_STEP_WORDS(c.hidden, c.ffn), st)
+                : ps_call_setup(tab, ws.table, ws.masks, ps_mask_clear_words(c, ws, M), (uint32_t *)ws.records, ps_record_words(ws, M), st));
     QuantIn qin;
     if (qin_arg) {
         // the decoded rows live in the buffer that only the outputs of odd blocks use: block 0 reads them (LayerNorm,
@@ -632,11 +644,18 @@ int petals_debug_layernorm(petals_span *sp, int32_t block, int32_t which, const 
     uint32_t *mk = ws.masks;
     if (M > 1) HIP_TRY(ps_fill_u32(mk, ws.mask_words, 0u, st));
     if (M > 64) HIP_TRY(ps_fill_u32((uint32_t *)ws.flags, (size_t)c.hidden / 4, 0u, st));
+    if (ps_record_words(ws, M)) HIP_TRY(ps_fill_u32((uint32_t *)ws.records, ps_record_words(ws, M), 0u, st));
     if (int rc = run_linear(sp, which ? 2 : 0, L, (const __half *)x, which ? W.ln2g : W.ln1g, which ? W.ln2b : W.ln1b, M, mk,
                             ws.flags, M > 1, plain_out(ws.g, PETALS_EPILOGUE_NONE, nullptr), xq, true, st)) return rc;
     HIP_TRY(ps_copy_bytes(ws.a, y, (size_t)M * c.hidden * 2, st));
     if (sx) HIP_TRY(ps_copy_bytes(ws.sx, sx, (size_t)M * 4, st));
     if (outlier_mask) HIP_TRY(ps_mask_to_bytes(mk, L.K, outlier_mask, st));
+    return PETALS_OK;
+}
+
+int petals_debug_norm_patience(petals_span *sp, uint32_t ticks) {
+    if (!sp) return fail(PETALS_ERR_INVALID_ARG, "null pointer");
+    sp->norm_patience = ticks;
     return PETALS_OK;
 }
 

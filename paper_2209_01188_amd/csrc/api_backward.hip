@@ -154,7 +154,7 @@ int petals_span_backward(petals_span *sp, void *dev_store, int32_t B, int32_t T,
     hipStream_t st = (hipStream_t)stream;
     Workspace &ws = sp->ws;
     const int M = B * T, H = c.hidden, nh = c.n_heads, d = H / nh;
-    HIP_TRY(ps_call_setup(tab, ws.table, ws.masks, ps_mask_clear_words(c, ws, M), st));
+    HIP_TRY(ps_call_setup(tab, ws.table, ws.masks, ps_mask_clear_words(c, ws, M), (uint32_t *)ws.records, ps_record_words(ws, M), st));
     if (int rc = ps_forward_blocks(sp, M, T, T, (const __half *)hidden_in, y, &bs.save, st)) return rc;
 
     // backward, last block first; gy: gradient w.r.t. the output of the block at hand

@@ -18,15 +18,17 @@ constexpr int ATTN_SPLIT_BELOW = 256;
 // minus the maximum is -infinity, whose exponential is 0, also before the first visible key - no test per key.
 constexpr double ATTN_LOWEST = -1e300;
 
-// Start of a call: workgroup 0 copies the table word by word, all of them clear the outlier masks (one launch: a launch
+// Start of a call: workgroup 0 copies the table word by word, all of them clear the outlier masks and the records of the LayerNorms (or a row's words) (one launch: a launch
 // of its own costs 2 to 4.5 us whatever it does).
-__global__ void __launch_bounds__(256) k_call_setup(SessTable t, SessTable *dst, uint32_t *masks, size_t n_masks) {
+__global__ void __launch_bounds__(256) k_call_setup(SessTable t, SessTable *dst, uint32_t *masks, size_t n_masks, uint32_t *more,
+                                                    size_t n_more) {
     if (blockIdx.x == 0) {
         const uint32_t *s = (const uint32_t *)&t;
         uint32_t *d = (uint32_t *)dst;
         for (int i = threadIdx.x; i < (int)(sizeof(SessTable) / 4); i += 256) d[i] = s[i];
     }
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_masks; i += (size_t)gridDim.x * 256) masks[i] = 0u;
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_more; i += (size_t)gridDim.x * 256) more[i] = 0u;
 }
 
 // N consecutive halves at an address aligned to min(16, 2 N) bytes
@@ -634,9 +636,9 @@ hipError_t attn_launch(const __half *q, const SessTable *sess, int blk, int M, i
 
 }  // namespace
 
-hipError_t ps_call_setup(const SessTable &host_table, SessTable *dev_table, uint32_t *masks, size_t n_masks, hipStream_t st) {
-    const size_t want = (n_masks + 255) / 256;
-    k_call_setup<<<(unsigned)(want < 1 ? 1 : want > 256 ? 256 : want), 256, 0, st>>>(host_table, dev_table, masks, n_masks);
+hipError_t ps_call_setup(const SessTable &host_table, SessTable *dev_table, uint32_t *masks, size_t n_masks, uint32_t *more, size_t n_more, hipStream_t st) {
+    const size_t want = ((n_masks > n_more ? n_masks : n_more) + 255) / 256;
+    k_call_setup<<<(unsigned)(want < 1 ? 1 : want > 256 ? 256 : want), 256, 0, st>>>(host_table, dev_table, masks, n_masks, more, n_more);
     return hipGetLastError();
 }
 

@@ -131,6 +131,19 @@ struct RowDigits {
 hipError_t ps_rowquant_tiled(const __half *X, int M, int K, uint32_t *mask, const uint8_t *flags, int8_t *xq_tiled,
                              int8_t *xo_tiled, float *sx, int8_t *xq_rowmajor_dbg, const OutlierPrep &pr, const RowDigits &rd,
                              hipStream_t st);
+// LayerNorm and row quantizer of a call of 2 to PS_NORM_ROWS_MAX rows in one launch (quant.hip): y, the mask (whose bits need not
+// be cleared) and all that ps_rowquant_tiled writes.  qin (may be null): the rows arrive as 8-bit codes, x is ignored
+#define PS_NORM_ROWS_MAX 128
+#define PS_NORM_RECORD_WORDS 16   // 32-bit words of a row's record
+struct NormExchange {
+    uint64_t *records;           // [PS_NORM_ROWS_MAX] records, no word of which holds the tag
+    uint32_t *masks;             // [PS_NORM_ROWS_MAX][H / 32]
+    uint32_t tag;                // 1 to 65535
+    uint32_t patience;           // ticks of the 100 MHz clock that a row waits for the others
+};
+hipError_t ps_layernorm_codes(const __half *x, const QuantIn *qin, const __half *g, const __half *b, float eps, int M, int H, __half *y,
+                              uint32_t *mask, int8_t *xq_tiled, int8_t *xo_tiled, float *sx, int8_t *xq_dbg, float theta,
+                              const NormExchange &ex, hipStream_t st);
 hipError_t ps_mask_to_bytes(const uint32_t *mask, int K, uint8_t *out, hipStream_t st);
 hipError_t ps_mask_count(const uint32_t *masks, int n_masks, int words, int32_t *out, hipStream_t st);
 
@@ -213,8 +226,8 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M);
 int ps_gemm_lds_ksplit(int N, int ktiles, int M);
 
 // attention of M = B*T query rows against the caches (new keys/values already appended)
-// the call's table, and (n_masks > 0) its outlier masks cleared
-hipError_t ps_call_setup(const SessTable &host_table, SessTable *dev_table, uint32_t *masks, size_t n_masks, hipStream_t st);
+// the call's table, and (n_masks, n_more > 0) its outlier masks and what else starts from zero cleared
+hipError_t ps_call_setup(const SessTable &host_table, SessTable *dev_table, uint32_t *masks, size_t n_masks, uint32_t *more, size_t n_more, hipStream_t st);
 #define PS_ATTN_MAX_SPLITS 16
 #define PS_ATTN_PARTIAL_SLOTS 8192   // (row, head, split) triples that may need a partial result
 // mask (may be null): outlier-column bits of ctx are ORed into it (|ctx| >= theta)

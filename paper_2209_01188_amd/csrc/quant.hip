@@ -626,6 +626,242 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
     }
 }
 
+// LayerNorm and row quantizer in one launch, for calls of up to PS_NORM_ROWS_MAX rows: the codes of a row need the outlier
+// columns of ALL rows, which the workgroups - one per row - tell each other while they run.  A row's columns go into a record
+// of eight 64-bit words in device memory: three columns and the tag of this LayerNorm in each, written and read by relaxed
+// atomics of agent scope, so that a word that carries the tag is complete; more than 24 columns go as a bit mask that is in
+// memory before the record says so.  What this saves is a launch (2.5 us) and the rows' way through memory; the exchange takes
+// about 1 us.  8 rows of 4096: LayerNorm 5.7 and quantizer 4.7 us, together 6.5 (decode step of 8 sessions through four such
+// blocks 400 -> 370); 128 rows of 1024 3.8 and 4.5, together 6.4, where a workgroup reads 8 KB of records: the line of
+// PS_NORM_ROWS_MAX.
+// A workgroup that has waited for `patience` ticks of the 100 MHz clock (not all of them may be resident at once when other
+// work shares the device) finds the outlier columns by itself, from all rows.
+constexpr int NORM_WORDS = 8, NORM_COLS = 3 * NORM_WORDS, NORM_NONE = 0xffff, NORM_MASK = 0xfffe;
+
+template <int NT, int PER, bool Q8>
+__global__ void __launch_bounds__(NT) k_layernorm_codes(const __half *__restrict__ x, QuantIn qin, const __half *__restrict__ g,
+                                                        const __half *__restrict__ b, float eps, int M, int H, __half *__restrict__ y,
+                                                        uint32_t *__restrict__ mask, int8_t *__restrict__ xq_tiled,
+                                                        int8_t *__restrict__ xo_tiled, float *__restrict__ sx, int8_t *__restrict__ xq_dbg,
+                                                        uint32_t theta_bits, double inv_h, NormExchange ex, int rows, int grid) {
+    extern __shared__ __align__(16) unsigned char dyn[];             // the normalised row, [H] halves
+    __half *row = (__half *)dyn;
+    __shared__ double sm[2][NT / 64];
+    __shared__ uint32_t smm[NT / 64], cols[512];                     // cols: outlier columns, a bit each
+    __shared__ uint16_t mine[NORM_COLS];
+    __shared__ int n_mine, late, masks;
+    __shared__ float table[Q8 ? 256 : 1];
+    const int t = rowquant_row(grid), KT = H >> 6, nchunk = H >> 4, words = H >> 5;
+    if (t >= M) return;                                              // the rows that pad the last tile are cleared below
+    for (int i = threadIdx.x; i < words; i += NT) cols[i] = 0u;
+    if (threadIdx.x == 0) n_mine = late = masks = 0;
+    if constexpr (Q8)
+        for (int i = threadIdx.x; i < 256; i += NT) table[i] = d_code_table.code[i];
+    __syncthreads();
+
+    uint32_t v[PER][2], own[PER];                                    // this thread's four columns, PER times; outliers among them
+    auto normalise = [&](int r, bool store) {
+        const size_t row0 = (size_t)r * H;
+        double s = 0.0, q = 0.0;
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            const int k = (threadIdx.x + i * NT) * 4;
+            v[i][0] = v[i][1] = 0u;
+            if (k >= H) continue;
+            if constexpr (Q8) {                                      // H and the codec block are multiples of 4: one block
+                const float am = qin.absmax[(row0 + k) / (size_t)qin.block];
+                const uint32_t a = *(const uint16_t *)(qin.q + row0 + k), c = *(const uint16_t *)(qin.q + row0 + k + 2);
+                v[i][0] = (uint32_t)__half_as_ushort(decode_q8(table, a & 255u, am)) | (uint32_t)__half_as_ushort(decode_q8(table, a >> 8, am)) << 16;
+                v[i][1] = (uint32_t)__half_as_ushort(decode_q8(table, c & 255u, am)) | (uint32_t)__half_as_ushort(decode_q8(table, c >> 8, am)) << 16;
+                if (store) *(uint2 *)(qin.x_out + row0 + k) = make_uint2(v[i][0], v[i][1]);
+            } else {
+                const uint32_t *from = (const uint32_t *)(x + row0 + k);
+                v[i][0] = from[0];
+                v[i][1] = from[1];
+            }
+        }
+        auto value = [&](int i, int e) { return (double)__half2float(__ushort_as_half((unsigned short)(v[i][e >> 1] >> ((e & 1) * 16)))); };
+#pragma unroll
+        for (int i = 0; i < PER; i++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) s += value(i, e);            // (zeros beyond the row)
+        // (a workgroup's sum with one barrier: the next one goes to another array; quotients by the row's length from its
+        // reciprocal and the exact remainder)
+        auto row_mean = [&](double p, int which) {
+            p = wave_sum(p);
+            if ((threadIdx.x & 63) == 0) sm[which][threadIdx.x >> 6] = p;
+            lds_barrier();
+            p = sm[which][0];
+#pragma unroll
+            for (int i = 1; i < NT / 64; i++) p += sm[which][i];
+            const double m = p * inv_h;
+            return fma(fma(-m, (double)H, p), inv_h, m);
+        };
+        const double mean = row_mean(s, 0);
+#pragma unroll
+        for (int i = 0; i < PER; i++)
+            if ((int)(threadIdx.x + i * NT) * 4 < H)
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const double d = value(i, e) - mean;
+                    q += d * d;
+                }
+        const double inv = rsqrt_f64(row_mean(q, 1) + (double)eps);
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            const int k = (threadIdx.x + i * NT) * 4;
+            own[i] = 0;
+            if (k >= H) continue;
+            const uint2 gw = *(const uint2 *)(g + k), bw = *(const uint2 *)(b + k);
+            uint32_t out[2];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const uint32_t gs = e < 2 ? gw.x : gw.y, bs = e < 2 ? bw.x : bw.y;
+                const __half gh = __ushort_as_half((unsigned short)(gs >> ((e & 1) * 16))), bh = __ushort_as_half((unsigned short)(bs >> ((e & 1) * 16)));
+                const uint32_t o = __half_as_ushort(d2h_rn((value(i, e) - mean) * inv * (double)__half2float(gh) + (double)__half2float(bh)));
+                const uint32_t a = o & 0x7fffu;                      // NaN is no outlier, see k_layernorm_rows
+                own[i] |= (a >= theta_bits && a <= 0x7c00u ? 1u : 0u) << e;
+                out[e >> 1] = e & 1 ? out[e >> 1] | o << 16 : o;
+            }
+            v[i][0] = out[0];
+            v[i][1] = out[1];
+            if (store) {
+                *(uint2 *)(y + row0 + k) = make_uint2(out[0], out[1]);
+                *(uint2 *)(row + k) = make_uint2(out[0], out[1]);
+            }
+            if (own[i]) atomicOr(&cols[k >> 5], own[i] << (k & 31));
+        }
+    };
+    normalise(t, true);
+#pragma unroll
+    for (int i = 0; i < PER; i++)
+        for (uint32_t left = own[i]; left; left &= left - 1) {
+            const int at = atomicAdd(&n_mine, 1);
+            if (at < NORM_COLS) mine[at] = (uint16_t)((threadIdx.x + i * NT) * 4 + __ffs(left) - 1);
+        }
+    __syncthreads();
+    const uint64_t tagged = (uint64_t)ex.tag << 48;
+    const bool as_mask = n_mine > NORM_COLS;
+    if (as_mask) {
+        for (int i = threadIdx.x; i < words; i += NT)
+            __hip_atomic_store(ex.masks + (size_t)t * words + i, cols[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this wave's words are where every XCD sees them
+        __syncthreads();
+    }
+    if (threadIdx.x < NORM_WORDS) {
+        uint64_t w = tagged;
+#pragma unroll
+        for (int e = 0; e < 3; e++) {
+            const int i = 3 * threadIdx.x + e;
+            w |= (uint64_t)(as_mask ? NORM_MASK : i < n_mine ? mine[i] : NORM_NONE) << (16 * e);
+        }
+        __hip_atomic_store(ex.records + (size_t)t * NORM_WORDS + threadIdx.x, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the other rows' records, AT words per thread at once (one, but for short rows and many of them)
+    constexpr int AT = NT == 256 ? 4 : 2;
+    static_assert(AT * NT >= PS_NORM_ROWS_MAX * NORM_WORDS, "every word has a thread");
+    {
+        uint64_t w[AT], start = 0;
+        for (int spins = 0;; spins++) {
+            bool there = true;
+#pragma unroll
+            for (int a = 0; a < AT; a++) {
+                const int i = threadIdx.x + a * NT;
+                w[a] = i < M * NORM_WORDS && i / NORM_WORDS != t ? __hip_atomic_load(ex.records + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                                                 : tagged | 0xffffffffffffull;
+            }
+#pragma unroll
+            for (int a = 0; a < AT; a++) there = there && w[a] >> 48 == ex.tag;
+            if (there) break;
+            if ((spins & 7) == 7) {
+                const uint64_t now = __builtin_amdgcn_s_memrealtime();
+                if (!start) start = now;
+                if (now - start >= ex.patience) { late = 1; break; }
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < AT; a++)
+#pragma unroll
+            for (int e = 0; e < 3; e++) {
+                const int c = (int)(w[a] >> (16 * e)) & 0xffff;
+                if (w[a] >> 48 != ex.tag) continue;
+                if (c < H) atomicOr(&cols[c >> 5], 1u << (c & 31));
+                else if (c == NORM_MASK) masks = 1;
+            }
+    }
+    __syncthreads();
+    if (late) {                                                      // rare; the same in all threads
+        uint32_t keep[PER][2];
+#pragma unroll
+        for (int i = 0; i < PER; i++) { keep[i][0] = v[i][0]; keep[i][1] = v[i][1]; }
+        for (int r = 0; r < M; r++)
+            if (r != t) normalise(r, false);
+#pragma unroll
+        for (int i = 0; i < PER; i++) { v[i][0] = keep[i][0]; v[i][1] = keep[i][1]; }
+        __syncthreads();
+    } else if (masks) {                                              // rare: rows with many outlier columns
+        for (int r = 0; r < M; r++) {
+            const uint64_t w = __hip_atomic_load(ex.records + (size_t)r * NORM_WORDS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (r == t || (int)(w & 0xffff) != NORM_MASK) continue;
+            for (int i = threadIdx.x; i < words; i += NT)
+                cols[i] |= __hip_atomic_load(ex.masks + (size_t)r * words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+    }
+    if (t == 0)
+        for (int i = threadIdx.x; i < words; i += NT) mask[i] = cols[i];
+
+    uint32_t m = 0, bits[PER];
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int k = (threadIdx.x + i * NT) * 4;
+        bits[i] = k < H ? cols[k >> 5] >> (k & 31) & 15u : 0u;
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+            const uint32_t two = bits[i] >> (2 * e);
+            m = pk_max_u16(m, v[i][e] & (((two & 1u) ? 0u : 0x7fffu) | ((two & 2u) ? 0u : 0x7fff0000u)));
+        }
+    }
+    const float s = row_scale<NT / 64>(m, smm);
+    if (threadIdx.x == 0) sx[t] = s;
+    const float r = s > 0.0f ? 127.0f / s : 0.0f;
+    const size_t tile_row = (size_t)(t >> 4) * KT;
+    float neg0 = -0.0f;
+    asm("" : "+v"(neg0));
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int k = (threadIdx.x + i * NT) * 4, c = k >> 4;
+        if (k >= H) continue;
+        uint32_t u[4];                                               // see chunk_codes
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+            u[e] = __float_as_uint(fmaf(__half2float(__ushort_as_half((unsigned short)(v[i][e >> 1] >> ((e & 1) * 16)))), r, neg0) + 12582912.0f);
+        uint32_t o = __builtin_amdgcn_perm(__builtin_amdgcn_perm(u[3], u[2], 0x0c0c0400), __builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400), 0x05040100);
+        if (bits[i]) {
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+                if (bits[i] >> e & 1u) o &= ~(0xffu << (8 * e));
+        }
+        const size_t slot = ((tile_row + (c >> 2)) * 64 + (c & 3) * 16 + (t & 15)) * 16;
+        *(uint32_t *)(xq_tiled + slot + (k & 15)) = o;
+        if (xq_dbg) *(uint32_t *)(xq_dbg + (size_t)t * H + k) = o;
+        const uint32_t all = cols[c >> 1] >> ((c & 1) * 16) & 0xffffu;
+        if ((k & 15) == 0 && all) {                                  // the group's first 8 outlier values, ascending column order
+            __half first[8];
+            uint32_t rest = all;
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                first[e] = rest ? row[k + __ffs(rest) - 1] : __ushort_as_half(0);
+                rest &= rest - 1;
+            }
+            *(v4i *)(xo_tiled + slot) = *(const v4i *)first;
+        }
+    }
+    for (int p = M + t; p < rows; p += M)                            // rows that pad the last tile
+        for (int c = threadIdx.x; c < nchunk; c += NT)
+            *(v4i *)(xq_tiled + (((size_t)(p >> 4) * KT + (c >> 2)) * 64 + (c & 3) * 16 + (p & 15)) * 16) = (v4i){0, 0, 0, 0};
+}
+
 // out[i] = number of set bits of the i-th mask of `words` words (one workgroup per mask)
 __global__ void __launch_bounds__(256) k_mask_count(const uint32_t *__restrict__ masks, int words, int32_t *__restrict__ out) {
     __shared__ float sm[4];
@@ -886,6 +1122,22 @@ hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b,
         return launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, flags, theta, st);
     if (M <= 256 && H >= 4096) (flags ? k_layernorm_q8<1024, true> : k_layernorm_q8<1024, false>)<<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
     else (flags ? k_layernorm_q8<256, true> : k_layernorm_q8<256, false>)<<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
+    return hipGetLastError();
+}
+hipError_t ps_layernorm_codes(const __half *x, const QuantIn *qin, const __half *g, const __half *b, float eps, int M, int H, __half *y,
+                              uint32_t *mask, int8_t *xq_tiled, int8_t *xo_tiled, float *sx, int8_t *xq_dbg, float theta,
+                              const NormExchange &ex, hipStream_t st) {
+    if (M < 2 || M > PS_NORM_ROWS_MAX || H % 64 || H > 16384 || !ex.records || !ex.tag) return hipErrorInvalidValue;
+    const int rows = (M + 15) / 16 * 16, grid = rowquant_grid(rows);
+    const uint32_t tb = ps_theta_to_bits(theta);
+    const QuantIn q = qin ? *qin : QuantIn{};
+#define PS_NORM(NT_, PER_) (qin ? k_layernorm_codes<NT_, PER_, true> : k_layernorm_codes<NT_, PER_, false>)<<<grid, NT_, H * 2, st>>>(x, q, g, b, eps, M, H, y, mask, xq_tiled, xo_tiled, sx, xq_dbg, tb, 1.0 / H, ex, rows, grid)
+    if (H <= 1024) PS_NORM(256, 1);
+    else if (H <= 2048) PS_NORM(512, 1);
+    else if (H <= 4096) PS_NORM(1024, 1);
+    else if (H <= 8192) PS_NORM(1024, 2);
+    else PS_NORM(1024, 4);
+#undef PS_NORM
     return hipGetLastError();
 }
 hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask, hipStream_t st) {

@@ -28,6 +28,8 @@ struct Workspace {
     ManyOutliers many;     // only carved when max_rows_per_call > 64
     int8_t *xd;            // wide spans: digits of the outlier columns of calls of 17 to 64 rows, see gemm_digits.h
     DigitCall digits;
+    uint64_t *records;     // outlier columns that the rows of a LayerNorm tell each other, see k_layernorm_codes; null: one row
+    uint32_t *record_masks;
     uint32_t *step;        // narrow spans: rows on their way between workgroups in a one-row step, see decode_row.hip
     size_t mask_words;
     size_t total;
@@ -62,6 +64,7 @@ struct petals_span {
     int open_sessions;
     // optional cache of the transposed dequantized weights for the backward pass: [block][linear]
     __half *bwd_cache = nullptr;
+    uint32_t norm_patience = 10000;      // 100 us: what a row of a LayerNorm waits for the others' outlier columns
     std::vector<uint8_t> bwd_cached;     // 1: the tiles of (block, linear) are in the cache
 };
 
@@ -82,6 +85,10 @@ struct SaveSet {
 // what a call of M rows clears first: nothing, the masks, or the masks and the flags behind them
 inline size_t ps_mask_clear_words(const petals_span_config &c, const Workspace &ws, int M) {
     return M <= 1 ? 0 : (size_t)c.n_blocks * 4 * ws.mask_words + (M > 64 ? (size_t)c.n_blocks * 2 * c.hidden / 4 : 0);
+}
+// ... and in 32-bit words the records of its LayerNorms
+inline size_t ps_record_words(const Workspace &ws, int M) {
+    return M <= 1 || !ws.records || M > PS_NORM_ROWS_MAX ? 0 : (size_t)M * PS_NORM_RECORD_WORDS;
 }
 // N and K of linear `which` (0 qkv, 1 dense, 2 up, 3 down)
 void ps_linear_dims(const petals_span_config &c, int which, int *N, int *K);

@@ -1,0 +1,90 @@
+"""LayerNorm and row quantizer in one launch (calls of few rows): the rows tell each other their outlier columns while they run,
+or work them out by themselves when they have waited too long."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import oracle  # noqa: E402
+from paper_2209_01188_amd import binding, synth  # noqa: E402
+from tests.gpu_util import DEV, build_pair, midsize, to_dev, to_np  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _span(H, nh, M, r):
+    span = binding.Span(1, H, nh, 64, M, device=DEV)
+    p = {n: torch.zeros(s, dtype=torch.float32, device=DEV)
+         for n, s in (("w_qkv", (3 * H, H)), ("w_dense", (H, H)), ("w_up", (64, H)), ("w_down", (H, 64)))}
+    for n, s in (("b_qkv", 3 * H), ("b_dense", H), ("b_up", 64), ("b_down", H)):
+        p[n] = torch.zeros(s, dtype=torch.float16, device=DEV)
+    ln = {n: r.normal(1.0 if n.endswith("g") else 0.0, 0.1, H).astype(np.float16) for n in ("ln1_g", "ln1_b", "ln2_g", "ln2_b")}
+    span.load_block(0, dict(p, **{n: to_dev(v) for n, v in ln.items()}))
+    return span, ln
+
+
+# M: the fewest rows, a full and a ragged tile, the most of the batched-decode kernel, the first of several launches' rows and the
+# most of this form; H: every number of threads and of columns per thread, and their edges; out: outlier columns per row, each row's
+# own (none, one, the most of a record, one more, a tenth of the row)
+@pytest.mark.parametrize("M,H,nh", [(2, 64, 4), (16, 1024, 16), (17, 1088, 17), (3, 2048, 16), (40, 2112, 33), (64, 4096, 32),
+                                    (65, 1024, 16), (128, 1024, 16), (128, 4096, 32), (5, 4160, 65), (9, 8192, 64), (33, 8256, 129),
+                                    (7, 16384, 128)])
+def test_layernorm_codes(M, H, nh):
+    r = np.random.default_rng(M + H)
+    span, ln = _span(H, nh, M, r)
+    for out in ([0] * 5, [1, 0, 0, 2, 0], [24, 1, 0, 25, 3], [H // 10, 24, 0, 25, H // 10]):
+        x = np.clip(r.standard_normal((M, H)), -2.5, 2.5)
+        for t in range(M):
+            n = min(out[t % 5], H // 10)
+            x[t, r.choice(H, n, replace=False)] = 40.0 * r.choice([-1.0, 1.0], n)
+        x = x.astype(np.float16)
+        y = oracle.layernorm(x, ln["ln2_g"], ln["ln2_b"])
+        mask = (np.abs(y.astype(np.float32)) >= 6.0).any(0)
+        reg = np.where(mask[None], np.float32(0), y.astype(np.float32))
+        s = np.abs(reg).max(1)
+        with np.errstate(divide="ignore"):
+            codes = np.rint(reg * np.where(s > 0, np.float32(127) / s, np.float32(0)).astype(np.float32)[:, None])
+        for patience in (10000, 0):
+            binding.petals_debug_norm_patience(span.handle, patience)
+            with midsize("chunks"):
+                got = span.debug_layernorm(0, 1, to_dev(x), want_quantized=True)
+            assert np.array_equal(to_np(got["y"]).view(np.uint16), y.view(np.uint16)), (out, patience)
+            assert np.array_equal(to_np(got["mask"]).astype(bool), mask), (out, patience)
+            assert np.array_equal(to_np(got["sx"]), s), (out, patience)
+            assert np.array_equal(to_np(got["xq"]), codes.astype(np.int8)), (out, patience)
+    span.close()
+
+
+@pytest.mark.parametrize("B,T,H", [(5, 1, 1024), (20, 1, 4096), (1, 100, 1024), (2, 64, 192)])
+@pytest.mark.parametrize("coded", [False, True])
+def test_rows_that_do_not_wait_give_the_same_calls(B, T, H, coded):
+    """Two blocks, fp16 rows and 8-bit codes, with rows that wait for each other and with rows that do not; a NaN row of one
+    session leaves the others as they are."""
+    cfg = synth.SpanConfig("codes", 2, H, H // 64, B, T, 1, 1, (20.0, 40.0), 3)
+    osp, span, _ = build_pair(cfg, max_rows=B * T)
+    x = synth.hidden_states(cfg, 0, B, T)
+    outs = []
+    for patience, poison in ((10000, False), (0, False), (10000, True), (0, True)):
+        binding.petals_debug_norm_patience(span.handle, patience)
+        xi = x.copy()
+        if poison:
+            xi[0, 0, 5] = np.nan
+        ses = [span.open_session(T) for _ in range(B)]
+        with midsize("chunks"):
+            if coded and not poison:
+                n = xi.size
+                q, am = torch.empty(n, dtype=torch.uint8, device=DEV), torch.empty(-(-n // 64), dtype=torch.float32, device=DEV)
+                binding.petals_hidden_quantize(to_dev(xi), 64, q, am)
+                y = span.prefill_q8(ses, T, q, am, 64)
+            else:
+                y = span.prefill(ses, to_dev(xi))
+        outs.append(to_np(y))
+        for s in ses:
+            s.close()
+    assert np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
+    assert np.array_equal(outs[2].view(np.uint16), outs[3].view(np.uint16))
+    if not coded and B > 1:
+        assert np.isfinite(outs[2][1:]).all()
+    span.close(); osp.destroy()
