@@ -193,7 +193,7 @@ struct StepArgs {
     int *ticket;                 // next work item; [1] not zero: a workgroup has waited too long
     int *done;                   // [PS_MAX_HEADS] key ranges that have been summed up
     double *partials;
-    int ranges;                  // of keys per head (this and the next set by the launcher)
+    int ranges;                  // of keys per head (this and what follows set by the launcher)
     double inv_h;                // 1 / H
 };
 #define PS_STEP_WORDS(H, F) ((size_t)6 * (H) + (F) + 64 + PS_MAX_HEADS)

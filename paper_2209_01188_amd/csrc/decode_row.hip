@@ -44,21 +44,30 @@ __device__ __forceinline__ uint64_t load_words2(const uint32_t *p) {
 __device__ __forceinline__ void publish(uint32_t *p, uint32_t tag, __half v) {
     __hip_atomic_store(p, tag << 16 | __half_as_ushort(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// N pairs of words into packed halves, once all of them carry the tag
-template <int N>
+// N pairs of words into packed halves, once all of them carry the tag.  STEP > 1: every STEP-th pair is polled before all of them
+// are (a thread's consecutive words were stored together): the polling of wide rows keeps the words' memory channels busy.
+template <int N, int STEP = 1>
 __device__ __forceinline__ void await_words(const uint32_t *const (&p)[N], uint32_t tag, int (&out)[N], int *gave_up) {
     const uint64_t want = (uint64_t)(tag << 16) << 32 | tag << 16;
     unsigned long long start = 0;
     for (int spins = 0;; spins++) {
         uint64_t w[N], off = 0;
+        if constexpr (STEP > 1) {
 #pragma unroll
-        for (int i = 0; i < N; i++) w[i] = load_words2(p[i]);
+            for (int i = 0; i < N; i += STEP) w[i] = load_words2(p[i]);
 #pragma unroll
-        for (int i = 0; i < N; i++) {
-            off |= w[i] ^ want;
-            out[i] = (int)__builtin_amdgcn_perm((uint32_t)(w[i] >> 32), (uint32_t)w[i], 0x05040100);
+            for (int i = 0; i < N; i += STEP) off |= w[i] ^ want;
         }
-        if (!(off & 0xffff0000ffff0000ull)) return;
+        if (!(off & 0xffff0000ffff0000ull)) {
+#pragma unroll
+            for (int i = 0; i < N; i++) w[i] = load_words2(p[i]);
+#pragma unroll
+            for (int i = 0; i < N; i++) {
+                off |= w[i] ^ want;
+                out[i] = (int)__builtin_amdgcn_perm((uint32_t)(w[i] >> 32), (uint32_t)w[i], 0x05040100);
+            }
+            if (!(off & 0xffff0000ffff0000ull)) return;
+        }
         __builtin_amdgcn_s_sleep(1);
         if ((spins & 1023) == 1023) {
             const unsigned long long now = __builtin_amdgcn_s_memrealtime();
@@ -100,12 +109,14 @@ struct Words {
 
 template <int CW, int D>
 struct Lds {
-    static constexpr int KMAX = 2048 * CW;           // widest row
+    static constexpr int KMAX = CW == 8 ? 12288 : 2048 * CW;     // widest row
     __align__(16) int8_t codes[KMAX];
-    __align__(16) __half row[KMAX];                  // the values that were quantized, for outlier columns
+    union {
+        __align__(16) __half row[KMAX];              // the values that were quantized, for outlier columns
+        double ao[WAVES][D];                         // attention: the waves' sums
+    };
     uint16_t mask[KMAX / 16];                        // outlier columns of each 16
     double sum[WAVES], sq[WAVES], red_f[WAVES][64], am[WAVES], al[WAVES];
-    double ao[WAVES][D];
     int mx[WAVES], red_i[WAVES][64];
     int next, last;
 };
@@ -129,18 +140,24 @@ __device__ __forceinline__ float prepare_row(Lds<CW, D> &l, int tid, int K, cons
 #pragma unroll
         for (int e = 0; e < NP; e++) { gr[e] = *(const int *)(gain + c + 2 * e); br[e] = *(const int *)(bias + c + 2 * e); }
     }
+    if (words) {
+        const uint32_t *p[NCH * NP];
+#pragma unroll
+        for (int i = 0; i < NCH; i++) {
+            const int c = (tid + THREADS * i) * CT;
+#pragma unroll
+            for (int e = 0; e < NP; e++) p[i * NP + e] = words + (c < K ? c : 0) + 2 * e;
+        }
+        if (mine0) await_words<NCH * NP, (CW == 8 ? NP : 1)>(p, tag, *(int(*)[NCH * NP])v, s.ticket + 1);
+    }
 #pragma unroll
     for (int i = 0; i < NCH; i++) {
         const int c = (tid + THREADS * i) * CT;
+        if (c >= K) {
 #pragma unroll
-        for (int e = 0; e < NP; e++) v[i][e] = 0;
-        if (c < K) {
-            if (words) {
-                const uint32_t *p[NP];
-#pragma unroll
-                for (int e = 0; e < NP; e++) p[e] = words + c + 2 * e;
-                await_words<NP>(p, tag, v[i], s.ticket + 1);
-            } else if (coded) {                      // the columns of a thread share a codec block
+            for (int e = 0; e < NP; e++) v[i][e] = 0;
+        } else if (!words) {
+            if (coded) {                      // the columns of a thread share a codec block
                 const float am = s.q8_absmax[c / s.q8_block];
 #pragma unroll
                 for (int e = 0; e < NP; e++) {
@@ -236,33 +253,46 @@ __device__ __forceinline__ float prepare_row(Lds<CW, D> &l, int tid, int K, cons
     return s_x;
 }
 
+// 16 bytes of a matrix that is read once; zeros from `bytes` on (no branch around the loads: registers that are written on one
+// side of a branch only cost the kernel 32 spilled ones)
+__device__ __forceinline__ v4i load_tile(const int8_t *base, int bytes, uint32_t offset) {
+    const auto x = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc((void *)base, 0, bytes, 0x00020000), offset, 0, 2 /* non-temporal */);
+    return (v4i){(int)x[0], (int)x[1], (int)x[2], (int)x[3]};
+}
+
 __device__ __forceinline__ int byte_of(const v4i &w, int j) {
     const int word = (j < 8) ? ((j < 4) ? w[0] : w[1]) : ((j < 12) ? w[2] : w[3]);
     return (int)(int8_t)((word >> ((j & 3) * 8)) & 0xff);
 }
 
-// PN 16-row panels of a linear, the K / 64 tiles shared out over the waves (wave w takes tiles w, w + 8, ...; WT of them at
-// most, all requested before the row is there).  Returns in the first 16 PN lanes of wave 0 the sums before GeLU and residual.
+// PN 16-row panels of a linear, the K / 64 tiles shared out over the waves (wave w takes tiles w, w + 8, ...; WT of
+// them at most, all requested before the row is there).  Returns in the first 16 PN lanes of wave 0 the sums before GeLU and
+// residual.  ready: what row the codes in LDS are of (tag and linear); a second item of a stage finds its row prepared.
 template <bool LN, int CT, int NCH, int WT, int PN, int CW, int D, typename AFTER>
-__device__ __forceinline__ double panels(Lds<CW, D> &l, int tid, const StepArgs &s, const LinearW &w, size_t offset, int p0, const __half *plain, bool coded,
+__device__ __forceinline__ double panels(Lds<CW, D> &l, int tid, const StepArgs &s, const LinearW &w, size_t offset, int p0, int which, int &ready, float &s_x, const __half *plain, bool coded,
                                          const uint32_t *turn, uint32_t turn_tag, const uint32_t *words, uint32_t tag,
                                          const __half *gain, const __half *bias, AFTER after) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kg = lane >> 4, K = w.K, KT = K >> 6, last = w.N / 16 - 1;
     v4i wv[PN][WT];
 #pragma unroll
-    for (int p = 0; p < PN; p++) {
-        const v4i *wp = (const v4i *)(w.wt + offset + (size_t)min(p0 + p, last) * KT * 1024) + lane;
+    for (int p = 0; p < PN; p++)
 #pragma unroll
-        for (int u = 0; u < WT; u++) wv[p][u] = __builtin_nontemporal_load(wp + (size_t)min(wave + WAVES * u, KT - 1) * 64);
-    }
+        for (int u = 0; u < WT; u++) {
+            const int kt = wave + WAVES * u;
+            wv[p][u] = load_tile(w.wt + offset + (size_t)p0 * KT * 1024, min(PN, last + 1 - p0) * KT * 1024, kt < KT ? (uint32_t)((p * KT + kt) * 1024 + lane * 16) : ~0u);
+        }
     float swd[PN];
 #pragma unroll
     for (int p = 0; p < PN; p++) swd[p] = ((const float *)((const uint8_t *)w.sw + offset))[min(p0 + p, last) * 16 + (lane & 15)] / 127.0f;
     const int n = min(p0 * 16 + min(lane, PN * 16 - 1), w.N - 1);            // the output that this lane finishes, if it does
     const float sn = ((const float *)((const uint8_t *)w.sw + offset))[n] / 127.0f;
     const float bn = __half2float(((const __half *)((const uint8_t *)w.bias + offset))[n]);
-    await_turn(turn, turn_tag, tid, s.ticket + 1);
-    const float s_x = prepare_row<LN, CT, NCH, CW, D>(l, tid, K, s, plain, coded, words, tag, gain, bias);
+    const int row = (int)tag * 4 + which;
+    if (row != ready) {                              // the same in all threads
+        await_turn(turn, turn_tag, tid, s.ticket + 1);
+        s_x = prepare_row<LN, CT, NCH, CW, D>(l, tid, K, s, plain, coded, words, tag, gain, bias);
+        ready = row;
+    }
     after();                                         // requests whose data the tail needs
     int acc[PN];
     double outl[PN];
@@ -283,7 +313,8 @@ __device__ __forceinline__ double panels(Lds<CW, D> &l, int tid, const StepArgs 
                 bits &= bits - 1;
                 const double x = (double)__half2float(l.row[kt * 64 + kg * 16 + j]);
 #pragma unroll
-                for (int p = 0; p < PN; p++) outl[p] += x * (double)dequant_w16(byte_of(wv[p][u], j), swd[p]);
+                for (int p = 0; p < PN; p++)
+                    outl[p] += x * (double)dequant_w16(byte_of(wv[p][u], j), swd[p]);
             }
         }
     }
@@ -433,12 +464,14 @@ __device__ __forceinline__ void attention(Lds<CW, D> &l, int tid, const StepArgs
 }
 
 // Panels per item: with one per workgroup QKV and up of 1024 columns would be 192 and 256 items, each of which prepares the row
-// and polls it (and waits longer for it: the words' memory channels are busy), with CW of them 96 and 128.
+// and polls it (and waits longer for it: the words' memory channels are busy); with two 96 and 128.  WT: tiles of a panel per
+// wave, of down four times as many.
 template <int CW, int D>
 __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
     __shared__ Lds<CW, D> l;
-    constexpr int PN = CW;
-    const int H = s.H, F = s.F, nq = (3 * H / 16 + PN - 1) / PN, na = s.nh * s.ranges, nd = H / 16, nu = (F / 16 + PN - 1) / PN;
+    constexpr int PQ = CW == 8 ? 3 : CW, PU = CW == 8 ? 4 : CW, WT = CW == 8 ? 6 : CW, NCH = CW == 8 ? 3 : CW / 2;
+    const int H = s.H, F = s.F;
+    const int nq = (3 * H / 16 + PQ - 1) / PQ, na = s.nh * s.ranges, nd = H / 16, nu = (F / 16 + PU - 1) / PU;
     const int per_block = nq + na + 2 * nd + nu, total = per_block * s.n_blocks;
     Words words;
     words.x = s.words;
@@ -448,7 +481,8 @@ __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
     words.g = words.x1 + H;
     if (threadIdx.x == 0) l.next = __hip_atomic_fetch_add(s.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     lds_barrier();
-    int t = l.next;
+    int t = l.next, ready = -1;
+    float s_x = 0.0f;
     while (t < total) {
         int tid = threadIdx.x;                       // opaque: what depends on it is worked out again for every item, not kept over all
         asm volatile("" : "+v"(tid));
@@ -462,16 +496,17 @@ __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
         auto at = [&](const __half *p) { return (const __half *)((const uint8_t *)p + off); };
         auto none = [] {};
         if (i < nq) {
-            const double v = panels<true, CW, 1, CW, PN, CW, D>(l, tid, s, s.lin[0], off, i * PN, s.x, s.q8 != nullptr, first ? nullptr : words.g + spread_g,
+            const double v = panels<true, CW, 1, WT, PQ, CW, D>(l, tid, s, s.lin[0], off, i * PQ, 0, ready, s_x, s.x, s.q8 != nullptr, first ? nullptr : words.g + spread_g,
                                                              (uint32_t)b, first ? nullptr : words.x, (uint32_t)b, at(s.ln1g), at(s.ln1b), none);
-            const int n = i * PN * 16 + lane;
-            if (tid < PN * 16 && n < 3 * H) publish(words.qkv + n, tag, d2h_rn(v));
+            const int n = i * PQ * 16 + lane;
+            if (tid < PQ * 16 && n < 3 * H) publish(words.qkv + n, tag, d2h_rn(v));
         } else if ((i -= nq) < na) {
+            ready = -1;                              // (the attention's sums lie where the row was)
             attention<D, CW>(l, tid, s, b, i / s.ranges, i % s.ranges, first ? nullptr : words.x + spread, (uint32_t)b, tag, words);
         } else if ((i -= na) < nd) {
             uint32_t res = 0;
             const int n = i * 16 + (lane & 15);
-            const double v = panels<false, CW, 1, CW, 1, CW, D>(l, tid, s, s.lin[1], off, i, nullptr, false, words.qkv + spread, tag, words.ctx, tag, nullptr, nullptr, [&] {
+            const double v = panels<false, CW, 1, WT, 1, CW, D>(l, tid, s, s.lin[1], off, i, 1, ready, s_x, nullptr, false, words.qkv + spread, tag, words.ctx, tag, nullptr, nullptr, [&] {
                 if (tid >= 16) return;
                 if (!first) res = __hip_atomic_load(words.x + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 else if (s.q8) res = __half_as_ushort(decode_q8(d_code_table.code, s.q8[n], s.q8_absmax[n / s.q8_block]));
@@ -479,15 +514,15 @@ __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
             });
             if (tid < 16) publish(words.x1 + n, tag, d2h_rn(v + (double)low_half((int)res)));
         } else if ((i -= nd) < nu) {
-            const double v = panels<true, CW, 1, CW, PN, CW, D>(l, tid, s, s.lin[2], off, i * PN, nullptr, false, words.ctx + spread, tag, words.x1, tag,
+            const double v = panels<true, CW, 1, WT, PU, CW, D>(l, tid, s, s.lin[2], off, i * PU, 2, ready, s_x, nullptr, false, words.ctx + spread, tag, words.x1, tag,
                                                              at(s.ln2g), at(s.ln2b), none);
-            const int n = i * PN * 16 + lane;
-            if (tid < PN * 16 && n < F) publish(words.g + n, tag, d2h_rn(gelu_tanh(v)));
+            const int n = i * PU * 16 + lane;
+            if (tid < PU * 16 && n < F) publish(words.g + n, tag, d2h_rn(gelu_tanh(v)));
         } else {
             i -= nu;
             uint32_t res = 0;
             const int n = i * 16 + (lane & 15);
-            const double v = panels<false, 8, CW / 2, 4 * CW, 1, CW, D>(l, tid, s, s.lin[3], off, i, nullptr, false, words.x1 + spread, tag, words.g, tag, nullptr, nullptr, [&] {
+            const double v = panels<false, 8, NCH, 4 * WT, 1, CW, D>(l, tid, s, s.lin[3], off, i, 3, ready, s_x, nullptr, false, words.x1 + spread, tag, words.g, tag, nullptr, nullptr, [&] {
                 if (tid < 16) res = __hip_atomic_load(words.x1 + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             });
             if (tid < 16) {
@@ -506,8 +541,10 @@ __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
 
 }  // namespace
 
+// The line: a stage of 4096 columns is as many items as there are workgroups, none of which then waits with weights on the way for
+// the next one (4096 columns, 64 keys: 55.3 us a block as five launches, 55.8 in one; 3072: 45.3 and 40.3; 2560: 43.3 and 34.8).
 bool ps_decode_row_applies(int H, int F, int d, int n_blocks) {
-    return H <= 2048 && F <= 8192 && (d == 64 || d == 128) && n_blocks < 65535;
+    return H <= 3072 && F <= 12288 && (d == 64 || d == 128) && n_blocks < 65535;
 }
 
 hipError_t ps_decode_row(const StepArgs &s0, int d, int max_keys, hipStream_t st) {
@@ -518,8 +555,10 @@ hipError_t ps_decode_row(const StepArgs &s0, int d, int max_keys, hipStream_t st
     // keys: 1 range 205, 3 ranges 189), and together no more than half of the workgroups (4 blocks of 2048 columns, 32 heads,
     // 2000 keys: 8 ranges 126 us, 4 ranges 115).
     s.ranges = max(1, min(min(max_keys * d / 32768, 128 / s.nh), PS_ATTN_MAX_SPLITS));
-    const bool narrow = s.H <= 1024 && s.F <= 4096;
-    auto kern = narrow ? (d == 64 ? k_decode_row<2, 64> : k_decode_row<2, 128>) : (d == 64 ? k_decode_row<4, 64> : k_decode_row<4, 128>);
+    const int form = s.H <= 1024 && s.F <= 4096 ? 0 : s.H <= 2048 && s.F <= 8192 ? 1 : 2;
+    auto kern = form == 0   ? (d == 64 ? k_decode_row<2, 64> : k_decode_row<2, 128>)
+                : form == 1 ? (d == 64 ? k_decode_row<4, 64> : k_decode_row<4, 128>)
+                            : (d == 64 ? k_decode_row<8, 64> : k_decode_row<8, 128>);
     kern<<<256, THREADS, 0, st>>>(s);
     return hipGetLastError();
 }
