@@ -109,7 +109,7 @@ struct Words {
 
 template <int CW, int D>
 struct Lds {
-    static constexpr int KMAX = CW == 8 ? 12288 : 2048 * CW;     // widest row
+    static constexpr int KMAX = 2048 * CW;           // widest row
     __align__(16) int8_t codes[KMAX];
     union {
         __align__(16) __half row[KMAX];              // the values that were quantized, for outlier columns
@@ -466,10 +466,10 @@ __device__ __forceinline__ void attention(Lds<CW, D> &l, int tid, const StepArgs
 // Panels per item: with one per workgroup QKV and up of 1024 columns would be 192 and 256 items, each of which prepares the row
 // and polls it (and waits longer for it: the words' memory channels are busy); with two 96 and 128.  WT: tiles of a panel per
 // wave, of down four times as many.
-template <int CW, int D>
+template <int CW, int WT, int D>
 __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
     __shared__ Lds<CW, D> l;
-    constexpr int PQ = CW == 8 ? 3 : CW, PU = CW == 8 ? 4 : CW, WT = CW == 8 ? 6 : CW, NCH = CW == 8 ? 3 : CW / 2;
+    constexpr int PQ = CW == 8 ? 3 : CW, PU = CW == 8 ? 4 : CW, NCH = WT / 2;
     const int H = s.H, F = s.F;
     const int nq = (3 * H / 16 + PQ - 1) / PQ, na = s.nh * s.ranges, nd = H / 16, nu = (F / 16 + PU - 1) / PU;
     const int per_block = nq + na + 2 * nd + nu, total = per_block * s.n_blocks;
@@ -542,9 +542,10 @@ __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
 }  // namespace
 
 // The line: a stage of 4096 columns is as many items as there are workgroups, none of which then waits with weights on the way for
-// the next one (4096 columns, 64 keys: 55.3 us a block as five launches, 55.8 in one; 3072: 45.3 and 40.3; 2560: 43.3 and 34.8).
+// the next one (64 keys, per block: 4096 columns 55.1 us as five launches, 53.7 in one; 3840 62.8 and 48.8; 3072 45.2 and 35.8;
+// 2560 41.7 and 30.7).
 bool ps_decode_row_applies(int H, int F, int d, int n_blocks) {
-    return H <= 3072 && F <= 12288 && (d == 64 || d == 128) && n_blocks < 65535;
+    return H <= 4096 && F <= 16384 && (d == 64 || d == 128) && n_blocks < 65535;
 }
 
 hipError_t ps_decode_row(const StepArgs &s0, int d, int max_keys, hipStream_t st) {
@@ -555,10 +556,13 @@ hipError_t ps_decode_row(const StepArgs &s0, int d, int max_keys, hipStream_t st
     // keys: 1 range 205, 3 ranges 189), and together no more than half of the workgroups (4 blocks of 2048 columns, 32 heads,
     // 2000 keys: 8 ranges 126 us, 4 ranges 115).
     s.ranges = max(1, min(min(max_keys * d / 32768, 128 / s.nh), PS_ATTN_MAX_SPLITS));
-    const int form = s.H <= 1024 && s.F <= 4096 ? 0 : s.H <= 2048 && s.F <= 8192 ? 1 : 2;
-    auto kern = form == 0   ? (d == 64 ? k_decode_row<2, 64> : k_decode_row<2, 128>)
-                : form == 1 ? (d == 64 ? k_decode_row<4, 64> : k_decode_row<4, 128>)
-                            : (d == 64 ? k_decode_row<8, 64> : k_decode_row<8, 128>);
+    // columns of a LayerNorm row per thread, tiles of a panel per wave: the smallest form that takes the span (fewer registers,
+    // fewer loads beyond the panels' ends)
+    auto fits = [&](int h) { return s.H <= h && s.F <= 4 * h; };
+    auto kern = fits(1024)   ? (d == 64 ? k_decode_row<2, 2, 64> : k_decode_row<2, 2, 128>)
+                : fits(2048) ? (d == 64 ? k_decode_row<4, 4, 64> : k_decode_row<4, 4, 128>)
+                : fits(3072) ? (d == 64 ? k_decode_row<8, 6, 64> : k_decode_row<8, 6, 128>)
+                             : (d == 64 ? k_decode_row<8, 8, 64> : k_decode_row<8, 8, 128>);
     kern<<<256, THREADS, 0, st>>>(s);
     return hipGetLastError();
 }

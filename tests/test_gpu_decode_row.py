@@ -24,7 +24,8 @@ def _config(blocks, H, nh, F):
     (2, 64, 1, 256, 0, 6.0), (3, 128, 1, 64, 1, 6.0), (2, 192, 3, 448, 63, 6.0), (2, 1024, 16, 4096, 64, 6.0),
     (1, 1024, 8, 4096, 400, 0.5), (2, 960, 15, 4160, 129, 6.0), (2, 1088, 17, 4352, 512, 6.0), (2, 2048, 16, 8192, 300, 6.0),
     (1, 2048, 32, 1024, 1500, 0.0), (2, 2112, 33, 8448, 70, 6.0), (2, 3072, 24, 12288, 300, 6.0), (1, 2944, 46, 9216, 1200, 6.0),
-    (1, 512, 8, 12288, 20, 6.0), (1, 1152, 9, 8192, 2500, 6.0), (1, 128, 2, 512, 3000, 6.0)])
+    (1, 512, 8, 12288, 20, 6.0), (2, 3136, 49, 12544, 100, 6.0), (2, 4096, 32, 16384, 64, 6.0), (1, 4096, 64, 15360, 900, 6.0),
+    (1, 1024, 8, 16384, 5, 0.5), (1, 1152, 9, 8192, 2500, 6.0), (1, 128, 2, 512, 3000, 6.0)])
 def test_a_row_in_one_launch(blocks, H, nh, F, L, theta):
     cfg = _config(blocks, H, nh, F)
     spans = [binding.Span(blocks, H, nh, F, 1, 1e-5, theta, DEV) for _ in range(2)]
