@@ -219,11 +219,10 @@ struct DigitCall {
 };
 bool ps_gemm_digits_applies(int N, int K, int M);
 // Calls of more than 64 rows that are better served by ps_gemm, 64 rows per workgroup (the weights are streamed once
-// per 64 rows, with every compute unit busy) than by the 256 x 256 output blocks of ps_gemm_lds, which
-// leave most of the GPU idle when the call has few of them.  PS_CHUNKED_ROWS_MAX bounds such calls.
+// per 64 rows, with every compute unit busy) than by the output blocks of ps_gemm_lds with their kernels for
+// outlier columns.  PS_CHUNKED_ROWS_MAX bounds such calls.
 bool ps_gemm_prefers_chunks(const LinearW &w, int M);
-// workgroups that share the contraction of one output block of ps_gemm_lds
-int ps_gemm_lds_ksplit(int N, int ktiles, int M);
+double ps_gemm_lds_us(int N, int K, int M);       // estimate of a linear of M > 64 rows in output blocks, with its row kernels
 
 // attention of M = B*T query rows against the caches (new keys/values already appended)
 // the call's table, and (n_masks, n_more > 0) its outlier masks and what else starts from zero cleared

@@ -271,18 +271,13 @@ static double gemm_rows64_us(const LinearW &w, int M, int wn, bool &four) {
 }
 
 // Rough times in microseconds of a linear with its row kernels, fitted to both forms measured on the four linears of
-// blocks 1024 to 14336 wide at 65 to 512 rows (468 points; the choice is then never worse than 5 % and 0.05 % on average).
-// 64 rows per workgroup: see above, 14 us for the row kernels in front.  All rows go in one launch: charged by 64 rows, as
+// blocks 1024 to 14336 wide at 65 to 512 rows (the choice is 0.6 % behind the faster one on average; at worst 7 %, 5120 x 5120
+// at 80 rows, 43 us for 40).
+// 64 rows per workgroup: see above, 12 us for the row kernels in front.  All rows go in one launch: charged by 64 rows, as
 // when each 64 were a launch, narrow outputs went to the blocks too early (1024 x 1024 at 320 rows: 24 us in this form, 36 in
 // blocks).
-// Output blocks: a 256 x 256 block walks K/64 stages of about 0.7 us
-// (0.45 us for the 256 x 128 blocks that ps_gemm_lds takes when the call has at most 128 rows or at most 128
-// blocks, whose stages are shared out if there are few of them: 8 us more for adding up), 256 blocks at a time, never
-// faster than the weights stream at 4 TB/s, behind about 32 us of row and digit kernels that are launched whatever the
-// data.
+// Output blocks: ps_gemm_lds_us.
 // PETALS_SPAN_MIDSIZE=blocks / =chunks in the environment overrides the choice (tests run both ways).
-constexpr double BLOCKS_FIXED = 32.0;
-
 bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
     if (M <= 64 || M > PS_CHUNKED_ROWS_MAX) return false;
     if (const char *force = getenv("PETALS_SPAN_MIDSIZE")) {
@@ -290,17 +285,7 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
         if (!strcmp(force, "chunks")) return true;
     }
     bool four;
-    const double bytes = (double)w.N * w.K;
-    const double t_chunks = 14.0 + gemm_rows64_us(w, M, gemm_panels_per_wg(w.N) > 1 ? 2 : 1, four);
-    double blocks = (double)((w.N + 255) / 256) * ((M + 255) / 256), stage = 0.7;
-    int split = 1;
-    if (M <= 128 || blocks * 2 <= 256) {
-        split = ps_gemm_lds_ksplit(w.N, w.K / 64, M);
-        blocks = (double)((w.N + 255) / 256) * ((M + 127) / 128) * split;
-        stage = 0.45;
-    }
-    const double t_blocks = BLOCKS_FIXED + (split > 1 ? 8.0 : 0.0) + fmax(ceil(blocks / 256.0) * (w.K / 64) / split * stage, bytes / 4.0e6);
-    return t_chunks < t_blocks;
+    return 12.0 + gemm_rows64_us(w, M, gemm_panels_per_wg(w.N) > 1 ? 2 : 1, four) < ps_gemm_lds_us(w.N, w.K, M);
 }
 
 hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,

@@ -3,8 +3,8 @@
 // Regular columns: int8 x int8 -> int32 with v_mfma_i32_16x16x64_i8.  Both operands already sit
 // in HBM in 16x64 tiles whose 1024 bytes are in the lane order of that instruction, so a tile
 // travels global -> LDS -> registers as plain 16-byte per-lane copies (bank-conflict free, no
-// transposition).  A workgroup computes a 256 x 256 block of the output; k-tiles move through a
-// 4-slot LDS ring filled by asynchronous global->LDS copies.
+// transposition).  A workgroup computes a block of the output, 256 x 256 in large calls; k-tiles move
+// through a 4-slot LDS ring filled by asynchronous global->LDS copies.
 //
 // Outlier columns: up to PS_EXACT_OUTLIERS of them are added exactly in the epilogue (fp64 matrix
 // instruction on compacted operands, see outlier_prep.h).  More than that: the fp16 x fp16 product over the
@@ -31,7 +31,6 @@
 
 namespace {
 
-constexpr int STRIP = 4;       // m-blocks per rasterization strip
 constexpr int PS_KSPLIT_MAX = 8;   // workgroups that share one output block's contraction, at most
 
 // ---------------------------------------------------------------------------------------------
@@ -268,13 +267,13 @@ constexpr int EPI_PARTIAL = 3;
 // argument because the tail's arithmetic must be straight-line code for the 16 outputs a lane finishes at a time
 // to overlap (with run-time switches inside, every output's chain of dependent fp64 operations ran on its own).
 template <int MODE, int WVN, int WVM, int TN, int TM, int NSLOT, int EPI>
-__global__ void __launch_bounds__(64 * WVN * WVM, 2)   // two waves per SIMD: at most 256 registers
+__global__ void __launch_bounds__(64 * WVN * WVM, TN * TM <= 8 ? 4 : 2)   // waves per SIMD: at most 256 registers, small blocks 128
 k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, const double *__restrict__ outl, OutDesc o,
            const SessTable *__restrict__ sess) {
     constexpr bool F16 = MODE == GEMM_F16, DIG = MODE == GEMM_DIGITS;
-    constexpr int NW = WVN * WVM, BN = WVN * TN, BM = WVM * TM, STAGE = BN + BM, LOADS = STAGE / NW;
+    constexpr int NW = WVN * WVM, BN = WVN * TN, BM = WVM * TM, STAGE = BN + BM, LOADS = (STAGE + NW - 1) / NW;
+    constexpr int FULL = STAGE % NW;                 // waves that copy LOADS tiles per stage, the others one less (0: all copy LOADS)
     constexpr int PD = NSLOT - 1;                    // stages requested ahead
-    static_assert(STAGE % NW == 0, "every wave copies the same number of tiles per stage");
     extern __shared__ __align__(16) unsigned char lds[];
     const int n_out = F16 ? ga.ktiles * 32 : os.count[0];
     const bool many = F16 || n_out > PS_EXACT_OUTLIERS;
@@ -285,8 +284,11 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     int NS = !F16 && !DIG && n_out == ga.ktiles * 64 ? 0 : KTILES;
 
     // Workgroup -> output block.  Consecutive workgroup ids land on different XCDs (8 of them, each
-    // with its own L2); give each XCD a contiguous run of blocks, ordered in strips of STRIP
+    // with its own L2); give each XCD a contiguous run of blocks, ordered in strips of up to STRIP
     // m-blocks, so that the blocks an XCD works on at one time share weight and token tiles in its L2.
+    // Small blocks: strips of about the same width; in one of a single m-block an XCD reads the weights of its
+    // whole run of feature blocks by itself (3072 x 3072 at 300 rows, 5 m-blocks as 4 + 1 39 us, as 3 + 2 31).  Wider
+    // strips: 2048 x 2048 at 1024 rows 35 -> 42.
     const int nb_n = ga.nb_n, nb_m = ga.nb_m, ksplit = EPI == EPI_PARTIAL ? ga.ksplit : 1;
     const int total = nb_n * nb_m * ksplit, per_xcd = (total + 7) >> 3;
     int ord = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -298,10 +300,11 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
         s_first = (int)((long long)NS * split / ksplit);
         NS = (int)((long long)NS * (split + 1) / ksplit) - s_first;
     }
-    const int nstrips = (nb_m + STRIP - 1) / STRIP;
-    const int strip = min(ord / (STRIP * nb_n), nstrips - 1);
-    const int rem = ord - strip * STRIP * nb_n, sw_this = min(STRIP, nb_m - strip * STRIP);
-    const int bn = rem / sw_this, bm = strip * STRIP + rem % sw_this;
+    constexpr int STRIP = 4;
+    const int nstrips = (nb_m + STRIP - 1) / STRIP, width = BN + BM < 24 ? (nb_m + nstrips - 1) / nstrips : STRIP;
+    const int strip = min(ord / (width * nb_n), nstrips - 1);
+    const int rem = ord - strip * width * nb_n, sw_this = min(width, nb_m - strip * width);
+    const int bn = rem / sw_this, bm = strip * width + rem % sw_this;
 
     // Digit product: planes 0..3 first, then, only when some outlier value reaches 127.5 in magnitude, planes 4.. as a
     // second pass over the same block, which adds to what the first one stored (as a launch of its own the second pass
@@ -358,16 +361,22 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     // [16 l, 16 l + 16) and the hardware writing them to tile base + 16 l.  The ring holds PD stages
     // in flight, which covers the latency of an L2 miss.  Copies of one wave complete in order, so
     // "stage s has landed" is "at most LOADS * (stages requested after s) copies outstanding".
-    auto dma_stage = [&](int s) {
+    auto dma_part = [&](int s, int j0, int j1) {
         unsigned char *slot = lds + (size_t)(s % NSLOT) * STAGE * 1024;
 #pragma unroll
-        for (int j = 0; j < LOADS; j++)
+        for (int j = j0; j < j1; j++) {
+            if (FULL && j == LOADS - 1 && wave >= FULL) break;
             __builtin_amdgcn_global_load_lds(
                 (const __attribute__((address_space(1))) void *)(src[j] + (size_t)s * 1024),
                 (__attribute__((address_space(3))) void *)(slot + (size_t)(wave + NW * j) * 1024), 16, 0, 0);
+        }
     };
     auto wait_own = [&](int in_flight_after) {
-        if (in_flight_after >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * 2) : "memory");
+        if (FULL && wave >= FULL) {
+            if (in_flight_after >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * 2 - 2) : "memory");
+            else if (in_flight_after == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS - 1) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        } else if (in_flight_after >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * 2) : "memory");
         else if (in_flight_after == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
@@ -379,7 +388,7 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
 #pragma unroll
         for (int j = 0; j < TM; j++) fb[j] = *(const v4i *)(base + (size_t)(BN + wm * TM + j) * 1024);
     };
-    for (int s = 0; s < PD && s < NS; s++) dma_stage(s);
+    for (int s = 0; s < PD && s < NS; s++) dma_part(s, 0, LOADS);
 
     // Fragments are double buffered in registers: while stage s is multiplied, the fragments of stage
     // s + 1 are read from LDS.  So at the barrier of iteration s, stage s + 1 must have landed.
@@ -390,31 +399,22 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
         asm volatile("" ::: "memory");
         frag_load(0, fa0, fb0);
     }
-    auto multiply = [&](const v4i *ca, const v4i *cb, int i0, int i1) {
+    auto multiply = [&](const v4i *ca, const v4i *cb, int e0, int e1) {     // eighths [e0, e1) of a stage
 #pragma unroll
-        for (int i = i0; i < i1; i++)
-#pragma unroll
-            for (int j = 0; j < TM; j++) {
-                if constexpr (F16)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*(const v8h *)&ca[i], *(const v8h *)&cb[j], acc[i][j], 0, 0, 0);
-                else
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ca[i], cb[j], acc[i][j], 0, 0, 0);
-            }
+        for (int q = TN * TM * e0 / 8; q < TN * TM * e1 / 8; q++) {
+            const int i = q / TM, j = q % TM;
+            if constexpr (F16)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*(const v8h *)&ca[i], *(const v8h *)&cb[j], acc[i][j], 0, 0, 0);
+            else
+                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ca[i], cb[j], acc[i][j], 0, 0, 0);
+        }
     };
     // The fragment reads of stage s + 1 are issued in the middle of the multiplications of stage s, so they
     // have half a stage to complete before the wait that precedes their first use.  No branch may separate
     // them from the multiplications: where two paths with different numbers of LDS reads in flight meet, the
     // compiler waits for all of them.  So the last stage goes through the same motions (its barrier is one
     // too many, its fragment reads fetch its own stage again).
-    // pieces of the next stage's traffic, to be spread between the multiplications
-    auto dma_part = [&](int s, int j0, int j1) {
-        unsigned char *slot = lds + (size_t)(s % NSLOT) * STAGE * 1024;
-#pragma unroll
-        for (int j = j0; j < j1; j++)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void *)(src[j] + (size_t)s * 1024),
-                (__attribute__((address_space(3))) void *)(slot + (size_t)(wave + NW * j) * 1024), 16, 0, 0);
-    };
+    // pieces of the next stage's fragment reads, to be spread between the multiplications
     auto frag_part = [&](int s, v4i *fa, v4i *fb, int part) {           // part 0: token side, 1 / 2: halves of the weight side
         const unsigned char *base = lds + (size_t)(s % NSLOT) * STAGE * 1024 + lane * 16;
         if (part == 0) {
@@ -422,7 +422,7 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
             for (int j = 0; j < TM; j++) fb[j] = *(const v4i *)(base + (size_t)(BN + wm * TM + j) * 1024);
         } else {
 #pragma unroll
-            for (int i = (part - 1) * (TN / 2); i < part * (TN / 2); i++)
+            for (int i = part == 1 ? 0 : TN / 2; i < (part == 1 ? TN / 2 : TN); i++)
                 fa[i] = *(const v4i *)(base + (size_t)(wn * TN + i) * 1024);
         }
     };
@@ -434,28 +434,27 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
         // while the matrix pipe is busy, not in front of it
         const bool more = s + PD < NS;
         const int sn = min(s + 1, NS - 1);
-        constexpr int E = TN / 8 > 0 ? TN / 8 : 1;   // weight fragments per eighth of a stage
-        multiply(ca, cb, 0, E);
+        multiply(ca, cb, 0, 1);
         __builtin_amdgcn_sched_barrier(0);
         if (more) dma_part(s + PD, 0, LOADS / 2);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(ca, cb, E, 2 * E);
+        multiply(ca, cb, 1, 2);
         __builtin_amdgcn_sched_barrier(0);
         if (more) dma_part(s + PD, LOADS / 2, LOADS);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(ca, cb, 2 * E, 3 * E);
+        multiply(ca, cb, 2, 3);
         __builtin_amdgcn_sched_barrier(0);
         frag_part(sn, na, nb, 0);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(ca, cb, 3 * E, 4 * E);
+        multiply(ca, cb, 3, 4);
         __builtin_amdgcn_sched_barrier(0);
         frag_part(sn, na, nb, 1);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(ca, cb, 4 * E, 5 * E);
+        multiply(ca, cb, 4, 5);
         __builtin_amdgcn_sched_barrier(0);
         frag_part(sn, na, nb, 2);
         __builtin_amdgcn_sched_barrier(0);
-        multiply(ca, cb, 5 * E, TN);
+        multiply(ca, cb, 5, 8);
     };
     for (int s = 0; s < NS; s += 2) {
         step(s, fa0, fb0, fa1, fb1);
@@ -473,8 +472,8 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     // TN*TM inlined copies.  What depends only on the output column (weight scale / 127, bias, where a
     // fused-QKV column goes) is tabulated in LDS once per block; what depends only on the token (row
     // scale / 127, row addresses) sits in registers: the loop body has no division left.
-    constexpr int QN = TN / 2, NPARK = 2;                                // weight panels per parked half
-    static_assert(TN % 8 == 0, "a stage is multiplied in eighths; the epilogue parks half of the accumulators at a time");
+    constexpr int NPARK = TN % 2 ? 1 : 2, QN = TN / NPARK;               // weight panels parked at a time
+    static_assert(BN % 2 == 0, "a block begins at a whole word of the outlier mask");
     acc_t *mine = (acc_t *)lds + (size_t)wave * (QN * TM * 64) + lane;
     if constexpr (DIG) {
         // acc[digit * 4 + p][j]: lane (token row l%16, features 4 * (l/16) + r) of panel p, weight digit, plane j.
@@ -740,13 +739,13 @@ __global__ void __launch_bounds__(256) k_split_finish(GemmArgs ga, LinearW w, co
     if (t < ga.M) emit_output4(o, sess, ga.N, t, n0, acc, od, sx[t] / 127.0f, w.sw, w.bias);
 }
 
-template <int MODE, int TM, int EPI = 0>
-hipError_t launch_one(const GemmArgs &ga, const LinearW &w, const float *sx, const OutlierSet &os, const double *outl,
+template <int MODE, int WVN, int WVM, int TN, int TM, int EPI = 0>
+hipError_t launch_one(GemmArgs ga, const LinearW &w, const float *sx, const OutlierSet &os, const double *outl,
                       const OutDesc &o, const SessTable *sess, hipStream_t st) {
-    constexpr int WVN = 2, WVM = 4, TN = 8, NSLOT = 4, BN = WVN * TN, BM = WVM * TM;   // 8 waves, 128 x (16 TM) per wave
+    constexpr int NSLOT = 4, BN = WVN * TN, BM = WVM * TM, QN = TN % 2 ? TN : TN / 2;   // a wave: 16 TN features x 16 TM tokens
     const int total = ga.nb_n * ga.nb_m * (EPI == EPI_PARTIAL ? ga.ksplit : 1);
     const size_t lds_stage = (size_t)NSLOT * (BN + BM) * 1024;
-    const size_t lds_epi = (size_t)WVN * WVM * (TN / 2) * TM * 1024 + (size_t)BN * 16 * 16 + (size_t)BN * 4 * 8 + (size_t)BN / 2 * 4;
+    const size_t lds_epi = (size_t)WVN * WVM * QN * TM * 1024 + (size_t)BN * 16 * 16 + (size_t)BN * 4 * 8 + (size_t)BN / 2 * 4;
     const size_t lds = lds_stage > lds_epi ? lds_stage : lds_epi;
     auto kern = k_gemm_lds<MODE, WVN, WVM, TN, TM, NSLOT, EPI>;
     static std::mutex attr_lock;
@@ -763,58 +762,151 @@ hipError_t launch_one(const GemmArgs &ga, const LinearW &w, const float *sx, con
     return hipGetLastError();
 }
 
+// The block forms of the int8 product: panels of 16 features x token tiles of 16.  What a launch takes, in microseconds,
+// fitted to 310 linears (all four of blocks 1024 to 14336 wide, 80 to 4096 rows, every form; mean error 6 %, and the form it
+// picks is 0.6 % behind the best one on average): workgroups go in rounds of 256 * resident; per k-tile a round takes
+// stage + next * (further workgroups on the same unit), or its tiles at COPY if that is more; the first round costs `base` besides, a further one at least 2.
+// What the rule is for: 256 compute units and few blocks.  With 256 x 128 blocks as the smallest, calls of 65 to 1500 rows
+// left most of the units idle or split the contraction, which writes its sums and reads them again: 6144 x 2048 at 351 rows
+// 51 us split, 34 in blocks of 128 x 128; 12288 x 4096 at 351 rows 64 -> 57 (96 x 192: 256 blocks instead of 144) and at 1400
+// 142 -> 109 (192 x 192: 512 blocks instead of 288); 4096 x 1024 at 351 34 -> 28.  Deeper rings and another first k-tile
+// for each workgroup cost all forms 1 to 15 %: it is neither latency nor memory channels that bound the stages of the small
+// forms, but their copies (about 10 KB per microsecond and 256th of the chip) and the instructions around them.
+struct BlockForm {
+    int bn, bm, resident;
+    double stage, next, base;
+};
+enum { FORM_16x16, FORM_16x8, FORM_12x12, FORM_6x12, FORM_8x8, FORM_4x4, FORMS };
+constexpr BlockForm BLOCK_FORMS[FORMS] = {
+    {16, 16, 1, 0.627, 0, 4.0}, {16, 8, 1, 0.438, 0, -0.9}, {12, 12, 1, 0.449, 0, 0.9},
+    {6, 12, 1, 0.349, 0, -0.6}, {8, 8, 2, 0.320, 0.188, -1.0}, {4, 4, 1, 0.131, 0, -3.0},
+};
+constexpr double COPY = 16300;     // tiles per microsecond
+constexpr int UNITS = 256;
+
+int form_blocks(int form, int NT, int MTT) {
+    const BlockForm &f = BLOCK_FORMS[form];
+    return ((NT + f.bn - 1) / f.bn) * ((MTT + f.bm - 1) / f.bm);
+}
+double form_us(int form, int blocks, int ktiles) {
+    const BlockForm &f = BLOCK_FORMS[form];
+    const int cap = UNITS * f.resident, rounds = blocks / cap, rest = blocks % cap;
+    auto round_us = [&](int n) { return ktiles * fmax(f.stage + f.next * ((n - 1) / UNITS), n * (f.bn + f.bm) / COPY); };
+    return f.base + (rounds + (rest > 0) - 1) * fmax(f.base, 2.0) + rounds * round_us(cap) + (rest ? round_us(rest) : 0.0);
+}
+
+struct BlockPlan {
+    int form, ksplit;       // ksplit > 1: FORM_16x8, the contraction split
+    int tail_n;             // 256-feature blocks that go to a second launch in blocks of FORM_16x8
+    double us;
+};
+
 // One workgroup per compute unit (128 KB of LDS): a launch of 256 x 256 blocks takes ceil(blocks / 256) rounds of
 // equal length, and a last round that fills half of the units or less costs as much as a full one (896 blocks: 4
-// rounds for the work of 3.5).  In that case the feature blocks of the last round go to a second launch with
-// blocks of half the token height (256 x 128, 128 x 32 per wave), which fills all units for a shorter round
-// (measured: 2 to 4 % of the linear's time; 4-wave workgroups with a 3-slot ring, two per unit, were slower).
-template <int MODE, int TM>
-hipError_t launch_epi(const GemmArgs &ga, const LinearW &w, const float *sx, const OutlierSet &os, const double *outl,
+// rounds for the work of 3.5).  In that case the feature blocks of the last round can go to a second launch with
+// blocks of half the token height, which fills all units for a shorter round (measured: 2 to 4 % of the linear's time;
+// 4-wave workgroups with a 3-slot ring, two per unit, were slower).
+int tail_blocks(int NT, int MTT) {
+    const int nb_n = (NT + 15) / 16, nb_m = (MTT + 15) / 16, total = nb_n * nb_m, rest = total % UNITS;
+    return total > UNITS && rest > 0 && rest <= UNITS / 2 && rest % nb_m == 0 ? rest / nb_m : 0;
+}
+
+// Workgroups that share the k-tiles of a 256 x 128 output block of a call that makes few blocks (351 rows of
+// 4096 x 16384: 48 blocks on 256 compute units, 110 us; split five ways 32 us, and 9 us for
+// adding up): as many as fill the compute units once, each with at least 16 k-tiles to walk.
+int split_of(int NT, int ktiles, int MTT) {
+    const int blocks = form_blocks(FORM_16x8, NT, MTT);
+    return max(1, min(min(UNITS / blocks, ktiles / 16), PS_KSPLIT_MAX));
+}
+
+BlockPlan plan_blocks(int NT, int ktiles, int MTT, size_t part_bytes) {
+    BlockPlan best = {FORM_16x16, 1, 0, form_us(FORM_16x16, form_blocks(FORM_16x16, NT, MTT), ktiles)};
+    auto offer = [&](int form, int ksplit, int tail_n, double us) {
+        if (us < best.us) best = {form, ksplit, tail_n, us};
+    };
+    if (const int tail = tail_blocks(NT, MTT))
+        offer(FORM_16x16, 1, tail, form_us(FORM_16x16, form_blocks(FORM_16x16, NT - tail * 16, MTT), ktiles) +
+                                   form_us(FORM_16x8, form_blocks(FORM_16x8, tail * 16, MTT), ktiles) + 2.0);
+    for (int form = FORM_16x8; form < FORMS; form++) {
+        const int blocks = form_blocks(form, NT, MTT);
+        // 64 x 64: beyond one round, or with a long contraction, its times lie far above the estimate (8192 x 8192 at 80 rows
+        // 58 us against 52 split)
+        if (form == FORM_4x4 && (blocks > UNITS || ktiles > 64)) continue;
+        offer(form, 1, 0, form_us(form, blocks, ktiles));
+    }
+    // split: the sums of all shares are written and read again (0.15 us per MB, and 11 us more from about 5 to 13 MB: the
+    // kernels themselves hardly grow there, the gaps between them do); the weights stream at 5.6 TB/s at best
+    int split = split_of(NT, ktiles, MTT);
+    while (split > 1 && (size_t)split * NT * MTT * 1024 > part_bytes) split--;
+    if (split > 1) {
+        const double mb = 1.024e-3 * NT * MTT * split;
+        const double share = (ktiles + split - 1) / split * fmax(0.485, split * form_blocks(FORM_16x8, NT, MTT) * 24 / COPY);
+        offer(FORM_16x8, split, 0, -3.5 + 0.15 * mb + 11.4 * fmin(1.0, fmax(0.0, (mb - 5.0) / 8.0)) + fmax(share, NT * 1024.0 * ktiles / 5.6e6));
+    }
+    return best;
+}
+
+template <int MODE, int EPI>
+hipError_t launch_form(int form, const GemmArgs &ga0, const LinearW &w, const float *sx, const OutlierSet &os, const double *outl,
+                       const OutDesc &o, const SessTable *sess, hipStream_t st) {
+    GemmArgs ga = ga0;
+    const BlockForm &f = BLOCK_FORMS[form];
+    if (!ga.nb_n) ga.nb_n = (ga.N / 16 + f.bn - 1) / f.bn;
+    ga.nb_m = ((ga.M + 15) / 16 + f.bm - 1) / f.bm;
+    if (form == FORM_16x16) return launch_one<MODE, 2, 4, 8, 4, EPI>(ga, w, sx, os, outl, o, sess, st);
+    if (form == FORM_16x8) return launch_one<MODE, 4, 2, 4, 4, EPI>(ga, w, sx, os, outl, o, sess, st);
+    if constexpr (MODE == GEMM_INT8) {
+        if (form == FORM_12x12) return launch_one<MODE, 2, 4, 6, 3, EPI>(ga, w, sx, os, outl, o, sess, st);
+        if (form == FORM_6x12) return launch_one<MODE, 2, 4, 3, 3, EPI>(ga, w, sx, os, outl, o, sess, st);
+        if (form == FORM_8x8) return launch_one<MODE, 2, 4, 4, 2, EPI>(ga, w, sx, os, outl, o, sess, st);
+        if (form == FORM_4x4) return launch_one<MODE, 2, 4, 2, 1, EPI>(ga, w, sx, os, outl, o, sess, st);
+    }
+    return hipErrorInvalidValue;
+}
+template <int MODE>
+hipError_t launch_epi(int form, const GemmArgs &ga, const LinearW &w, const float *sx, const OutlierSet &os, const double *outl,
                       const OutDesc &o, const SessTable *sess, hipStream_t st) {
     if constexpr (MODE == GEMM_INT8) {
-        if (o.epilogue == 1) return launch_one<MODE, TM, 1>(ga, w, sx, os, outl, o, sess, st);
-        if (o.epilogue == 2) return launch_one<MODE, TM, 2>(ga, w, sx, os, outl, o, sess, st);
+        if (o.epilogue == 1) return launch_form<MODE, 1>(form, ga, w, sx, os, outl, o, sess, st);
+        if (o.epilogue == 2) return launch_form<MODE, 2>(form, ga, w, sx, os, outl, o, sess, st);
     }
-    return launch_one<MODE, TM, 0>(ga, w, sx, os, outl, o, sess, st);
+    return launch_form<MODE, 0>(form, ga, w, sx, os, outl, o, sess, st);
 }
 
 template <int MODE>
 hipError_t launch_lds(const GemmArgs &ga0, const LinearW &w, const float *sx, const OutlierSet &os, const double *outl,
                       const OutDesc &o, const SessTable *sess, hipStream_t st, size_t part_bytes = 0) {
-    constexpr int BN = 16, BM = 16, UNITS = 256;
     GemmArgs ga = ga0;
     const int NT = ga.N / 16, MTT = (ga.M + 15) / 16;
-    ga.nb_n = (NT + BN - 1) / BN;
-    ga.nb_m = (MTT + BM - 1) / BM;
-    ga.nb_n0 = 0;
-    const int total = ga.nb_n * ga.nb_m, rest = total % UNITS;
-    if (MTT <= BM / 2 || total * 2 <= UNITS) {
-        // at most 128 rows, or so few blocks that half the compute units would idle: blocks of half the height
-        // (no block is half empty, and there are twice as many of them)
-        ga.nb_m = (MTT + BM / 2 - 1) / (BM / 2);
-        if constexpr (MODE == GEMM_INT8) {
-            ga.ksplit = ps_gemm_lds_ksplit(ga.N, ga.ktiles, ga.M);
-            while (ga.ksplit > 1 && (size_t)ga.ksplit * NT * MTT * 1024 > part_bytes) ga.ksplit--;
-            if (ga.ksplit > 1) {
-                hipError_t e = launch_one<MODE, 2, EPI_PARTIAL>(ga, w, sx, os, outl, o, sess, st);
-                if (e != hipSuccess) return e;
-                k_split_finish<<<(NT * MTT + 3) / 4, 256, 0, st>>>(ga, w, sx, os, outl, o, sess);
-                return hipGetLastError();
-            }
+    ga.nb_n = ga.nb_n0 = 0;
+    BlockPlan plan;
+    if constexpr (MODE == GEMM_INT8) {
+        plan = plan_blocks(NT, ga.ktiles, MTT, part_bytes);
+        if (plan.ksplit > 1) {
+            ga.ksplit = plan.ksplit;
+            ga.nb_n = (NT + 15) / 16;
+            ga.nb_m = (MTT + 7) / 8;
+            hipError_t e = launch_one<MODE, 4, 2, 4, 4, EPI_PARTIAL>(ga, w, sx, os, outl, o, sess, st);
+            if (e != hipSuccess) return e;
+            k_split_finish<<<(NT * MTT + 3) / 4, 256, 0, st>>>(ga, w, sx, os, outl, o, sess);
+            return hipGetLastError();
         }
-        return launch_epi<MODE, 2>(ga, w, sx, os, outl, o, sess, st);
+    } else {
+        // fp16 (the backward pass, 128 rows and more): blocks of half the height for at most 128 rows, or so few blocks
+        // that half of the units would idle
+        const bool half = MTT <= 8 || 2 * form_blocks(FORM_16x16, NT, MTT) <= UNITS;
+        plan = {half ? FORM_16x8 : FORM_16x16, 1, half ? 0 : tail_blocks(NT, MTT), 0};
     }
-    if (total > UNITS && rest > 0 && rest <= UNITS / 2 && rest % ga.nb_m == 0) {
+    if (plan.tail_n) {
         GemmArgs gb = ga;
-        gb.nb_n = rest / ga.nb_m;
-        ga.nb_n -= gb.nb_n;
+        gb.nb_n = plan.tail_n;
+        ga.nb_n = (NT + 15) / 16 - plan.tail_n;
         gb.nb_n0 = ga.nb_n;
-        gb.nb_m = (MTT + BM / 2 - 1) / (BM / 2);
-        hipError_t e = launch_epi<MODE, 4>(ga, w, sx, os, outl, o, sess, st);
+        hipError_t e = launch_epi<MODE>(FORM_16x16, ga, w, sx, os, outl, o, sess, st);
         if (e != hipSuccess) return e;
-        return launch_epi<MODE, 2>(gb, w, sx, os, outl, o, sess, st);
+        return launch_epi<MODE>(FORM_16x8, gb, w, sx, os, outl, o, sess, st);
     }
-    return launch_epi<MODE, 4>(ga, w, sx, os, outl, o, sess, st);
+    return launch_epi<MODE>(plan.form, ga, w, sx, os, outl, o, sess, st);
 }
 
 GemmArgs gemm_args(const void *a_tiles, const void *b_tiles, int ktiles, int M, int N) {
@@ -830,13 +922,11 @@ GemmArgs gemm_args(const void *a_tiles, const void *b_tiles, int ktiles, int M, 
 
 }  // namespace
 
-// Workgroups that share the k-tiles of a 256 x 128 output block of a call that makes few blocks (a 351-row call on a
-// 4096 x 16384 linear: 48 blocks on 256 compute units, 110 us; split five ways 32 us, and 9 us for
-// adding up): as many as fill the compute
-// units once, each with at least 16 k-tiles to walk.
-int ps_gemm_lds_ksplit(int N, int ktiles, int M) {
-    const int blocks = ((N + 255) / 256) * ((M + 127) / 128);
-    return max(1, min(min(256 / blocks, ktiles / 16), PS_KSPLIT_MAX));
+// Rough microseconds of a linear of M rows in blocks with its row and digit kernels (see BLOCK_FORMS), to hold against the
+// other forms of a call.
+double ps_gemm_lds_us(int N, int K, int M) {
+    const BlockPlan plan = plan_blocks(N / 16, K / 64, (M + 15) / 16, ~(size_t)0);
+    return fmax(25.4 + 0.58e-6 * M * K + 1.4e-6 * M * N + plan.us, 25.0 + (double)N * K / 4.0e6);
 }
 
 hipError_t ps_gemm_f16_tiles(const __half *feat_tiles, const __half *tok_tiles, int ktiles, int M, int n_feat,
@@ -869,7 +959,7 @@ hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t 
     gd.od = mo.od;
     gd.nb_n = (w.N / 16 + 7) / 8;                // 8 panels and 4 token tiles per block (times 2 digits, 4 planes)
     gd.nb_m = ((M + 15) / 16 + 3) / 4;
-    e = launch_one<GEMM_DIGITS, 4>(gd, w, sx, os, nullptr, o, sess, st);
+    e = launch_one<GEMM_DIGITS, 2, 4, 8, 4>(gd, w, sx, os, nullptr, o, sess, st);
     if (e != hipSuccess) return e;
     GemmArgs gi = gemm_args(w.wt, xq_tiled, w.K / 64, M, w.N);
     gi.part = (v4i *)mo.wd;                  // the digit tiles have been read when the int8 product starts

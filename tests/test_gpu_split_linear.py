@@ -71,6 +71,34 @@ def test_four_waves_per_workgroup(ffn, hidden, nh, M):
     osp.destroy()
 
 
+# Every form of output block (panels of 16 features x token tiles of 16): 4 x 4 (one block, and as many as it takes at most), 8 x 8,
+# 12 x 12, 6 x 12, 16 x 8, 16 x 16; one to seventeen k-tiles, last blocks ragged both ways, all three tails, without outlier
+# columns, with a few, with more than the fp64 path takes, with all
+@pytest.mark.parametrize("ffn,hidden,nh,M,n_out,epilogue", [
+    (64, 64, 1, 65, 3, 0), (4096, 192, 3, 256, 0, 1), (4096, 192, 3, 241, 70, 2), (8320, 192, 3, 77, 5, 2), (8320, 192, 3, 128, 100, 1),
+    (8320, 192, 3, 113, 192, 0), (13120, 192, 3, 525, 64, 1), (13248, 192, 3, 577, 9, 2), (16576, 1088, 17, 141, 66, 2), (16576, 1088, 17, 190, 2, 1),
+    (16576, 320, 5, 653, 1, 2), (16576, 1088, 17, 397, 65, 0)])
+def test_every_block_form(ffn, hidden, nh, M, n_out, epilogue):
+    cfg = synth.SpanConfig("forms", 1, hidden, nh, 1, M, 1, 1, (20.0, 40.0), 5, ffn=ffn)
+    osp, gsp, params = build_pair(cfg, max_rows=M)
+    r = np.random.default_rng(M + ffn)
+    X = np.clip(r.standard_normal((M, hidden)) * 2, -5.9, 5.9)
+    cols = r.choice(hidden, n_out, replace=False)
+    X[r.integers(0, M, n_out), cols] = r.uniform(6.0, 30.0, n_out) * r.choice([-1, 1], n_out)
+    X = X.astype(np.float16)
+    resid = (r.standard_normal((M, ffn)) * 4).astype(np.float16) if epilogue == 2 else None
+    wq, sw = osp.get_weight(0, 2)
+    Y, dbg = oracle.linear(X, wq, sw, params[0]["b_up"], 6.0, epilogue, resid, want_debug=True)
+    with midsize("blocks"):
+        out = gsp.debug_linear(0, 2, to_dev(X), epilogue, None if resid is None else to_dev(resid))
+        torch.cuda.synchronize()
+    assert dbg["mask"].sum() == n_out and np.array_equal(to_np(out["mask"]), dbg["mask"])
+    assert np.array_equal(to_np(out["acc"]), dbg["acc"])
+    assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
+    gsp.close()
+    osp.destroy()
+
+
 # Which form a call of 65 to 512 rows takes: the estimate behind the choice must not miss the faster one by much.
 @pytest.mark.parametrize("H,nh,which,M", [(1024, 16, 1, 320), (1024, 16, 3, 448), (1536, 12, 1, 257), (2048, 16, 3, 160), (4096, 32, 0, 320), (4096, 32, 2, 512)])
 def test_the_faster_form_is_chosen(H, nh, which, M):
