@@ -90,6 +90,7 @@ Workspace carve(const petals_span_config &c, uint8_t *base, bool with_rest = tru
         w.x64 = (double *)take(Mp / 16 * PS_OUTLIER_CHUNKS * 64 * 8);
         const size_t NKmax = (size_t)(3 * H > F ? 3 * H : F) * H > H * F ? (size_t)(3 * H > F ? 3 * H : F) * H : H * F;
         w.many.list = (int *)take((Kmax + 64) * 4);
+        w.many.regular = (int *)take((Kmax + 64) * 4);
         w.many.xl = (int8_t *)take((size_t)PS_X_DIGITS * Mp * (Kmax + 64));
         w.many.wd_bytes = 2 * (NKmax + 64 * Nmax);
         w.many.wd = (int8_t *)take(w.many.wd_bytes);
@@ -180,7 +181,7 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
         } else if (!mask_ready) {
             HIP_TRY(ps_colmask(X, M, w.K, theta, mask, st));
         }
-        const OutlierPrep prep = {w, small ? nullptr : ws.ocount, ws.wd64, ws.x64, ws.many.list};
+        const OutlierPrep prep = {w, small ? nullptr : ws.ocount, ws.wd64, ws.x64, ws.many.list, ws.many.regular};
         // (a LayerNorm's output has few outlier columns: only the inputs that attention and GeLU write go for digits)
         const bool digits = !ln_g && ws.xd && w.N == c.hidden && ps_gemm_digits_applies(w.N, w.K, M);
         const RowDigits rd = {digits ? ws.xd : nullptr, ws.ocount, ws.digits.done};

@@ -152,11 +152,19 @@ hipError_t ps_mask_count(const uint32_t *masks, int n_masks, int words, int32_t 
 #define PS_X_DIGITS 6            // balanced 8-bit digits of an fp16 activation in units of 2^-24 (4 cover |x| < 127.5)
 struct ManyOutliers {
     int *list;      // [K] outlier column indices, ascending, padded with -1 to a multiple of 64
-    int8_t *xl;     // digit tiles of the activations [PS_X_DIGITS][ceil(M/16)][ceil(n_out/64)][1024]
-    int8_t *wd;     // digit tiles of the dequantized weights [2][N/16][ceil(n_out/64)][1024]
+    int *regular;   // [K] the other columns, likewise, where ps_regular_compacted
+    int8_t *xl;     // digit tiles of the activations [PS_X_DIGITS][ceil(M/16)][ceil(n_out/64)][1024], behind them the codes
+    int8_t *wd;     // digit tiles of the dequantized weights [2][N/16][ceil(n_out/64)][1024] of the regular columns (rows, weights)
     double *od;     // [M, N] the outlier product
     size_t wd_bytes;   // room at wd: once the digit products are done it holds the partial sums of a split contraction
 };
+// Where many columns are outliers, the codes of the other ones are gathered beside the digits and the int8 product walks only
+// these (its codes of outlier columns are zero).  Gathering a column costs what multiplying some 2000 rows takes: 2048 rows
+// with half of the columns -1 to +2 %, with seven in ten -4 % (8192 wide), with nine in ten -7 %; 1024 rows with seven in ten
+// -2 to -4 %; 4096 rows of a 14336-wide block with 84 and 61 % 1.05 times as fast altogether.
+__host__ __device__ inline bool ps_regular_compacted(int n_out, int K, int M) {
+    return n_out > PS_EXACT_OUTLIERS && n_out < K && (long long)n_out * M >= (long long)(K - n_out) * 2000;
+}
 // LDS-staged linear for M > 64 rows (any number of outlier columns)
 hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t *mask, const __half *X, const float *sx,
                        int M, const OutlierSet &os, const ManyOutliers &mo, const OutDesc &o, const SessTable *sess,

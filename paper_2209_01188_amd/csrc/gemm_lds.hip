@@ -219,6 +219,7 @@ __device__ __forceinline__ void token_digits_compacted(const __half *__restrict_
 struct GemmArgs {
     const unsigned char *a_tiles;   // weight-side tiles: [rows][KTILES][1024]
     const unsigned char *b_tiles;   // token-side tiles:  [rows][KTILES][1024]
+    const unsigned char *a_regular, *b_regular;     // int8: ManyOutliers' wd and xl
     int ktiles;                     // int8: K/64.  fp16: the plain product's tile count.  digits: derived from the outlier count
     int M, N;
     int nb_n, nb_m;                 // output blocks of this launch along the features and along the tokens
@@ -235,19 +236,49 @@ struct GemmArgs {
     float *f32_out;           // plain fp16 product: [M, N] fp32 result
 };
 
+// Tiles [rows][tiles of `list`][1024] of the listed columns of src, which has KT tiles to a row; 0 where the list has -1.
+__device__ __forceinline__ void gather_codes(const int8_t *__restrict__ src, int rows, int KT, const int *__restrict__ list, int n,
+                                             int8_t *__restrict__ dst, int bid, int nblk) {
+    const int RT = (n + 63) >> 6, lane = threadIdx.x & 63, row = lane & 15;
+    for (int item = bid; item < rows * RT; item += nblk) {
+        const int r = item / RT, rt = item - r * RT;
+        int id[16], c[16];
+#pragma unroll
+        for (int q = 0; q < 4; q++) *(int4 *)(id + 4 * q) = ((const int4 *)(list + rt * 64 + (lane >> 4) * 16))[q];
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int k = max(id[e], 0);
+            c[e] = src[((size_t)r * KT + (k >> 6)) * 1024 + (((k & 63) >> 4) * 16 + row) * 16 + (k & 15)];
+        }
+        v4i codes;
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            codes[q] = pack4(id[4 * q] < 0 ? 0 : c[4 * q], id[4 * q + 1] < 0 ? 0 : c[4 * q + 1], id[4 * q + 2] < 0 ? 0 : c[4 * q + 2], id[4 * q + 3] < 0 ? 0 : c[4 * q + 3]);
+        *(v4i *)(dst + ((size_t)item * 64 + lane) * 16) = codes;
+    }
+}
+
 // Both kinds of digit tiles in one launch (a launch costs as much as the work of a call with few tiles): the first NBX waves
 // cut the activations, the rest the weights.  Workgroups of four waves, which share nothing: a launch that finds nothing to
 // do costs by its number of workgroups.  Does nothing unless the call has more outlier columns than the fp64 path takes.
 __global__ void __launch_bounds__(256) k_digit_tiles(const __half *__restrict__ X, int M, LinearW w, const uint32_t *__restrict__ mask,
                                                       int *__restrict__ count, const int *__restrict__ list,
-                                                      int8_t *__restrict__ xl, int8_t *__restrict__ wd, int NBX) {
+                                                      int8_t *__restrict__ xl, int8_t *__restrict__ wd, int NBX,
+                                                      const int8_t *__restrict__ xq_tiled, const int *__restrict__ regular) {
     __shared__ __align__(16) __half stage[4][DT_TILES * 64 * 16];
     const int n_out = count[0];
     if (n_out <= PS_EXACT_OUTLIERS) return;
-    const int wave = threadIdx.x >> 6, wv = (int)blockIdx.x * 4 + wave;
+    const int wave = threadIdx.x >> 6, wv = (int)blockIdx.x * 4 + wave, KT = w.K >> 6, CT = (n_out + 63) >> 6;
+    const bool gather = regular && ps_regular_compacted(n_out, w.K, M);
     if (wv >= NBX) {
+        const int NT = w.N >> 4;
         weight_digits(w, list, wd, n_out, wv - NBX, (int)gridDim.x * 4 - NBX);
+        if (gather) gather_codes(w.wt, NT, KT, regular, w.K - n_out, wd + (size_t)2 * NT * CT * 1024, wv - NBX, (int)gridDim.x * 4 - NBX);
         return;
+    }
+    if (gather) {
+        const int MTT = (M + 15) >> 4;
+        gather_codes(xq_tiled, MTT, KT, regular, w.K - n_out, xl + (size_t)PS_X_DIGITS * MTT * CT * 1024, wv, NBX);
     }
     int need = 0;
     if (n_out * 7 >= w.K * 4) token_digits_compacted(X, M, w.K, (const uint64_t *)mask, list, xl, n_out, stage[wave], wv, NBX, need);
@@ -280,7 +311,15 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     if (DIG && !many) return;
     // k-tiles to walk (64 int8 or 32 fp16 columns each).  If EVERY column is an outlier all int8 codes are
     // zero: the int8 product is skipped and only the epilogue runs.
-    const int KTILES = F16 ? ga.ktiles : DIG ? (n_out + 63) >> 6 : ga.ktiles;       // tiles per row of the operands
+    int KTILES = F16 ? ga.ktiles : DIG ? (n_out + 63) >> 6 : ga.ktiles;       // tiles per row of the operands
+    const unsigned char *a_tiles = ga.a_tiles, *b_tiles = ga.b_tiles;
+    if constexpr (MODE == GEMM_INT8 && EPI != EPI_PARTIAL) {
+        if (many && ps_regular_compacted(n_out, ga.ktiles * 64, ga.M)) {        // the regular columns' codes by themselves
+            KTILES = ga.ktiles - (n_out >> 6);
+            a_tiles = ga.a_regular + (size_t)2 * (ga.N >> 4) * ((n_out + 63) >> 6) * 1024;
+            b_tiles = ga.b_regular + (size_t)PS_X_DIGITS * ((ga.M + 15) >> 4) * ((n_out + 63) >> 6) * 1024;
+        }
+    }
     int NS = !F16 && !DIG && n_out == ga.ktiles * 64 ? 0 : KTILES;
 
     // Workgroup -> output block.  Consecutive workgroup ids land on different XCDs (8 of them, each
@@ -344,8 +383,8 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
                 src[j] = ga.b_tiles + ((size_t)plane * MTT + min(bm * WVM + t / TM, MTT - 1)) * KTILES * 1024 + lane * 16;
             }
         } else {
-            if (s < BN) src[j] = ga.a_tiles + ((size_t)min(nt0 + s, NT - 1) * KTILES + s_first) * 1024 + lane * 16;
-            else src[j] = ga.b_tiles + ((size_t)min(mt0 + s - BN, MTT - 1) * KTILES + s_first) * 1024 + lane * 16;
+            if (s < BN) src[j] = a_tiles + ((size_t)min(nt0 + s, NT - 1) * KTILES + s_first) * 1024 + lane * 16;
+            else src[j] = b_tiles + ((size_t)min(mt0 + s - BN, MTT - 1) * KTILES + s_first) * 1024 + lane * 16;
         }
     }
 
@@ -952,7 +991,9 @@ hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t 
     // The outlier-heavy case first (every kernel of it returns at once when the call has few outlier columns):
     // digit tiles of the activations and of the dequantized weights, the digit products.
     // (768 workgroups: those that are resident at once; twice as many cost a call that has nothing to cut 0.3 us more)
-    k_digit_tiles<<<768, 256, 0, st>>>(X, M, w, mask, (int *)os.count, mo.list, mo.xl, mo.wd, 1024);
+    // (a split product walks all columns: its sums go where the regular ones' codes would be)
+    const bool split = plan_blocks(w.N / 16, w.K / 64, (M + 15) / 16, mo.wd_bytes).ksplit > 1;
+    k_digit_tiles<<<768, 256, 0, st>>>(X, M, w, mask, (int *)os.count, mo.list, mo.xl, mo.wd, 1024, xq_tiled, split ? nullptr : mo.regular);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     GemmArgs gd = gemm_args(mo.wd, mo.xl, 0, M, w.N);
@@ -962,6 +1003,8 @@ hipError_t ps_gemm_lds(const LinearW &w, const int8_t *xq_tiled, const uint32_t 
     e = launch_one<GEMM_DIGITS, 2, 4, 8, 4>(gd, w, sx, os, nullptr, o, sess, st);
     if (e != hipSuccess) return e;
     GemmArgs gi = gemm_args(w.wt, xq_tiled, w.K / 64, M, w.N);
+    gi.a_regular = (const unsigned char *)mo.wd;
+    gi.b_regular = (const unsigned char *)mo.xl;
     gi.part = (v4i *)mo.wd;                  // the digit tiles have been read when the int8 product starts
     return launch_lds<GEMM_INT8>(gi, w, sx, os, mo.od, o, sess, st, mo.wd_bytes);
 }

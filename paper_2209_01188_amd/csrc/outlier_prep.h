@@ -8,7 +8,7 @@ struct OutlierPrep {
     LinearW w;
     int *count;          // null: nothing to prepare
     double *wd64, *x64;
-    int *full_list;
+    int *full_list, *regular_list;
 };
 // waves of work: one per 16 output rows and one per 16 tokens, and no fewer than the list has groups of 1024 columns (an
 // output of 64 rows has four panels, its 65536 columns 64 groups)
@@ -59,6 +59,14 @@ __device__ __forceinline__ void outlier_prep_wave(const OutlierPrep &pr, const u
         if (item * 64 >= nchunk || !pr.full_list) return;
         uint32_t b = chunk(item * 64 + lane);
         int at = (int)wave_reduce(before, 0u, sum) + lanes_before(b);
+        if (ps_regular_compacted(total, K, M)) {
+            const int k0 = (item * 64 + lane) * 16;
+            int to = k0 - at;
+            if (k0 < K)
+                for (int e = 0; e < 16; e++)
+                    if (!((b >> e) & 1u)) pr.regular_list[to++] = k0 + e;
+            if (item == 0 && lane < ((total - K) & 63)) pr.regular_list[K - total + lane] = -1;
+        }
         while (b) {
             pr.full_list[at++] = (item * 64 + lane) * 16 + __ffs(b) - 1;
             b &= b - 1;

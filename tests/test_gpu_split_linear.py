@@ -154,6 +154,28 @@ def test_digit_tiles_of_many_columns(n_out, big):
     osp.destroy()
 
 
+# The int8 product over the regular columns' gathered codes: one column below the line, on it, 65, 64, 63 and 1 regular columns
+@pytest.mark.parametrize("n_out", [718, 719, 1023, 1024, 1025, 1087])
+def test_regular_columns_by_themselves(n_out):
+    M, hidden, nh = 1030, 1088, 17
+    cfg = synth.SpanConfig("regular", 1, hidden, nh, 1, M, 1, 1, (20.0, 40.0), 6, ffn=192)
+    osp, gsp, params = build_pair(cfg, max_rows=M)
+    r = np.random.default_rng(n_out)
+    X = np.clip(r.standard_normal((M, hidden)) * 2, -5.9, 5.9)
+    X[r.integers(0, M, n_out), r.choice(hidden, n_out, replace=False)] = r.uniform(6.0, 127.0, n_out) * r.choice([-1, 1], n_out)
+    X = X.astype(np.float16)
+    wq, sw = osp.get_weight(0, 1)
+    resid = r.standard_normal((M, hidden)).astype(np.float16)
+    Y, dbg = oracle.linear(X, wq, sw, params[0]["b_dense"], 6.0, 2, resid, want_debug=True)
+    assert dbg["mask"].sum() == n_out
+    out = gsp.debug_linear(0, 1, to_dev(X), 2, to_dev(resid))
+    torch.cuda.synchronize()
+    assert np.array_equal(to_np(out["acc"]), dbg["acc"])
+    assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
+    gsp.close()
+    osp.destroy()
+
+
 # Outputs so narrow that the preparation has fewer waves of gathers than the column list has groups of 1024 (12, 37 and 61 for
 # 64), and just as many as it needs (65)
 @pytest.mark.parametrize("hidden,nh,M", [(64, 1, 128), (64, 1, 513), (896, 7, 65), (960, 15, 65)])
