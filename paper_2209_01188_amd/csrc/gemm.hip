@@ -56,14 +56,14 @@ k_gemm(LinearW w, const int8_t *__restrict__ xq_tiled, const int8_t *__restrict_
     }
     const int K = w.K, KT = K >> 6, N = w.N;
     if (gridDim.y > 1) {
-        // a call of more than 64 rows: blockIdx.y takes rows 64 y .. +64 of it
-        const int r0 = blockIdx.y * 64;
+        // a call of more rows than MT token tiles: blockIdx.y takes MT of them
+        const int r0 = blockIdx.y * 16 * MT;
         const size_t at = (size_t)r0 * N;
         xq_tiled += (size_t)(r0 >> 4) * KT * 1024;
         xo_tiled += (size_t)(r0 >> 4) * KT * 1024;
         X += (size_t)r0 * K;
         sx += r0;
-        M = min(64, M - r0);
+        M = min(16 * MT, M - r0);
         if (o.scatter) {
             o.t0 = r0;
         } else {
@@ -235,7 +235,7 @@ hipError_t launch(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_til
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    kern<<<dim3(wgs > digit_wgs ? wgs : digit_wgs, (M + 63) / 64), 64 * WVK, lds, st>>>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, digit_arg<DIG>(dc));
+    kern<<<dim3(wgs > digit_wgs ? wgs : digit_wgs, (M + 16 * MT - 1) / (16 * MT)), 64 * WVK, lds, st>>>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, digit_arg<DIG>(dc));
     return hipGetLastError();
 }
 
@@ -270,10 +270,26 @@ static double gemm_rows64_us(const LinearW &w, int M, int wn, bool &four) {
     return fmin(t4, t8);
 }
 
+// The forms of 33 to 512 rows: 64 rows per workgroup as above, or 32.  32 rows: two panels and four waves, three workgroups to a
+// compute unit, so rounds of 768 (2.75 us + 0.24 per tile), where 64 rows fill their rounds badly or their waves wait for each
+// other: 6144 x 2048 at 128 rows 31.3 -> 24.4 us, 2048 x 2048 at 300 31.8 -> 24.0, 4096 x 16384 at 300 156 -> 136 (16384 x 4096 at
+// 128 rows the other way round: 55.5 against 68.5); or one panel and sixteen waves in rounds of 256 (3.5 us + 0.06), where there
+// are few panels and many tiles: 2048 x 8192 at 64 rows 27.9 -> 23.5, 1024 x 4096 at 128 22.1 -> 19.9.  On 72 linears of 1024- to 4096-wide
+// blocks at 40 to 300 rows 5 % less, none more.
+enum { ROWS64_8, ROWS64_4, ROWS32_4, ROWS32_16 };
+static double gemm_rows_us(const LinearW &w, int M, int &form) {
+    bool four;
+    const int panels = w.N / 16, y = (M + 31) / 32;
+    const double tiles = w.K / 64, us64 = gemm_rows64_us(w, M, gemm_panels_per_wg(w.N) > 1 ? 2 : 1, four);
+    const double us4 = panels % 2 ? 1e30 : (panels / 2 * y + 767) / 768 * (2.75 + 0.24 * tiles), us16 = (panels * y + 255) / 256 * (3.5 + 0.06 * tiles);
+    form = us64 <= us4 && us64 <= us16 ? (four ? ROWS64_4 : ROWS64_8) : us4 <= us16 ? ROWS32_4 : ROWS32_16;
+    return fmin(us64, fmin(us4, us16));
+}
+
 // Rough times in microseconds of a linear with its row kernels, fitted to both forms measured on the four linears of
-// blocks 1024 to 14336 wide at 65 to 512 rows (the choice is 0.6 % behind the faster one on average; at worst 7 %, 5120 x 5120
-// at 80 rows, 43 us for 40).
-// 64 rows per workgroup: see above, 12 us for the row kernels in front.  All rows go in one launch: charged by 64 rows, as
+// blocks 1024 to 14336 wide at 65 to 512 rows (the choice is 0.6 % behind the faster one on average; at worst 7 %, 2048 x 8192
+// at 351 rows, 55 us for 51).
+// 64 rows per workgroup: see above, 13 us for the row kernels in front.  All rows go in one launch: charged by 64 rows, as
 // when each 64 were a launch, narrow outputs went to the blocks too early (1024 x 1024 at 320 rows: 24 us in this form, 36 in
 // blocks).
 // Output blocks: ps_gemm_lds_us.
@@ -284,8 +300,8 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
         if (!strcmp(force, "blocks")) return false;
         if (!strcmp(force, "chunks")) return true;
     }
-    bool four;
-    return 12.0 + gemm_rows64_us(w, M, gemm_panels_per_wg(w.N) > 1 ? 2 : 1, four) < ps_gemm_lds_us(w.N, w.K, M);
+    int form;
+    return 13.0 + gemm_rows_us(w, M, form) < ps_gemm_lds_us(w.N, w.K, M);
 }
 
 hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,
@@ -329,12 +345,14 @@ hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_ti
         if (wn == 2) PS_GEMM_CASE4(2, 2, 2);
         PS_GEMM_CASE4(1, 2, 2);
     }
-    if (M <= PS_CHUNKED_ROWS_MAX) {   // more than 64 rows: 64 per workgroup, see the kernel
-        bool four;
-        gemm_rows64_us(w, M, wn >= 2 ? 2 : 1, four);
-        if (wn >= 2 && four) return launch<2, 4, 1, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
+    if (M <= PS_CHUNKED_ROWS_MAX) {   // 64 or 32 rows per workgroup, see the kernel
+        int form;
+        gemm_rows_us(w, M, form);
+        if (form == ROWS32_4) return launch<2, 2, 1, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
+        if (form == ROWS32_16) return launch<1, 2, 1, 16>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
+        if (wn >= 2 && form == ROWS64_4) return launch<2, 4, 1, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
         if (wn >= 2) PS_GEMM_CASE(2, 4, 1);
-        if (four) return launch<1, 4, 1, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
+        if (form == ROWS64_4) return launch<1, 4, 1, 4>(w, xq_tiled, xo_tiled, mask, X, sx, M, o, sess, dc, st);
         PS_GEMM_CASE(1, 4, 1);
     }
 #undef PS_GEMM_CASE4

@@ -99,6 +99,32 @@ def test_every_block_form(ffn, hidden, nh, M, n_out, epilogue):
     osp.destroy()
 
 
+# 32 rows per workgroup: one panel and sixteen waves (fewer k-tiles than waves, more, an odd number), two panels and four waves (one
+# round of workgroups, several); ragged last rows, one workgroup of rows that holds a single one, residual and GeLU tails
+@pytest.mark.parametrize("ffn,hidden,nh,which,M,epilogue", [
+    (2112, 192, 3, 3, 33, 2), (4160, 192, 3, 3, 65, 0), (4160, 192, 3, 3, 64, 2), (8256, 192, 3, 3, 130, 2),
+    (8192, 320, 5, 2, 100, 1), (4160, 192, 3, 2, 200, 2), (7232, 192, 3, 2, 225, 1), (7232, 192, 3, 2, 500, 0)])
+def test_32_rows_per_workgroup(ffn, hidden, nh, which, M, epilogue):
+    cfg = synth.SpanConfig("rows32", 1, hidden, nh, 1, M, 1, 1, (20.0, 40.0), 4, ffn=ffn)
+    osp, gsp, params = build_pair(cfg, max_rows=M)
+    N, K = gsp.shapes(which)
+    r = np.random.default_rng(M + ffn)
+    X = np.clip(r.standard_normal((M, K)) * 2, -5.9, 5.9)
+    X[r.integers(0, M, 20), r.choice(K, 20, replace=False)] = 9.0
+    X[M - 1, K - 1] = -40.0
+    X = X.astype(np.float16)
+    resid = (r.standard_normal((M, N)) * 4).astype(np.float16) if epilogue == 2 else None
+    wq, sw = osp.get_weight(0, which)
+    Y, dbg = oracle.linear(X, wq, sw, params[0]["b_up" if which == 2 else "b_down"], 6.0, epilogue, resid, want_debug=True)
+    with midsize("chunks"):
+        out = gsp.debug_linear(0, which, to_dev(X), epilogue, None if resid is None else to_dev(resid))
+        torch.cuda.synchronize()
+    assert np.array_equal(to_np(out["acc"]), dbg["acc"])
+    assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
+    gsp.close()
+    osp.destroy()
+
+
 # Which form a call of 65 to 512 rows takes: the estimate behind the choice must not miss the faster one by much.
 @pytest.mark.parametrize("H,nh,which,M", [(1024, 16, 1, 320), (1024, 16, 3, 448), (1536, 12, 1, 257), (2048, 16, 3, 160), (4096, 32, 0, 320), (4096, 32, 2, 512)])
 def test_the_faster_form_is_chosen(H, nh, which, M):
