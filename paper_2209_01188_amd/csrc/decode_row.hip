@@ -554,8 +554,14 @@ hipError_t ps_decode_row(const StepArgs &s0, int d, int max_keys, hipStream_t st
     // One workgroup per head up to 64 KB of keys; more ranges than that cost more in their merge (4 to 5 us a block) than they save
     // (8 blocks of 1024 columns, 16 heads of 64, 2048 keys: 4 ranges 188 us, 8 ranges 202, 16 ranges 252; 8 heads of 128, 1000
     // keys: 1 range 205, 3 ranges 189), and together no more than half of the workgroups (4 blocks of 2048 columns, 32 heads,
-    // 2000 keys: 8 ranges 126 us, 4 ranges 115).
-    s.ranges = max(1, min(min(max_keys * d / 32768, 128 / s.nh), PS_ATTN_MAX_SPLITS));
+    // 2000 keys: 8 ranges 126 us, 4 ranges 115) - three quarters once half would leave each 192 KB of keys and as many values:
+    // from there on it is the units that read the cache that count (us a block at 128, 192, 256 ranges in all, and as five launches:
+    // 48 heads of 64, 16384 keys: 103, 78, 75, 87; 32 heads of 128, 32768 keys: 187, 154, 152, 159; below that line 16 heads of 128,
+    // 4096 keys: 36, 38, 41, 47; 16 heads of 64, 8192 keys: 32, 33, 36, 42).  All of them leave no unit to what comes behind (32 heads
+    // of 128, 4096 keys: 71 at 192, 72 at 256).
+    const int half = max(128 / s.nh, 1);
+    const int most = (long long)max_keys * d >= 98304ll * half ? 192 / s.nh : half;
+    s.ranges = max(1, min(min((long long)max_keys * d / 32768, (long long)most), (long long)PS_ATTN_MAX_SPLITS));
     // columns of a LayerNorm row per thread, tiles of a panel per wave: the smallest form that takes the span (fewer registers,
     // fewer loads beyond the panels' ends)
     auto fits = [&](int h) { return s.H <= h && s.F <= 4 * h; };

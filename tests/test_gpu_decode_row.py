@@ -25,7 +25,9 @@ def _config(blocks, H, nh, F):
     (1, 1024, 8, 4096, 400, 0.5), (2, 960, 15, 4160, 129, 6.0), (2, 1088, 17, 4352, 512, 6.0), (2, 2048, 16, 8192, 300, 6.0),
     (1, 2048, 32, 1024, 1500, 0.0), (2, 2112, 33, 8448, 70, 6.0), (2, 3072, 24, 12288, 300, 6.0), (1, 2944, 46, 9216, 1200, 6.0),
     (1, 512, 8, 12288, 20, 6.0), (2, 3136, 49, 12544, 100, 6.0), (2, 4096, 32, 16384, 64, 6.0), (1, 4096, 64, 15360, 900, 6.0),
-    (1, 1024, 8, 16384, 5, 0.5), (1, 1152, 9, 8192, 2500, 6.0), (1, 128, 2, 512, 3000, 6.0)])
+    (1, 1024, 8, 16384, 5, 0.5), (1, 1152, 9, 8192, 2500, 6.0), (1, 128, 2, 512, 3000, 6.0),
+    # from here on three quarters of the workgroups share the keys instead of half; two blocks
+    (2, 4096, 32, 16384, 3068, 6.0), (2, 4096, 64, 1024, 3072, 6.0), (2, 1024, 16, 1024, 12290, 6.0)])
 def test_a_row_in_one_launch(blocks, H, nh, F, L, theta):
     cfg = _config(blocks, H, nh, F)
     spans = [binding.Span(blocks, H, nh, F, 1, 1e-5, theta, DEV) for _ in range(2)]
@@ -91,3 +93,31 @@ def test_rows_of_two_spans_on_two_streams():
             assert torch.equal(a, b)
     for s in spans:
         s.close()
+
+
+# Long caches are a matter of how many compute units read them: what a step takes more with 32768 keys than with 16384 (half of the
+# units: 3.2 to 4.2 TB/s, three quarters as well as the separate launches 5.8).
+@pytest.mark.parametrize("H,nh", [(3072, 48), (4096, 64), (4096, 32)])
+def test_long_caches_stream(H, nh):
+    span = binding.Span(1, H, nh, 64, 1, 1e-5, 6.0, DEV)
+    cfg = _config(1, H, nh, 64)
+    span.load_block(0, synth.block_params_device(cfg, 0, DEV))
+    x = to_dev(synth.hidden_states(cfg, 1, 1, 1)[:, 0])
+    us = []
+    for L in (16384, 32768):
+        s = span.open_session(L + 64)
+        s.import_kv(0, torch.zeros((2, nh, L, H // nh), dtype=torch.float16, device=DEV))
+        best = 1e30
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(12):
+                span.decode_step([s], x)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1000 / 12)
+        us.append(best)
+        s.close()
+    rate = 16384 * H * 4 / (us[1] - us[0]) * 1e-6
+    assert rate > 4.8, "%.1f and %.1f us: %.1f TB/s" % (us[0], us[1], rate)
+    span.close()
