@@ -649,12 +649,14 @@ __global__ void __launch_bounds__(NT) k_layernorm_codes(const __half *__restrict
     __shared__ double sm[2][NT / 64];
     __shared__ uint32_t smm[NT / 64], cols[512];                     // cols: outlier columns, a bit each
     __shared__ uint16_t mine[NORM_COLS];
-    __shared__ int n_mine, late, masks;
+    __shared__ int n_mine, late;
+    __shared__ uint32_t masked[PS_NORM_ROWS_MAX / 32];               // other rows whose columns are a mask, a bit each
     __shared__ float table[Q8 ? 256 : 1];
     const int t = rowquant_row(grid), KT = H >> 6, nchunk = H >> 4, words = H >> 5;
     if (t >= M) return;                                              // the rows that pad the last tile are cleared below
     for (int i = threadIdx.x; i < words; i += NT) cols[i] = 0u;
-    if (threadIdx.x == 0) n_mine = late = masks = 0;
+    if (threadIdx.x == 0) n_mine = late = 0;
+    if (threadIdx.x < PS_NORM_ROWS_MAX / 32) masked[threadIdx.x] = 0u;
     if constexpr (Q8)
         for (int i = threadIdx.x; i < 256; i += NT) table[i] = d_code_table.code[i];
     __syncthreads();
@@ -780,14 +782,19 @@ __global__ void __launch_bounds__(NT) k_layernorm_codes(const __half *__restrict
             }
         }
 #pragma unroll
-        for (int a = 0; a < AT; a++)
+        for (int a = 0; a < AT; a++) {
+            if (w[a] >> 48 != ex.tag) continue;
+            const int i = threadIdx.x + a * NT, r = i / NORM_WORDS;
+            if ((int)(w[a] & 0xffff) == NORM_MASK) {
+                if (i % NORM_WORDS == 0) atomicOr(&masked[r >> 5], 1u << (r & 31));
+                continue;
+            }
 #pragma unroll
             for (int e = 0; e < 3; e++) {
                 const int c = (int)(w[a] >> (16 * e)) & 0xffff;
-                if (w[a] >> 48 != ex.tag) continue;
                 if (c < H) atomicOr(&cols[c >> 5], 1u << (c & 31));
-                else if (c == NORM_MASK) masks = 1;
             }
+        }
     }
     __syncthreads();
     if (late) {                                                      // rare; the same in all threads
@@ -799,14 +806,30 @@ __global__ void __launch_bounds__(NT) k_layernorm_codes(const __half *__restrict
 #pragma unroll
         for (int i = 0; i < PER; i++) { v[i][0] = keep[i][0]; v[i][1] = keep[i][1]; }
         __syncthreads();
-    } else if (masks) {                                              // rare: rows with many outlier columns
-        for (int r = 0; r < M; r++) {
-            const uint64_t w = __hip_atomic_load(ex.records + (size_t)r * NORM_WORDS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (r == t || (int)(w & 0xffff) != NORM_MASK) continue;
-            for (int i = threadIdx.x; i < words; i += NT)
-                cols[i] |= __hip_atomic_load(ex.masks + (size_t)r * words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        uint32_t any = 0;
+#pragma unroll
+        for (int i = 0; i < PS_NORM_ROWS_MAX / 32; i++) any |= masked[i];
+        if (any) {
+            // rare: rows with many outlier columns.  A thread takes one word of every G-th row, eight of them requested at once (the
+            // rows one after the other, two round trips to memory each, cost 128 rows of 1024 some 40 us).
+            const int G = NT / words, g = (int)threadIdx.x / words, i = (int)threadIdx.x - g * words;    // H <= 32 NT: at least one row
+            if (g < G) {
+                uint32_t sum = 0;
+                for (int r0 = g; r0 < M; r0 += 8 * G) {
+                    uint32_t a[8];
+#pragma unroll
+                    for (int u = 0; u < 8; u++) {
+                        const int r = r0 + u * G;
+                        a[u] = r < M && (masked[r >> 5] >> (r & 31) & 1u) ? __hip_atomic_load(ex.masks + (size_t)r * words + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; u++) sum |= a[u];
+                }
+                if (sum) atomicOr(&cols[i], sum);
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
     if (t == 0)
         for (int i = threadIdx.x; i < words; i += NT) mask[i] = cols[i];
