@@ -653,7 +653,12 @@ __global__ void __launch_bounds__(NT) k_layernorm_codes(const __half *__restrict
     __shared__ uint32_t masked[PS_NORM_ROWS_MAX / 32];               // other rows whose columns are a mask, a bit each
     __shared__ float table[Q8 ? 256 : 1];
     const int t = rowquant_row(grid), KT = H >> 6, nchunk = H >> 4, words = H >> 5;
-    if (t >= M) return;                                              // the rows that pad the last tile are cleared below
+    if (t >= M) {                                                    // rows that pad the last tile
+        if (t < rows)
+            for (int c = threadIdx.x; c < nchunk; c += NT)
+                *(v4i *)(xq_tiled + (((size_t)(t >> 4) * KT + (c >> 2)) * 64 + (c & 3) * 16 + (t & 15)) * 16) = (v4i){0, 0, 0, 0};
+        return;
+    }
     for (int i = threadIdx.x; i < words; i += NT) cols[i] = 0u;
     if (threadIdx.x == 0) n_mine = late = 0;
     if (threadIdx.x < PS_NORM_ROWS_MAX / 32) masked[threadIdx.x] = 0u;
@@ -880,9 +885,6 @@ __global__ void __launch_bounds__(NT) k_layernorm_codes(const __half *__restrict
             *(v4i *)(xo_tiled + slot) = *(const v4i *)first;
         }
     }
-    for (int p = M + t; p < rows; p += M)                            // rows that pad the last tile
-        for (int c = threadIdx.x; c < nchunk; c += NT)
-            *(v4i *)(xq_tiled + (((size_t)(p >> 4) * KT + (c >> 2)) * 64 + (c & 3) * 16 + (p & 15)) * 16) = (v4i){0, 0, 0, 0};
 }
 
 // out[i] = number of set bits of the i-th mask of `words` words (one workgroup per mask)

@@ -122,3 +122,19 @@ def test_rows_with_many_outlier_columns_cost_little_more(M, H, nh):
             us.append(_us(span, x, torch.empty_like(x)))
     span.close()
     assert us[1] - us[0] < 8.0, us
+
+
+# The rows that pad a call's last token tile are cleared by workgroups of their own.  (By the call's rows: two rows cleared seven each
+# behind their own work, 2 rows of 14336 took 3 us more than 16.)
+@pytest.mark.parametrize("H,nh", [(12288, 96), (14336, 112)])
+def test_two_rows_take_no_longer_than_sixteen(H, nh):
+    r = np.random.default_rng(H)
+    span, _ = _span(H, nh, 16, r)
+    us = []
+    for M in (2, 16):
+        x = to_dev(r.standard_normal((M, H)).astype(np.float16))
+        y = torch.empty_like(x)
+        _us(span, x, y)
+        us.append(_us(span, x, y))
+    span.close()
+    assert us[0] < us[1] + 1.0, us
