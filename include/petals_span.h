@@ -296,7 +296,7 @@ int petals_debug_outlier_counts(petals_span *span, int32_t *counts, void *stream
 
 /*
  * For tests: how long, in ticks of the GPU's 100 MHz clock, a row of a LayerNorm waits for the outlier columns of the
- * other rows of its call before it works them out by itself (10000 unless set; the results are the same).
+ * other rows of its call before it works them out by itself (10000 unless set; 0: it never looks; the results are the same).
  */
 int petals_debug_norm_patience(petals_span *span, uint32_t ticks);
 

@@ -139,7 +139,7 @@ struct NormExchange {
     uint64_t *records;           // [PS_NORM_ROWS_MAX] records, no word of which holds the tag
     uint32_t *masks;             // [PS_NORM_ROWS_MAX][H / 32]
     uint32_t tag;                // 1 to 65535
-    uint32_t patience;           // ticks of the 100 MHz clock that a row waits for the others
+    uint32_t patience;           // ticks of the 100 MHz clock that a row waits for the others; 0: it does without them
 };
 hipError_t ps_layernorm_codes(const __half *x, const QuantIn *qin, const __half *g, const __half *b, float eps, int M, int H, __half *y,
                               uint32_t *mask, int8_t *xq_tiled, int8_t *xo_tiled, float *sx, int8_t *xq_dbg, float theta,

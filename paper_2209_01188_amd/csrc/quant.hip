@@ -635,7 +635,7 @@ __global__ void __launch_bounds__(NT) k_rowquant_tiled_wide(const __half *__rest
 // blocks 400 -> 370); 128 rows of 1024 3.8 and 4.5, together 6.4, where a workgroup reads 8 KB of records: the line of
 // PS_NORM_ROWS_MAX.
 // A workgroup that has waited for `patience` ticks of the 100 MHz clock (not all of them may be resident at once when other
-// work shares the device) finds the outlier columns by itself, from all rows.
+// work shares the device) finds the outlier columns by itself, from all rows; with a patience of 0 every one does.
 constexpr int NORM_WORDS = 8, NORM_COLS = 3 * NORM_WORDS, NORM_NONE = 0xffff, NORM_MASK = 0xfffe;
 
 template <int NT, int PER, bool Q8>
@@ -767,7 +767,9 @@ __global__ void __launch_bounds__(NT) k_layernorm_codes(const __half *__restrict
     // the other rows' records, AT words per thread at once (one, but for short rows and many of them)
     constexpr int AT = NT == 256 ? 4 : 2;
     static_assert(AT * NT >= PS_NORM_ROWS_MAX * NORM_WORDS, "every word has a thread");
-    {
+    if (ex.patience == 0) {                                          // not even looked at
+        late = 1;
+    } else {
         uint64_t w[AT], start = 0;
         for (int spins = 0;; spins++) {
             bool there = true;

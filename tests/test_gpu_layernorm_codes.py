@@ -138,3 +138,20 @@ def test_two_rows_take_no_longer_than_sixteen(H, nh):
         us.append(_us(span, x, y))
     span.close()
     assert us[0] < us[1] + 1.0, us
+
+
+# The runs without patience above are there for the rows that work out the outlier columns of all rows by themselves: that they do
+# shows in the time of 100 rows, each of which normalises them all (many times what waiting takes, which is a few us of the call).
+def test_rows_without_patience_work_the_columns_out():
+    M, H = 100, 4096
+    r = np.random.default_rng(1)
+    span, _ = _span(H, 32, M, r)
+    x = to_dev(r.standard_normal((M, H)).astype(np.float16))
+    y = torch.empty_like(x)
+    us = []
+    with midsize("chunks"):
+        for patience in (10000, 0):
+            binding.petals_debug_norm_patience(span.handle, patience)
+            us.append(_us(span, x, y))
+    span.close()
+    assert us[1] > 3.0 * us[0], us
