@@ -628,15 +628,18 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
                 capd[j] = cap * o.d;
             }
         }
-        // exact outlier part: the token-side operands of the first XC chunks stay in registers
-        constexpr int XC = 2;
+        // exact outlier part: the token-side operands of the first XC chunks stay in registers; the rest comes XR chunks at a time,
+        // for all token tiles at once (one tile after the other, a weight operand and a latency for each: 4096 rows of 16384 x 4096
+        // with 64 outlier columns 655 -> 528 us, 351 rows 116 -> 105).  No further ahead: 16 columns there 348 -> 428.
+        constexpr int XC = TM == 1 ? 8 : 2, XR = TM == 1 ? 4 : 2;
         const int nch = many ? 0 : (n_out + 3) >> 2;
         double xw[TM][XC];
+        if (nch > 0)
 #pragma unroll
-        for (int j = 0; j < TM; j++)
+            for (int j = 0; j < TM; j++)
 #pragma unroll
-            for (int c = 0; c < XC; c++)
-                xw[j][c] = c < nch ? os.x64[((size_t)min(mt0 + wm * TM + j, MTT - 1) * PS_OUTLIER_CHUNKS + c) * 64 + lane] : 0.0;
+                for (int c = 0; c < XC; c++)
+                    xw[j][c] = os.x64[((size_t)min(mt0 + wm * TM + j, MTT - 1) * PS_OUTLIER_CHUNKS + min(c, nch - 1)) * 64 + lane];
         __syncthreads();                                                 // tables visible
 
 #pragma unroll
@@ -653,10 +656,11 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
                 const v4d swd4 = *(const v4d *)(col_swd + ntl * 16 + 4 * kg);
                 const v4d bias4 = *(const v4d *)(col_bias + ntl * 16 + 4 * kg);
                 const int2 sc = o.scatter ? col_sc[ntl * 4 + kg] : make_int2(-1, n0);
+                const double *ap = os.wd64 + (size_t)nt * PS_OUTLIER_CHUNKS * 64 + lane;
                 double aw[XC];
+                if (nch > 0)
 #pragma unroll
-                for (int c = 0; c < XC; c++)
-                    aw[c] = c < nch ? os.wd64[((size_t)nt * PS_OUTLIER_CHUNKS + c) * 64 + lane] : 0.0;
+                    for (int c = 0; c < XC; c++) aw[c] = ap[min(c, nch - 1) * 64];
                 // 1. operands of the TM token tiles of this panel: parked sums, residuals, the outlier part
                 v4i a4[TM];
                 v4h r4[TM];
@@ -673,16 +677,24 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
                         if (trow[j] >= 0) od[j] = *(const v4d *)(outl + (size_t)trow[j] * N + n0);
                 } else if (nch > 0) {
 #pragma unroll
-                    for (int j = 0; j < TM; j++) {
+                    for (int c = 0; c < XC; c++)
+                        if (c < nch)
 #pragma unroll
-                        for (int c = 0; c < XC; c++)
-                            if (c < nch) od[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw[c], xw[j][c], od[j], 0, 0, 0);
-                        if (nch > XC) {
-                            const double *ap = os.wd64 + (size_t)nt * PS_OUTLIER_CHUNKS * 64 + lane;
-                            const double *bp = os.x64 + (size_t)min(mt0 + wm * TM + j, MTT - 1) * PS_OUTLIER_CHUNKS * 64 + lane;
-                            for (int c = XC; c < nch; c++)
-                                od[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[c * 64], bp[c * 64], od[j], 0, 0, 0);
+                            for (int j = 0; j < TM; j++) od[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw[c], xw[j][c], od[j], 0, 0, 0);
+                    for (int c0 = XC; c0 < nch; c0 += XR) {
+                        double a[XR], b[XR][TM];
+#pragma unroll
+                        for (int u = 0; u < XR; u++) {
+                            const int c = min(c0 + u, nch - 1) * 64;
+                            a[u] = ap[c];
+#pragma unroll
+                            for (int j = 0; j < TM; j++) b[u][j] = os.x64[(size_t)min(mt0 + wm * TM + j, MTT - 1) * PS_OUTLIER_CHUNKS * 64 + lane + c];
                         }
+#pragma unroll
+                        for (int u = 0; u < XR; u++)
+                            if (c0 + u < nch)
+#pragma unroll
+                                for (int j = 0; j < TM; j++) od[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u][j], od[j], 0, 0, 0);
                     }
                 }
                 // 2. the arithmetic of the 4 TM outputs, no branch inside, written one operation at a time over all of

@@ -298,3 +298,25 @@ def test_a_smaller_output_is_no_slower(H, nh, small, large, M):
         span.close()
         torch.cuda.empty_cache()
     assert times[0] <= 1.03 * times[1], times
+
+
+# The outlier columns of the fp64 path beyond the first eight (or, in blocks of 4 x 4, 32) come several at a time, for all token tiles of a
+# wave at once: last groups of one to four columns, every block form
+@pytest.mark.parametrize("ffn,hidden,nh,M", [(64, 192, 3, 65), (4096, 192, 3, 241), (8320, 192, 3, 77), (8320, 192, 3, 113), (13248, 192, 3, 577), (16576, 320, 5, 653)])
+@pytest.mark.parametrize("n_out", [8, 9, 13, 20, 32, 33, 41, 64])
+def test_outlier_columns_of_the_fp64_path(ffn, hidden, nh, M, n_out):
+    cfg = synth.SpanConfig("fp64", 1, hidden, nh, 1, M, 1, 1, (20.0, 40.0), 7, ffn=ffn)
+    osp, gsp, params = build_pair(cfg, max_rows=M)
+    r = np.random.default_rng(M + n_out)
+    X = np.clip(r.standard_normal((M, hidden)) * 2, -5.9, 5.9)
+    X[r.integers(0, M, n_out), r.choice(hidden, n_out, replace=False)] = r.uniform(6.0, 30.0, n_out) * r.choice([-1, 1], n_out)
+    X = X.astype(np.float16)
+    wq, sw = osp.get_weight(0, 2)
+    Y, dbg = oracle.linear(X, wq, sw, params[0]["b_up"], 6.0, 1, want_debug=True)
+    with midsize("blocks"):
+        out = gsp.debug_linear(0, 2, to_dev(X), 1)
+        torch.cuda.synchronize()
+    assert dbg["mask"].sum() == n_out
+    assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
+    gsp.close()
+    osp.destroy()
