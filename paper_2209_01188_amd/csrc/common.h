@@ -89,10 +89,15 @@ struct QuantIn {
     __half *x_out;
 };
 
-// Up to this many outlier columns the fp16 part of a multi-row linear is computed exactly
-// (fp64 matrix instructions on compacted operands); beyond it, on the fp16 matrix cores.
+// Up to so many outlier columns the fp16 part of a linear in output blocks goes through fp64 matrix instructions on compacted
+// operands, beyond that through the digit products, which cost the same for 53 columns as for 200.  Calls of up to 1024 rows are few
+// blocks, whose units do the fp64 products alone (192 rows of 9216 x 3072: 43 us without, 62 with 40, 73 with 64 columns, 61 in
+// digits; 72 rows of 19968 x 6656: 57, 80, 92, 83; 256 rows 72, 103, 123, 111).  Where a unit has no more than 16 of the 16 x 16 tiles
+// fp64 stays ahead (352 rows of 2560 x 2560, 64 columns 41 against 52), and so it does in larger calls, which would write and read
+// more fp64 sums than that saves (1400 rows of 16384 x 4096: 237 against 281, 4096 rows 520 against 755).
 #define PS_EXACT_OUTLIERS 64
 #define PS_OUTLIER_CHUNKS (PS_EXACT_OUTLIERS / 4)
+__host__ __device__ inline int ps_exact_outliers(int N, int M) { return M <= 1024 && (N / 16) * ((M + 15) / 16) > 3600 ? 52 : PS_EXACT_OUTLIERS; }
 // Compacted outlier operands of one linear call, in v_mfma_f64_16x16x4_f64 lane order:
 // chunk c of tile r holds 64 doubles, lane l = column list[4c + l/16] of row 16r + l%16
 // (weight rows permuted inside a tile, see outlier_prep_wave).
@@ -147,7 +152,7 @@ hipError_t ps_layernorm_codes(const __half *x, const QuantIn *qin, const __half 
 hipError_t ps_mask_to_bytes(const uint32_t *mask, int K, uint8_t *out, hipStream_t st);
 hipError_t ps_mask_count(const uint32_t *masks, int n_masks, int words, int32_t *out, hipStream_t st);
 
-// Scratch of the outlier-heavy case of a prefill-size call (more than PS_EXACT_OUTLIERS columns): the fp16
+// Scratch of the outlier-heavy case of a prefill-size call (more than ps_exact_outliers columns): the fp16
 // product over the outlier columns is taken exactly, as int8 digit products (see gemm_lds.hip)
 #define PS_X_DIGITS 6            // balanced 8-bit digits of an fp16 activation in units of 2^-24 (4 cover |x| < 127.5)
 struct ManyOutliers {

@@ -6,7 +6,7 @@
 // transposition).  A workgroup computes a block of the output, 256 x 256 in large calls; k-tiles move
 // through a 4-slot LDS ring filled by asynchronous global->LDS copies.
 //
-// Outlier columns: up to PS_EXACT_OUTLIERS of them are added exactly in the epilogue (fp64 matrix
+// Outlier columns: up to ps_exact_outliers of them are added exactly in the epilogue (fp64 matrix
 // instruction on compacted operands, see outlier_prep.h).  More than that: the fp16 x fp16 product over the
 // outlier columns is computed EXACTLY in integer arithmetic on the int8 matrix cores.  Every fp16 value
 // is an integer multiple of 2^-24, so an activation is x = 2^-24 * sum_j 256^j * L_j with balanced
@@ -34,7 +34,7 @@ namespace {
 constexpr int PS_KSPLIT_MAX = 8;   // workgroups that share one output block's contraction, at most
 
 // ---------------------------------------------------------------------------------------------
-// outlier column list and fp16 gathers (only do work when the call has > PS_EXACT_OUTLIERS)
+// outlier column list and fp16 gathers (only do work when the call has > ps_exact_outliers)
 
 // Digit tiles of the outlier columns, in the int8 operand order (16 rows x 64 compacted columns = 1024 bytes, lane l owns row
 // l%16 and columns (l/16)*16 .. +16), one wave per tile or run of tiles.
@@ -267,7 +267,7 @@ __global__ void __launch_bounds__(256) k_digit_tiles(const __half *__restrict__ 
                                                       const int8_t *__restrict__ xq_tiled, const int *__restrict__ regular) {
     __shared__ __align__(16) __half stage[4][DT_TILES * 64 * 16];
     const int n_out = count[0];
-    if (n_out <= PS_EXACT_OUTLIERS) return;
+    if (n_out <= ps_exact_outliers(w.N, M)) return;
     const int wave = threadIdx.x >> 6, wv = (int)blockIdx.x * 4 + wave, KT = w.K >> 6, CT = (n_out + 63) >> 6;
     const bool gather = regular && ps_regular_compacted(n_out, w.K, M);
     if (wv >= NBX) {
@@ -307,7 +307,7 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     constexpr int PD = NSLOT - 1;                    // stages requested ahead
     extern __shared__ __align__(16) unsigned char lds[];
     const int n_out = F16 ? ga.ktiles * 32 : os.count[0];
-    const bool many = F16 || n_out > PS_EXACT_OUTLIERS;
+    const bool many = F16 || n_out > ps_exact_outliers(ga.N, ga.M);
     if (DIG && !many) return;
     // k-tiles to walk (64 int8 or 32 fp16 columns each).  If EVERY column is an outlier all int8 codes are
     // zero: the int8 product is skipped and only the epilogue runs.
@@ -781,7 +781,7 @@ __global__ void __launch_bounds__(256) k_split_finish(GemmArgs ga, LinearW w, co
     v4i acc = {0, 0, 0, 0};
     for (int s = 0; s < ga.ksplit; s++) acc += ga.part[(((size_t)s * NT + nt) * MTT + mt) * 64 + lane];
     v4d od = {0.0, 0.0, 0.0, 0.0};
-    if (n_out > PS_EXACT_OUTLIERS) {
+    if (n_out > ps_exact_outliers(ga.N, ga.M)) {
         if (t < ga.M) od = *(const v4d *)(outl + (size_t)t * ga.N + n0);
     } else {
         const double *ap = os.wd64 + (size_t)nt * PS_OUTLIER_CHUNKS * 64 + lane, *bp = os.x64 + (size_t)mt * PS_OUTLIER_CHUNKS * 64 + lane;

@@ -17,7 +17,7 @@ __host__ __device__ inline int outlier_prep_items(const OutlierPrep &p, int M) {
     return !p.count ? 0 : gathers > groups ? gathers : groups;
 }
 
-// Counts the outlier columns and, when there are at most PS_EXACT_OUTLIERS, gathers their
+// Counts the outlier columns and, when there are at most ps_exact_outliers, gathers their
 // dequantized weights (items [0, N/16)) and activations (the next ceil(M/16)) as doubles in matrix-instruction lane order.
 // Every wave rebuilds the short column list from the bit mask itself.  list: PS_EXACT_OUTLIERS ints of LDS of this wave.
 __device__ __forceinline__ void outlier_prep_wave(const OutlierPrep &pr, const uint32_t *__restrict__ mask, const uint8_t *__restrict__ flags,
@@ -52,7 +52,7 @@ __device__ __forceinline__ void outlier_prep_wave(const OutlierPrep &pr, const u
         }
         return incl - n;
     };
-    if (total > PS_EXACT_OUTLIERS) {
+    if (total > ps_exact_outliers(w.N, M)) {
         // more columns than the fp64 path takes: their ascending list for the digit products, each group's part by the wave
         // of that number, padded with -1 up to the next multiple of 64.  (The whole list by one wave was what this launch
         // waited for: 200 rows of 32768 with 500 outlier columns 17 us.)
