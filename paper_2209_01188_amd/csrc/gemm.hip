@@ -287,11 +287,15 @@ static double gemm_rows_us(const LinearW &w, int M, int &form) {
 }
 
 // Rough times in microseconds of a linear with its row kernels, fitted to both forms measured on the four linears of
-// blocks 1024 to 14336 wide at 65 to 512 rows (the choice is 0.6 % behind the faster one on average; at worst 7 %, 2048 x 8192
-// at 351 rows, 55 us for 51).
+// blocks 1024 to 14336 wide at 65 to 512 rows with few outlier columns (the choice is 0.6 % behind the faster one on average).
+// They know nothing of many: there blocks win, whose digit products cost the same for all, while the 64-row form grows with each
+// (3072 x 3072 at 352 rows: 10 columns 37 us, in blocks 41; 460 columns 86 and 68).
 // 64 rows per workgroup: see above, 13 us for the row kernels in front.  All rows go in one launch: charged by 64 rows, as
 // when each 64 were a launch, narrow outputs went to the blocks too early (1024 x 1024 at 320 rows: 24 us in this form, 36 in
 // blocks).
+// From 2.1 to 2.6 million codes in the call it grows by 11 us (an XCD's L2 holds 4 MB, and the weights pass through it as well): 2048 x
+// 8192 at 280, 300, 320 and 376 rows 53, 56, 59, 59 us where 46 were expected, in blocks 53, 54, 54, 54 (with half of the
+// columns outliers 264 and 111).
 // Output blocks: ps_gemm_lds_us.
 // PETALS_SPAN_MIDSIZE=blocks / =chunks in the environment overrides the choice (tests run both ways).
 bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
@@ -301,7 +305,8 @@ bool ps_gemm_prefers_chunks(const LinearW &w, int M) {
         if (!strcmp(force, "chunks")) return true;
     }
     int form;
-    return 13.0 + gemm_rows_us(w, M, form) < ps_gemm_lds_us(w.N, w.K, M);
+    const double beyond_l2 = 11.0 * fmin(1.0, fmax(0.0, ((double)M * w.K - 2.1e6) / 0.5e6));
+    return 13.0 + beyond_l2 + gemm_rows_us(w, M, form) < ps_gemm_lds_us(w.N, w.K, M);
 }
 
 hipError_t ps_gemm(const LinearW &w, const int8_t *xq_tiled, const int8_t *xo_tiled, const uint32_t *mask,
