@@ -156,6 +156,17 @@ int petals_span_decode_step(petals_span *span, petals_session *const *sessions, 
                             const void *hidden_in, void *hidden_out, void *stream);
 
 /*
+ * One token of ONE session (any of the calls with one row) goes through all blocks of a span of up to 4096 columns and
+ * 16384 MLP columns, head_dim 64 or 128, in a single launch, whose workgroups wait for each other's rows.  Every such
+ * wait ends by construction; should a defect make one not end, the waiting workgroup gives up after 2^24 polls (ten
+ * seconds and more of running; time in which the GPU runs something else does not count) instead of hanging the GPU.
+ * The call has returned PETALS_OK by then: its output, and the cached keys and values of that position, hold NaN where
+ * they depend on what was missing, and the session has its new length.  *dev_count (dev int32) receives, in stream order,
+ * how many calls of this process have ended so on the current GPU: 0 unless there is a defect.
+ */
+int petals_steps_given_up(int32_t *dev_count, void *stream);
+
+/*
  * petals_span_decode_step for callers that cannot provide or allocate device memory at the time of the call
  * (code running under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same step,
  * same arguments, same results bit for bit, but every intermediate buffer lives in a fixed device array that
@@ -212,6 +223,8 @@ const char *petals_last_error(void);
  * launches are timed, later ones run untimed).  profile_end waits for the
  * recorded events and returns, per class, the summed kernel time in ms and the
  * number of timed launches.  Arrays have PETALS_PROFILE_CLASSES entries (host).
+ * A one-row call that otherwise is a single launch (see petals_steps_given_up) runs as the launches of these classes
+ * while it is profiled: the same results, other times.
  */
 #define PETALS_PROFILE_GEMV      0  /* one-row int8 linear (decode, batch 1) */
 #define PETALS_PROFILE_GEMM      1  /* multi-row MFMA linear */
@@ -299,6 +312,9 @@ int petals_debug_outlier_counts(petals_span *span, int32_t *counts, void *stream
  * other rows of its call before it works them out by itself (10000 unless set; 0: it never looks; the results are the same).
  */
 int petals_debug_norm_patience(petals_span *span, uint32_t ticks);
+
+/* For tests: after how many polls a workgroup of a one-launch step gives up (see petals_steps_given_up; 2^24 unless set). */
+int petals_debug_step_patience(petals_span *span, uint32_t polls);
 
 /* Row-major int8 codes [N, K] and row scales [N] of a loaded linear (dev outputs). */
 int petals_debug_export_weight(petals_span *span, int32_t block, int32_t which, int8_t *wq,

@@ -60,7 +60,7 @@ EXPORTS = ["petals_span_weight_bytes", "petals_span_workspace_bytes", "petals_sp
            "petals_span_profile_begin", "petals_span_profile_end", "petals_debug_layernorm", "petals_session_replay",
            "petals_span_backward_bytes", "petals_span_backward", "petals_debug_backward_product",
            "petals_span_backward_cache_bytes", "petals_span_backward_attach_cache", "petals_bench_mfma", "petals_bench_stage", "petals_debug_outlier_counts",
-           "petals_debug_norm_patience"]
+           "petals_debug_norm_patience", "petals_debug_step_patience", "petals_steps_given_up"]
 CLIENT_EXPORTS = ["petals_client_workspace_bytes", "petals_client_create", "petals_client_destroy",
                   "petals_client_embed", "petals_client_lm_head", "petals_client_sample"]
 PROFILE_GEMV, PROFILE_GEMM, PROFILE_ATTENTION, PROFILE_LINEAR0 = 0, 1, 2, 3
@@ -262,6 +262,14 @@ def petals_debug_outlier_counts(span, counts):
 
 def petals_debug_norm_patience(span, ticks):
     _check(lib().petals_debug_norm_patience(span, C.c_uint32(ticks)))
+
+
+def petals_debug_step_patience(span, polls):
+    _check(lib().petals_debug_step_patience(span, C.c_uint32(polls)))
+
+
+def petals_steps_given_up(count):
+    _check(lib().petals_steps_given_up(_ptr(count), _stream()))
 
 
 def petals_debug_export_weight(span, block, which, wq, sw):

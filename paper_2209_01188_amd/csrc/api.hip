@@ -276,6 +276,7 @@ int forward_row(petals_span *sp, int max_keys, const __half *hidden_in, __half *
     s.sess = sp->ws.table;
     s.words = sp->ws.step;
     s.ticket = (int *)(s.words + (size_t)6 * c.hidden + c.ffn);
+    s.patience = sp->step_patience;
     s.done = s.ticket + 64;
     s.partials = sp->ws.partials;
     HIP_TRY(ps_decode_row(s, c.hidden / c.n_heads, max_keys, st));
@@ -657,6 +658,18 @@ int petals_debug_layernorm(petals_span *sp, int32_t block, int32_t which, const 
 int petals_debug_norm_patience(petals_span *sp, uint32_t ticks) {
     if (!sp) return fail(PETALS_ERR_INVALID_ARG, "null pointer");
     sp->norm_patience = ticks;
+    return PETALS_OK;
+}
+
+int petals_debug_step_patience(petals_span *sp, uint32_t polls) {
+    if (!sp) return fail(PETALS_ERR_INVALID_ARG, "null pointer");
+    sp->step_patience = polls;
+    return PETALS_OK;
+}
+
+int petals_steps_given_up(int32_t *dev_count, void *stream) {
+    if (!dev_count) return fail(PETALS_ERR_INVALID_ARG, "null pointer");
+    HIP_TRY(ps_steps_given_up(dev_count, (hipStream_t)stream));
     return PETALS_OK;
 }
 

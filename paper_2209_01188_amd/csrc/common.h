@@ -203,7 +203,8 @@ struct StepArgs {
     __half *out;
     const SessTable *sess;
     uint32_t *words;             // [PS_STEP_WORDS(H, F)], cleared before the launch: rows on their way, then ticket and done
-    int *ticket;                 // next work item; [1] not zero: a workgroup has waited too long
+    int *ticket;                 // next work item; [1] not zero: a reader has given up
+    uint32_t patience;           // polls after which one does
     int *done;                   // [PS_MAX_HEADS] key ranges that have been summed up
     double *partials;
     int ranges;                  // of keys per head (this and what follows set by the launcher)
@@ -212,6 +213,7 @@ struct StepArgs {
 #define PS_STEP_WORDS(H, F) ((size_t)6 * (H) + (F) + 64 + PS_MAX_HEADS)
 bool ps_decode_row_applies(int H, int F, int d, int n_blocks);
 hipError_t ps_decode_row(const StepArgs &s, int d, int max_keys, hipStream_t st);
+hipError_t ps_steps_given_up(int *dev_count, hipStream_t st);     // on this device, since the library was loaded
 #define PS_CHUNKED_ROWS_MAX 512
 // batched-decode linear, 2 <= M <= PS_CHUNKED_ROWS_MAX rows, 64 per workgroup (int8 MFMA, outlier columns exactly on fp64 MFMA inside the
 // loop); xq_tiled and xo_tiled as written by ps_rowquant_tiled

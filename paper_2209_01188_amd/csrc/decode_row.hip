@@ -8,10 +8,11 @@
 // 1024 with 1000 keys 257 -> 188.  What is left of a stage, 3 us: 0.7 until its row is seen, 1.1 for LayerNorm and codes, 0.4 for
 // the products, 0.5 for the reduction and the tail.
 //
-// One workgroup per compute unit, 256 in all: a stage has 64 to 200 items, so those of the next stages are waited for, with
-// their weights on the way, by the workgroups that have none of this one.  (Two per unit: 41 spilled registers; and with
-// 512 workgroups polling the words' few memory channels the stores to them starved, 42 ms a step.  The next item's number taken
-// while an item is worked on: workgroups end up with two items of a stage, 567 us.)
+// One workgroup per compute unit, 256 in all: a stage has 16 (attention of 16 heads) to 256 items (QKV, dense, up and down of 4096
+// columns), so those of the next stages are waited for, with their weights on the way, by the workgroups that have none of
+// this one.  (Two per unit: 41 spilled registers; and with 512 workgroups polling the words' few memory channels the stores to
+// them starved, 42 ms a step.  The next item's number taken while an item is worked on: workgroups end up with two items of a
+// stage, 567 us.)
 //
 // Rows go from workgroup to workgroup as 32-bit words in device memory: the fp16 value in the low half, the number of the
 // block (counted from 1) in the high half, written and read by relaxed atomics of agent scope, which every XCD sees.  A reader
@@ -32,9 +33,11 @@
 namespace {
 
 constexpr int THREADS = 512, WAVES = 8;
-// a reader gives up after this many ticks of the 100 MHz clock and tells the others; the values that it did not get count as
-// NaN, which the layers carry into the output
-constexpr unsigned long long GIVE_UP = 1000000000ull;
+// Every wait ends (see above); so that a defect cannot hang the GPU all the same, a reader gives up after s.patience polls and
+// tells the others; the values that it did not get count as NaN, which the layers carry into the output.  (Polls, not time: a
+// call that something else keeps off the GPU for long doesn't poll meanwhile.)  Counted here, as nothing else outlives the call.
+static __device__ int d_given_up;
+__global__ void k_given_up(int *out) { *out = __hip_atomic_load(&d_given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 static __device__ const CodeTable d_code_table = ps_make_code_table();
 
@@ -47,10 +50,10 @@ __device__ __forceinline__ void publish(uint32_t *p, uint32_t tag, __half v) {
 // N pairs of words into packed halves, once all of them carry the tag.  STEP > 1: every STEP-th pair is polled before all of them
 // are (a thread's consecutive words were stored together): the polling of wide rows keeps the words' memory channels busy.
 template <int N, int STEP = 1>
-__device__ __forceinline__ void await_words(const uint32_t *const (&p)[N], uint32_t tag, int (&out)[N], int *gave_up) {
+__device__ __forceinline__ void await_words(const uint32_t *const (&p)[N], uint32_t tag, int (&out)[N], const StepArgs &s) {
     const uint64_t want = (uint64_t)(tag << 16) << 32 | tag << 16;
-    unsigned long long start = 0;
-    for (int spins = 0;; spins++) {
+    int *gave_up = s.ticket + 1;
+    for (uint32_t spins = 0;; spins++) {
         uint64_t w[N], off = 0;
         if constexpr (STEP > 1) {
 #pragma unroll
@@ -69,14 +72,10 @@ __device__ __forceinline__ void await_words(const uint32_t *const (&p)[N], uint3
             if (!(off & 0xffff0000ffff0000ull)) return;
         }
         __builtin_amdgcn_s_sleep(1);
-        if ((spins & 1023) == 1023) {
-            const unsigned long long now = __builtin_amdgcn_s_memrealtime();
-            if (!start) start = now;
-            if (__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            if (now - start > GIVE_UP) {
-                __hip_atomic_store(gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
+        if ((spins & 1023) == 1023 && __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+        if (spins >= s.patience) {
+            if (!__hip_atomic_exchange(gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicAdd(&d_given_up, 1);
+            break;
         }
     }
 #pragma unroll
@@ -86,17 +85,12 @@ __device__ __forceinline__ void await_words(const uint32_t *const (&p)[N], uint3
 // Waits, with one lane and pauses, until the stage before an item's own has something to work on: the rows are polled only by
 // the workgroups whose turn is next, not by all that wait (with everybody polling, the words' few memory channels are so
 // busy that the stores to them starve).  p may be null.
-__device__ __forceinline__ void await_turn(const uint32_t *p, uint32_t tag, int tid, int *gave_up) {
+__device__ __forceinline__ void await_turn(const uint32_t *p, uint32_t tag, int tid, const StepArgs &s) {
     if (!p) return;
     if (tid == 0) {
-        unsigned long long start = 0;
-        for (int spins = 0; __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 != tag; spins++) {
+        for (uint32_t spins = 0; __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16 != tag && spins < s.patience; spins++) {
             __builtin_amdgcn_s_sleep(8);
-            if ((spins & 1023) == 1023) {
-                const unsigned long long now = __builtin_amdgcn_s_memrealtime();
-                if (!start) start = now;
-                if (__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || now - start > GIVE_UP) break;
-            }
+            if ((spins & 1023) == 1023 && __hip_atomic_load(s.ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
         }
     }
     lds_barrier();
@@ -148,7 +142,7 @@ __device__ __forceinline__ float prepare_row(Lds<CW, D> &l, int tid, int K, cons
 #pragma unroll
             for (int e = 0; e < NP; e++) p[i * NP + e] = words + (c < K ? c : 0) + 2 * e;
         }
-        if (mine0) await_words<NCH * NP, (CW == 8 ? NP : 1)>(p, tag, *(int(*)[NCH * NP])v, s.ticket + 1);
+        if (mine0) await_words<NCH * NP, (CW == 8 ? NP : 1)>(p, tag, *(int(*)[NCH * NP])v, s);
     }
 #pragma unroll
     for (int i = 0; i < NCH; i++) {
@@ -289,7 +283,7 @@ __device__ __forceinline__ double panels(Lds<CW, D> &l, int tid, const StepArgs 
     const float bn = __half2float(((const __half *)((const uint8_t *)w.bias + offset))[n]);
     const int row = (int)tag * 4 + which;
     if (row != ready) {                              // the same in all threads
-        await_turn(turn, turn_tag, tid, s.ticket + 1);
+        await_turn(turn, turn_tag, tid, s);
         s_x = prepare_row<LN, CT, NCH, CW, D>(l, tid, K, s, plain, coded, words, tag, gain, bias);
         ready = row;
     }
@@ -367,7 +361,7 @@ __device__ __forceinline__ void attention(Lds<CW, D> &l, int tid, const StepArgs
         }
     };
     load(wb);
-    await_turn(turn, turn_tag, tid, s.ticket + 1);
+    await_turn(turn, turn_tag, tid, s);
     v8h qv, kn, vn;
     {
         const uint32_t *p[12];
@@ -375,7 +369,7 @@ __device__ __forceinline__ void attention(Lds<CW, D> &l, int tid, const StepArgs
         const uint32_t *from = words.qkv + h * 3 * D + sub * 8;
 #pragma unroll
         for (int e = 0; e < 12; e++) p[e] = from + (e >> 2) * D + (e & 3) * 2;
-        await_words<12>(p, tag, w, s.ticket + 1);
+        await_words<12>(p, tag, w, s);
         qv = *(const v8h *)w;
         kn = *(const v8h *)(w + 4);
         vn = *(const v8h *)(w + 8);
@@ -546,6 +540,11 @@ __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
 // 2560 41.7 and 30.7).
 bool ps_decode_row_applies(int H, int F, int d, int n_blocks) {
     return H <= 4096 && F <= 16384 && (d == 64 || d == 128) && n_blocks < 65535;
+}
+
+hipError_t ps_steps_given_up(int *dev_count, hipStream_t st) {
+    k_given_up<<<1, 1, 0, st>>>(dev_count);
+    return hipGetLastError();
 }
 
 hipError_t ps_decode_row(const StepArgs &s0, int d, int max_keys, hipStream_t st) {

@@ -64,6 +64,7 @@ struct petals_span {
     int open_sessions;
     // optional cache of the transposed dequantized weights for the backward pass: [block][linear]
     __half *bwd_cache = nullptr;
+    uint32_t step_patience = 1u << 24;   // polls for a row of a one-launch step, of half a microsecond and more each
     uint32_t norm_patience = 10000;      // 100 us: what a row of a LayerNorm waits for the others' outlier columns
     std::vector<uint8_t> bwd_cached;     // 1: the tiles of (block, linear) are in the cache
 };

@@ -121,3 +121,32 @@ def test_long_caches_stream(H, nh):
     rate = 16384 * H * 4 / (us[1] - us[0]) * 1e-6
     assert rate > 4.8, "%.1f and %.1f us: %.1f TB/s" % (us[0], us[1], rate)
     span.close()
+
+
+def _given_up():
+    n = torch.zeros(1, dtype=torch.int32, device=DEV)
+    binding.petals_steps_given_up(n)
+    return n.item()
+
+
+@pytest.mark.parametrize("H,nh,L", [(1024, 16, 40), (1024, 8, 1200), (3072, 24, 64)])
+def test_a_step_that_gives_up_says_so(H, nh, L):
+    """Readers that may not wait at all: the launch ends, the output is no number, the call is counted once, and the span's next
+    calls are as ever."""
+    cfg = _config(2, H, nh, H)
+    span = binding.Span(2, H, nh, H, 1, 1e-5, 6.0, DEV)
+    kv = [synth.kv_prefix_device(cfg, b, 0, L, 2.4, DEV) for b in range(2)]
+    for b in range(2):
+        span.load_block(b, synth.block_params_device(cfg, b, DEV))
+    x, before, outs = to_dev(synth.hidden_states(cfg, 1, 1, 1)[:, 0]), _given_up(), []
+    for polls, more in ((1 << 24, 0), (0, 1), (1 << 24, 1)):
+        s = span.open_session(L + 2)
+        for b in range(2):
+            s.import_kv(b, kv[b])
+        binding.petals_debug_step_patience(span.handle, polls)
+        outs.append(to_np(span.decode_step([s], x)))
+        assert _given_up() == before + more and s.length == L + 1
+        s.close()
+    assert np.isnan(outs[1]).any()
+    assert np.isfinite(outs[0]).all() and np.array_equal(outs[0].view(np.uint16), outs[2].view(np.uint16))
+    span.close()
