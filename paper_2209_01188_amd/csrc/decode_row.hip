@@ -537,7 +537,11 @@ __global__ void __launch_bounds__(THREADS, 2) k_decode_row(StepArgs s) {
 
 // The line: a stage of 4096 columns is as many items as there are workgroups, none of which then waits with weights on the way for
 // the next one (64 keys, per block: 4096 columns 55.1 us as five launches, 53.7 in one; 3840 62.8 and 48.8; 3072 45.2 and 35.8;
-// 2560 41.7 and 30.7).
+// 2560 41.7 and 30.7; with 5 % of the columns outliers 4096 96 and 70, with 2048 keys 70 and 67).
+// The price: with more than 128 registers a workgroup has its unit for itself, so the steps of several spans on several streams run
+// one after the other instead of into each other.  Three blocks, 256 keys, one, two, three spans at a time, us a step of all: 2048 columns 71, 124,
+// 165 (as separate launches 107, 146, 185); 3072 112, 211, 268 (145, 196, 265); 3840 150, 293, 424 (193, 270, 361); 4096 163, 321, 461
+// (176, 262, 349).
 bool ps_decode_row_applies(int H, int F, int d, int n_blocks) {
     return H <= 4096 && F <= 16384 && (d == 64 || d == 128) && n_blocks < 65535;
 }
