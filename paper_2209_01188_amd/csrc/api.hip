@@ -109,7 +109,7 @@ Workspace carve(const petals_span_config &c, uint8_t *base, bool with_rest = tru
         w.digits.done = (int *)take(PS_DIGIT_DONE * 4);
     }
     const size_t norm_rows = M < PS_NORM_ROWS_MAX ? M : PS_NORM_ROWS_MAX;
-    const bool records = with_rest && M > 1 && c.n_blocks * 4 < 65535;
+    const bool records = with_rest && M > 1;
     w.records = records ? (uint64_t *)take(norm_rows * PS_NORM_RECORD_WORDS * 4) : nullptr;
     w.record_masks = records ? (uint32_t *)take(norm_rows * H / 8) : nullptr;
     w.step = with_rest && ps_decode_row_applies((int)H, (int)F, (int)H / c.n_heads, c.n_blocks) ? (uint32_t *)take(PS_STEP_WORDS(H, F) * 4) : nullptr;
@@ -147,8 +147,8 @@ namespace {
 // X is the input of the LayerNorm that precedes the linear (fused on the one-row path, a kernel of its own
 // writing ws.a otherwise).  debug: copy the integer intermediates out (one-row path: into ws.xq/mask/ws.sx).
 // mask_ready (multi-row calls without LayerNorm): the kernel that wrote X has already flagged the outlier
-// columns in mask; with a LayerNorm the mask must arrive cleared and the LayerNorm kernel flags them - in calls of more
-// than 64 rows in flags, cleared as well, from which the row quantizer writes the mask.
+// columns in mask.  With a LayerNorm, mask is written here: by the LayerNorm kernel of few rows itself, otherwise by the row
+// quantizer from flags, which must arrive cleared.
 int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, const __half *ln_g, const __half *ln_b, int M,
                uint32_t *mask, uint8_t *flags, bool mask_ready, const OutDesc &o, int8_t *xq_dbg, bool debug, hipStream_t st,
                const QuantIn *qin = nullptr) {
@@ -162,21 +162,21 @@ int run_linear(petals_span *sp, int which, const LinearW &w, const __half *X, co
         HIP_TRY(ps_gemv_row(w, X, ln_g, ln_b, c.ln_eps, theta, dbg, o, ws.table, qin, st));
         sp->prof.end(pr, st);
     } else {
-        // calls of a few hundred rows whose output would be too few 256 x 256 blocks to fill the GPU go through
-        // the batched-decode kernel, 64 rows per workgroup (same outlier columns for all: those of the whole call)
+        // calls of a few hundred rows whose output would be too few blocks to fill the GPU go through the batched-decode
+        // kernel, 32 or 64 rows per workgroup (same outlier columns for all: those of the whole call)
         const bool chunks = ps_gemm_prefers_chunks(w, M);
         const bool small = M <= 64 || chunks;
         // few rows: LayerNorm and row quantizer are one launch
-        const bool fused = ln_g && small && M <= PS_NORM_ROWS_MAX && ws.records;
+        const bool fused = ln_g && small && M <= PS_NORM_ROWS_MAX;
         if (!mask_ready) HIP_TRY(ps_fill_u32(mask, ws.mask_words, 0u, st));
         if (fused) {
-            const NormExchange ex = {ws.records, ws.record_masks, (uint32_t)((mask - ws.masks) / ws.mask_words) + 1, sp->norm_patience};
+            // (tags only have to differ from those of the LayerNorms just before)
+            const NormExchange ex = {ws.records, ws.record_masks, (uint32_t)((mask - ws.masks) / ws.mask_words % 65535) + 1, sp->norm_patience};
             HIP_TRY(ps_layernorm_codes(X, qin, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, ws.xq, ws.xo, ws.sx, xq_dbg, theta, ex, st));
             X = ws.a;
         } else if (ln_g) {
-            if (M <= 64) flags = nullptr;
-            if (qin) HIP_TRY(ps_layernorm_q8(*qin, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, flags, theta, st));
-            else HIP_TRY(ps_layernorm(X, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, mask, flags, theta, st));
+            if (qin) HIP_TRY(ps_layernorm_q8(*qin, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, flags, theta, st));
+            else HIP_TRY(ps_layernorm(X, ln_g, ln_b, c.ln_eps, M, c.hidden, ws.a, flags, theta, st));
             X = ws.a;
         } else if (!mask_ready) {
             HIP_TRY(ps_colmask(X, M, w.K, theta, mask, st));

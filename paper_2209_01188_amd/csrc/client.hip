@@ -1281,7 +1281,7 @@ int petals_client_lm_head(petals_client *c, const void *hidden_in, int32_t M, fl
     const __half *lng = (const __half *)c->p.final_ln_g, *lnb = (const __half *)c->p.final_ln_b;
     if (M == 1) {
         // one row: the matrix streams at 6.6 TB/s past one fp64 multiply-add per value
-        HIP_TRY(ps_layernorm(x, lng, lnb, c->cfg.ln_eps, 1, H, c->a, nullptr, nullptr, 0.0f, st));
+        HIP_TRY(ps_layernorm(x, lng, lnb, c->cfg.ln_eps, 1, H, c->a, nullptr, 0.0f, st));
         const size_t lds = (size_t)H * 8;
         {   // the limit belongs to the function, for all clients of the process: set once, to the widest row there is
             static std::mutex attr_lock;

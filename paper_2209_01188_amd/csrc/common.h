@@ -112,13 +112,12 @@ hipError_t ps_quantize_weight(const float *W, int N, int K, int8_t *wt, float *s
 hipError_t ps_untile_weight(const int8_t *wt, int N, int K, int8_t *wq_rowmajor, hipStream_t st);
 hipError_t ps_fill_u32(uint32_t *p, size_t n, uint32_t v, hipStream_t st);
 hipError_t ps_copy_bytes(const void *src, void *dst, size_t n, hipStream_t st);
-// mask (may be null): outlier-column bits of y are ORed into it (|y| >= theta); flags (null, or instead of mask, zeroed):
-// one byte per column, set to 1 where a row reaches theta
+// flags (null, or zeroed): one byte per column, set to 1 where a row reaches theta
 hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float eps, int M, int H,
-                        __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st);
+                        __half *y, uint8_t *flags, float theta, hipStream_t st);
 // LayerNorm of rows that arrive as 8-bit codes (also writes the decoded rows to qin.x_out)
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
-                           int H, __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st);
+                           int H, __half *y, uint8_t *flags, float theta, hipStream_t st);
 hipError_t ps_colmask(const __half *X, int M, int K, float theta, uint32_t *mask, hipStream_t st);
 // M rows -> tiled int8 codes (rows padded to 16 with zeros), row scales; mask given, or (flags not null) given as one byte
 // per column and then written to mask

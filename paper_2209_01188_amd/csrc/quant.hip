@@ -69,14 +69,13 @@ __global__ void k_copy_bytes(const uint8_t *__restrict__ s, uint8_t *__restrict_
 
 // One workgroup per row that arrives as blockwise 8-bit codes: every thread decodes the elements it will normalise, stores
 // them as the fp16 row the residual reads later, and normalises that row (1024 threads: the sums of k_layernorm_wide, in
-// the same order).
+// the same order).  These kernels flag outlier columns as bytes, for calls of more than 64 rows that k_layernorm_codes doesn't take.
 static __device__ const CodeTable d_code_table = ps_make_code_table();
 
-template <int NT, bool FLAGS>
+template <int NT>
 __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *__restrict__ g,
                                                      const __half *__restrict__ b, float eps, int H,
-                                                     __half *__restrict__ y, uint32_t *__restrict__ mask,
-                                                     uint8_t *__restrict__ flags, float theta) {
+                                                     __half *__restrict__ y, uint8_t *__restrict__ flags, float theta) {
     __shared__ double sm[NT / 64];
     __shared__ float table[256];
     for (int i = threadIdx.x; i < 256; i += NT) table[i] = d_code_table.code[i];
@@ -97,8 +96,7 @@ __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *
                                     *(const __half2 *)(b + k), mean, inv);
         *(__half2 *)(yr + k) = o;
         const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
-        if constexpr (FLAGS) flag_outlier_bytes(flags, k, bits);
-        else if (mask) flag_outlier_bits(mask, k >> 5, bits << (k & 31));
+        flag_outlier_bytes(flags, k, bits);
     }
 }
 
@@ -107,8 +105,7 @@ __global__ void __launch_bounds__(NT) k_layernorm_q8(QuantIn qin, const __half *
 template <bool FLAGS>
 __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restrict__ x, const __half *__restrict__ g,
                                                          const __half *__restrict__ b, float eps, int H,
-                                                         __half *__restrict__ y, uint32_t *__restrict__ mask,
-                                                         uint8_t *__restrict__ flags, float theta) {
+                                                         __half *__restrict__ y, uint8_t *__restrict__ flags, float theta) {
     constexpr int NT = 1024, PER = 8;
     __shared__ double sm[NT / 64];
     const __half *xr = x + (size_t)blockIdx.x * H;
@@ -141,9 +138,8 @@ __global__ void __launch_bounds__(1024) k_layernorm_wide(const __half *__restric
         if (k < H) {
             const __half2 o = ln_affine(v[i], *(const __half2 *)(g + k), *(const __half2 *)(b + k), mean, inv);
             *(__half2 *)(yr + k) = o;
-            const uint32_t bits = (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u);
-            if constexpr (FLAGS) flag_outlier_bytes(flags, k, bits);
-            else if (mask) flag_outlier_bits(mask, k >> 5, bits << (k & 31));
+            if constexpr (FLAGS)
+                flag_outlier_bytes(flags, k, (fabsf(__half2float(o.x)) >= theta ? 1u : 0u) | (fabsf(__half2float(o.y)) >= theta ? 2u : 0u));
         }
     }
 }
@@ -160,7 +156,7 @@ template <int PER, bool Q8>
 __global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restrict__ x, QuantIn qin,
                                                         const __half *__restrict__ g, const __half *__restrict__ b,
                                                         float eps, int M, int H, __half *__restrict__ y,
-                                                        uint32_t *__restrict__ mask, uint8_t *__restrict__ cols, uint32_t theta_bits) {
+                                                        uint8_t *__restrict__ cols, uint32_t theta_bits) {
     constexpr int NT = 256;
     // narrow rows: gain and bias stay in registers as fp64 over the rows of the workgroup, and so do a row's values over
     // its three passes (two conversions each, where a pass has one to three operations on a value)
@@ -295,20 +291,17 @@ __global__ void __launch_bounds__(256, 3) k_layernorm_rows(const __half *__restr
             }
         }
     }
-    if (mask || cols) {
+    if (!cols) return;
 #pragma unroll
-        for (int i = 0; i < PER; i++) {
-            const int k = (threadIdx.x + i * NT) * 8;
-            if (k >= H) continue;
-            if (cols) flag_outlier_bytes(cols, k, flags[i]);
-            else flag_outlier_bits(mask, k >> 5, flags[i] << (k & 31));
-        }
+    for (int i = 0; i < PER; i++) {
+        const int k = (threadIdx.x + i * NT) * 8;
+        if (k < H) flag_outlier_bytes(cols, k, flags[i]);
     }
 }
 
 template <bool Q8>
 hipError_t launch_layernorm_rows(const __half *x, const QuantIn &qin, const __half *g, const __half *b, float eps, int M, int H,
-                                 __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
+                                 __half *y, uint8_t *flags, float theta, hipStream_t st) {
     const int v = H <= 2048 ? 0 : H <= 4096 ? 1 : H <= 8192 ? 2 : 3;
     const uint32_t tb = ps_theta_to_bits(theta);
     auto kern = v == 0 ? k_layernorm_rows<1, Q8> : v == 1 ? k_layernorm_rows<2, Q8> : v == 2 ? k_layernorm_rows<4, Q8> : k_layernorm_rows<8, Q8>;
@@ -322,7 +315,7 @@ hipError_t launch_layernorm_rows(const __half *x, const QuantIn &qin, const __ha
         if (per_unit < 1) return hipErrorInvalidConfiguration;
         resident[v].store(per_unit, std::memory_order_relaxed);
     }
-    kern<<<M < 256 * per_unit ? M : 256 * per_unit, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, mask, flags, tb);
+    kern<<<M < 256 * per_unit ? M : 256 * per_unit, 256, 0, st>>>(x, qin, g, b, eps, M, H, y, flags, tb);
     return hipGetLastError();
 }
 
@@ -1132,23 +1125,23 @@ hipError_t ps_copy_bytes(const void *src, void *dst, size_t n, hipStream_t st) {
     return hipGetLastError();
 }
 hipError_t ps_layernorm(const __half *x, const __half *g, const __half *b, float eps, int M, int H, __half *y,
-                        uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
+                        uint8_t *flags, float theta, hipStream_t st) {
     // few rows: more threads per row (latency), many rows: more rows in flight (prefill calls of a 4096-wide block, two
     // LayerNorms each: 140 rows 188 us with 1024 threads per row, 199 with several rows per 256 threads; 351 rows 244
     // and 242: the line lies between).  Rows below 4096 columns, of which 1024 threads would hold two pairs each or fewer,
     // always take 256 threads.
     if (H % 8 || H > 16384) return hipErrorInvalidValue;       // span and client take multiples of 64 up to 16384
-    if (M >= 256 || H < 4096) return launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, mask, flags, theta, st);
-    (flags ? k_layernorm_wide<true> : k_layernorm_wide<false>)<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, mask, flags, theta);
+    if (M >= 256 || H < 4096) return launch_layernorm_rows<false>(x, QuantIn{}, g, b, eps, M, H, y, flags, theta, st);
+    (flags ? k_layernorm_wide<true> : k_layernorm_wide<false>)<<<M, 1024, 0, st>>>(x, g, b, eps, H, y, flags, theta);
     return hipGetLastError();
 }
 hipError_t ps_layernorm_q8(const QuantIn &qin, const __half *g, const __half *b, float eps, int M,
-                           int H, __half *y, uint32_t *mask, uint8_t *flags, float theta, hipStream_t st) {
+                           int H, __half *y, uint8_t *flags, float theta, hipStream_t st) {
     // the line of ps_layernorm (measured there, on fp16 rows)
     if ((M >= 256 || H < 4096) && H % 8 == 0 && H <= 16384 && ((uintptr_t)qin.q & 7) == 0)
-        return launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, mask, flags, theta, st);
-    if (M <= 256 && H >= 4096) (flags ? k_layernorm_q8<1024, true> : k_layernorm_q8<1024, false>)<<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
-    else (flags ? k_layernorm_q8<256, true> : k_layernorm_q8<256, false>)<<<M, 256, 0, st>>>(qin, g, b, eps, H, y, mask, flags, theta);
+        return launch_layernorm_rows<true>(nullptr, qin, g, b, eps, M, H, y, flags, theta, st);
+    if (M <= 256 && H >= 4096) k_layernorm_q8<1024><<<M, 1024, 0, st>>>(qin, g, b, eps, H, y, flags, theta);
+    else k_layernorm_q8<256><<<M, 256, 0, st>>>(qin, g, b, eps, H, y, flags, theta);
     return hipGetLastError();
 }
 hipError_t ps_layernorm_codes(const __half *x, const QuantIn *qin, const __half *g, const __half *b, float eps, int M, int H, __half *y,

@@ -155,3 +155,28 @@ def test_rows_without_patience_work_the_columns_out():
             us.append(_us(span, x, y))
     span.close()
     assert us[1] > 3.0 * us[0], us
+
+
+# A span of so many blocks that the tags of its LayerNorms come round: the same as with rows that look at no record
+def test_more_layernorms_than_tags():
+    blocks, H = 16386, 64
+    span = binding.Span(blocks, H, 1, 64, 3, device=DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+    p = {n: torch.empty(s, device=DEV).normal_(0.0, 0.02, generator=g)
+         for n, s in (("w_qkv", (3 * H, H)), ("w_dense", (H, H)), ("w_up", (64, H)), ("w_down", (H, 64)))}
+    for n, s in (("b_qkv", 3 * H), ("b_dense", H), ("b_up", 64), ("b_down", H), ("ln1_b", H), ("ln2_b", H)):
+        p[n] = torch.zeros(s, dtype=torch.float16, device=DEV)
+    p["ln1_g"] = p["ln2_g"] = torch.ones(H, dtype=torch.float16, device=DEV)
+    for b in range(blocks):
+        binding.petals_span_load_block(span.handle, b, p)
+    x = torch.empty((1, 3, H), device=DEV).normal_(generator=g).half()
+    x[0, 1, 5] = 40.0
+    outs = []
+    for patience in (10000, 0):
+        binding.petals_debug_norm_patience(span.handle, patience)
+        s = span.open_session(3)
+        outs.append(to_np(span.prefill([s], x)))
+        s.close()
+    assert np.isfinite(outs[0]).all() and np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
+    span.close()
