@@ -9,7 +9,7 @@ if not torch.cuda.is_available():
 
 import oracle  # noqa: E402
 from paper_2209_01188_amd import binding, synth  # noqa: E402
-from tests.gpu_util import DEV, build_pair, midsize, to_dev, to_np  # noqa: E402
+from tests.gpu_util import DEV, build_pair, hidden_close, midsize, to_dev, to_np  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -65,27 +65,36 @@ def test_rows_that_do_not_wait_give_the_same_calls(B, T, H, coded):
     cfg = synth.SpanConfig("codes", 2, H, H // 64, B, T, 1, 1, (20.0, 40.0), 3)
     osp, span, _ = build_pair(cfg, max_rows=B * T)
     x = synth.hidden_states(cfg, 0, B, T)
+    q, am = torch.empty(x.size, dtype=torch.uint8, device=DEV), torch.empty(-(-x.size // 64), dtype=torch.float32, device=DEV)
+    if coded:
+        binding.petals_hidden_quantize(to_dev(x), 64, q, am)
+        decoded = torch.empty(x.shape, dtype=torch.float16, device=DEV)
+        binding.petals_hidden_dequantize(q, am, 64, decoded)
+        x = to_np(decoded)
+    want = osp.step([osp.open_session(T) for _ in range(B)], x)
     outs = []
     for patience, poison in ((10000, False), (0, False), (10000, True), (0, True)):
         binding.petals_debug_norm_patience(span.handle, patience)
-        xi = x.copy()
-        if poison:
-            xi[0, 0, 5] = np.nan
         ses = [span.open_session(T) for _ in range(B)]
         with midsize("chunks"):
-            if coded and not poison:
-                n = xi.size
-                q, am = torch.empty(n, dtype=torch.uint8, device=DEV), torch.empty(-(-n // 64), dtype=torch.float32, device=DEV)
-                binding.petals_hidden_quantize(to_dev(xi), 64, q, am)
-                y = span.prefill_q8(ses, T, q, am, 64)
+            if coded:                            # poison: the maximum of a block of 64 codes of the first row
+                am_i = am.clone()
+                if poison:
+                    am_i[0] = np.nan
+                y = span.prefill_q8(ses, T, q, am_i, 64)
             else:
+                xi = x.copy()
+                if poison:
+                    xi[0, 0, 5] = np.nan
                 y = span.prefill(ses, to_dev(xi))
         outs.append(to_np(y))
         for s in ses:
             s.close()
     assert np.array_equal(outs[0].view(np.uint16), outs[1].view(np.uint16))
     assert np.array_equal(outs[2].view(np.uint16), outs[3].view(np.uint16))
-    if not coded and B > 1:
+    hidden_close(outs[0], want)
+    assert np.isnan(outs[2][0, 0]).all()
+    if B > 1:
         assert np.isfinite(outs[2][1:]).all()
     span.close(); osp.destroy()
 
