@@ -26,6 +26,8 @@ def _config(blocks, H, nh, F):
     (1, 2048, 32, 1024, 1500, 0.0), (2, 2112, 33, 8448, 70, 6.0), (2, 3072, 24, 12288, 300, 6.0), (1, 2944, 46, 9216, 1200, 6.0),
     (1, 512, 8, 12288, 20, 6.0), (2, 3136, 49, 12544, 100, 6.0), (2, 4096, 32, 16384, 64, 6.0), (1, 4096, 64, 15360, 900, 6.0),
     (1, 1024, 8, 16384, 5, 0.5), (1, 1152, 9, 8192, 2500, 6.0), (1, 128, 2, 512, 3000, 6.0),
+    # several ranges in several blocks, the last range with keys and (1024 columns, 4100 keys) without
+    (3, 1024, 8, 4096, 1500, 6.0), (2, 2048, 32, 8192, 2100, 6.0), (2, 4096, 32, 16384, 1100, 6.0), (2, 1024, 8, 1024, 4100, 6.0),
     # from here on three quarters of the workgroups share the keys instead of half; two blocks
     (2, 4096, 32, 16384, 3068, 6.0), (2, 4096, 64, 1024, 3072, 6.0), (2, 1024, 16, 1024, 12290, 6.0)])
 def test_a_row_in_one_launch(blocks, H, nh, F, L, theta):

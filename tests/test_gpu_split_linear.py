@@ -9,7 +9,7 @@ if not torch.cuda.is_available():
 
 import oracle  # noqa: E402
 from paper_2209_01188_amd import binding, synth  # noqa: E402
-from tests.gpu_util import DEV, build_pair, midsize, to_dev, to_np  # noqa: E402
+from tests.gpu_util import DEV, build_pair, hidden_close, midsize, to_dev, to_np  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -121,6 +121,26 @@ def test_32_rows_per_workgroup(ffn, hidden, nh, which, M, epilogue):
         torch.cuda.synchronize()
     assert np.array_equal(to_np(out["acc"]), dbg["acc"])
     assert np.array_equal(to_np(out["y"]).view(np.uint16), Y.view(np.uint16))
+    gsp.close()
+    osp.destroy()
+
+
+# The fused QKV linear with 32 rows per workgroup (four waves for 192 columns, sixteen for 320): the rows of a workgroup behind the
+# first belong to several sessions, whose keys and values go to their caches
+@pytest.mark.parametrize("H,nh", [(192, 3), (320, 5)])
+@pytest.mark.parametrize("B,T", [(4, 15), (3, 23), (2, 50), (33, 2)])
+def test_32_rows_per_workgroup_append_to_the_caches(H, nh, B, T):
+    cfg = synth.SpanConfig("rows32", 1, H, nh, B, T, 1, 1, (20.0, 40.0), 6)
+    osp, gsp, _ = build_pair(cfg, max_rows=B * T)
+    oses, gses = [osp.open_session(2 * T) for _ in range(B)], [gsp.open_session(2 * T) for _ in range(B)]
+    for call in range(2):                                    # the second one behind cached keys
+        x = synth.hidden_states(cfg, call, B, T)
+        want = osp.step(oses, x)
+        with midsize("chunks"):
+            got = to_np(gsp.prefill(gses, to_dev(x)))
+        hidden_close(got, want)
+    for o, g in zip(oses, gses):
+        assert np.array_equal(to_np(g.export_kv(0)).view(np.uint16), o.export_kv(0).view(np.uint16))
     gsp.close()
     osp.destroy()
 
