@@ -108,9 +108,9 @@ __global__ void __launch_bounds__(LM_THREADS) k_lm_head(const __half *__restrict
 // straight line so that the matrix unit has work beside that (342 us, 6.0 TB/s; 14336 columns at 2 rows 1440 -> 1155;
 // 17 to 32 rows, where a digit read from LDS meets one matrix tile only and products and arithmetic are the bound, 484 ->
 // 470).  Every workgroup starts at another chunk: from column 0 on all of them fall on a few memory channels (417 us).
-// A piece with a value of 0.246 and more takes a fourth digit, a third more products and twice the arithmetic: two pieces in a
-// straight line there as well, except for 17 to 32 rows, where that costs the others 4 % (60000 x 4096, values of 0.3, 8 and 32 rows:
-// 115 -> 111 and 150 -> 146 us; loaded as operands 108 and 135, values of 0.02 106 and 124, now 90 and 117).
+// A piece with a value of 0.246 and more takes a fourth digit, a third more products and twice the arithmetic; a multiply-add
+// straight from fp16 is worth 5 % there (250880 x 4096, values of 0.3, 8 and 32 rows: 449 -> 426 and 636 -> 615 us; values of 0.02
+// take 333 and 486; two pieces in a straight line there as well: 428 and 614, and the others 341).
 // Two matrix tiles per wave also for 17 to 32 rows: 75 spilled registers, 731 us.  The hidden rows' digits (k_lm_prepare)
 // go through LDS as well, shared by the 8 waves, one barrier per chunk.
 //
@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                 const v2h both = lm_max_abs(big[0], big[1]);
                 const uint32_t bits = *(const uint32_t *)&both & 0x7fff7fffu;
                 const bool full = ch * CH + CH <= KT;
-                if (__builtin_expect(full && !__any(max(bits & 0xffffu, bits >> 16) >= LMD_SMALL), 1)) {
+                if (full && !__any(max(bits & 0xffffu, bits >> 16) >= LMD_SMALL)) {
                     // nearly always: straight-line, so that one piece's arithmetic runs beside the other's products
 #pragma unroll
                     for (int u = 0; u < CH; u++) {
@@ -465,11 +465,12 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                             }
                     }
                 } else {
-                    const auto multiply4 = [&](int u) {
-                        v4i d[WN][4], xb[4];
-                        if constexpr (MT == 1)                   // asked for before the arithmetic
 #pragma unroll
-                            for (int j = 0; j < 4; j++) xb[j] = *(const v4i *)(sb + (u * 4 + j) * 1024);
+                    for (int u = 0; u < CH; u++) {
+                        if (ch * CH + u >= KT) continue;         // ragged last chunk
+                        const uint32_t ub = *(const uint32_t *)&big[u] & 0x7fff7fffu;
+                        slow |= (bool)__any(max(ub & 0xffffu, ub >> 16) >= LMD_BIG_E);
+                        v4i d[WN][4];
 #pragma unroll
                         for (int p = 0; p < WN; p++)
 #pragma unroll
@@ -488,30 +489,13 @@ __global__ void __launch_bounds__(512, 2) k_lm_head_digits(const __half *__restr
                         for (int j = 0; j < 4; j++)
 #pragma unroll
                             for (int m = 0; m < MT; m++) {
-                                const v4i b = MT == 1 ? xb[j] : *(const v4i *)(sb + ((u * 4 + j) * MT + m) * 1024);
+                                const v4i xb = *(const v4i *)(sb + ((u * 4 + j) * MT + m) * 1024);
 #pragma unroll
                                 for (int i = 0; i < 4; i++)
 #pragma unroll
                                     for (int p = 0; p < WN; p++)
-                                        acc[p][m][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[p][i], b, acc[p][m][i + j], 0, 0, 0);
+                                        acc[p][m][i + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(d[p][i], xb, acc[p][m][i + j], 0, 0, 0);
                             }
-                    };
-                    const auto look = [&](uint32_t m) { slow |= (bool)__any(max(m & 0xffffu, m >> 16) >= LMD_BIG_E); };
-                    if constexpr (MT == 1) {
-                        look(full ? bits : *(const uint32_t *)&big[0] & 0x7fff7fffu);
-                        if (full) {                              // in a straight line as well
-                            multiply4(0);
-                            multiply4(1);
-                        } else {                                 // ragged last chunk: one piece
-                            multiply4(0);
-                        }
-                    } else {
-#pragma unroll
-                        for (int u = 0; u < CH; u++) {
-                            if (ch * CH + u >= KT) continue;     // ragged last chunk
-                            look(*(const uint32_t *)&big[u] & 0x7fff7fffu);
-                            multiply4(u);
-                        }
                     }
                 }
                 ch = ch + 1 == nch ? 0 : ch + 1;         // behind the last chunk comes the first of the next round
