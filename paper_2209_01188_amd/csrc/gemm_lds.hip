@@ -222,6 +222,7 @@ struct GemmArgs {
     const unsigned char *a_regular, *b_regular;     // int8: ManyOutliers' wd and xl
     int ktiles;                     // int8: K/64.  fp16: the plain product's tile count.  digits: derived from the outlier count
     int M, N;
+    int exact;                      // ps_exact_outliers
     int nb_n, nb_m;                 // output blocks of this launch along the features and along the tokens
     int nb_n0;                      // first feature block of this launch (a linear may be split over two launches)
     // plain fp16 product only: instead of the fp32 result, store fp16(result * GeLU'(gelu_pre)) in the tile order
@@ -307,7 +308,7 @@ k_gemm_lds(GemmArgs ga, LinearW w, const float *__restrict__ sx, OutlierSet os, 
     constexpr int PD = NSLOT - 1;                    // stages requested ahead
     extern __shared__ __align__(16) unsigned char lds[];
     const int n_out = F16 ? ga.ktiles * 32 : os.count[0];
-    const bool many = F16 || n_out > ps_exact_outliers(ga.N, ga.M);
+    const bool many = F16 || n_out > ga.exact;
     if (DIG && !many) return;
     // k-tiles to walk (64 int8 or 32 fp16 columns each).  If EVERY column is an outlier all int8 codes are
     // zero: the int8 product is skipped and only the epilogue runs.
@@ -781,7 +782,7 @@ __global__ void __launch_bounds__(256) k_split_finish(GemmArgs ga, LinearW w, co
     v4i acc = {0, 0, 0, 0};
     for (int s = 0; s < ga.ksplit; s++) acc += ga.part[(((size_t)s * NT + nt) * MTT + mt) * 64 + lane];
     v4d od = {0.0, 0.0, 0.0, 0.0};
-    if (n_out > ps_exact_outliers(ga.N, ga.M)) {
+    if (n_out > ga.exact) {
         if (t < ga.M) od = *(const v4d *)(outl + (size_t)t * ga.N + n0);
     } else {
         const double *ap = os.wd64 + (size_t)nt * PS_OUTLIER_CHUNKS * 64 + lane, *bp = os.x64 + (size_t)mt * PS_OUTLIER_CHUNKS * 64 + lane;
@@ -968,6 +969,7 @@ GemmArgs gemm_args(const void *a_tiles, const void *b_tiles, int ktiles, int M, 
     g.ktiles = ktiles;
     g.M = M;
     g.N = N;
+    g.exact = ps_exact_outliers(N, M);
     return g;
 }
 
