@@ -69,7 +69,7 @@ int petals_client_embed(petals_client *client, const int32_t *token_ids, int32_t
  * of the largest logit (greedy decoding), decided on the fp64 values; may be NULL if
  * logits_out is given.  hidden_in: dev fp16 [M, H].  The embedding matrix is streamed once per call
  * for one row and once per group of up to 32 rows otherwise, whose products are taken exactly as int8
- * digit products (on the fp64 matrix instruction for matrix tiles with a value of 127.5 or more and for
+ * digit products (on the fp64 matrix instruction for matrix tiles with a value of 127 or more and for
  * hidden rows with an infinity or NaN).
  */
 int petals_client_lm_head(petals_client *client, const void *hidden_in, int32_t M,

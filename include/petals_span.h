@@ -129,8 +129,8 @@ int petals_session_close(petals_session *session);
  * Every linear uses the 8-bit mixed decomposition (Section 3.1): columns whose
  * magnitude reaches outlier_threshold in any of the B*T rows go through fp16
  * with weights dequantized from int8, the rest through int8 x int8 -> int32.
- * Calls of 65 to 512 rows run each linear either as 256 x 256 output blocks or 64 rows at a time through the
- * batched-decode kernel, whichever a cost estimate says is faster for that matrix; both give the same bits.
+ * Calls of 65 to 512 rows run each linear either in output blocks (of 64 x 64 to 256 x 256) or 32 or 64 rows at a time
+ * through the batched-decode kernel, whichever a cost estimate says is faster for that matrix; both give the same bits.
  * Test hook: PETALS_SPAN_MIDSIZE=blocks or =chunks in the environment (read at every call) forces one of them.
  * Each session's length grows by T.  Errors: B > PETALS_MAX_SESSIONS_PER_CALL,
  * B*T > max_rows_per_call or a full cache -> PETALS_ERR_CAPACITY; the same
@@ -170,7 +170,7 @@ int petals_steps_given_up(int32_t *dev_count, void *stream);
  * petals_span_decode_step for callers that cannot provide or allocate device memory at the time of the call
  * (code running under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same step,
  * same arguments, same results bit for bit, but every intermediate buffer lives in a fixed device array that
- * is part of the library image (96 MiB per GPU, held until the process ends) instead of the span's workspace.
+ * is part of the library image (97 MiB per GPU, held until the process ends) instead of the span's workspace.
  * The call allocates nothing, on the host or on the device.  A step whose intermediates do not fit the 32 MiB of
  * them that are for these (the others are for exact sums over outlier columns, for which they always suffice)
  * (B * hidden of the order of a few hundred thousand; for BLOOM-176B-shaped blocks up to about 40 sessions)

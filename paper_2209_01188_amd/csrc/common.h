@@ -214,7 +214,7 @@ bool ps_decode_row_applies(int H, int F, int d, int n_blocks);
 hipError_t ps_decode_row(const StepArgs &s, int d, int max_keys, hipStream_t st);
 hipError_t ps_steps_given_up(int *dev_count, hipStream_t st);     // on this device, since the library was loaded
 #define PS_CHUNKED_ROWS_MAX 512
-// batched-decode linear, 2 <= M <= PS_CHUNKED_ROWS_MAX rows, 64 per workgroup (int8 MFMA, outlier columns exactly on fp64 MFMA inside the
+// batched-decode linear, 2 <= M <= PS_CHUNKED_ROWS_MAX rows, up to 64 per workgroup (int8 MFMA, outlier columns exactly on fp64 MFMA inside the
 // loop); xq_tiled and xo_tiled as written by ps_rowquant_tiled
 // dc (dc.xd may be null): for calls of 17 to 64 rows on wide matrices, whose outlier columns are then taken as digits if the row
 // quantizer has written them for all rows, see gemm_digits.h.  (That is known on the device only: both forms are in one launch.)
@@ -232,8 +232,8 @@ struct DigitCall {
     int *part_acc;                // the same of the regular columns' sums
 };
 bool ps_gemm_digits_applies(int N, int K, int M);
-// Calls of more than 64 rows that are better served by ps_gemm, 64 rows per workgroup (the weights are streamed once
-// per 64 rows, with every compute unit busy) than by the output blocks of ps_gemm_lds with their kernels for
+// Calls of more than 64 rows that are better served by ps_gemm, 32 or 64 rows per workgroup (the weights are streamed once
+// per 32 or 64 rows, with every compute unit busy) than by the output blocks of ps_gemm_lds with their kernels for
 // outlier columns.  PS_CHUNKED_ROWS_MAX bounds such calls.
 bool ps_gemm_prefers_chunks(const LinearW &w, int M);
 double ps_gemm_lds_us(int N, int K, int M);       // estimate of a linear of M > 64 rows in output blocks, with its row kernels

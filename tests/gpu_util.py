@@ -25,9 +25,9 @@ def say(msg):
 
 @contextlib.contextmanager
 def midsize(mode):
-    """How the library runs the linears of calls of 65 to 512 rows inside the block: "blocks" = 256 x 256 output
-    blocks on the LDS-pipelined kernel (with the digit products for many outlier columns), "chunks" = the
-    batched-decode kernel on 64 rows at a time, None = its own choice (a cost estimate per linear).  The library
+    """How the library runs the linears of calls of 65 to 512 rows inside the block: "blocks" = output blocks
+    on the LDS-pipelined kernel (with the digit products for many outlier columns), "chunks" = the
+    batched-decode kernel on 32 or 64 rows at a time, None = its own choice (a cost estimate per linear).  The library
     reads PETALS_SPAN_MIDSIZE at every call."""
     old = os.environ.get("PETALS_SPAN_MIDSIZE")
     if mode is None:

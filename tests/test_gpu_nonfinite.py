@@ -39,7 +39,7 @@ def test_a_key_with_a_nan_score_is_not_left_out(d, B, L, T, at):
     span.close()
 
 
-# GeLU behind the up linear, one row, batched decode and both prefill forms (64 rows per workgroup; output blocks, there
+# GeLU behind the up linear, one row, batched decode and both prefill forms (rows through the batched-decode kernel; output blocks, there
 # also with the contraction split): an infinite outlier value times a positive weight is +infinity, GeLU of it too.
 @pytest.mark.parametrize("M,H,ffn,form", [(1, 64, 256, None), (8, 64, 256, None), (100, 64, 256, "chunks"), (100, 64, 256, "blocks"), (70, 2048, 256, "blocks")])
 def test_gelu_of_infinity(M, H, ffn, form):
